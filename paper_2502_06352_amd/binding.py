@@ -7,6 +7,7 @@ no fallback: a missing library raises at import of this module's loader.
 """
 import ctypes as C
 import os
+import struct
 from typing import Optional
 
 import numpy as np
@@ -69,18 +70,18 @@ def lib() -> C.CDLL:
     L.lpp_relaxed_verify_workspace.argtypes = [vp, i32, i32, i32]
     L.lpp_relaxed_verify.restype = i32
     L.lpp_relaxed_verify.argtypes = [vp, vp, vp, i64, i32, i32, i32, vp, vp, i32, i32, f32, vp, vp,
-                                     C.POINTER(VerifyOut), vp, sz, vp]
+                                     vp, vp, sz, vp]
     L.lpp_relaxed_verify_static.restype = i32
     L.lpp_relaxed_verify_static.argtypes = [vp, vp, vp, i64, i32, i32, i32, vp, vp, i32, i32, f32, vp, vp,
-                                            C.POINTER(VerifyOut), vp]
+                                            vp, vp]
     L.lpp_relaxed_verify_additive.restype = i32
     L.lpp_relaxed_verify_additive.argtypes = L.lpp_relaxed_verify.argtypes
     L.lpp_relaxed_verify_sampled.restype = i32
     L.lpp_relaxed_verify_sampled.argtypes = [vp, vp, vp, f32, i32, vp, i64, i32, i32, i32, vp, vp, i32, i32, f32, vp, vp,
-                                             C.POINTER(VerifyOut), vp, sz, vp]
+                                             vp, vp, sz, vp]
     L.lpp_relaxed_verify_opts.restype = i32
     L.lpp_relaxed_verify_opts.argtypes = [vp, vp, vp, i64, i32, i32, i32, vp, vp, i32, i32, vp, vp, vp,
-                                          C.POINTER(VerifyOut), vp, sz, vp]
+                                          vp, vp, sz, vp]
     L.lpp_commit_kv.restype = i32
     L.lpp_commit_kv.argtypes = [vp, i32, vp, vp, vp, vp, vp, i32, i32, i32, i32, vp, vp, vp, vp]
     L.lpp_probe_stream_read.restype = i32
@@ -89,16 +90,44 @@ def lib() -> C.CDLL:
     return L
 
 
+# One call's marshalling is part of every step's latency (a step is three calls whose kernels take a
+# few microseconds each): the current stream is asked for as a raw handle (torch.cuda.current_stream()
+# wraps it in a Stream object: 3.0 us against 0.3 us), and lpp_verify_out is packed as ten pointers in
+# one go (a ctypes structure filled by keyword takes 1.8 us, this 0.9 us).
 def _ptr(t) -> Optional[int]:
-    return None if t is None else int(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _bytes(ws) -> int:
+    return 0 if ws is None else ws.numel() * ws.element_size()
+
+
+_torch = _raw_stream = None
 
 
 def _stream(stream) -> Optional[int]:
+    global _torch, _raw_stream
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
+        if _torch is None:
+            import torch
+            _torch = torch
+            _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if _raw_stream is not None and _torch.cuda.is_initialized():
+            return _raw_stream(_torch._C._cuda_getDevice()) or None
+        stream = _torch.cuda.current_stream()
     s = int(getattr(stream, "cuda_stream", stream))
     return s or None
+
+
+_OUT_FIELDS = tuple(n for n, _ in VerifyOut._fields_)
+_pack_out = struct.Struct("%dP" % len(_OUT_FIELDS)).pack
+assert struct.calcsize("%dP" % len(_OUT_FIELDS)) == C.sizeof(VerifyOut)
+
+
+def _verify_out(out: dict) -> bytes:
+    """lpp_verify_out for ``out`` (field name -> tensor; missing / None = null), read during the call only."""
+    get = out.get
+    return _pack_out(*[0 if (t := get(n)) is None else t.data_ptr() for n in _OUT_FIELDS])
 
 
 def _check(status: int, where: str) -> None:
@@ -144,8 +173,8 @@ def lpp_build_neighbours_workspace(V: int, D: int, k: int) -> int:
 
 def lpp_build_neighbours(E, k: int, neigh, ws, stream=None) -> None:
     V, D = E.shape
-    _check(lib().lpp_build_neighbours(_ptr(E), V, D, k, _ptr(neigh), _ptr(ws),
-                                      0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)),
+    _check(lib().lpp_build_neighbours(_ptr(E), V, D, k, _ptr(neigh), _ptr(ws), _bytes(ws),
+                                      _stream(stream)),
            "lpp_build_neighbours")
 
 
@@ -156,8 +185,8 @@ def lpp_tree_attention_workspace(tree: Tree, B: int, H: int, S: int, Dh: int) ->
 def lpp_tree_attention(tree: Tree, dtype: int, q, k_cache, v_cache, k_tree, v_tree, seq_len,
                        B: int, H: int, S: int, Dh: int, scale: float, out, ws, stream=None) -> None:
     _check(lib().lpp_tree_attention(tree.handle, dtype, _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_tree),
-                                    _ptr(v_tree), _ptr(seq_len), B, H, S, Dh, scale, _ptr(out), _ptr(ws),
-                                    0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)),
+                                    _ptr(v_tree), _ptr(seq_len), B, H, S, Dh, scale, _ptr(out), _ptr(ws), _bytes(ws),
+                                    _stream(stream)),
            "lpp_tree_attention")
 
 
@@ -165,12 +194,15 @@ def lpp_tree_attention_gqa(tree: Tree, dtype: int, out_dtype: int, q, k_cache, v
                            B: int, H: int, Hkv: int, S: int, Dh: int, scale: float, out, ws, stream=None) -> None:
     _check(lib().lpp_tree_attention_gqa(tree.handle, dtype, out_dtype, _ptr(q), _ptr(k_cache), _ptr(v_cache),
                                         _ptr(k_tree), _ptr(v_tree), _ptr(seq_len), B, H, Hkv, S, Dh, scale,
-                                        _ptr(out), _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(),
-                                        _stream(stream)), "lpp_tree_attention_gqa")
+                                        _ptr(out), _ptr(ws), _bytes(ws), _stream(stream)),
+           "lpp_tree_attention_gqa")
 
 
 class AttentionLayer(C.Structure):
     _fields_ = [(n, C.c_void_p) for n in ("q", "k_cache", "v_cache", "k_tree", "v_tree", "out")]
+
+
+_LAYER_FIELDS = tuple(n for n, _ in AttentionLayer._fields_)
 
 
 def lpp_tree_attention_layers_workspace(tree: Tree, L: int, B: int, H: int, S: int, Dh: int) -> int:
@@ -180,11 +212,11 @@ def lpp_tree_attention_layers_workspace(tree: Tree, L: int, B: int, H: int, S: i
 def lpp_tree_attention_layers(tree: Tree, dtype: int, out_dtype: int, layers, seq_len, B: int, H: int, Hkv: int,
                               S: int, Dh: int, scale: float, ws, stream=None) -> None:
     """``layers``: a sequence of dicts with the tensors q, k_cache, v_cache, k_tree, v_tree, out of one layer each."""
-    arr = (AttentionLayer * len(layers))(*[AttentionLayer(**{n: _ptr(y.get(n)) for n, _ in AttentionLayer._fields_})
-                                           for y in layers])
-    _check(lib().lpp_tree_attention_layers(tree.handle, dtype, out_dtype, arr, len(layers), _ptr(seq_len), B, H, Hkv,
-                                           S, Dh, scale, _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(),
-                                           _stream(stream)), "lpp_tree_attention_layers")
+    table = struct.pack("%dP" % (len(_LAYER_FIELDS) * len(layers)),
+                        *[0 if (t := y.get(n)) is None else t.data_ptr() for y in layers for n in _LAYER_FIELDS])
+    _check(lib().lpp_tree_attention_layers(tree.handle, dtype, out_dtype, table, len(layers), _ptr(seq_len), B, H, Hkv,
+                                           S, Dh, scale, _ptr(ws), _bytes(ws), _stream(stream)),
+           "lpp_tree_attention_layers")
 
 
 def lpp_relaxed_verify_workspace(tree: Tree, B: int, V: int, k: int) -> int:
@@ -195,11 +227,10 @@ def lpp_relaxed_verify(tree: Tree, target_logits, drafter_logits, ldv: int, voca
                        B: int, tokens, neigh, kstride: int, k: int, lam: float, u_accept, u_final,
                        out: dict, ws, stream=None) -> None:
     """``out`` maps lpp_verify_out field names to tensors (missing / None = not wanted)."""
-    vo = VerifyOut(**{n: _ptr(out.get(n)) for n, _ in VerifyOut._fields_})
     _check(lib().lpp_relaxed_verify(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv, vocab_offset,
                                     V, B, _ptr(tokens), _ptr(neigh), kstride, k, lam, _ptr(u_accept),
-                                    _ptr(u_final), C.byref(vo), _ptr(ws),
-                                    0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)),
+                                    _ptr(u_final), _verify_out(out), _ptr(ws),
+                                    _bytes(ws), _stream(stream)),
            "lpp_relaxed_verify")
 
 
@@ -207,10 +238,9 @@ def lpp_relaxed_verify_static(tree: Tree, target_logits, drafter_logits, ldv: in
                               B: int, tokens, neigh, kstride: int, k: int, lam: float, u_accept, u_final,
                               out: dict, stream=None) -> None:
     """As lpp_relaxed_verify, without a workspace: the library's static device array holds the walk words."""
-    vo = VerifyOut(**{n: _ptr(out.get(n)) for n, _ in VerifyOut._fields_})
     _check(lib().lpp_relaxed_verify_static(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv, vocab_offset,
                                            V, B, _ptr(tokens), _ptr(neigh), kstride, k, lam, _ptr(u_accept),
-                                           _ptr(u_final), C.byref(vo), _stream(stream)),
+                                           _ptr(u_final), _verify_out(out), _stream(stream)),
            "lpp_relaxed_verify_static")
 
 
@@ -218,11 +248,10 @@ def lpp_relaxed_verify_additive(tree: Tree, target_logits, drafter_logits, ldv: 
                                 B: int, tokens, neigh, kstride: int, k: int, delta: float, u_accept, u_final,
                                 out: dict, ws, stream=None) -> None:
     """As lpp_relaxed_verify, under the additive bound ``sum_A r < delta``."""
-    vo = VerifyOut(**{n: _ptr(out.get(n)) for n, _ in VerifyOut._fields_})
     _check(lib().lpp_relaxed_verify_additive(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv,
                                              vocab_offset, V, B, _ptr(tokens), _ptr(neigh), kstride, k, delta,
-                                             _ptr(u_accept), _ptr(u_final), C.byref(vo), _ptr(ws),
-                                             0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)),
+                                             _ptr(u_accept), _ptr(u_final), _verify_out(out), _ptr(ws),
+                                             _bytes(ws), _stream(stream)),
            "lpp_relaxed_verify_additive")
 
 
@@ -241,12 +270,11 @@ def lpp_relaxed_verify_opts(tree: Tree, target_logits, drafter_logits, ldv: int,
                             stream=None, *, bound: int = 0, bound_value: float = 0.0, rule: int = 0,
                             siblings: int = 0, uncond_logits=None, cfg_scale: float = 0.0, top_k: int = 0) -> None:
     """lpp_relaxed_verify with the bound, the choice of A, the sibling scheme and the front end as options."""
-    vo = VerifyOut(**{n: _ptr(out.get(n)) for n, _ in VerifyOut._fields_})
     opts = VerifyOptions(bound, bound_value, rule, siblings, _ptr(uncond_logits), cfg_scale, top_k)
     _check(lib().lpp_relaxed_verify_opts(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv, vocab_offset,
                                          V, B, _ptr(tokens), _ptr(neigh), kstride, k, C.byref(opts),
-                                         _ptr(u_accept), _ptr(u_final), C.byref(vo), _ptr(ws),
-                                         0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)),
+                                         _ptr(u_accept), _ptr(u_final), _verify_out(out), _ptr(ws),
+                                         _bytes(ws), _stream(stream)),
            "lpp_relaxed_verify_opts")
 
 
@@ -262,12 +290,11 @@ def lpp_relaxed_verify_sampled(tree: Tree, cond_logits, uncond_logits, cfg_scale
                                kstride: int, k: int, lam: float, u_accept, u_final, out: dict, ws,
                                stream=None) -> None:
     """As lpp_relaxed_verify, with guidance and top-k applied to the target rows inside the kernel."""
-    vo = VerifyOut(**{n: _ptr(out.get(n)) for n, _ in VerifyOut._fields_})
     _check(lib().lpp_relaxed_verify_sampled(tree.handle, _ptr(cond_logits), _ptr(uncond_logits), cfg_scale, top_k,
                                             _ptr(drafter_logits), ldv, vocab_offset, V, B, _ptr(tokens),
                                             _ptr(neigh), kstride, k, lam, _ptr(u_accept), _ptr(u_final),
-                                            C.byref(vo), _ptr(ws),
-                                            0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)),
+                                            _verify_out(out), _ptr(ws),
+                                            _bytes(ws), _stream(stream)),
            "lpp_relaxed_verify_sampled")
 
 

@@ -52,8 +52,7 @@ extern "C" int32_t lpp_commit_kv(const lpp_tree* tree, int32_t dtype, const void
   const int esz = dtype == LPP_F32 ? 4 : 2;
   if ((Dh * esz) % 16 != 0) return LPP_EUNSUPPORTED;
   if ((int64_t)B * H > 0x7FFFFFFF) return LPP_EUNSUPPORTED;
-  int ndev = 0;
-  if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) { (void)hipGetLastError(); return LPP_EHIP; }
+  if (!tree->d_anc) return LPP_EHIP;                         // host-only handle: no device
   CommitArgs a;
   a.kt = (const unsigned char*)k_tree; a.vt = (const unsigned char*)v_tree;
   a.kc = (unsigned char*)k_cache; a.vc = (unsigned char*)v_cache;

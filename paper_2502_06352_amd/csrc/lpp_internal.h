@@ -19,6 +19,9 @@ struct lpp_tree {
   int32_t words = 0;         // 64-bit words per ancestor bitmask
   std::vector<int32_t> parent, row_depth, child_ptr, child_idx;
   std::vector<int32_t> heavy_first;  // rows by descending number of children (ties: ascending row)
+  // row table of the verify kernel, in that order: row | children << 8 | first child row << 16 |
+  // offset into child_idx << 24 (a kernel argument: made once here instead of on every call)
+  uint32_t rowinfo[LPP_MAX_ROWS] = {};
   std::vector<uint64_t> anc; // [M * words]
   // device copies (null for a host-only handle)
   int device = -1;

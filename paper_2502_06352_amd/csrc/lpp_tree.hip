@@ -56,6 +56,11 @@ extern "C" int32_t lpp_tree_create(const int32_t* parent_host, int32_t M, lpp_tr
   std::stable_sort(t->heavy_first.begin(), t->heavy_first.end(),
                    [&](int32_t x, int32_t y) { return cnt[x] > cnt[y]; });
   for (int32_t i = 0; i < M; ++i) {
+    const int32_t row = t->heavy_first[i], c0 = t->child_ptr[row], nc = cnt[row];
+    const int32_t first = nc > 0 ? t->child_idx[c0] : 0;
+    t->rowinfo[i] = (uint32_t)row | ((uint32_t)nc << 8) | ((uint32_t)first << 16) | ((uint32_t)(nc > 0 ? c0 : 0) << 24);
+  }
+  for (int32_t i = 0; i < M; ++i) {
     uint64_t* row = &t->anc[(size_t)i * t->words];
     if (i > 0)
       for (int32_t w = 0; w < t->words; ++w) row[w] = t->anc[(size_t)t->parent[i] * t->words + w];

@@ -39,7 +39,7 @@
 // The additive bound of the earlier LANTERN method is a run-time choice of the cap.
 #include <limits.h>
 #include <math.h>
-#include <stdlib.h>
+#include <string.h>
 
 #include <algorithm>
 #include <atomic>
@@ -1247,16 +1247,8 @@ int32_t relaxed_verify_impl(int32_t additive, int32_t skip, int32_t norepl, bool
   a.child_idx = tree->d_child_idx;
   a.consecutive = tree->consecutive_children ? 1 : 0;
   TreeTab tt;
-  for (int i = 0; i < LPP_MAX_ROWS; ++i) {
-    uint32_t ri = 0;
-    if (i < tree->M) {
-      const int32_t row = tree->heavy_first[i];
-      const int32_t c0 = tree->child_ptr[row], nc = tree->child_ptr[row + 1] - c0;
-      const int32_t first = nc > 0 ? tree->child_idx[c0] : 0;
-      ri = (uint32_t)row | ((uint32_t)nc << 8) | ((uint32_t)first << 16) | ((uint32_t)(nc > 0 ? c0 : 0) << 24);
-    }
-    tt.rowinfo[i] = ri;
-  }
+  static_assert(sizeof(tt.rowinfo) == sizeof(tree->rowinfo), "the handle holds the kernel's row table");
+  memcpy(tt.rowinfo, tree->rowinfo, sizeof(tt.rowinfo));
   // Whole grid resident at once (one block per compute unit, the plain step only): rows hold their
   // loads back by chain length and the walk needs no tickets (see the kernel).  With more blocks
   // than compute units the launch order, most children first, already staggers the rows; with a
