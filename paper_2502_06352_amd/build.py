@@ -12,6 +12,9 @@ LIB = os.path.join(HERE, "liblpp.so")
 SOURCES = ["lpp_tree.hip", "lpp_verify.hip", "lpp_attention.hip", "lpp_knn.hip", "lpp_commit.hip", "lpp_probe.hip"]
 FLAGS = ["-O3", "-ffp-contract=off", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # matrix results in vector registers: every kernel here works on them right away, and out of the
+         # accumulation registers each value costs a copy
+         "-mllvm", "-amdgpu-mfma-vgpr-form",
          "-Wall", "-Wno-unused-function", "-Wno-unknown-attributes", "-Wno-unused-command-line-argument"]
 
 

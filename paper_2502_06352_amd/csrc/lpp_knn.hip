@@ -3,33 +3,43 @@
 //
 // The result is defined by the float64 inner product (products added in index
 // order) with ties to the lower index, so it does not depend on how the matrix
-// cores round.  Three kernels:
-//   pack    zero-padded copy of the codebook (rows of DP floats, DP = 16..256 a power of two >= D), row
-//           norms and their maximum (for the rounding bound below).
-//   select  the dense V x V contraction on the matrix cores, swept twice per block of
-//           query codes and never written out: sweep 1 histograms each row's
-//           similarities into 1024 bins and finds the bin b* holding the (k-1)-th
-//           largest; sweep 2 appends every code whose bin is >= b* - 1 - m to the
-//           row's candidate list.  Rows of up to 16 floats: fp32 MFMA 16x16x4, 16
-//           queries per block, m = 0.  Longer rows: the sweeps are bound by streaming
-//           the codebook out of the last-level cache once per block and sweep, so they
-//           run on a bf16 copy of it (half the bytes, MFMA 16x16x32) with 32 queries
-//           per block (half the blocks), and m bins of margin make up for the rounding
-//           of the copy (see row_eps).
-//   rank    per row: exact float64 keys of the candidates (FMA chain in index
-//           order), rank by (key desc, index asc) with value buckets in LDS, write the row.
-// Why the candidate list is enough: a code that is not a candidate has an
-// approximate similarity below the lower edge e of the lowest bin taken, hence an exact
-// key below e + eps, eps bounding the rounding of the approximate similarity.  If the (k-1)-th exact key
-// among the candidates is >= e + eps, no outsider can belong to the row.  Rows
-// that fail this test, or overflow the candidate list, take an exact (slow)
-// radix-select path over all V codes instead.
+// cores round.  The V x V similarities are never written out and the float64 keys
+// are only formed where they decide something:
+//   stats    padded float32 copy of the codebook (and halves of short rows), norms, 1-norms, largest magnitude
+//   limbs    (rows of more than 16 floats) fixed-point image of the codebook as three
+//            8-bit limbs, in matrix-core fragment order
+//   sample   per row: histogram of its similarities with a hashed, stratified sample of
+//            about 4096 codes; the threshold is the sample's quantile at which, five
+//            standard deviations of the sample's share allowed, k - 1 codes lie above
+//   collect  the dense V x V contraction on the matrix cores, once: every code above the
+//            row's threshold is appended to its list as one 32-bit word, similarity
+//            (fixed point) over code index
+//   rank     per row: the list is sorted by its approximate similarities (value buckets in
+//            LDS); runs of entries whose similarities differ by less than twice the bound on
+//            their error are ordered by their exact float64 keys, everything else already is
+// Small codebooks of short rows (V <= kDirectCodes, D <= 16) take one kernel that does all of it.
+//
+// Why the list is enough: an outsider's similarity is at most threshold + e, e bounding the error of
+// an approximate similarity.  If the (k-1)-th largest approximate similarity of the list exceeds
+// the threshold by more than 2 e, the k - 1 largest all exceed every outsider.  Rows that fail this
+// test, overflow their list or hold fewer than k - 1 entries (a sample that misleads, heavy ties)
+// take an exact, slow radix select over all V codes instead.
+//
+// The approximate similarities and their bound e:
+//   rows of up to 16 floats: x = h + l in halves of 11 bits, h h' + l h' + h l' on the f16 matrix
+//   cores; what is left out is below 3 2^-22 |e_i| |e_j|, the sums are rounded by 2^-23 each.
+//   longer rows: x = q D + d with a 24-bit integer q = 2^16 a + 2^8 b + c (a, b, c signed 8-bit
+//   limbs), |d| <= D / 2, D = largest magnitude / (127 2^16).  All limb products but c c are summed
+//   exactly in int32 by the i8 matrix cores (eight MFMA 16x16x64 per 64 dimensions), so the only
+//   errors are the quantisation, D/2 (|e_i|_1 + |e_j|_1), and a few units of the last place kept.
+//   This is far tighter than what can be proved for fp32 accumulation of the same rows, at four times
+//   its rate; at unit rows of 256 floats about one entry in twenty needs its float64 key.
 #include <limits.h>
 #include <math.h>
 
-#include <type_traits>
-
+#include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "lpp_internal.h"
 
@@ -37,409 +47,658 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kBins = 1024;                   // the bf16 sweeps: two 16-bit counts per LDS word,
-constexpr float kBinScale = 512.0f;           // bin = floor((s + 1) * 512), clamped
-constexpr int kBinsF = 512;                   // the fp32 sweeps (rows of up to 16 floats, similarities spread
-constexpr float kBinScaleF = 256.0f;          // widely): 32-bit counts, bin = floor((s + 1) * 256), clamped
-constexpr int kSelWaves = 4;
-constexpr int kSelRows = 16;                  // query codes per select block
-constexpr int kSel2Waves = 8;                 // the bf16 sweeps: 8 waves and
-constexpr int kSel2Rows = 32;                 // 32 query codes per block
-constexpr int kRankThreads = 256;
-constexpr int kSlack = 1024;                  // candidate list = k - 1 + slack (rounded); rows of up to 16
-constexpr int kSlackShort = 512;              // floats spread their similarities widely: half of it
+constexpr int kShortRow = 16;                 // rows of up to this many floats: fp32 similarities
+constexpr int kDirectCodes = 1024;            // codebooks of short rows up to this size: one kernel
+constexpr int kSampleCodes = 4096;            // codes a row's threshold is estimated from
+constexpr int kSampleBins = 1024;             // bins of the estimate, [-|e_i| max|e_j|, +]
+constexpr int kSampleThreads = 1024;
+constexpr int kCollectWaves = 4;              // (long rows) waves per block
+constexpr int kStatBlocks = 128, kStatThreads = 1024;
+constexpr float kHalfScale = 4096.0f;         // short rows as halves: largest entry 15.9
+constexpr float kLimbRange = 8323072.0f;      // 127 * 2^16: the largest |q|
+
+// What the collecting kernel needs of a row: a code passes where d = similarity - thr is not negative, and
+// leaves min(d a, qmax) (short rows: in float32, in the units of the scaled halves; long rows: int32, units
+// of 2^24 unit^2).  E: entries whose left values differ by at most E may be in either order.
+struct RowPlan {
+  float a;
+  union { float thr; int32_t thr_u; };
+  int32_t E;
+  int32_t flags;                              // kAll: every code passes; kAnyNan: some code holds a NaN; kNoList: exact path
+};
+constexpr int kAll = 1, kAnyNan = 2, kNoList = 4;
+constexpr int kMaxSplits = 16;                // segments of a long row's list
 
 struct KnnArgs {
   const float* E;
-  int32_t V, D, DP, Vp, k, cap;
-  float* Ep;            // [Vp][DP]
-  uint16_t* Eh;         // [Vp][DP] bf16 (round to nearest even) of Ep, or null: the sweeps run in fp32
-  float bin_scale;      // bins per unit of similarity in the sweeps' histograms
-  float* norms;         // [Vp]
-  uint32_t* maxnorm;    // float bits
-  int32_t* bstar;       // [Vp] lowest bin whose codes became candidates
-  int32_t* cnt;         // [Vp]
-  uint16_t* cand;       // [V][cap]
+  int32_t V, D, k;
+  int32_t PD;           // floats per row of Ep: D rounded up to 4
+  int32_t Vp;           // V rounded up to 128
+  int32_t cap;          // entries a row's list holds
+  int32_t ib;           // index bits of a list word; 32 - ib value bits (at most 24)
+  int32_t vmask_bits;   // value bits
+  int32_t stride, ns, m;   // sample: one of every `stride` codes, ns in all, threshold at its m-th largest
+  int32_t take_all;     // the list takes every code
+  int32_t splits, cap_split;   // (long rows) segments of a row's list, one per block that collects for it, and their size
+  int32_t statblocks;
+  float* Ep;            // [V][PD]
+  i32x4* Ef;            // long rows: [Vp/16][KS][3 limbs][64 lanes] fragments
+                        // short rows: [Vp][2 N] pieces of 8 halves, the upper ones, then the lower ones
+  i32x4* Es;            // the sample's codes, packed: long rows [ns/16][KS][64 lanes] upper limbs, short rows [ns][2 N]
+  float* norms;         // [V]
+  float* l1;            // [V]
+  float4* part;         // [kStatBlocks]: max norm, max |x|, max 1-norm, any NaN
+  RowPlan* plan;        // [Vp]
+  int32_t* cnt;         // [V][splits]
+  uint32_t* cand;       // [V][cap]
   int32_t* neigh;       // [V][k]
 };
 
-__global__ void knn_init_kernel(KnnArgs a) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *a.maxnorm = 0u;
+struct Stats { float norm, mabs, l1, nan; };
+
+// Four halves of a short row's upper (h) and lower (l) parts, dimensions d .. d + 3; what lies behind them in
+// the piece of eight is zeroed by the lane that holds the row's last four.
+template <typename F4>
+__device__ __forceinline__ void put_halves(i32x4* base, int row, int n8, int d, F4 h, F4 l) {
+  F4* hp = reinterpret_cast<F4*>(base + (int64_t)row * 2 * n8) + d / 4;
+  F4* lp = reinterpret_cast<F4*>(base + (int64_t)row * 2 * n8 + n8) + d / 4;
+  *hp = h;
+  *lp = l;
 }
 
-// A wave per row, 16 rows per wave: padded copy, norm; one atomic per block for the max norm.
-constexpr int kPackRows = 64;   // rows per block of 4 waves
-__global__ __launch_bounds__(256) void knn_pack_kernel(KnnArgs a) {
-  __shared__ float s_max[4];
+// The four maxima over the stat kernel's blocks; every lane of the wave returns them.
+__device__ __forceinline__ Stats reduce_stats(const KnnArgs& a, int lane) {
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < kStatBlocks / 64; ++i) {
+    const float4 x = a.part[min(lane + 64 * i, a.statblocks - 1)];
+    v[0] = fmaxf(v[0], x.x); v[1] = fmaxf(v[1], x.y); v[2] = fmaxf(v[2], x.z); v[3] = fmaxf(v[3], x.w);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = fmaxf(v[q], __shfl_xor(v[q], o));
+  return Stats{v[0], v[1], v[2], v[3]};
+}
+
+// The sample: of every `stride` consecutive codes (a power of two) one, at a place that a hash of the
+// stratum picks, so that a codebook with an order of its own is sampled evenly.  Its number, or -1.
+__device__ __forceinline__ int sample_slot(const KnnArgs& a, int code) {
+  const int j = code / a.stride;
+  const uint32_t off = (((uint32_t)j * 2654435761u) >> 15) & (uint32_t)(a.stride - 1);
+  return j < a.ns && code == j * a.stride + (int)off ? j : -1;
+}
+
+// G lanes per row, 16 bytes per lane and step.
+template <int G>
+__global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
+  constexpr int W = kStatThreads / 64;
+  __shared__ float s_part[4][W];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float mx = 0.f;
-  for (int i = 0; i < kPackRows / 4; ++i) {
-    const int row = blockIdx.x * kPackRows + 4 * i + wave;
-    if (row >= a.Vp) break;
-    float ss = 0.f;
-    for (int d = lane; d < a.DP; d += 64) {
-      float v = 0.f;
-      if (row < a.V && d < a.D) v = a.E[(int64_t)row * a.D + d];
-      a.Ep[(int64_t)row * a.DP + d] = v;
-      if (a.Eh) {
-        const uint32_t u = __float_as_uint(v);
-        // round to nearest even on the upper 16 bits; NaN stays NaN (quiet bit set)
-        const uint32_t h = (u & 0x7FFFFFFFu) > 0x7F800000u ? ((u >> 16) | 0x40u) : ((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-        a.Eh[(int64_t)row * a.DP + d] = (uint16_t)h;
+  const int sub = threadIdx.x % G;
+  const bool vec = (a.D & 3) == 0 && (reinterpret_cast<uintptr_t>(a.E) & 15) == 0;
+  float mx[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int row = blockIdx.x * (kStatThreads / G) + threadIdx.x / G; row < a.V; row += gridDim.x * (kStatThreads / G)) {
+    const float* src = a.E + (int64_t)row * a.D;
+    float* dst = a.Ep + (int64_t)row * a.PD;
+    float ss = 0.f, sa = 0.f, mb = 0.f;
+    // (short rows: whole pieces of eight halves, zero past the row)
+    const int dend = G == 4 ? (a.D > 8 ? 16 : 8) : a.PD;
+    for (int d = 4 * sub; d < dend; d += 4 * G) {
+      float v[4];
+      if (vec && d < a.D) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(src + d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = x[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = d + e < a.D ? src[d + e] : 0.f;
       }
-      ss += v * v;
+      if (d < a.PD) *reinterpret_cast<f32x4*>(dst + d) = f32x4{v[0], v[1], v[2], v[3]};
+      if (G == 4) {
+        // 4096 x = h + l + rest: two halves of 11 bits each (rest: at most 2^-24 of it, or 2^-25)
+        typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+        f16x4 h, l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = v[e] * kHalfScale;
+          h[e] = (_Float16)x;
+          l[e] = (_Float16)(x - (float)h[e]);
+        }
+        const int n8 = a.D > 8 ? 2 : 1;                     // pieces of 8 halves per part
+        put_halves(a.Ef, row, n8, d, h, l);
+        const int j = sample_slot(a, row);
+        if (j >= 0) put_halves(a.Es, j, n8, d, h, l);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        ss += v[e] * v[e];
+        sa += fabsf(v[e]);
+        mb = fmaxf(mb, fabsf(v[e]));
+      }
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    for (int o = G / 2; o > 0; o >>= 1) {
+      ss += __shfl_xor(ss, o);
+      sa += __shfl_xor(sa, o);
+      mb = fmaxf(mb, __shfl_xor(mb, o));
+    }
     const float n = sqrtf(ss);
-    if (lane == 0) a.norms[row] = n;
-    if (row < a.V) mx = fmaxf(mx, n);
+    if (sub == 0) { a.norms[row] = n; a.l1[row] = sa; }
+    // (a row that holds a NaN has a NaN norm and takes no part in the maxima)
+    const bool bad = !(n == n);
+    mx[0] = fmaxf(mx[0], n);
+    mx[1] = fmaxf(mx[1], bad ? 0.f : mb);
+    mx[2] = fmaxf(mx[2], sa);
+    mx[3] = fmaxf(mx[3], bad ? 1.f : 0.f);
   }
-  if (lane == 0) s_max[wave] = mx;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) mx[q] = fmaxf(mx[q], __shfl_xor(mx[q], o));
+  if (lane == 0)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s_part[q][wave] = mx[q];
   __syncthreads();
-  if (threadIdx.x == 0)
-    atomicMax(a.maxnorm, __float_as_uint(fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]))));
+  if (threadIdx.x < 4) {
+    const int q = threadIdx.x;
+    float m = s_part[q][0];
+#pragma unroll
+    for (int w = 1; w < W; ++w) m = fmaxf(m, s_part[q][w]);
+    reinterpret_cast<float*>(a.part + blockIdx.x)[q] = m;
+  }
 }
 
-// Bound on |approximate - exact| similarity of row i with any code.  fp32 sweeps: the matrix
-// core's additions, (DP + 4) roundings of 2^-23 on sums of at most |e_i| |e_j|.  bf16 sweeps: each
-// operand carries a relative rounding of 2^-9, so each product one of 2^-8 + 2^-18 (the products
-// themselves are exact in fp32), summed: (2^-8 + 2^-18) sum |e_i,t e_j,t| <= that times |e_i| |e_j|;
-// plus the additions as before.  2.5e-7 covers the rounding of the bin map.
-__device__ __forceinline__ float row_eps(const KnnArgs& a, int i) {
-  const float add = (float)(a.DP + 4) * 1.1920929e-07f;
-  const float rel = a.Eh ? 0.00390625f * 1.01f + add : add;
-  return rel * a.norms[i] * __uint_as_float(*a.maxnorm) * 1.001f + 2.5e-7f;
-}
-// Bins of margin below b* - 1 that the candidates of row i take in.  The (k-1)-th largest
-// approximate similarity lies in bin b*, so the (k-1)-th exact key of the candidates is at least
-// b*'s lower edge less eps; the rank kernel's test wants it eps above the lower edge of the lowest
-// bin taken, b* - 1 - m: (1 + m) bins >= 2 eps.  (Huge for rows whose eps is: everything is taken.)
-__device__ __forceinline__ int row_margin(const KnnArgs& a, int i) {
-  if (!a.Eh) return 0;
-  const float m = ceilf(2.0f * row_eps(a, i) * a.bin_scale - 1.0f);
-  return m < (float)kBins ? (m > 0.f ? (int)m : 0) : kBins;      // (NaN norms: kBins)
+// Unit of the fixed-point image (as a double: q = round(x / unit) is then exact to half a unit).
+__device__ __forceinline__ double limb_unit(float mabs) {
+  return mabs > 0.f && mabs < INFINITY ? (double)mabs / (double)kLimbRange : 1.0;
 }
 
-// b* of one row's histogram (two 16-bit counts per word): the highest bin whose count from the top
-// reaches kk, 0 if none does.  One wave; every lane returns it.
-__device__ __forceinline__ int find_bstar(const uint32_t* h, int kk, int lane) {
-  // lane covers bins [1023 - 16*lane - 15, 1023 - 16*lane], scanned downwards
-  int cntv[16];
-  int local = 0;
+// One lane per (tile of 16 codes, step of 64 dimensions, fragment lane): 16 dimensions of one code.
+template <int KS>
+__global__ __launch_bounds__(256) void knn_limb_kernel(KnnArgs a) {
+  const Stats st = reduce_stats(a, threadIdx.x & 63);
+  const int idx = blockIdx.x * 256 + threadIdx.x;            // (the grid covers Vp/16 * KS * 64 lanes exactly)
+  const int lane = idx & 63, ks = (idx >> 6) % KS, tile = (idx >> 6) / KS;
+  const int row = tile * 16 + (lane & 15), d0 = ks * 64 + (lane >> 4) * 16;
+  const double inv = 1.0 / limb_unit(st.mabs);
+  const bool ok = row < a.V && a.norms[min(row, a.V - 1)] == a.norms[min(row, a.V - 1)];
+  uint32_t limb[3][4];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const uint32_t w = h[(kBins / 2 - 1) - 8 * lane - j];   // bins (hi, lo) = (odd, even)
-    cntv[2 * j] = (int)(w >> 16);
-    cntv[2 * j + 1] = (int)(w & 0xFFFFu);
-    local += cntv[2 * j] + cntv[2 * j + 1];
-  }
-  int incl = local;
+  for (int c = 0; c < 4; ++c) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    if (ok && d0 + 4 * c < a.PD) x = *reinterpret_cast<const f32x4*>(a.Ep + (int64_t)row * a.PD + d0 + 4 * c);
+    uint32_t wa = 0, wb = 0, wc = 0;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(incl, o);
-    if (lane >= o) incl += t;
-  }
-  const unsigned long long bal = __ballot(incl >= kk);
-  int bs = 0;
-  if (bal) {
-    const int fl = __ffsll((long long)bal) - 1;
-    int run = __shfl(incl - local, fl);
-    int found = 0;
-    if (lane == fl) {
-      found = kBins - 1 - 16 * lane - 15;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        run += cntv[j];
-        if (run >= kk) { found = kBins - 1 - 16 * lane - j; break; }
-      }
+    for (int e = 0; e < 4; ++e) {
+      const double r = fmin(fmax((double)x[e] * inv, -(double)kLimbRange), (double)kLimbRange);
+      const int q = (int)rint(r);
+      const int lc = ((q + 128) & 255) - 128, q1 = (q - lc) >> 8;
+      const int lb = ((q1 + 128) & 255) - 128, la = (q1 - lb) >> 8;      // |la| <= 127
+      wa |= (uint32_t)(la & 255) << (8 * e);
+      wb |= (uint32_t)(lb & 255) << (8 * e);
+      wc |= (uint32_t)(lc & 255) << (8 * e);
     }
-    bs = __shfl(found, fl);
+    limb[0][c] = wa; limb[1][c] = wb; limb[2][c] = wc;
   }
-  return bs;
+  i32x4* dst = a.Ef + ((int64_t)(tile * KS + ks) * 3) * 64 + lane;
+#pragma unroll
+  for (int l = 0; l < 3; ++l) dst[64 * l] = i32x4{(int)limb[l][0], (int)limb[l][1], (int)limb[l][2], (int)limb[l][3]};
+  const int j = row < a.V ? sample_slot(a, row) : -1;
+  if (j >= 0) a.Es[(int64_t)((j >> 4) * KS + ks) * 64 + (lane & 48) + (j & 15)] = dst[0];
 }
 
-// b* of one row's histogram of kBinsF 32-bit counts, as find_bstar.
-__device__ __forceinline__ int find_bstar32(const uint32_t* h, int kk, int lane) {
-  // lane covers bins [511 - 8*lane - 7, 511 - 8*lane], scanned downwards
-  int cntv[8];
-  int local = 0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    cntv[j] = (int)h[(kBinsF - 1) - 8 * lane - j];
-    local += cntv[j];
+// Short rows on the f16 matrix cores: x = h + l, and h h' + l h' + h l' of up to 8 N dimensions take N
+// MFMA of 32 (16 cycles each and beside the vector instructions; the fp32 MFMA takes 32 cycles per 4
+// dimensions and competes with them).  Slot g of the first MFMA: N = 1: h l h - of the code against
+// h h l 0 of the query; N = 2: h0 h1 l0 l1 against h0 h1 h0 h1, and in the second h0 h1 - - against
+// l0 l1 0 0 (- : any of the code's own numbers).
+template <int N>
+struct HalfOperand {
+  f16x8 x[N];
+  __device__ __forceinline__ void load_code(const i32x4* row, int g4) {
+    x[0] = __builtin_bit_cast(f16x8, row[N == 1 ? (g4 == 1 ? 1 : 0) : g4]);
+    if (N == 2) x[N - 1] = __builtin_bit_cast(f16x8, row[g4 & 1]);
   }
-  int incl = local;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(incl, o);
-    if (lane >= o) incl += t;
-  }
-  const unsigned long long bal = __ballot(incl >= kk);
-  int bs = 0;
-  if (bal) {
-    const int fl = __ffsll((long long)bal) - 1;
-    int run = __shfl(incl - local, fl);
-    int found = 0;
-    if (lane == fl) {
-      found = kBinsF - 1 - 8 * lane - 7;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        run += cntv[j];
-        if (run >= kk) { found = kBinsF - 1 - 8 * lane - j; break; }
-      }
+  __device__ __forceinline__ void load_query(const i32x4* row, int g4) {
+    const i32x4 zero = {0, 0, 0, 0};
+    if (N == 1) {
+      x[0] = __builtin_bit_cast(f16x8, g4 == 3 ? zero : row[g4 == 2 ? 1 : 0]);
+    } else {
+      x[0] = __builtin_bit_cast(f16x8, row[g4 & 1]);
+      x[N - 1] = __builtin_bit_cast(f16x8, g4 >= 2 ? zero : row[2 + g4]);
     }
-    bs = __shfl(found, fl);
   }
-  return bs;
-}
+  __device__ __forceinline__ f32x4 times(const HalfOperand& q, f32x4 acc) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[i], q.x[i], acc, 0, 0, 0);
+    return acc;
+  }
+};
 
-// The sweeps in fp32, for rows of up to 16 floats (DP = 16: one float4 per lane and code).
-// Contraction slot (step, g) of the 16x16x4 MFMA is dimension 4*g + step on both operands.
-// A block owns 16 query codes; its 4 waves take the code tiles (16 codes each) in turn and share
-// the rows' histograms in LDS, so that a compute unit holds many waves and the latency of the
-// tile loads (served by L2: the codebook is small) is covered.  U tiles are in flight per wave.
-// The sweeps are bound by the instructions issued per similarity: tiles that hold neither the
-// queries' own codes nor padding (all but two) take a path with no test and no branch per
-// similarity, and a similarity costs a multiply-add, a convert, a clamp, an address and the LDS add.
-__global__ __launch_bounds__(kSelWaves * 64) void knn_select_f32_kernel(KnnArgs a) {
-  constexpr int U = 4;
-  extern __shared__ uint32_t s_hist[];          // [kSelRows][kBinsF]
-  __shared__ int s_cnt[kSelRows];
-  __shared__ int s_low[kSelRows];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (tile numbers stay scalar)
+// Histogram of 16 rows' similarities with the sample, the threshold bin of each row, and its plan.
+// N: pieces of 8 dimensions (short rows, FIXED = false) or steps of 64 limbs (FIXED).  The
+// histogram is laid out bin by bin with the 16 rows side by side, so the 64 lanes of an LDS add,
+// four per row, meet in at most a few banks: [bins][16] counts, 64 KB, two
+// blocks per compute unit.  (With rows of bins one after the other the adds collide at random and a
+// wave-wide add takes about 29 cycles.)
+template <bool FIXED, int N>
+__global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a) {
+  extern __shared__ __align__(16) uint32_t s_hist[];      // [kSampleBins][16]
+  constexpr int SEG = kSampleThreads / 16, SW = kSampleBins / SEG;   // segments of the bins, bins of each
+  __shared__ int s_seg[kSampleThreads / 64][16];           // counts of a wave's segments, per row
+  __shared__ int s_top[16], s_bin[16];
+  constexpr int W = kSampleThreads / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
-  const int row0 = blockIdx.x * kSelRows;               // the block's 16 query codes
-  const int qrow = row0 + l16;                          // the lane's query code (B operand column)
-  const int V = a.V;
-  const int kk = a.k - 1;                               // neighbours besides the code itself
-  const int ntiles = a.Vp / 16;
-  const int own_tile = row0 / 16, full_tiles = (row0 + kSelRows <= V) ? V / 16 : 0;   // plain: t != own_tile && t < full_tiles
+  const int row0 = blockIdx.x * 16, row = row0 + l16, rowc = min(row, a.V - 1);
+  const Stats st = reduce_stats(a, lane);
+  const float norm = a.norms[rowc];
+  const float top = norm * st.norm * 1.0001f;              // |similarity| stays below
+  const double unit = FIXED ? limb_unit(st.mabs) : 1.0 / kHalfScale;
+  // one step of the histogram's argument: products of scaled halves, or of upper limbs (2^32 unit^2)
+  const float to_sim = (float)(FIXED ? unit * unit * 4294967296.0 : unit * unit);
+  const bool finite = top > 0.f && top < INFINITY && (FIXED || st.mabs * kHalfScale < 65504.0f);
+  const float bscale = finite ? (kSampleBins / 2) * to_sim / top : 0.f;
 
-  const f32x4 qv = *reinterpret_cast<const f32x4*>(a.Ep + (int64_t)qrow * 16 + 4 * g4);
-
-  for (int i = threadIdx.x; i < kSelRows * kBinsF; i += kSelWaves * 64) s_hist[i] = 0u;
-  if (threadIdx.x < kSelRows) s_cnt[threadIdx.x] = 0;
-  __syncthreads();
-
-  // second sweep: candidates are the codes with x >= thr (bin >= the lowest bin taken; -inf takes
-  // everything that is a number).  x = (s + 1) * 256 is the bin before truncation and the map is
-  // monotone, so the second sweep compares floats.
-  float thr = -INFINITY;
-  const float* lane_row = a.Ep + (int64_t)l16 * 16 + 4 * g4;
-  uint32_t* my_hist = s_hist + l16 * kBinsF;
-  auto sweep = [&](auto phase_tag) {
-    constexpr int PHASE = decltype(phase_tag)::value;
-    for (int t0 = wave; t0 < ntiles; t0 += kSelWaves * U) {
-      f32x4 av[U];
+  if (!a.take_all) {
+    for (int i = tid; i < kSampleBins * 4; i += kSampleThreads) reinterpret_cast<uint4*>(s_hist)[i] = make_uint4(0, 0, 0, 0);
+    if (tid < 16) { s_top[tid] = 0; s_bin[tid] = 0; }
+    __syncthreads();
+    const int ntiles = (a.ns + 15) / 16;
+    auto add = [&](float v) {
+      const uint32_t bin = min((uint32_t)__builtin_fmaf(v, bscale, kSampleBins / 2), kSampleBins - 1u);   // (negative, NaN: 0)
+      atomicAdd(&s_hist[bin * 16 + l16], 1u);
+    };
+    // (codes past the sample's end are not counted)
+    auto count = [&](float x0, float x1, float x2, float x3, int t) {
+      const float x[4] = {x0, x1, x2, x3};
+      if ((t + 1) * 16 <= a.ns) {                          // uniform
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int t = min(t0 + kSelWaves * u, ntiles - 1);      // (past the end: a re-read that is not used)
-        av[u] = *reinterpret_cast<const f32x4*>(lane_row + (int64_t)t * 256);
+        for (int r = 0; r < 4; ++r) add(x[r]);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (t * 16 + 4 * g4 + r < a.ns) add(x[r]);
       }
+    };
+    constexpr int U = FIXED && N >= 3 ? 1 : (FIXED && N == 2 ? 2 : 4);
+    if constexpr (FIXED) {
+      i32x4 q[N];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][0], qv[0], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][1], qv[1], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][2], qv[2], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][3], qv[3], acc, 0, 0, 0);
-        const int t = t0 + kSelWaves * u;
-        if (t >= ntiles) continue;
-        // lane holds sim(code 16 t + 4*g4 + r, query qrow), r = 0..3
-        float x[4];
+      for (int ks = 0; ks < N; ++ks) q[ks] = a.Ef[((int64_t)(blockIdx.x * N + ks) * 3) * 64 + lane];
+      for (int t0 = wave; t0 < ntiles; t0 += W * U) {
+        i32x4 f[U][N];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) x[r] = __builtin_fmaf(acc[r], kBinScaleF, kBinScaleF);
-        const bool plain = t != own_tile && t < full_tiles;    // uniform
-        if (PHASE == 0) {
-          if (plain) {
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-              atomicAdd(&my_hist[min(max((int)x[r], 0), kBinsF - 1)], 1u);     // (int) truncates and sends NaN to 0
-          } else {
+          for (int ks = 0; ks < N; ++ks) f[u][ks] = a.Es[(min(t0 + W * u, ntiles - 1) * N + ks) * 64 + lane];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int code = t * 16 + 4 * g4 + r;
-              if (!(code >= V || code == qrow || qrow >= V)) atomicAdd(&my_hist[min(max((int)x[r], 0), kBinsF - 1)], 1u);
-            }
-          }
-        } else {
-          bool pass[4];
+        for (int u = 0; u < U; ++u) {
+          i32x4 acc = {0, 0, 0, 0};
 #pragma unroll
-          for (int r = 0; r < 4; ++r) pass[r] = x[r] >= thr;
-          if (!plain) {
+          for (int ks = 0; ks < N; ++ks) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[u][ks], q[ks], acc, 0, 0, 0);
+          if (t0 + W * u < ntiles) count((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3], t0 + W * u);
+        }
+      }
+    } else {
+      HalfOperand<N> q;
+      q.load_query(a.Ef + (int64_t)rowc * 2 * N, g4);
+      for (int t0 = wave; t0 < ntiles; t0 += W * U) {
+        HalfOperand<N> f[U];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int code = t * 16 + 4 * g4 + r;
-              pass[r] = pass[r] && !(code >= V || code == qrow || qrow >= V);
-            }
-          }
-          if (__ballot(pass[0] || pass[1] || pass[2] || pass[3])) {   // about one code in sixteen passes
+        for (int u = 0; u < U; ++u) f[u].load_code(a.Es + (int64_t)min((t0 + W * u) * 16 + l16, a.ns - 1) * 2 * N, g4);
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (pass[r]) {
-                const int pos = atomicAdd(&s_cnt[l16], 1);
-                if (pos < a.cap) a.cand[(int64_t)qrow * a.cap + pos] = (uint16_t)(t * 16 + 4 * g4 + r);
-              }
-          }
+        for (int u = 0; u < U; ++u) {
+          const f32x4 acc = f[u].times(q, f32x4{0.f, 0.f, 0.f, 0.f});
+          if (t0 + W * u < ntiles) count(acc[0], acc[1], acc[2], acc[3], t0 + W * u);
         }
       }
     }
-  };
-  sweep(std::integral_constant<int, 0>());
-  __syncthreads();
-  // lowest bin taken, per row: b* - 1, b* the highest bin whose count from the top reaches kk; a wave takes 4 rows
-  for (int r = wave * (kSelRows / kSelWaves); r < (wave + 1) * (kSelRows / kSelWaves); ++r) {
-    const int bs = find_bstar32(s_hist + r * kBinsF, kk, lane);
-    if (lane == 0) {
-      s_low[r] = bs - 1;
-      if (row0 + r < a.Vp) a.bstar[row0 + r] = bs - 1;
+    __syncthreads();
+    // thread (row, segment of bins): its count, then the segment the m-th largest lies in.  A wave
+    // holds four segments of every row: sums over the waves go through LDS, inside a wave over lanes.
+    const int hr = tid & 15, seg = tid >> 4;
+    int local = 0, high = -1;
+#pragma unroll
+    for (int i = 0; i < SW; ++i) {
+      const uint32_t c = s_hist[(seg * SW + i) * 16 + hr];
+      local += (int)c;
+      if (c) high = SW * seg + i;
     }
+    int above = 0;                                         // counts of the segments above mine
+    {
+      const int x1 = __shfl_down(local, 16), x2 = __shfl_down(local, 32), x3 = __shfl_down(local, 48);
+      above = (g4 < 3 ? x1 : 0) + (g4 < 2 ? x2 : 0) + (g4 < 1 ? x3 : 0);
+      if (g4 == 0) s_seg[wave][hr] = above + local;
+    }
+    if (high >= 0) atomicMax(&s_top[hr], high);
+    __syncthreads();
+    for (int w = wave + 1; w < W; ++w) above += s_seg[w][hr];
+    if (above < a.m && a.m <= above + local) {
+      int i = SW - 1;
+      for (; i > 0; --i) {
+        above += (int)s_hist[(seg * SW + i) * 16 + hr];
+        if (above >= a.m) break;
+      }
+      s_bin[hr] = SW * seg + i;
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  thr = s_low[l16] <= 0 ? -INFINITY : (float)s_low[l16];      // (bin 0 also holds what is below -1)
-  sweep(std::integral_constant<int, 1>());
-  __syncthreads();
-  if (threadIdx.x < kSelRows && row0 + threadIdx.x < a.Vp) a.cnt[row0 + threadIdx.x] = s_cnt[threadIdx.x];
+  if (tid >= 16) return;
+
+  // ---- the row's plan (lane = row)
+  RowPlan p;
+  const int vb = a.vmask_bits;
+  const float qmax = (float)((1u << vb) - 2u);
+  const bool all = a.take_all || !finite;
+  float thr, hi;
+  if (all) {
+    thr = finite ? -top : 0.f;
+    hi = finite ? top : 1.f;
+  } else {
+    // (bin 0 also holds what lies below the range)
+    const float width = top / (kSampleBins / 2);
+    thr = s_bin[tid] > 0 ? (float)(s_bin[tid] - kSampleBins / 2) * width : -top;
+    hi = (float)(s_top[tid] + 1 - kSampleBins / 2) * width;
+    hi = fminf(hi + 0.125f * (hi - thr), top);
+    hi = fmaxf(hi, thr + 0.25f * width);
+  }
+  // rounding bound of an approximate similarity
+  float e;
+  if (FIXED) {
+    const double u = unit;
+    const double trunc = 3.0 * 16777216.0 * u * u;         // cut low parts: below three units of the value kept
+    e = (float)(0.5005 * u * ((double)a.l1[rowc] + (double)st.l1) * 1.001 + a.D * u * u + trunc);
+  } else {
+    // 32 N products on top of the threshold, each sum rounded by 2^-23; l l' and what the halves leave of
+    // each number: 3 2^-22, or 2^-25 of the scaled number
+    e = (float)(32 * N + 6) * 1.1920929e-07f * (norm * st.norm + fabsf(thr)) * 1.001f + 7.2e-07f * norm * st.norm +
+        2.9802322e-08f / kHalfScale * (a.l1[rowc] + st.l1) * 1.001f + 1e-30f;
+  }
+  e += norm * st.norm * 1e-9f;
+  float range = hi - thr;
+  // below the bin's edge by more than the test at the end asks of the (k-1)-th entry
+  const float slack = 2.2f * e + 6.0f * range / qmax;
+  thr -= slack;
+  range += slack;
+  p.flags = (all ? kAll : 0) | (st.nan > 0.f ? kAnyNan : 0) | (finite ? 0 : kNoList);
+  const double uu = FIXED ? unit * unit * 16777216.0 : unit * unit;      // real value of one unit of d
+  p.a = (float)((double)qmax / ((double)range / uu));
+  if (FIXED) p.thr_u = (int)fmin(fmax(floor((double)thr / uu), -1073741824.0), 1073741823.0);
+  else p.thr = (float)((double)thr / uu);
+  // (values are floors of products rounded by less than a tenth)
+  p.E = (int)fmin(floor(2.002 * (double)e * (double)qmax / (double)range + 0.2) + 1.0, 1073741824.0);
+  if (row >= a.V || !finite) {                              // nothing passes
+    p.a = 0.f;
+    if (FIXED) p.thr_u = 1 << 30;
+    else p.thr = INFINITY;
+  }
+  if (!(e < INFINITY)) p.E = 1 << 30;
+  a.plan[row] = p;
 }
 
-// The sweeps on the bf16 copy of the codebook.  KS = contraction steps of 32 (DP = 32 * KS).
-// A block owns 32 query codes -- two B operands per wave, so a code tile that was loaded feeds two
-// MFMA chains -- and its 8 waves take the code tiles (16 codes each) in turn; U tiles are in flight
-// per wave.  Slot (g, e) of a step is dimension 32*step + 8*g + e on both operands.
-template <int KS>
-__global__ __launch_bounds__(kSel2Waves * 64) void knn_select_bf16_kernel(KnnArgs a) {
-  constexpr int U = KS >= 8 ? 2 : 4;
-  extern __shared__ uint32_t s_hist[];          // [kSel2Rows][kBins/2], two 16-bit counts per word
-  __shared__ int s_cnt[kSel2Rows];
-  __shared__ int s_low[kSel2Rows];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (tile numbers stay scalar)
-  const int l16 = lane & 15, g4 = lane >> 4;
-  const int row0 = blockIdx.x * kSel2Rows;              // the block's 32 query codes (Vp is a multiple of 64)
-  const int DP = a.DP, V = a.V;
-  const int kk = a.k - 1;
-  const int ntiles = a.Vp / 16;
+// What both collecting kernels do with the similarities they form: a lane holds four of one row per
+// code tile, less the row's threshold (which the sums start from).  It parks them in LDS as they are (one
+// 16-byte write, nothing else leaves the registers) and shifts their sign bits into a mask, one
+// instruction each.  After a window of tiles the lanes take the clear bits of their masks and write
+// the list words.  (With one LDS write per similarity, to a ring that only moved on where a
+// similarity passed, the kernel was bound by issuing those writes.)
+__device__ __forceinline__ uint32_t shift_in_sign(uint32_t mask, int d) { return __builtin_amdgcn_alignbit(mask, (uint32_t)d, 31); }
 
-  bf16x8 qv[2][KS];
+// mask: bit 31 - s set where similarity s of the window passes; tile s >> 2, parked at [tile][lane][s & 3].
+// `at`: where the lane's entries go in cand, `room` of them at most.
+template <typename Value>
+__device__ __forceinline__ void emit_window(const KnnArgs& a, uint32_t mask, const uint32_t* parked, uint32_t code0, uint32_t tile_step,
+                                            int lane, uint32_t at, int room, Value value) {
+  const uint32_t* mine = parked + lane * 4;
+  const uint32_t end = at + (uint32_t)max(room, 0), qmax = (1u << a.vmask_bits) - 2u;
+  while (__any(mask != 0u)) {
+    if (mask != 0u) {
+      const uint32_t s = __builtin_clz(mask), hi = s >> 2, lo = s & 3;
+      mask &= ~(0x80000000u >> s);
+      const uint32_t v = min(value(mine[hi * 256 + lo]), qmax);
+      const uint32_t code = __umul24(hi, tile_step) + code0;
+      if (at < end) a.cand[at] = (v << a.ib) | code | lo;
+      ++at;
+    }
+  }
+}
+
+// Short rows: a block owns 16 queries, its waves (as many as fill the chip) take the code tiles (16
+// codes) in turn.
+constexpr int kCollectMaxWaves = 16;
+template <int N>
+__global__ __launch_bounds__(kCollectMaxWaves * 64) void knn_collect_f16_kernel(KnnArgs a) {
+  constexpr int T = 8;                                     // tiles per window: 32 similarities, 32 bits
+  extern __shared__ __align__(16) uint32_t s_park[];       // [wave][T][64 lanes][4]
+  __shared__ int s_cnt[16];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int row = blockIdx.x * 16 + l16, rowc = min(row, a.V - 1);
+  const RowPlan p = a.plan[row];
+  const int ntiles = (a.V + 15) >> 4;
+  const float c0 = -p.thr;
+  HalfOperand<N> q;
+  q.load_query(a.Ef + (int64_t)rowc * 2 * N, g4);
+  if (threadIdx.x < 16) s_cnt[threadIdx.x] = 0;
+  __syncthreads();
+  uint32_t* const parked = s_park + wave * (T * 256);
+  const uint32_t list = (uint32_t)rowc * (uint32_t)a.cap;
+  const int step = blockDim.x >> 6;
+  // (tile numbers past the end are clamped: read again, not used; rows V .. Vp - 1 are there, whatever
+  // they hold: their codes are dropped when the list is ranked)
+  const i32x4* const lane_row = a.Ef + l16 * 2 * N;
+  auto load = [&](HalfOperand<N> (&f)[4], int t0) {
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt)
+    for (int u = 0; u < 4; ++u) f[u].load_code(lane_row + (int64_t)min(t0 + step * u, ntiles - 1) * (32 * N), g4);
+  };
+  HalfOperand<N> f[4];
+  load(f, wave);
+  for (int t0 = wave; t0 < ntiles; t0 += step * T) {
+    uint32_t fail = 0;
+#pragma unroll
+    for (int h = 0; h < T; h += 4) {
+      f32x4 acc[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc[u] = f[u].times(q, f32x4{c0, c0, c0, c0});
+      load(f, t0 + step * (h + 4));
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        *reinterpret_cast<f32x4*>(parked + ((h + u) * 64 + lane) * 4) = acc[u];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) fail = shift_in_sign(fail, __float_as_int(acc[u][r]));
+      }
+    }
+    // tiles past the end: their bits are the last ones
+    uint32_t mask = ~fail;
+    if (t0 + step * (T - 1) >= ntiles) mask &= ~(0xFFFFFFFFu >> (4 * ((ntiles - t0 + step - 1) / step)));      // uniform
+    const int n = __popc(mask);
+    const int base = n > 0 ? atomicAdd(&s_cnt[l16], n) : 0;
+    emit_window(a, mask, parked, (uint32_t)(t0 * 16 + 4 * g4), (uint32_t)(16 * step), lane, list + base,
+                row < a.V ? a.cap - base : 0, [&](uint32_t v) { return (uint32_t)(__uint_as_float(v) * p.a); });
+  }
+  __syncthreads();
+  if (threadIdx.x < 16 && blockIdx.x * 16 + threadIdx.x < a.V) a.cnt[blockIdx.x * 16 + threadIdx.x] = s_cnt[threadIdx.x];
+}
+
+// Long rows, fixed point: a wave owns 32 queries (two B operands, held in registers with all their
+// limbs), a block's four waves 128.  Code tiles come through LDS, fragment by fragment as they lie
+// in memory, one copy for the four waves (each limb fragment read feeds 32 queries), the next two
+// chunks' loads in flight while one is worked on.  Two blocks per compute unit.  The code tiles are
+// dealt to `splits` blocks, each with a segment of its own in a row's list: where an entry goes is
+// known without asking anybody (a counter per row in memory makes the wave wait for it, and the other
+// three for that wave at the next barrier).  8192 rows of 256: 134 us, matrix cores busy 46 % of it (the
+// similarities alone, in bf16 and twice over, took 259 us and told less).
+template <int KS>
+__global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(KnnArgs a) {
+  constexpr int T = 4;                                     // tiles per window: 16 similarities per row and lane
+  constexpr int CT = KS == 1 ? 4 : (KS == 2 ? 2 : 1);      // code tiles per chunk
+  constexpr int TQ = KS * 3 * 64;                          // 16-byte pieces per tile
+  constexpr int CQ = CT * TQ;                              // ... per chunk
+  constexpr int NTHR = kCollectWaves * 64;
+  static_assert(CQ % 64 == 0 && T % CT == 0, "chunks end with windows");
+  constexpr int PER = (CQ + NTHR - 1) / NTHR;
+  __shared__ i32x4 s_code[2][CQ];
+  __shared__ i32x4 s_park[kCollectWaves][2][T * 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int group = blockIdx.x / a.splits, split = blockIdx.x - group * a.splits;
+  const int qtile = group * (kCollectWaves * 2) + wave * 2;
+  const int ntiles = (a.V + 15) >> 4;
+  const i32x4* const Ef = a.Ef;
+  int start[2], out[2] = {0, 0};                             // out: places of the row's segment taken (by all its lanes)
+  float scale[2];
+  uint32_t list[2];
+  i32x4 q[2][KS][3];
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+    const int row = (qtile + n) * 16 + l16;
+    const RowPlan p = a.plan[row];                         // (rows past V: nothing passes)
+    start[n] = -p.thr_u; scale[n] = p.a;
+    list[n] = ((uint32_t)min(row, a.V - 1) * (uint32_t)a.splits + (uint32_t)split) * (uint32_t)a.cap_split;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      qv[qt][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(
-          a.Eh + (int64_t)(row0 + 16 * qt + l16) * DP + 32 * ks + 8 * g4));
-
-  for (int i = threadIdx.x; i < kSel2Rows * (kBins / 2); i += kSel2Waves * 64) s_hist[i] = 0u;
-  if (threadIdx.x < kSel2Rows) s_cnt[threadIdx.x] = 0;
-  __syncthreads();
-
-  float thr[2] = {-INFINITY, -INFINITY};   // second sweep: x >= thr; -inf takes everything that is a number
-  const uint16_t* lane_row = a.Eh + (int64_t)l16 * DP + 8 * g4;
-  auto sweep = [&](auto phase_tag) {
-    constexpr int PHASE = decltype(phase_tag)::value;
-    for (int t0 = wave; t0 < ntiles; t0 += kSel2Waves * U) {
-      bf16x8 av[U][KS];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int t = min(t0 + kSel2Waves * u, ntiles - 1);     // (past the end: a re-read that is not used)
-        const uint16_t* arow = lane_row + (int64_t)t * (16 * DP);
+      for (int l = 0; l < 3; ++l) q[n][ks][l] = Ef[((int64_t)((qtile + n) * KS + ks) * 3 + l) * 64 + lane];
+  }
+  // this block's tiles: split + i splits, i = 0 .. own - 1; chunk c holds i = c CT ..
+  const int own = split < ntiles ? (ntiles - split + a.splits - 1) / a.splits : 0;
+  // two chunks' loads are in flight while a third is worked on (past the end: the last tile again, not used)
+  struct Chunk { i32x4 x[PER]; };
+  auto fetch = [&](int c) {
+    Chunk k;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          av[u][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(arow + 32 * ks));
+    for (int i = 0; i < PER; ++i) {
+      const int o = min(tid + i * NTHR, CQ - 1);
+      const int t = min(split + (c * CT + o / TQ) * a.splits, ntiles - 1);
+      k.x[i] = Ef[(int64_t)t * TQ + o % TQ];
+    }
+    return k;
+  };
+  auto park = [&](const Chunk& k, int b) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (CQ % NTHR == 0 || tid + i * NTHR < CQ) s_code[b][tid + i * NTHR] = k.x[i];
+  };
+  uint32_t fail[2] = {0, 0};
+  auto tile_work = [&](const i32x4* tile, int i) {         // i: the block's tile number
+    i32x4 aa[2], ab[2], bb[2], bc[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      aa[n] = bb[n] = bc[n] = i32x4{0, 0, 0, 0};
+      ab[n] = i32x4{start[n], start[n], start[n], start[n]};
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const i32x4 fa = tile[(ks * 3 + 0) * 64], fb = tile[(ks * 3 + 1) * 64], fc = tile[(ks * 3 + 2) * 64];
+      // (products that add into the same sum are kept apart, so that none waits for the one before it)
+#define LPP_LIMB(sum, f, l)                                                                    \
+      sum[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f, q[0][ks][l], sum[0], 0, 0, 0);         \
+      sum[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f, q[1][ks][l], sum[1], 0, 0, 0)
+      LPP_LIMB(aa, fa, 0);
+      LPP_LIMB(ab, fa, 1);
+      LPP_LIMB(bb, fa, 2);
+      LPP_LIMB(bc, fb, 2);
+      LPP_LIMB(ab, fb, 0);
+      LPP_LIMB(bb, fb, 1);
+      LPP_LIMB(bc, fc, 1);
+      LPP_LIMB(bb, fc, 0);
+#undef LPP_LIMB
+    }
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      i32x4 d;                                             // the similarity less the threshold, in units of 2^24 unit^2 (each below 2^30)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        d[r] = (aa[n][r] << 8) + ab[n][r] + ((bb[n][r] + (bc[n][r] >> 8)) >> 8);
+        fail[n] = shift_in_sign(fail[n], d[r]);
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u][ks], qv[0][ks], acc[0], 0, 0, 0);
-          acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u][ks], qv[1][ks], acc[1], 0, 0, 0);
-        }
-        const int t = t0 + kSel2Waves * u;
-        if (t >= ntiles) continue;
-        // tiles without the queries' own codes and without padding take no check per similarity
-        const bool plain = (t >> 1) != row0 / 32 && t * 16 + 16 <= V && row0 + kSel2Rows <= V;    // uniform
-#pragma unroll
-        for (int qt = 0; qt < 2; ++qt) {
-          // lane holds sim(code 16 t + 4*g4 + r, query row0 + 16 qt + l16), r = 0..3
-          const int qrow = row0 + 16 * qt + l16;
-          float x[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) x[r] = __builtin_fmaf(acc[qt][r], kBinScale, kBinScale);
-          if (PHASE == 0) {
-            uint32_t* my_hist = s_hist + (16 * qt + l16) * (kBins / 2);
-            if (plain) {
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const int bin = min(max((int)x[r], 0), kBins - 1);      // (int) truncates and sends NaN to 0
-                atomicAdd(&my_hist[bin >> 1], 1u << ((bin & 1) << 4));
-              }
-            } else {
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const int code = t * 16 + 4 * g4 + r;
-                const int bin = min(max((int)x[r], 0), kBins - 1);
-                if (!(code >= V || code == qrow || qrow >= V)) atomicAdd(&my_hist[bin >> 1], 1u << ((bin & 1) << 4));
-              }
-            }
-          } else {
-            bool pass[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) pass[r] = x[r] >= thr[qt];
-            if (!plain) {
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                const int code = t * 16 + 4 * g4 + r;
-                pass[r] = pass[r] && !(code >= V || code == qrow || qrow >= V);
-              }
-            }
-            if (__ballot(pass[0] || pass[1] || pass[2] || pass[3])) {
-#pragma unroll
-              for (int r = 0; r < 4; ++r)
-                if (pass[r]) {
-                  const int pos = atomicAdd(&s_cnt[16 * qt + l16], 1);
-                  if (pos < a.cap) a.cand[(int64_t)qrow * a.cap + pos] = (uint16_t)(t * 16 + 4 * g4 + r);
-                }
-            }
-          }
-        }
-      }
+      s_park[wave][n][(i % T) * 64 + lane] = d;
     }
   };
-  sweep(std::integral_constant<int, 0>());
-  __syncthreads();
-  // lowest bin taken, per row: b* - 1 less the margin for the rounding of the copy; a wave takes 4 rows
-  for (int r = wave * (kSel2Rows / kSel2Waves); r < (wave + 1) * (kSel2Rows / kSel2Waves); ++r) {
-    const int bs = find_bstar(s_hist + r * (kBins / 2), kk, lane);
-    if (lane == 0) {
-      const int low = row0 + r < a.Vp ? bs - 1 - row_margin(a, row0 + r) : 0;
-      s_low[r] = low;
-      if (row0 + r < a.Vp) a.bstar[row0 + r] = low;
-    }
-  }
-  __syncthreads();
+  // the window that ends with the block's tile number i - 1
+  auto emit = [&](int i) {
+    const int i0 = (i - 1) / T * T, have = i - i0;
+    const uint32_t code0 = (uint32_t)((split + i0 * a.splits) * 16 + 4 * g4);
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt) thr[qt] = s_low[16 * qt + l16] <= 0 ? -INFINITY : (float)s_low[16 * qt + l16];
-  sweep(std::integral_constant<int, 1>());
+    for (int n = 0; n < 2; ++n) {
+      // the four lanes of a row put their entries one after the other
+      const uint32_t m = ~fail[n] << (32 - 4 * have);
+      const int cnt = __popc(m);
+      const int c1 = __shfl(cnt, l16), c2 = __shfl(cnt, l16 + 16), c3 = __shfl(cnt, l16 + 32), c4 = __shfl(cnt, l16 + 48);
+      const int base = out[n] + (g4 > 0 ? c1 : 0) + (g4 > 1 ? c2 : 0) + (g4 > 2 ? c3 : 0);
+      emit_window(a, m, reinterpret_cast<const uint32_t*>(s_park[wave][n]), code0, (uint32_t)(16 * a.splits), lane, list[n] + base,
+                  (qtile + n) * 16 + l16 < a.V ? a.cap_split - base : 0,
+                  [&](uint32_t v) { return (uint32_t)((float)(int)v * scale[n]); });
+      out[n] += c1 + c2 + c3 + c4;
+      fail[n] = 0;
+    }
+  };
+  auto work = [&](int c, int b) {
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+      const int i = c * CT + j;
+      if (i >= own) break;                                 // uniform
+      tile_work(s_code[b] + j * TQ + lane, i);
+      if ((i + 1) % T == 0 || i + 1 == own) emit(i + 1);
+    }
+  };
+  Chunk n0 = fetch(0), n1 = fetch(1);
+  park(n0, 0);
   __syncthreads();
-  if (threadIdx.x < kSel2Rows && row0 + threadIdx.x < a.Vp) a.cnt[row0 + threadIdx.x] = s_cnt[threadIdx.x];
+  for (int c = 0; c * CT < own; c += 2) {
+    n0 = fetch(c + 2);
+    work(c, 0);
+    park(n1, 1);
+    __syncthreads();
+    if ((c + 1) * CT >= own) break;                        // uniform
+    n1 = fetch(c + 3);
+    work(c + 1, 1);
+    park(n0, 0);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+    const int row = (qtile + n) * 16 + l16;
+    if (g4 == 0 && row < a.V) a.cnt[(int64_t)row * a.splits + split] = out[n];
+  }
 }
+
+// ------------------------------------------------------------------------------------------ ranking
 
 __device__ __forceinline__ uint64_t orderable(double x) {
   const uint64_t u = (uint64_t)__double_as_longlong(x);
   return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
 }
 
-// exact key of the pair (row i held in LDS as floats, code j): float64 FMA chain in index order
-__device__ __forceinline__ uint64_t exact_key(const float* ei, const float* Ep, int DP, int D, int j) {
-  const float* ej = Ep + (int64_t)j * DP;
+// The codebook as the exact keys read it.  quads: rows start on 16 bytes and are padded with zeros to
+// whole groups of four (a product of zeros leaves the chain as it is: it starts at +0 and can
+// never be -0).
+struct Rows {
+  const float* p;
+  int32_t pitch, D;
+  bool quads;
+};
+
+// exact key of the pair (row i held in LDS as doubles, code j): float64 FMA chain in index order
+__device__ __forceinline__ uint64_t exact_key(const double* ei, const Rows& R, int j) {
+  const float* ej = R.p + (int64_t)j * R.pitch;
   double acc = 0.0;
-  for (int t0 = 0; t0 < D; t0 += 4) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(ej + t0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (t0 + e < D) acc = __builtin_fma((double)ei[t0 + e], (double)v[e], acc);
+  if (R.quads) {
+    for (int t = 0; t < R.D; t += 4) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(ej + t);
+      const f64x2 e0 = *reinterpret_cast<const f64x2*>(ei + t), e1 = *reinterpret_cast<const f64x2*>(ei + t + 2);
+      acc = __builtin_fma(e0[0], (double)v[0], acc);
+      acc = __builtin_fma(e0[1], (double)v[1], acc);
+      acc = __builtin_fma(e1[0], (double)v[2], acc);
+      acc = __builtin_fma(e1[1], (double)v[3], acc);
+    }
+  } else {
+    for (int t = 0; t < R.D; ++t) acc = __builtin_fma(ei[t], (double)ej[t], acc);
   }
   return orderable(acc);
 }
@@ -449,24 +708,273 @@ __device__ __forceinline__ bool before(uint64_t ka, uint32_t ia, uint64_t kb, ui
   return ka > kb || (ka == kb && ia < ib);
 }
 
+// Sum of one int per thread before this one, over a block of NTHR threads, and the total.
+template <int NTHR>
+__device__ __forceinline__ int block_exclusive(int v, int* s_w, int tid, int& total) {
+  const int lane = tid & 63, wv = tid >> 6;
+  int incl = v;
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  if (lane == 63) s_w[wv] = incl;
+  __syncthreads();
+  int base = 0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < NTHR / 64; ++w) {
+    if (w < wv) base += s_w[w];
+    total += s_w[w];
+  }
+  return base + incl - v;
+}
+
+// LDS of the ranking, in 4-byte words: the row as doubles [PD], then buckets [NB] and the entries by
+// bucket [P] (later the exact keys: NB >= P), the sorted entries [P], the list of those that need
+// their keys [P / 2 words].  P: list capacity rounded up; NB: buckets, a power of two.
+struct RankShape { int32_t P, lognb; };
+
+// One row: w[] are the thread's entries -- list words inverted, so that the nearest comes first in ascending
+// order: inverted value over inverted index -- `on` bit u set where w[u] is one.
+// Sorts them by value, orders what E leaves open by exact keys, writes the first kk codes to
+// out[1..].  False: the list does not prove its first kk entries (out may be written all the same).
+// Bound by LDS and vector instructions per entry, so each stage touches an entry once: an LDS add that gives the
+// place in the bucket, one read of the bucket's start, one write by bucket; entries more than E
+// below the bucket of the kk-th are left out from there on.  The buckets hold a few entries each: a wave takes 64
+// pairs in bucket order, 8 entries on either side shared with its neighbours, and eight rounds of
+// odd-even transposition (inside the pairs, across the lanes) put them in order; what is next to what is then
+// known in registers.
+// (An entry more than E below the kk-th value has kk entries before it for certain, and so has one that is
+// only before it by its key: neither can move anything among the first kk.)
+template <int NTHR, int EPT, bool STAGED>
+__device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int ib, int vb, int E, bool all, int kk, const Rows& R,
+                         RankShape sh, unsigned char* smem, int* s_w, int32_t* out, int tid) {
+  const int NB = 1 << sh.lognb;
+  double* eid = reinterpret_cast<double*>(smem);
+  uint32_t* bucket = reinterpret_cast<uint32_t*>(eid + ((R.D + 3) & ~3));
+  uint32_t* scat = bucket + NB;
+  uint32_t* sorted = scat + sh.P;
+  uint16_t* todo = reinterpret_cast<uint16_t*>(sorted + sh.P);
+  uint64_t* key = reinterpret_cast<uint64_t*>(bucket);
+  const int drop = 32 - min(sh.lognb, vb);                  // bucket number: the value's upper bits
+  const uint32_t mask = (1u << ib) - 1u;
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  enum { kTodo = 16, kKept, kLast, kCrowded };
+  constexpr int SIDE = 8;                                   // largest bucket the transposition rounds sort
+
+  for (int i = tid; i < NB / 4; i += NTHR) reinterpret_cast<uint4*>(bucket)[i] = make_uint4(0, 0, 0, 0);
+  if (tid == 0) { s_w[kTodo] = 0; s_w[kKept] = 0; s_w[kCrowded] = 0; }
+  __syncthreads();
+  uint32_t pos[EPT];
+#pragma unroll
+  for (int u = 0; u < EPT; ++u)
+    if ((on >> u) & 1u) pos[u] = atomicAdd(&bucket[w[u] >> drop], 1u);
+  __syncthreads();
+  int n;
+  {
+    const int per = NB / NTHR;                              // a multiple of four
+    int local = 0;
+    uint32_t most = 0;
+    for (int j = 0; j < per; j += 4) {
+      const uint4 c = *reinterpret_cast<const uint4*>(bucket + tid * per + j);
+      local += (int)(c.x + c.y + c.z + c.w);
+      most = max(max(most, max(c.x, c.y)), max(c.z, c.w));
+    }
+    uint32_t run = (uint32_t)block_exclusive<NTHR>(local, s_w, tid, n);
+    if (n < kk) return false;                               // uniform
+    // (buckets behind the kk-th entry's play no part, however full)
+    if ((int)run < kk && most > (uint32_t)SIDE) s_w[kCrowded] = 1;
+    if ((int)run < kk && (int)run + local >= kk) {          // the kk-th entry lies in one of my buckets
+      int c = (int)run, j = 0;
+      for (;; ++j) { c += (int)bucket[tid * per + j]; if (c >= kk) break; }
+      s_w[kLast] = tid * per + j;
+    }
+    for (int j = 0; j < per; j += 4) {                      // start | size << 16
+      uint4 c = *reinterpret_cast<const uint4*>(bucket + tid * per + j), s;
+      s.x = run; s.y = s.x + c.x; s.z = s.y + c.y; s.w = s.z + c.z; run = s.w + c.w;
+      *reinterpret_cast<uint4*>(bucket + tid * per + j) =
+          make_uint4(s.x | c.x << 16, s.y | c.y << 16, s.z | c.z << 16, s.w | c.w << 16);
+    }
+  }
+  __syncthreads();
+  // whole buckets, up to the one that holds the last value of the kk-th entry's bucket plus E
+  uint32_t last_bucket;
+  {
+    const uint32_t hi = ((uint32_t)(s_w[kLast] + 1) << drop) - 1u;
+    const uint32_t lim = min((hi >> ib) + (uint32_t)E, 0xFFFFFFFFu >> ib);
+    last_bucket = ((lim << ib) | mask) >> drop;
+    int kept = 0;
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) {
+      const bool keep = ((on >> u) & 1u) && (w[u] >> drop) <= last_bucket;
+      uint32_t b = 0;
+      if (keep) {
+        b = bucket[w[u] >> drop];
+        scat[(b & 0xFFFFu) + pos[u]] = w[u];
+      } else {
+        on &= ~(1u << u);
+      }
+      pos[u] = b;                                           // (from here on: start and size of the entry's bucket)
+      kept += __popcll(__ballot(keep));
+    }
+    if (lane == 0) atomicAdd(&s_w[kKept], kept);
+    if (__any((int)(last_bucket - s_w[kLast]) > 0)) {       // (buckets behind the kk-th's that are kept may be full as well)
+      bool full = false;
+#pragma unroll
+      for (int u = 0; u < EPT; ++u) full = full || (((on >> u) & 1u) && (pos[u] >> 16) > (uint32_t)SIDE);
+      if (full) s_w[kCrowded] = 1;
+    }
+  }
+  __syncthreads();
+  const int kept = s_w[kKept];
+  if (s_w[kCrowded]) {
+    // some bucket holds more than the rounds below sort (many near-equal values): count mates instead
+#pragma unroll
+    for (int u = 0; u < EPT; ++u)
+      if ((on >> u) & 1u) {
+        const int beg = (int)(pos[u] & 0xFFFFu), end = beg + (int)(pos[u] >> 16);
+        int at = beg;
+        for (int m = beg; m < end; ++m) at += scat[m] < w[u] ? 1 : 0;
+        sorted[at] = w[u];
+      }
+    __syncthreads();
+    for (int p = tid; p < kept; p += NTHR) scat[p] = sorted[p];
+    __syncthreads();
+  }
+  constexpr int WIN = 128 - 2 * SIDE;
+  for (int base = wv * WIN; base < kept; base += NTHR / 64 * WIN) {
+    const int p = base - SIDE + 2 * lane;                   // my two entries (reads before and behind the entries stay inside the buffers)
+    uint32_t x0 = scat[p], x1 = scat[p + 1];
+    x0 = p < 0 ? 0u : (p >= kept ? 0xFFFFFFFFu : x0);
+    x1 = p < 0 ? 0u : (p + 1 >= kept ? 0xFFFFFFFFu : x1);
+#pragma unroll
+    for (int r = 0; r < SIDE / 2; ++r) {
+      const uint32_t lo = min(x0, x1), hi = max(x0, x1);
+      // my second with the next lane's first, my first with the previous lane's second
+      x1 = min(hi, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, 0x130, 0xf, 0xf, false));
+      x0 = max(lo, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x138, 0xf, 0xf, false));
+    }
+    const int prev = (int)((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x1, 0x138, 0xf, 0xf, false) >> ib);
+    const int next = (int)((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x0, 0x130, 0xf, 0xf, false) >> ib);
+    const int v0 = (int)(x0 >> ib), v1 = (int)(x1 >> ib);
+    const bool mid = p + 1 < kept && v1 - v0 <= E;
+    const bool near0 = (p > 0 && v0 - prev <= E) || mid, near1 = mid || (p + 2 < kept && next - v1 <= E);
+    if (lane >= SIDE / 2 && lane < 64 - SIDE / 2 && p < kept) {
+      sorted[p] = x0;
+      if (near0) todo[atomicAdd(&s_w[kTodo], 1)] = (uint16_t)p;
+      else if (p < kk) out[1 + p] = (int32_t)(~x0 & mask);
+      if (p + 1 < kept) {
+        sorted[p + 1] = x1;
+        if (near1) todo[atomicAdd(&s_w[kTodo], 1)] = (uint16_t)(p + 1);
+        else if (p + 1 < kk) out[2 + p] = (int32_t)(~x1 & mask);
+      }
+    }
+  }
+  __syncthreads();
+  // an outsider lies below the threshold, value 0, and may be off by as much as any entry (and by the
+  // rounding of the threshold)
+  if (!all && (int)(~sorted[kk - 1] >> ib) <= E + 2) return false;      // uniform
+  const int m = s_w[kTodo];
+  if (STAGED) {
+    // rows of more than 16 floats: a wave takes 64 entries (there are 50 or so as a rule), stages 16
+    // floats of their rows at a time through LDS (whole 64-byte segments, four steps of them in flight) and
+    // every lane runs the chain of its own
+    constexpr int CH = 16, PITCH = CH + 4, DEEP = 4, TILES = NTHR >= 128 ? 2 : 1;
+    __shared__ __align__(16) float s_tile[TILES][64 * PITCH];
+    if (wv < TILES) {
+      float* tile = s_tile[wv];
+      for (int base = wv * 64; base < m; base += TILES * 64) {
+        const int p = todo[min(base + lane, m - 1)];
+        const int jown = (int)(~sorted[p] & mask), col = (lane & 3) * 4;
+        const float* r[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r[q] = R.p + (int64_t)__shfl(jown, 16 * q + (lane >> 2)) * R.pitch + col;
+        f32x4 x[DEEP][4];
+        auto fetch = [&](f32x4 (&y)[4], int st) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) y[q] = st + col < R.pitch ? *reinterpret_cast<const f32x4*>(r[q] + st) : f32x4{0.f, 0.f, 0.f, 0.f};
+        };
+#pragma unroll
+        for (int d = 0; d < DEEP; ++d) fetch(x[d], d * CH);
+        double acc = 0.0;
+        for (int st0 = 0; st0 < R.D; st0 += DEEP * CH) {
+#pragma unroll
+          for (int d = 0; d < DEEP; ++d) {
+            const int st = st0 + d * CH;
+            if (st >= R.D) break;                           // uniform
+#pragma unroll
+            for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(tile + (16 * q + (lane >> 2)) * PITCH + col) = x[d][q];
+            wave_lds_sync();
+            fetch(x[d], st + DEEP * CH);
+#pragma unroll
+            for (int t = 0; t < CH; t += 4) {
+              if (st + t >= R.D) break;                     // uniform
+              const f32x4 v = *reinterpret_cast<const f32x4*>(tile + lane * PITCH + t);
+              const double* eq = eid + st + t;
+              const f64x2 e0 = *reinterpret_cast<const f64x2*>(eq), e1 = *reinterpret_cast<const f64x2*>(eq + 2);
+              acc = __builtin_fma(e0[0], (double)v[0], acc);
+              acc = __builtin_fma(e0[1], (double)v[1], acc);
+              acc = __builtin_fma(e1[0], (double)v[2], acc);
+              acc = __builtin_fma(e1[1], (double)v[3], acc);
+            }
+            wave_lds_sync();
+          }
+        }
+        if (base + lane < m) key[p] = orderable(acc);
+      }
+    }
+  } else {
+    for (int f = tid; f < m; f += NTHR) {
+      const int p = todo[f];
+      key[p] = exact_key(eid, R, (int)(~sorted[p] & mask));
+    }
+  }
+  __syncthreads();
+  // inside a run of entries whose neighbours differ by at most E the keys decide; runs do not mix
+  for (int f = tid; f < m; f += NTHR) {
+    const int p = todo[f];
+    const uint32_t x = sorted[p];
+    const uint64_t K = key[p];
+    const uint32_t I = ~x & mask;
+    int at = p;
+    int v = (int)(x >> ib);
+    for (int s = p - 1; s >= 0; --s) {
+      const uint32_t y = sorted[s];
+      if (v - (int)(y >> ib) > E) break;
+      v = (int)(y >> ib);
+      at -= before(key[s], ~y & mask, K, I) ? 0 : 1;
+    }
+    v = (int)(x >> ib);
+    for (int s = p + 1; s < kept; ++s) {
+      const uint32_t y = sorted[s];
+      if ((int)(y >> ib) - v > E) break;
+      v = (int)(y >> ib);
+      at += before(key[s], ~y & mask, K, I) ? 1 : 0;
+    }
+    if (at < kk) out[1 + at] = (int32_t)I;
+  }
+  return true;
+}
+
 __device__ __forceinline__ double key_value(uint64_t K) {
   const uint64_t u = (K >> 63) ? (K & 0x7FFFFFFFFFFFFFFFull) : ~K;
   return __longlong_as_double((long long)u);
 }
 
-
 // Rank of each of the n entries of (skey, sidx) in the order (key desc, idx asc), without a
 // comparison sort: the keys are spread over NB buckets by a monotone map of their value
 // (bucket 0 = largest), bucket sizes are scanned, the entries' ids are scattered bucket by
 // bucket, and an entry's rank is its bucket's start plus the number of bucket mates that go
-// before it.  The first kk ranks are written to out[1 + rank]; the key of rank kk - 1 is left in
-// *kth.  cur[NB] and ord[n] are LDS scratch.  Ends with a barrier.
-__device__ void bucket_rank(const uint64_t* skey, const uint16_t* sidx, int n, int NB, uint32_t* cur,
-                            uint16_t* ord, uint64_t* s_red, int kk, int32_t* out, uint64_t* kth,
-                            int tid) {
+// before it.  The first kk ranks are written to out[1 + rank].  cur[NB] and ord[n] are LDS
+// scratch, NB a multiple of NTHR.  Part of the exact path.
+template <int NTHR>
+__device__ void bucket_rank(const uint64_t* skey, const uint16_t* sidx, int n, int NB, uint32_t* cur, uint16_t* ord,
+                            uint64_t* s_red, int* s_w, int kk, int32_t* out, int tid) {
   const int lane = tid & 63, wv = tid >> 6;
   uint64_t lo = ~0ull, hi = 0ull;
-  for (int c = tid; c < n; c += kRankThreads) {
+  for (int c = tid; c < n; c += NTHR) {
     const uint64_t K = skey[c];
     lo = K < lo ? K : lo;
     hi = K > hi ? K : hi;
@@ -478,10 +986,10 @@ __device__ void bucket_rank(const uint64_t* skey, const uint16_t* sidx, int n, i
     hi = h2 > hi ? h2 : hi;
   }
   if (lane == 0) { s_red[2 * wv] = lo; s_red[2 * wv + 1] = hi; }
-  for (int b = tid; b < NB; b += kRankThreads) cur[b] = 0u;
+  for (int b = tid; b < NB; b += NTHR) cur[b] = 0u;
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < kRankThreads / 64; ++w) {
+  for (int w = 0; w < NTHR / 64; ++w) {
     lo = s_red[2 * w] < lo ? s_red[2 * w] : lo;
     hi = s_red[2 * w + 1] > hi ? s_red[2 * w + 1] : hi;
   }
@@ -494,24 +1002,14 @@ __device__ void bucket_rank(const uint64_t* skey, const uint16_t* sidx, int n, i
     int b = f >= (double)(NB - 1) ? NB - 1 : (int)f;
     return f > 0.0 ? b : 0;                                // NaN and negatives to bucket 0
   };
-  for (int c = tid; c < n; c += kRankThreads) atomicAdd(&cur[bucket_of(skey[c])], 1u);
+  for (int c = tid; c < n; c += NTHR) atomicAdd(&cur[bucket_of(skey[c])], 1u);
   __syncthreads();
-  // exclusive scan of the NB counts: each lane owns NB / kRankThreads consecutive buckets
   {
-    const int per = NB / kRankThreads;                     // NB is a multiple of kRankThreads
+    const int per = NB / NTHR;
     uint32_t local = 0u;
     for (int j = 0; j < per; ++j) local += cur[tid * per + j];
-    uint32_t incl = local;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t t = __shfl_up(incl, o);
-      if (lane >= o) incl += t;
-    }
-    uint32_t* s_wt = reinterpret_cast<uint32_t*>(s_red + 8);
-    if (lane == 63) s_wt[wv] = incl;
-    __syncthreads();
-    uint32_t run = incl - local;
-    for (int w = 0; w < wv; ++w) run += s_wt[w];
+    int total;
+    uint32_t run = (uint32_t)block_exclusive<NTHR>((int)local, s_w, tid, total);
     for (int j = 0; j < per; ++j) {
       const uint32_t cnt = cur[tid * per + j];
       cur[tid * per + j] = run;
@@ -519,13 +1017,13 @@ __device__ void bucket_rank(const uint64_t* skey, const uint16_t* sidx, int n, i
     }
   }
   __syncthreads();
-  for (int c = tid; c < n; c += kRankThreads) {
+  for (int c = tid; c < n; c += NTHR) {
     const uint32_t pos = atomicAdd(&cur[bucket_of(skey[c])], 1u);
     ord[pos] = (uint16_t)c;
   }
   __syncthreads();
   // cur[b] is now the end of bucket b; its start is the end of bucket b - 1
-  for (int c = tid; c < n; c += kRankThreads) {
+  for (int c = tid; c < n; c += NTHR) {
     const uint64_t K = skey[c];
     const uint32_t I = sidx[c];
     const int b = bucket_of(K);
@@ -535,240 +1033,351 @@ __device__ void bucket_rank(const uint64_t* skey, const uint16_t* sidx, int n, i
       const int o = ord[m];
       rank += before(skey[o], sidx[o], K, I) ? 1 : 0;
     }
-    if (rank == kk - 1) *kth = K;
     if (rank < kk) out[1 + rank] = (int32_t)I;
   }
-  __syncthreads();
 }
 
-// CH floats of a codebook row are staged per step: a wave loads 64 candidate rows with 16-byte
-// pieces (whole 64- or 128-byte segments per row), parks them in its own LDS tile and every lane
-// then runs the float64 chain of its own candidate over the tile row.
-template <int CH>
-__global__ __launch_bounds__(kRankThreads) void knn_rank_kernel(KnnArgs a, int P) {
-  constexpr int LPR = CH / 4;            // lanes per staged row piece
-  constexpr int RPI = 64 / LPR;          // rows per load instruction
-  constexpr int PITCH = CH + 4;          // floats; 16-byte reads of 16 consecutive rows hit distinct banks
-  extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_hist[256];
-  __shared__ int s_misc[8];
-  __shared__ uint64_t s_red[12];
-  __shared__ uint64_t s_kth;
-  const int tid = threadIdx.x;
+// Exact path of one row over all V codes: radix select of the kk-th largest key.  Rare and slow.
+template <int NTHR>
+__device__ void exact_row(const Rows& R, int V, int i, int kk, unsigned char* smem, int* s_w, int32_t* out, int tid) {
   const int lane = tid & 63, wv = tid >> 6;
-  const int i = blockIdx.x;
-  const int V = a.V, D = a.D, DP = a.DP, kk = a.k - 1;
+  const int P = (kk + 1023) & ~1023;
+  double* eid = reinterpret_cast<double*>(smem);            // (already there)
+  uint64_t* skey = reinterpret_cast<uint64_t*>(eid + ((R.D + 3) & ~3));
+  uint32_t* cur = reinterpret_cast<uint32_t*>(skey + P);
+  uint16_t* sidx = reinterpret_cast<uint16_t*>(cur + P);
+  uint16_t* ord = sidx + P;
+  uint64_t* s_red = reinterpret_cast<uint64_t*>(ord + P);   // [2 NTHR / 64]
+  int* s_hist = reinterpret_cast<int*>(s_red + 2 * NTHR / 64);
+  int* s_misc = s_hist + 256;
+  uint64_t prefix = 0ull;
+  int need = kk;
+  for (int byte = 7; byte >= 0; --byte) {
+    __syncthreads();
+    for (int t = tid; t < 256; t += NTHR) s_hist[t] = 0;
+    __syncthreads();
+    for (int j = tid; j < V; j += NTHR) {
+      if (j == i) continue;
+      const uint64_t K = exact_key(eid, R, j);
+      const bool match = byte == 7 || (K >> (8 * (byte + 1))) == (prefix >> (8 * (byte + 1)));
+      if (match) atomicAdd(&s_hist[(int)((K >> (8 * byte)) & 255ull)], 1);
+    }
+    __syncthreads();
+    if (tid == 0) {
+      int cum = 0, bsel = 0;
+      for (int bkt = 255; bkt >= 0; --bkt) {
+        if (cum + s_hist[bkt] >= need) { bsel = bkt; break; }
+        cum += s_hist[bkt];
+      }
+      s_misc[0] = bsel;
+      s_misc[1] = need - cum;
+    }
+    __syncthreads();
+    prefix |= (uint64_t)s_misc[0] << (8 * byte);
+    need = s_misc[1];
+  }
+  // prefix = exact kk-th largest key; keep everything above it plus the `need`
+  // lowest-index codes equal to it
+  const int n_gt = kk - need;
+  __syncthreads();
+  if (tid == 0) { s_misc[2] = 0; s_misc[3] = 0; }
+  __syncthreads();
+  for (int j0 = 0; j0 < V; j0 += NTHR) {
+    const int j = j0 + tid;
+    uint64_t K = 0ull;
+    bool gt = false, eq = false;
+    if (j < V && j != i) {
+      K = exact_key(eid, R, j);
+      gt = K > prefix;
+      eq = K == prefix;
+    }
+    if (gt) {
+      const int pos = atomicAdd(&s_misc[2], 1);
+      skey[pos] = K; sidx[pos] = (uint16_t)j;
+    }
+    // ordered compaction of the ties (ascending index)
+    const unsigned long long bal = __ballot(eq);
+    if (lane == 0) s_hist[wv] = __popcll(bal);
+    __syncthreads();
+    int base = s_misc[3];
+    for (int w = 0; w < wv; ++w) base += s_hist[w];
+    const int rank = base + __popcll(bal & ((1ull << lane) - 1ull));
+    if (eq && rank < need) { skey[n_gt + rank] = K; sidx[n_gt + rank] = (uint16_t)j; }
+    __syncthreads();
+    if (tid == 0) {
+      int t = 0;
+      for (int w = 0; w < NTHR / 64; ++w) t += s_hist[w];
+      s_misc[3] += t;
+    }
+    __syncthreads();
+  }
+  bucket_rank<NTHR>(skey, sidx, kk, P, cur, ord, s_red, s_w, kk, out, tid);
+}
+
+// One block per row: NTHR threads, EPT list words each in registers.
+template <int NTHR, int EPT, bool STAGED>
+__global__ __launch_bounds__(NTHR) void knn_rank_kernel(KnnArgs a, RankShape sh) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int s_w[20];
+  const int tid = threadIdx.x, i = blockIdx.x, kk = a.k - 1;
   int32_t* out = a.neigh + (int64_t)i * a.k;
   if (tid == 0) out[0] = i;
   if (kk == 0) return;
-  uint64_t* skey = reinterpret_cast<uint64_t*>(smem);
-  uint16_t* sidx = reinterpret_cast<uint16_t*>(skey + P);     // (V <= 65536; P is a multiple of 256)
-  double* eid = reinterpret_cast<double*>(sidx + P);     // the query row as doubles
-  float* ei = reinterpret_cast<float*>(eid + DP);         // and as loaded (exact path)
-  // scratch: staging tiles while keys are computed, then the buckets of the ranking
-  unsigned char* scratch = reinterpret_cast<unsigned char*>(ei + DP);
-  float* tile = reinterpret_cast<float*>(scratch) + wv * 64 * PITCH;
-  uint32_t* cur = reinterpret_cast<uint32_t*>(scratch);
-  uint16_t* ord = reinterpret_cast<uint16_t*>(cur + P);
-  for (int d = tid; d < DP; d += kRankThreads) {
-    const float v = a.Ep[(int64_t)i * DP + d];
-    ei[d] = v;
-    eid[d] = (double)v;
+  const RowPlan p = a.plan[i];
+  const uint32_t* list = a.cand + (int64_t)i * a.cap;
+  const uint32_t mask = (1u << a.ib) - 1u;
+  uint32_t w[EPT], on = 0;
+  int n;
+  bool over;                                                // uniform: the list does not hold everything it should
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) w[u] = 0;
+  if constexpr (STAGED) {
+    // the list's segments one after the other: lane s of every wave holds the end of segment s
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane < a.splits ? a.cnt[(int64_t)i * a.splits + lane] : 0;
+    list = a.cand + (int64_t)i * a.splits * a.cap_split;
+    int end = c;
+#pragma unroll
+    for (int o = 1; o < kMaxSplits; o <<= 1) {
+      const int t = __shfl_up(end, o);
+      if (lane >= o) end += t;
+    }
+    n = __builtin_amdgcn_readlane(end, kMaxSplits - 1);    // (lanes behind the last segment hold the total as well)
+    over = __any(c > a.cap_split) || n > a.cap;
+    int s = 0, s0 = 0, s1 = __builtin_amdgcn_readlane(end, 0);
+    if (!over)
+#pragma unroll
+      for (int u = 0; u < EPT; ++u) {
+        const int g0 = wv * 64 + u * NTHR, g = g0 + lane;
+        while (s < a.splits && s1 <= g0) { s0 = s1; ++s; s1 = __builtin_amdgcn_readlane(end, s); }     // (scalar)
+        for (; s < a.splits; ) {                            // 64 entries lie in one or two segments as a rule
+          if (g >= s0 && g < s1) w[u] = list[s * a.cap_split + g - s0];
+          if (s1 >= g0 + 64) break;
+          s0 = s1; ++s; s1 = __builtin_amdgcn_readlane(end, s);
+        }
+      }
+  } else {
+    n = a.cnt[i];
+    over = n > a.cap;
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) {
+      const int c = tid + u * NTHR;
+      if (c < min(n, a.cap)) w[u] = list[c];
+    }
+  }
+  double* eid = reinterpret_cast<double*>(smem);
+  for (int d = tid; d < a.PD; d += NTHR) eid[d] = (double)a.Ep[(int64_t)i * a.PD + d];
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    const uint32_t j = w[u] & mask;                         // the row itself and padding are no neighbours
+    bool keep = tid + u * NTHR < n && j != (uint32_t)i && j < (uint32_t)a.V;
+    if (keep && (p.flags & kAnyNan)) keep = a.norms[j] == a.norms[j];      // (a code that holds a NaN is no neighbour)
+    on |= keep ? 1u << u : 0u;
+    w[u] = ~w[u];
+  }
+  const Rows R{a.Ep, a.PD, a.D, true};
+  if (!over && !(p.flags & kNoList)) {
+    if (rank_row<NTHR, EPT, STAGED>(w, on, a.ib, a.vmask_bits, p.E, (p.flags & kAll) != 0, kk, R, sh, smem, s_w, out, tid)) return;
+  }
+  __threadfence();                                          // (what was written of the row is written again by other lanes)
+  __syncthreads();
+  exact_row<NTHR>(R, a.V, i, kk, smem, s_w, out, tid);
+}
+
+// Small codebooks of short rows: one block per row forms the row's similarities with every code
+// (fp32, in registers) and ranks them; nothing goes through memory but the codebook and the row.
+constexpr int kDirectThreads = 256;
+__global__ __launch_bounds__(kDirectThreads) void knn_direct_kernel(KnnArgs a, RankShape sh) {
+  constexpr int EPT = kDirectCodes / kDirectThreads, W = kDirectThreads / 64;
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int s_w[20];
+  __shared__ float s_m[3][W];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, i = blockIdx.x, kk = a.k - 1;
+  const int D = a.D, V = a.V;
+  int32_t* out = a.neigh + (int64_t)i * a.k;
+  if (tid == 0) out[0] = i;
+  if (kk == 0) return;
+  double* eid = reinterpret_cast<double*>(smem);
+  const int PD = (D + 3) & ~3;
+  if (tid < PD) eid[tid] = tid < D ? (double)a.E[(int64_t)i * D + tid] : 0.0;
+  const bool quads = (D & 3) == 0 && (reinterpret_cast<uintptr_t>(a.E) & 15) == 0;
+  float q[kShortRow];                                       // (uniform: scalar loads)
+#pragma unroll
+  for (int d = 0; d < kShortRow; ++d) q[d] = d < D ? a.E[(int64_t)i * D + d] : 0.f;
+  float sim[EPT], lo = INFINITY, hi = -INFINITY, maxn2 = 0.f;
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    const int c = min(tid + u * kDirectThreads, V - 1);
+    const float* e = a.E + (int64_t)c * D;
+    float s = 0.f, n2 = 0.f;
+    if (quads) {
+#pragma unroll
+      for (int t = 0; t < kShortRow; t += 4)
+        if (t < D) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(e + t);
+#pragma unroll
+          for (int x = 0; x < 4; ++x) { s = __builtin_fmaf(q[t + x], v[x], s); n2 = __builtin_fmaf(v[x], v[x], n2); }
+        }
+    } else {
+#pragma unroll
+      for (int t = 0; t < kShortRow; ++t)
+        if (t < D) { const float v = e[t]; s = __builtin_fmaf(q[t], v, s); n2 = __builtin_fmaf(v, v, n2); }
+    }
+    sim[u] = s;
+    maxn2 = fmaxf(maxn2, n2);
+    lo = fminf(lo, s);
+    hi = fmaxf(hi, s);
+  }
+  lo = -lo;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = fmaxf(lo, __shfl_xor(lo, o));
+    hi = fmaxf(hi, __shfl_xor(hi, o));
+    maxn2 = fmaxf(maxn2, __shfl_xor(maxn2, o));
+  }
+  if (lane == 0) { s_m[0][wv] = lo; s_m[1][wv] = hi; s_m[2][wv] = maxn2; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < W; ++w) { lo = fmaxf(lo, s_m[0][w]); hi = fmaxf(hi, s_m[1][w]); maxn2 = fmaxf(maxn2, s_m[2][w]); }
+  lo = -lo;
+  float n2 = 0.f;
+#pragma unroll
+  for (int d = 0; d < kShortRow; ++d) n2 = __builtin_fmaf(q[d], q[d], n2);
+  const float qmax = (float)((1u << a.vmask_bits) - 2u);
+  // (the float product of the norms may underflow where the keys do not: a floor keeps E on the safe side)
+  const float e = (float)(PD + 4) * 1.1920929e-07f * sqrtf(n2) * sqrtf(maxn2) * 1.001f + 1e-36f;
+  const float range = fmaxf(hi - lo, fmaxf(e, 1e-30f));
+  const float pa = qmax / range, pb = 1.0f - lo * pa;
+  const int E = (int)fminf(ceilf(2.002f * e * pa) + 4.0f, 1073741824.0f);
+  uint32_t w[EPT], on = 0;
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    const int c = tid + u * kDirectThreads;
+    w[u] = ~(((uint32_t)fminf(fmaxf(__builtin_fmaf(sim[u], pa, pb), 0.f), qmax) << a.ib) | (uint32_t)c);
+    on |= c < V && c != i && sim[u] == sim[u] ? 1u << u : 0u;      // (a code that holds a NaN is no neighbour)
   }
   __syncthreads();
-
-  const int n = a.cnt[i];
-  bool slow = n > a.cap || n < kk;          // list overflowed: only the exact path is safe
-  if (!slow) {
-    const uint16_t* crow = a.cand + (int64_t)i * a.cap;
-    const int nsteps = (D + CH - 1) / CH;
-    for (int base = wv * 64; base < n; base += kRankThreads) {
-      const int c = base + lane;
-      const int jown = c < n ? (int)crow[c] : i;
-      double acc = 0.0;
-      if (CH == 16) {
-        // rows of 16 floats are one 64-byte segment: every lane reads its own candidate's row, no tile
-        // (Dimensions past D are zero in both rows of the padded copy, and a product of zeros added
-        // to the chain leaves it as it is -- the chain starts at +0 and can never be -0 -- so whole
-        // groups of four are taken with no test per dimension, and only the groups that hold any.)
-        const float* er = a.Ep + (int64_t)jown * DP;
-        const int nq = (D + 3) >> 2;                     // uniform
-        f32x4 v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (q < nq) v[q] = *reinterpret_cast<const f32x4*>(er + 4 * q);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (q < nq) {
-            const f64x2 e0 = *reinterpret_cast<const f64x2*>(eid + 4 * q);
-            const f64x2 e1 = *reinterpret_cast<const f64x2*>(eid + 4 * q + 2);
-            acc = __builtin_fma(e0[0], (double)v[q][0], acc);
-            acc = __builtin_fma(e0[1], (double)v[q][1], acc);
-            acc = __builtin_fma(e1[0], (double)v[q][2], acc);
-            acc = __builtin_fma(e1[1], (double)v[q][3], acc);
-          }
-        if (c < n) { skey[c] = orderable(acc); sidx[c] = (uint16_t)jown; }
-        continue;
-      }
-      f32x4 piece[LPR];
-#pragma unroll
-      for (int q = 0; q < LPR; ++q) {
-        const int jr = __shfl(jown, q * RPI + lane / LPR);
-        piece[q] = *reinterpret_cast<const f32x4*>(a.Ep + (int64_t)jr * DP + (lane % LPR) * 4);
-      }
-      for (int st = 0; st < nsteps; ++st) {
-#pragma unroll
-        for (int q = 0; q < LPR; ++q)
-          *reinterpret_cast<f32x4*>(tile + (q * RPI + lane / LPR) * PITCH + (lane % LPR) * 4) = piece[q];
-        wave_lds_sync();
-        if (st + 1 < nsteps) {
-#pragma unroll
-          for (int q = 0; q < LPR; ++q) {
-            const int jr = __shfl(jown, q * RPI + lane / LPR);
-            piece[q] = *reinterpret_cast<const f32x4*>(a.Ep + (int64_t)jr * DP + (st + 1) * CH + (lane % LPR) * 4);
-          }
-        }
-        const double* eq = eid + st * CH;
-        if (D - st * CH >= CH) {
-#pragma unroll
-          for (int t0 = 0; t0 < CH; t0 += 4) {
-            const f32x4 v = *reinterpret_cast<const f32x4*>(tile + lane * PITCH + t0);
-            const f64x2 e0 = *reinterpret_cast<const f64x2*>(eq + t0);
-            const f64x2 e1 = *reinterpret_cast<const f64x2*>(eq + t0 + 2);
-            acc = __builtin_fma(e0[0], (double)v[0], acc);
-            acc = __builtin_fma(e0[1], (double)v[1], acc);
-            acc = __builtin_fma(e1[0], (double)v[2], acc);
-            acc = __builtin_fma(e1[1], (double)v[3], acc);
-          }
-        } else {
-          const int lim = D - st * CH;                       // > 0: the ragged last step
-          for (int t = 0; t < lim; ++t) acc = __builtin_fma(eq[t], (double)tile[lane * PITCH + t], acc);
-        }
-        wave_lds_sync();
-      }
-      if (c < n) { skey[c] = orderable(acc); sidx[c] = (uint16_t)jown; }
-    }
-    __syncthreads();
-    bucket_rank(skey, sidx, n, P, cur, ord, s_red, kk, out, &s_kth, tid);
-    // can a code outside the candidate list still belong to the row?
-    const int low = a.bstar[i];
-    if (low >= 1) {
-      const float edge = (float)low / a.bin_scale - 1.0f;         // lower edge of the lowest bin taken
-      slow = s_kth < orderable((double)edge + (double)row_eps(a, i));
-    }
-    if (!slow) return;
-    // the row was written from the candidate list and is written again below by other lanes:
-    // make the first version reach memory before any lane goes on (rare path)
-    __threadfence();
-    __syncthreads();
-  }
-  // ---- exact path over all V codes: radix select of the kk-th largest key
-  {
-    uint64_t prefix = 0ull;
-    int need = kk;
-    for (int byte = 7; byte >= 0; --byte) {
-      s_hist[tid] = 0;
-      __syncthreads();
-      for (int j = tid; j < V; j += kRankThreads) {
-        if (j == i) continue;
-        const uint64_t K = exact_key(ei, a.Ep, DP, D, j);
-        const bool match = byte == 7 || (K >> (8 * (byte + 1))) == (prefix >> (8 * (byte + 1)));
-        if (match) atomicAdd(&s_hist[(int)((K >> (8 * byte)) & 255ull)], 1);
-      }
-      __syncthreads();
-      if (tid == 0) {
-        int cum = 0, bsel = 0;
-        for (int bkt = 255; bkt >= 0; --bkt) {
-          if (cum + s_hist[bkt] >= need) { bsel = bkt; break; }
-          cum += s_hist[bkt];
-        }
-        s_misc[0] = bsel;
-        s_misc[1] = need - cum;
-      }
-      __syncthreads();
-      prefix |= (uint64_t)s_misc[0] << (8 * byte);
-      need = s_misc[1];
-      __syncthreads();
-    }
-    // prefix = exact kk-th largest key; keep everything above it plus the `need`
-    // lowest-index codes equal to it
-    const int n_gt = kk - need;
-    if (tid == 0) { s_misc[2] = 0; s_misc[3] = 0; }
-    __syncthreads();
-    for (int j0 = 0; j0 < V; j0 += kRankThreads) {
-      const int j = j0 + tid;
-      uint64_t K = 0ull;
-      bool gt = false, eq = false;
-      if (j < V && j != i) {
-        K = exact_key(ei, a.Ep, DP, D, j);
-        gt = K > prefix;
-        eq = K == prefix;
-      }
-      if (gt) {
-        const int pos = atomicAdd(&s_misc[2], 1);
-        skey[pos] = K; sidx[pos] = (uint16_t)j;
-      }
-      // ordered compaction of the ties (ascending index)
-      const unsigned long long bal = __ballot(eq);
-      if (lane == 0) s_hist[wv] = __popcll(bal);
-      __syncthreads();
-      int base = s_misc[3];
-      for (int w = 0; w < wv; ++w) base += s_hist[w];
-      const int rank = base + __popcll(bal & ((1ull << lane) - 1ull));
-      if (eq && rank < need) { skey[n_gt + rank] = K; sidx[n_gt + rank] = (uint16_t)j; }
-      __syncthreads();
-      if (tid == 0) s_misc[3] += s_hist[0] + s_hist[1] + s_hist[2] + s_hist[3];
-      __syncthreads();
-    }
-    bucket_rank(skey, sidx, kk, P, cur, ord, s_red, kk, out, &s_kth, tid);
-  }
+  const Rows R{a.E, D, D, quads};
+  if (range < INFINITY && rank_row<kDirectThreads, EPT, false>(w, on, a.ib, a.vmask_bits, E, true, kk, R, sh, smem, s_w, out, tid))
+    return;
+  __threadfence();                                          // (as in knn_rank_kernel)
+  __syncthreads();
+  exact_row<kDirectThreads>(R, V, i, kk, smem, s_w, out, tid);
 }
 
-int32_t cap_for(int32_t k, int32_t DP) {
-  return (int32_t)lpp_align_up((size_t)(k - 1) + (DP <= 16 ? kSlackShort : kSlack), 64);
-}
+// -------------------------------------------------------------------------------------------- host
 
 struct KnnLayout {
-  size_t o_ep, o_eh, o_norms, o_max, o_bstar, o_cnt, o_cand, total;
-  int32_t DP, Vp, cap;
+  size_t o_ep, o_ef, o_es, o_norms, o_l1, o_part, o_plan, o_cnt, o_cand, total;
+  int32_t PD, KS, Vp, cap, ib, vb, stride, ns, m, take_all, splits, cap_split;
 };
 
 KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   KnnLayout L;
-  L.DP = 16;
-  while (L.DP < D) L.DP <<= 1;             // 16, 32, ..., 256
-  L.Vp = (int32_t)lpp_align_up((size_t)V, 64);
-  L.cap = cap_for(k, L.DP);
+  L.PD = (D + 3) & ~3;
+  L.KS = D > kShortRow ? (D + 63) / 64 : 0;
+  L.Vp = (int32_t)lpp_align_up((size_t)V, 128);
+  L.ib = 8;
+  while ((1 << L.ib) < L.Vp && L.ib < 16) ++L.ib;
+  L.vb = 32 - L.ib;
+  // The sample: codes above the k - 1 th largest are in it with probability 1 / stride each; the
+  // m-th largest of the sample lies below that one unless the sample holds five standard deviations
+  // too many of them (the z^2 / 4 term is for counts so small that they are not normal; 1.05 leaves
+  // some spread where the sample is the whole codebook: its similarities are rounded).
+  const int kk = k - 1;
+  L.stride = 1;
+  while (L.stride * 2 * kSampleCodes <= V) L.stride *= 2;
+  L.ns = V / L.stride;
+  const double mu = (double)kk / L.stride, z = 5.0;
+  L.m = (int)ceil(mu + z * sqrt(mu * (1.05 - 1.0 / L.stride)) + z * z / 4.0) + 1;
+  const double expect = (double)L.m * L.stride, dev = L.stride * sqrt((double)L.m * (1.0 - 0.999 / L.stride));
+  L.take_all = expect >= 0.75 * V;
+  // (the last term: the threshold is the lower edge of a bin, whose codes are all taken)
+  L.cap = L.take_all ? L.Vp : (int32_t)std::min<size_t>(L.Vp, lpp_align_up((size_t)(expect + 5.0 * dev) + 64 + V / 256, 64));
+  // long rows: blocks of 128 queries by `splits` shares of the code tiles, two blocks per compute unit
+  const int ntiles = (V + 15) / 16, groups = L.Vp / 128;
+  L.splits = L.KS ? std::max(1, std::min({512 / groups, ntiles, kMaxSplits})) : 1;
+  L.cap_split = L.cap;
+  if (L.splits > 1) {
+    const int tiles = (ntiles + L.splits - 1) / L.splits;
+    const double share = (expect + 5.0 * dev) / L.splits + 16;
+    L.cap_split = L.take_all ? 16 * tiles : std::min(16 * tiles, (int)lpp_align_up((size_t)(share + 6.0 * sqrt(share)), 16));
+  }
+  const size_t entries = (size_t)std::max(L.cap, L.splits * L.cap_split);
   size_t o = 0;
-  L.o_ep = o;    o += lpp_align_up((size_t)L.Vp * L.DP * sizeof(float), 256);
-  L.o_eh = o;    o += L.DP >= 32 ? lpp_align_up((size_t)L.Vp * L.DP * sizeof(uint16_t), 256) : 0;
-  L.o_norms = o; o += lpp_align_up((size_t)L.Vp * sizeof(float), 256);
-  L.o_max = o;   o += 256;
-  L.o_bstar = o; o += lpp_align_up((size_t)L.Vp * sizeof(int32_t), 256);
-  L.o_cnt = o;   o += lpp_align_up((size_t)L.Vp * sizeof(int32_t), 256);
-  L.o_cand = o;  o += lpp_align_up((size_t)V * L.cap * sizeof(uint16_t), 256);
+  auto take = [&](size_t bytes) { const size_t at = o; o += lpp_align_up(bytes, 256); return at; };
+  L.o_ep = take((size_t)V * L.PD * sizeof(float));
+  const int n8 = D > 8 ? 2 : 1;
+  L.o_ef = take(L.KS ? (size_t)(L.Vp / 16) * L.KS * 3 * 64 * 16 : (size_t)L.Vp * 2 * n8 * 16);
+  L.o_es = take(L.KS ? (size_t)((L.ns + 15) / 16) * L.KS * 64 * 16 : (size_t)L.ns * 2 * n8 * 16);
+  L.o_norms = take((size_t)V * sizeof(float));
+  L.o_l1 = take((size_t)V * sizeof(float));
+  L.o_part = take((size_t)kStatBlocks * sizeof(float4));
+  L.o_plan = take((size_t)L.Vp * sizeof(RowPlan));
+  L.o_cnt = take((size_t)V * L.splits * sizeof(int32_t));
+  L.o_cand = take((size_t)V * entries * sizeof(uint32_t));
   L.total = o;
   return L;
 }
 
-template <int KS>
-int32_t launch_select_bf16(const KnnArgs& a, hipStream_t s) {
-  const size_t lds = (size_t)kSel2Rows * (kBins / 2) * sizeof(uint32_t);
-  auto kern = knn_select_bf16_kernel<KS>;
+// LDS of one row's ranking or of its exact path, whichever is larger
+size_t rank_lds(int P, int NB, int PD, int kk) {
+  const size_t rank = (size_t)PD * 8 + (size_t)NB * 4 + (size_t)P * 8 + (size_t)P * 2;
+  const size_t PX = lpp_align_up((size_t)kk, 1024);
+  const size_t exact = (size_t)PD * 8 + PX * 16 + 2 * 16 * 8 + 260 * 4;
+  return std::max(rank, exact);
+}
+
+template <bool FIXED, int N>
+int32_t launch_sample(const KnnArgs& a, hipStream_t s) {
+  const size_t lds = (size_t)kSampleBins * 16 * sizeof(uint32_t);
+  auto kern = knn_sample_kernel<FIXED, N>;
   static LppLdsLimit limit;
   const int32_t st = lpp_ensure_lds(reinterpret_cast<const void*>(kern), limit, lds);
   if (st != LPP_OK) return st;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(a.Vp / kSel2Rows)), dim3(kSel2Waves * 64), lds, s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(a.Vp / 16)), dim3(kSampleThreads), lds, s, a);
   LPP_HIP_TRY(hipGetLastError());
   return LPP_OK;
 }
 
-int32_t launch_select_f32(const KnnArgs& a, hipStream_t s) {
-  const size_t lds = (size_t)kSelRows * kBinsF * sizeof(uint32_t);
-  static LppLdsLimit limit;
-  const int32_t st = lpp_ensure_lds(reinterpret_cast<const void*>(knn_select_f32_kernel), limit, lds);
+template <int N>
+int32_t launch_collect_f16(const KnnArgs& a, hipStream_t s) {
+  int32_t st = launch_sample<false, N>(a, s);
   if (st != LPP_OK) return st;
-  hipLaunchKernelGGL(knn_select_f32_kernel, dim3((unsigned)(a.Vp / kSelRows)), dim3(kSelWaves * 64), lds, s, a);
+  // a block per 16 queries: as many waves as give every compute unit 18 (8 KB of LDS each), 16 at most
+  const int blocks = (a.V + 15) / 16;
+  const int waves = std::max(4, std::min(kCollectMaxWaves, 256 * 18 / blocks));
+  const size_t lds = (size_t)waves * 8192;
+  auto kern = knn_collect_f16_kernel<N>;
+  static LppLdsLimit limit;
+  st = lpp_ensure_lds(reinterpret_cast<const void*>(kern), limit, lds, 48 * 1024);
+  if (st != LPP_OK) return st;
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3((unsigned)waves * 64), lds, s, a);
+  LPP_HIP_TRY(hipGetLastError());
+  return LPP_OK;
+}
+
+template <int KS>
+int32_t launch_collect_i8(const KnnArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(knn_limb_kernel<KS>, dim3((unsigned)(a.Vp / 16 * KS / 4)), dim3(256), 0, s, a);
+  LPP_HIP_TRY(hipGetLastError());
+  int32_t st = launch_sample<true, KS>(a, s);
+  if (st != LPP_OK) return st;
+  hipLaunchKernelGGL(knn_collect_i8_kernel<KS>, dim3((unsigned)(a.Vp / (kCollectWaves * 32) * a.splits)),
+                     dim3(kCollectWaves * 64), 0, s, a);
+  LPP_HIP_TRY(hipGetLastError());
+  return LPP_OK;
+}
+
+template <int NTHR, bool STAGED>
+int32_t launch_rank(const KnnArgs& a, RankShape sh, hipStream_t s) {
+  const size_t lds = rank_lds(sh.P, 1 << sh.lognb, a.PD, a.k - 1);
+  if (lds > 150 * 1024) return LPP_EUNSUPPORTED;
+  auto kern = knn_rank_kernel<NTHR, 8, STAGED>;
+  static LppLdsLimit limit;
+  const int32_t st = lpp_ensure_lds(reinterpret_cast<const void*>(kern), limit, lds, 48 * 1024);
+  if (st != LPP_OK) return st;
+  hipLaunchKernelGGL(kern, dim3((unsigned)a.V), dim3(NTHR), lds, s, a, sh);
   LPP_HIP_TRY(hipGetLastError());
   return LPP_OK;
 }
@@ -787,55 +1396,70 @@ extern "C" int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, in
   if (k > LPP_MAX_K || D > 256 || V > 65536) return LPP_EUNSUPPORTED;
   const KnnLayout L = knn_layout(V, D, k);
   if (!ws || ws_bytes < L.total) return LPP_ENOWORKSPACE;
-  int ndev = 0;
-  if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) { (void)hipGetLastError(); return LPP_EHIP; }
+  static std::atomic<bool> have_device{false};
+  if (!have_device.load(std::memory_order_relaxed)) {
+    int ndev = 0;
+    if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) { (void)hipGetLastError(); return LPP_EHIP; }
+    have_device.store(true, std::memory_order_relaxed);
+  }
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   unsigned char* w = reinterpret_cast<unsigned char*>(ws);
   KnnArgs a;
-  a.E = E; a.V = V; a.D = D; a.DP = L.DP; a.Vp = L.Vp; a.k = k; a.cap = L.cap;
+  a.E = E; a.V = V; a.D = D; a.k = k; a.PD = L.PD; a.Vp = L.Vp; a.cap = L.cap; a.ib = L.ib; a.vmask_bits = L.vb;
+  a.stride = L.stride; a.ns = L.ns; a.m = L.m; a.take_all = L.take_all; a.splits = L.splits; a.cap_split = L.cap_split;
   a.Ep = reinterpret_cast<float*>(w + L.o_ep);
-  a.Eh = L.DP >= 32 ? reinterpret_cast<uint16_t*>(w + L.o_eh) : nullptr;
-  a.bin_scale = a.Eh ? kBinScale : kBinScaleF;
+  a.Ef = reinterpret_cast<i32x4*>(w + L.o_ef);
+  a.Es = reinterpret_cast<i32x4*>(w + L.o_es);
   a.norms = reinterpret_cast<float*>(w + L.o_norms);
-  a.maxnorm = reinterpret_cast<uint32_t*>(w + L.o_max);
-  a.bstar = reinterpret_cast<int32_t*>(w + L.o_bstar);
+  a.l1 = reinterpret_cast<float*>(w + L.o_l1);
+  a.part = reinterpret_cast<float4*>(w + L.o_part);
+  a.plan = reinterpret_cast<RowPlan*>(w + L.o_plan);
   a.cnt = reinterpret_cast<int32_t*>(w + L.o_cnt);
-  a.cand = reinterpret_cast<uint16_t*>(w + L.o_cand);
+  a.cand = reinterpret_cast<uint32_t*>(w + L.o_cand);
   a.neigh = neigh;
+  auto log2_up = [](int x) { int l = 0; while ((1 << l) < x) ++l; return l; };
 
-  hipLaunchKernelGGL(knn_init_kernel, dim3(1), dim3(64), 0, s, a);
-  LPP_HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(knn_pack_kernel, dim3((unsigned)((L.Vp + kPackRows - 1) / kPackRows)), dim3(256), 0, s, a);
+  if (D <= kShortRow && V <= kDirectCodes) {
+    // values need no more than the float's bits; the key buffer over counters and scattered words wants NB >= P
+    const RankShape sh{kDirectCodes, log2_up(kDirectCodes)};
+    const size_t lds = rank_lds(sh.P, 1 << sh.lognb, L.PD, k - 1);
+    hipLaunchKernelGGL(knn_direct_kernel, dim3((unsigned)V), dim3(kDirectThreads), lds, s, a, sh);
+    LPP_HIP_TRY(hipGetLastError());
+    return LPP_OK;
+  }
+
+  const int G = D <= 16 ? 4 : (D <= 64 ? 16 : 64);
+  a.statblocks = std::min(kStatBlocks, (V + kStatThreads / G - 1) / (kStatThreads / G));
+  if (G == 4) hipLaunchKernelGGL(knn_stats_kernel<4>, dim3((unsigned)a.statblocks), dim3(kStatThreads), 0, s, a);
+  else if (G == 16) hipLaunchKernelGGL(knn_stats_kernel<16>, dim3((unsigned)a.statblocks), dim3(kStatThreads), 0, s, a);
+  else hipLaunchKernelGGL(knn_stats_kernel<64>, dim3((unsigned)a.statblocks), dim3(kStatThreads), 0, s, a);
   LPP_HIP_TRY(hipGetLastError());
   if (k > 1) {
     int32_t st;
-    switch (L.DP / 16) {
-      case 1: st = launch_select_f32(a, s); break;
-      case 2: st = launch_select_bf16<1>(a, s); break;
-      case 4: st = launch_select_bf16<2>(a, s); break;
-      case 8: st = launch_select_bf16<4>(a, s); break;
-      case 16: st = launch_select_bf16<8>(a, s); break;
-      default: st = LPP_EUNSUPPORTED; break;
+    if (D <= kShortRow) {
+      st = D <= 8 ? launch_collect_f16<1>(a, s) : launch_collect_f16<2>(a, s);
+    } else {
+      switch (L.KS) {
+        case 1: st = launch_collect_i8<1>(a, s); break;
+        case 2: st = launch_collect_i8<2>(a, s); break;
+        case 3: st = launch_collect_i8<3>(a, s); break;
+        default: st = launch_collect_i8<4>(a, s); break;
+      }
     }
     if (st != LPP_OK) return st;
   }
-  const int P = (int)lpp_align_up((size_t)L.cap, kRankThreads);
-  const int CH = L.DP < 32 ? 16 : 32;
-  // keys + indices + the query row (as doubles and floats) + max(staging tiles, bucket counters and order);
-  // rows of 16 floats need no staging tiles
-  const size_t stage = CH == 16 ? 0 : (size_t)(kRankThreads / 64) * 64 * (CH + 4) * sizeof(float);
-  const size_t sortb = (size_t)P * 6;
-  const size_t lds = (size_t)P * 10 + (size_t)L.DP * 12 + (stage > sortb ? stage : sortb);
-  if (lds > 150 * 1024) return LPP_EUNSUPPORTED;
-  static LppLdsLimit limit[2];   // (zero-initialised) one per kernel
-  const void* fn = CH == 16 ? reinterpret_cast<const void*>(knn_rank_kernel<16>)
-                            : reinterpret_cast<const void*>(knn_rank_kernel<32>);
-  const int32_t st = lpp_ensure_lds(fn, limit[CH == 32], lds);
-  if (st != LPP_OK) return st;
-  if (CH == 16)
-    hipLaunchKernelGGL(knn_rank_kernel<16>, dim3((unsigned)V), dim3(kRankThreads), lds, s, a, P);
-  else
-    hipLaunchKernelGGL(knn_rank_kernel<32>, dim3((unsigned)V), dim3(kRankThreads), lds, s, a, P);
-  LPP_HIP_TRY(hipGetLastError());
-  return LPP_OK;
+  // a list of up to eight words per thread: one wave for short lists (a block of four would mostly wait for
+  // its barriers), four for the usual ones
+  const bool staged = D > kShortRow;
+  if (L.cap <= 512) {
+    const RankShape sh{L.cap, std::max(8, log2_up(L.cap))};
+    return staged ? launch_rank<64, true>(a, sh, s) : launch_rank<64, false>(a, sh, s);
+  }
+  if (L.cap <= 2048) {
+    const RankShape sh{L.cap, std::max(10, log2_up(L.cap))};
+    return staged ? launch_rank<256, true>(a, sh, s) : launch_rank<256, false>(a, sh, s);
+  }
+  if (L.cap > 8192) return LPP_EUNSUPPORTED;
+  const RankShape sh{L.cap, std::max(12, log2_up(L.cap))};
+  return staged ? launch_rank<1024, true>(a, sh, s) : launch_rank<1024, false>(a, sh, s);
 }

@@ -1,0 +1,53 @@
+"""GPU parity of lpp_build_neighbours where its paths change: the one-kernel path for small codebooks of
+short rows, every number of contraction steps, the sample's strides, one wave / four / sixteen per ranked
+row, lists that take every code, rows that fall through to the exact path.  Bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import build_neighbours
+from gpu_common import run_knn
+
+pytestmark = pytest.mark.gpu
+
+
+def _unit(g, V, D):
+    E = g.standard_normal((V, D))
+    return (E / np.linalg.norm(E, axis=1, keepdims=True)).astype(np.float32)
+
+
+def _check(E, k, rows=None):
+    got = run_knn(E, k)
+    rows = np.arange(E.shape[0]) if rows is None else rows
+    want = build_neighbours(E, k, rows=rows)
+    bad = np.flatnonzero((got[rows] != want).any(axis=1))
+    assert bad.size == 0, f"{bad.size} of {len(rows)} rows differ; row {rows[bad[0]]}: {got[rows[bad[0]]][:8]} want {want[bad[0]][:8]}"
+
+
+@pytest.mark.parametrize("V,D,k", [
+    (2, 1, 2), (5, 16, 3), (255, 3, 255), (1023, 5, 1), (1024, 16, 1024), (1024, 8, 16), (1000, 13, 900),   # one kernel
+    (1025, 8, 16), (1040, 4, 700), (2049, 12, 65), (3000, 16, 300), (4095, 1, 50), (8200, 7, 9), (20000, 8, 40),
+    (129, 17, 5), (1024, 64, 16), (513, 65, 200), (1100, 128, 70), (700, 129, 700), (2600, 192, 31),
+    (1300, 193, 1000), (300, 255, 8), (9000, 32, 500), (5000, 96, 2500)])
+def test_knn_path_edges(V, D, k):
+    g = np.random.default_rng(V * 7 + D)
+    E = _unit(g, V, D)
+    _check(E, k, None if V <= 3000 else np.unique(np.concatenate([[0, V - 1], g.choice(V, size=150)])))
+
+
+@pytest.mark.parametrize("D", [8, 48])
+def test_knn_codebook_with_an_order_of_its_own(D):
+    # neighbouring codes close together (a sorted codebook), unused codes all zero, a spread of norms
+    g = np.random.default_rng(D)
+    E = np.cumsum(g.standard_normal((6000, D)) * 0.05, axis=0)
+    E = (E / np.linalg.norm(E, axis=1, keepdims=True)).astype(np.float32)
+    E[1000:1400] = 0.0
+    E[2000:2100] *= 3.0
+    _check(E, 120, np.unique(np.concatenate([[1000, 2050, 5999], g.choice(6000, size=150)])))
+
+
+@pytest.mark.parametrize("D", [6, 40])
+def test_knn_near_ties_inside_the_rounding_of_the_similarities(D):
+    # clusters whose members differ by less than the approximate similarities resolve
+    g = np.random.default_rng(D)
+    E = np.repeat(_unit(g, 250, D).astype(np.float64), 10, axis=0) + 3e-8 * g.standard_normal((2500, D))
+    _check((E / np.linalg.norm(E, axis=1, keepdims=True)).astype(np.float32), 25)
