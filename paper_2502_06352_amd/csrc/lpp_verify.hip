@@ -340,6 +340,16 @@ __device__ __forceinline__ void collect_and_walk(MailRound r, int32_t* mail, uin
   }
 }
 
+// Where bin b of the top-k front end's 2048-bin histogram is kept in LDS.  The search reads it with
+// 32 consecutive bins per lane, which in plain order puts all 64 lanes on two banks (32 turns a
+// read, 32 reads, in every wave of the block); here the lanes of one read fall on 64 different banks,
+// and neighbouring bins, which the counting hits together, still on neighbouring banks.
+// B = 1, 61 rows of 8192, guidance and top-k 2000: 20.55 -> 20.15 us a call.
+__device__ __forceinline__ int hist_slot(int b) {
+  const int r = b & 31;
+  return (r << 6) + (((b >> 5) + r) & 63);
+}
+
 // Sum (max), in wave order, of one float per wave held in LDS; every wave
 // computes the same value the same way.
 // WIDE: two broadcast reads and seven additions, a shorter chain than the row shifts (for the
@@ -571,14 +581,14 @@ __global__ __launch_bounds__(NT, (STAG || ALT || FRONT || NT > 512) ? 1 : 4) voi
           for (int e = 0; e < 4; ++e) {
             const float x = (c[e] - lo) * scale;                 // monotone in c; -inf, NaN -> bin 0
             bin[j][e] = x >= 2047.f ? 2047 : (x >= 0.f ? (int)x : 0);
-            atomicAdd(&hist[bin[j][e]], 1u);
+            atomicAdd(&hist[hist_slot(bin[j][e])], 1u);
           }
         }
         lds_barrier();
         int cnt[32];
         int local = 0;
 #pragma unroll
-        for (int i = 0; i < 32; ++i) { cnt[i] = (int)hist[2047 - 32 * lane - i]; local += cnt[i]; }
+        for (int i = 0; i < 32; ++i) { cnt[i] = (int)hist[hist_slot(2047 - 32 * lane - i)]; local += cnt[i]; }
         int incl = local;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -634,7 +644,7 @@ __global__ __launch_bounds__(NT, (STAG || ALT || FRONT || NT > 512) ? 1 : 4) voi
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const bool in = pass == 0 || (key[j][e] >> (shift + bits)) == (prefix >> (shift + bits));
-              if (in) atomicAdd(&hist[(key[j][e] >> shift) & (nb - 1)], 1u);
+              if (in) atomicAdd(&hist[hist_slot((int)((key[j][e] >> shift) & (nb - 1)))], 1u);
             }
           lds_barrier();
           // every wave walks the bins from the top (32 per lane) and finds the one holding the need-th key
@@ -643,7 +653,7 @@ __global__ __launch_bounds__(NT, (STAG || ALT || FRONT || NT > 512) ? 1 : 4) voi
 #pragma unroll
           for (int i = 0; i < 32; ++i) {
             const int b = 2047 - 32 * lane - i;
-            cnt[i] = b < nb ? (int)hist[b] : 0;
+            cnt[i] = b < nb ? (int)hist[hist_slot(b)] : 0;
             local += cnt[i];
           }
           int incl = local;
