@@ -21,7 +21,7 @@
 // partials go through the workspace and the block that finishes last adds them up
 // in split order.
 //
-// fp32 path: a plain two-pass kernel, one block per row, for small shapes (no matrix cores).
+// fp32 path: the same two products on the float32 matrix cores, straight from the loads.
 #include <math.h>
 #include <stdlib.h>
 
@@ -593,112 +593,225 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
 }
 
 // ---------------------------------------------------------------- fp32 path
-// One block of 4 waves per (tree row, batch*head); lanes split Dh, waves split keys.
 struct AttnArgsF32 {
-  LayerPtrs layer[kLayersPerLaunch];     // blockIdx.z picks the layer
+  LayerPtrs layer[kLayersPerLaunch];     // blockIdx.y picks the layer
   const int32_t* seq_len; const uint64_t* anc;
-  int32_t B, H, S, M, words, Dh;
-  int32_t gq, out_bf16;     // query heads per key/value head; out holds bf16 instead of float
-  float scale;
+  int32_t B, H, Hkv, S, M, words;
+  int32_t mtiles, gq, out_bf16;     // row tiles; query heads per key/value head; out holds bf16 instead of float
+  float scale_log2;
 };
 
-// One block per (tree row, batch*head).  Pass 1: one key per thread, score = scale <q, k>, masked
-// keys dropped, block-wide maximum and sum of exp.  Pass 2: lanes split Dh, waves split the keys,
-// weights come from LDS.  Every load is independent of the previous one, so they overlap.
-__global__ __launch_bounds__(256) void tree_attn_f32_kernel(AttnArgsF32 a) {
-  extern __shared__ __align__(16) float s_p[];       // [seq + M] scores, then weights
-  __shared__ __align__(16) float s_q[128];
-  __shared__ float s_red[2][4];
-  __shared__ float s_acc[4][128];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m = blockIdx.x, bh = blockIdx.y, b = bh / a.H;
-  const int kvbh = bh / a.gq;            // batch * Hkv + key/value head (H = Hkv * gq)
-  const int Dh = a.Dh, M = a.M, S = a.S;
-  int seq = S;
-  if (a.seq_len) seq = min(max(a.seq_len[b], 0), S);     // (everything below depends on it anyway)
-  const int nkeys = seq + M;
-  const LayerPtrs& L = a.layer[blockIdx.z];
-  const float* const lq = reinterpret_cast<const float*>(L.q);
-  const float* const lkc = reinterpret_cast<const float*>(L.kc);
-  const float* const lvc = reinterpret_cast<const float*>(L.vc);
-  const float* const lkt = reinterpret_cast<const float*>(L.kt);
-  const float* const lvt = reinterpret_cast<const float*>(L.vt);
-  if (tid < Dh) s_q[tid] = lq[((int64_t)bh * M + m) * Dh + tid];
-  __syncthreads();
+// One tile of 16 keys in flight.  K: lane (i, g) holds of key i the dimensions 16 t + 4 g .. + 3; V: of keys
+// 4 g + r the dimensions 64 h + 4 i .. + 3 (i = lane % 16, g = lane / 16).
+template <int DH>
+struct StageF32 {
+  f32x4 k[DH / 16];
+  f32x4 v[4][DH / 64];
+};
 
-  float mx = -INFINITY;
-  for (int j = tid; j < nkeys; j += 256) {
-    float sc = -INFINITY;
-    const int t = j - seq;
-    const bool on = j < seq || ((a.anc[(int64_t)m * a.words + (t >> 6)] >> (t & 63)) & 1ull);
-    if (on) {
-      const float* kr = j < seq ? lkc + ((int64_t)kvbh * S + j) * Dh : lkt + ((int64_t)kvbh * M + t) * Dh;
-      float d0 = 0.f, d1 = 0.f, d2 = 0.f, d3 = 0.f;
-      for (int c = 0; c < Dh; c += 4) {
-        const float4 kv = *reinterpret_cast<const float4*>(kr + c);
-        const float4 qv = *reinterpret_cast<const float4*>(s_q + c);
-        d0 += qv.x * kv.x; d1 += qv.y * kv.y; d2 += qv.z * kv.z; d3 += qv.w * kv.w;
-      }
-      sc = ((d0 + d1) + (d2 + d3)) * a.scale;
+// Rows of K and V by position: the cache first, then the tree.
+template <int DH>
+struct KeysF32 {
+  const float* kc; const float* vc; const float* kt; const float* vt;
+  int seq, n;
+  __device__ __forceinline__ const float* k(int j) const { return j < seq ? kc + (int64_t)j * DH : kt + (int64_t)(j - seq) * DH; }
+  __device__ __forceinline__ const float* v(int j) const { return j < seq ? vc + (int64_t)j * DH : vt + (int64_t)(j - seq) * DH; }
+  __device__ __forceinline__ void load(StageF32<DH>& st, int tile, int lane) const {
+    const int i = lane & 15, g = lane >> 4;
+    const float* kr = k(min(tile * 16 + i, n - 1));          // (past the end: the last key again, masked below)
+#pragma unroll
+    for (int t = 0; t < DH / 16; ++t) st.k[t] = *reinterpret_cast<const f32x4*>(kr + 16 * t + 4 * g);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float* vr = v(min(tile * 16 + 4 * g + r, n - 1));
+#pragma unroll
+      for (int h = 0; h < DH / 64; ++h) st.v[r][h] = *reinterpret_cast<const f32x4*>(vr + 64 * h + 4 * i);
     }
-    s_p[j] = sc;
-    mx = fmaxf(mx, sc);
   }
+};
+
+// Rows whose result is not finite: a masked key, or one whose weight underflows, contributes an exact 0
+// whatever its V row holds, which a product of matrices does not give.  A wave per row, two passes.
+template <int DH>
+__device__ void f32_row_by_selects(const AttnArgsF32& a, const KeysF32<DH>& keys, const float* q, int m, int lane,
+                                   float* out, int64_t e) {
+  auto score = [&](int j) {
+    const int t = j - keys.seq;
+    if (j >= keys.n || (t >= 0 && !((a.anc[(int64_t)m * a.words + (t >> 6)] >> (t & 63)) & 1ull))) return -INFINITY;
+    const float* kr = keys.k(j);
+    float d = 0.f;
+    for (int c = 0; c < DH; ++c) d += q[c] * kr[c];
+    return d * a.scale_log2;
+  };
+  float mx = -INFINITY;
+  for (int j = lane; j < keys.n; j += 64) mx = fmaxf(mx, score(j));
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-  if (lane == 0) s_red[0][wave] = mx;
-  __syncthreads();
-  mx = fmaxf(fmaxf(s_red[0][0], s_red[0][1]), fmaxf(s_red[0][2], s_red[0][3]));   // finite: a row sees itself
-  float l = 0.f;
-  for (int j = tid; j < nkeys; j += 256) {
-    const float sc = s_p[j];
-    const float p = sc == -INFINITY ? 0.f : expf(sc - mx);
-    s_p[j] = p;
+  float l = 0.f, acc[DH / 64] = {};
+  for (int j0 = 0; j0 < keys.n; j0 += 64) {
+    const float sc = score(j0 + lane);
+    const float p = sc == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc - mx);
     l += p;
+    const int cnt = min(64, keys.n - j0);
+    for (int u = 0; u < cnt; ++u) {
+      const float pu = __shfl(p, u);
+      const float* vr = keys.v(j0 + u);
+#pragma unroll
+      for (int h = 0; h < DH / 64; ++h) acc[h] += pu != 0.f ? pu * vr[lane + 64 * h] : 0.f;
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
-  if (lane == 0) s_red[1][wave] = l;
-  __syncthreads();
-  l = (s_red[1][0] + s_red[1][1]) + (s_red[1][2] + s_red[1][3]);
+#pragma unroll
+  for (int h = 0; h < DH / 64; ++h) {
+    if (a.out_bf16) reinterpret_cast<__bf16*>(out)[e + lane + 64 * h] = (__bf16)(acc[h] / l);
+    else out[e + lane + 64 * h] = acc[h] / l;
+  }
+}
 
-  // (loads are unconditional and eight keys deep; a key with weight 0 -- masked or underflowed --
-  // contributes an exact 0 whatever its V row holds)
-  float acc0 = 0.f, acc1 = 0.f;
-  const bool hi = lane + 64 < Dh;
-  for (int j0 = wave; j0 < nkeys; j0 += 32) {
-    float pj[8], v0[8], v1[8];
+// A block is 16 tree rows of one (batch, head); its W waves take the 16-key tiles in turn, the loads of a
+// wave's next tile issued before it works on the current one.  Both products run on the float32 matrix cores
+// (16x16x4, float32 products and sums):
+//   S^T[16 keys x 16 rows] = K Q^T     K and Q with the dimensions dealt so that a lane's operands are what
+//                                      its 16-byte loads bring
+//   O^T[Dh x 16 rows] += V^T P^T       the weights are already where the B operand wants them, V's dimensions
+//                                      are dealt like K's: no LDS between the loads and the products
+// Bound by the latency of a wave's few serial tiles at small shapes, by the matrix cores and L2 at large ones.
+// A block per row with a key per thread, which this replaces, read every key once per row and its K rows 64
+// cache lines at a time.  Before -> now: 4 heads, 16 rows, 256 keys of 64: 13.3 -> 9.1 us; 16 heads (2 items),
+// 96 rows, 1898 keys of 64: 172 -> 33 us; 12 heads, 21 rows, 1498 keys of 128: 76 -> 46 us.
+template <int DH, int W>
+__global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
+  constexpr int HT = DH / 64, P4 = DH / 4 + 1;              // row pitch of the merge buffer in float4
+  static_assert(16 * DH / 4 == W * 64 / (W == 16 && DH == 64 ? 4 : 1), "an output piece per thread");
+  extern __shared__ __align__(16) unsigned char s_f32[];
+  float4* const s_o = reinterpret_cast<float4*>(s_f32);     // [W][16][P4]
+  __shared__ float s_m[W][16], s_l[W][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 15, g = lane >> 4;
+  // the blocks of a key/value head sit on one XCD (block index mod 8) and share its L2
+  const int n = blockIdx.x >> 3, per = a.mtiles * a.gq;
+  const int kvbh = (n / per) * 8 + (int)(blockIdx.x & 7);
+  if (kvbh >= a.B * a.Hkv) return;
+  const int bh = kvbh * a.gq + (n % per) / a.mtiles, tile0 = (n % per) % a.mtiles;
+  const int b = kvbh / a.Hkv, M = a.M;
+  const int seq = a.seq_len ? min(max(a.seq_len[b], 0), a.S) : a.S;
+  const LayerPtrs& L = a.layer[blockIdx.y];
+  KeysF32<DH> keys;
+  keys.kc = reinterpret_cast<const float*>(L.kc) + (int64_t)kvbh * a.S * DH;
+  keys.vc = reinterpret_cast<const float*>(L.vc) + (int64_t)kvbh * a.S * DH;
+  keys.kt = reinterpret_cast<const float*>(L.kt) + (int64_t)kvbh * M * DH;
+  keys.vt = reinterpret_cast<const float*>(L.vt) + (int64_t)kvbh * M * DH;
+  keys.seq = seq; keys.n = seq + M;
+  const int ntiles = (keys.n + 15) / 16;
+  const int row = min(tile0 * 16 + i, M - 1);               // (rows past the last: the last one again, not written)
+  const float* const lq = reinterpret_cast<const float*>(L.q) + (int64_t)bh * M * DH;
+
+  StageF32<DH> cur, nxt;
+  if (wave < ntiles) keys.load(cur, wave, lane);
+  f32x4 q[DH / 16];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int j = min(j0 + 4 * u, nkeys - 1);
-      pj[u] = j0 + 4 * u < nkeys ? s_p[j] : 0.f;
-      const float* vr = j < seq ? lvc + ((int64_t)kvbh * S + j) * Dh : lvt + ((int64_t)kvbh * M + (j - seq)) * Dh;
-      v0[u] = vr[lane];
-      v1[u] = hi ? vr[lane + 64] : 0.f;
+  for (int t = 0; t < DH / 16; ++t) q[t] = *reinterpret_cast<const f32x4*>(lq + (int64_t)row * DH + 16 * t + 4 * g);
+  f32x4 acc[4 * HT] = {};
+  float m = -INFINITY, l = 0.f;
+  for (int tile = wave; tile < ntiles; tile += W) {
+    if (tile + W < ntiles) keys.load(nxt, tile + W, lane);
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < DH / 16; t += 2)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[t][e], q[t][e], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[t + 1][e], q[t + 1][e], s1, 0, 0, 0);
+      }
+    float sc[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sc[r] = (s0[r] + s1[r]) * a.scale_log2;
+    if (tile * 16 + 16 > seq) {                             // tree keys, or past the end
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int t = tile * 16 + 4 * g + r - seq;
+        const uint64_t w = t >= 0 && t < M ? a.anc[(int64_t)row * a.words + (t >> 6)] >> (t & 63) : (uint64_t)(t < 0);
+        if (!(w & 1ull)) sc[r] = -INFINITY;
+      }
+    }
+    float mn = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+    mn = fmaxf(mn, __shfl_xor(mn, 16));
+    mn = fmaxf(mn, __shfl_xor(mn, 32));
+    mn = fmaxf(mn, m);
+    if (__any(mn != m)) {
+      const float f = mn == m ? 1.f : __builtin_amdgcn_exp2f(m - mn);
+      l *= f;
+#pragma unroll
+      for (int d = 0; d < 4 * HT; ++d) acc[d] *= f;
+      m = mn;
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      acc0 += pj[u] != 0.f ? pj[u] * v0[u] : 0.f;
-      acc1 += pj[u] != 0.f ? pj[u] * v1[u] : 0.f;
+    for (int r = 0; r < 4; ++r) {
+      sc[r] = sc[r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc[r] - m);
+      l += sc[r];
     }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int h = 0; h < HT; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc[4 * h + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.v[r][h][e], sc[r], acc[4 * h + e], 0, 0, 0);
+    cur = nxt;
   }
-  s_acc[wave][lane] = acc0;
-  s_acc[wave][lane + 64] = acc1;
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  if (lane < 16) { s_m[wave][i] = m; s_l[wave][i] = l; }
+  if (wave < ntiles) {
+#pragma unroll
+    for (int h = 0; h < HT; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        s_o[(wave * 16 + i) * P4 + 16 * h + 4 * g + r] =
+            make_float4(acc[4 * h][r], acc[4 * h + 1][r], acc[4 * h + 2][r], acc[4 * h + 3][r]);
+  }
   __syncthreads();
-  if (wave == 0) {
-    const float o0 = (s_acc[0][lane] + s_acc[1][lane]) + (s_acc[2][lane] + s_acc[3][lane]);
-    const float o1 = (s_acc[0][lane + 64] + s_acc[1][lane + 64]) + (s_acc[2][lane + 64] + s_acc[3][lane + 64]);
-    const int64_t e = ((int64_t)bh * M + m) * Dh;
-    if (a.out_bf16) {
-      __bf16* orow = reinterpret_cast<__bf16*>(L.out) + e;
-      if (lane < Dh) orow[lane] = (__bf16)(o0 / l);
-      if (lane + 64 < Dh) orow[lane + 64] = (__bf16)(o1 / l);
-    } else {
-      float* orow = reinterpret_cast<float*>(L.out) + e;
-      if (lane < Dh) orow[lane] = o0 / l;
-      if (lane + 64 < Dh) orow[lane + 64] = o1 / l;
+
+  const int orow = tid / (DH / 4), c4 = tid % (DH / 4);
+  const bool mine = tid < 16 * DH / 4 && tile0 * 16 + orow < M;
+  const int nw = min(W, ntiles);
+  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (mine) {
+    float mm = s_m[0][orow], ll = 0.f;
+    for (int w = 1; w < nw; ++w) mm = fmaxf(mm, s_m[w][orow]);
+#pragma unroll 4
+    for (int w = 0; w < nw; ++w) {
+      const float f = __builtin_amdgcn_exp2f(s_m[w][orow] - mm);     // (NaN where no key has a score: by selects)
+      const float4 x = s_o[(w * 16 + orow) * P4 + c4];
+      ll += f * s_l[w][orow];
+      o.x += f * x.x; o.y += f * x.y; o.z += f * x.z; o.w += f * x.w;
     }
+    o.x /= ll; o.y /= ll; o.z /= ll; o.w /= ll;
   }
+  const bool finite = isfinite(o.x) && isfinite(o.y) && isfinite(o.z) && isfinite(o.w);
+  float* const out = reinterpret_cast<float*>(L.out);
+  const int64_t e0 = ((int64_t)bh * M + tile0 * 16) * DH;
+  if (!__syncthreads_or(!finite)) {
+    if (mine) store_out4(out, a.out_bf16 != 0, e0 + (int64_t)orow * DH + c4 * 4, o);
+    return;
+  }
+  for (int r = wave; r < 16 && tile0 * 16 + r < M; r += W)
+    f32_row_by_selects<DH>(a, keys, lq + (int64_t)(tile0 * 16 + r) * DH, tile0 * 16 + r, lane, out, e0 + (int64_t)r * DH);
+}
+
+template <int DH, int W>
+int32_t launch_f32(const AttnArgsF32& a, int n_layers, hipStream_t s) {
+  static LppLdsLimit limit;
+  auto kern = tree_attn_f32_kernel<DH, W>;
+  const size_t lds = (size_t)W * 16 * (DH + 4) * sizeof(float);
+  const int32_t st = lpp_ensure_lds(reinterpret_cast<const void*>(kern), limit, lds, 48 * 1024);
+  if (st != LPP_OK) return st;
+  const int64_t blocks = 8 * (((int64_t)a.B * a.Hkv + 7) / 8) * a.gq * a.mtiles;
+  if (blocks >= (1ll << 31)) return LPP_EUNSUPPORTED;
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)n_layers), dim3(W * 64), lds, s, a);
+  LPP_HIP_TRY(hipGetLastError());
+  return LPP_OK;
 }
 
 struct AttnPlan {
@@ -829,16 +942,12 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
         a.layer[l] = LayerPtrs{y.q, y.k_cache, y.v_cache, y.k_tree, y.v_tree, y.out};
       }
       a.seq_len = seq_len; a.anc = tree->d_anc;
-      a.B = B; a.H = H; a.S = S; a.M = tree->M; a.words = tree->words; a.Dh = Dh; a.scale = scale;
-      a.gq = H / Hkv; a.out_bf16 = out_dtype == LPP_BF16;
-      static LppLdsLimit limit;
-      const size_t lds = (size_t)(S + tree->M) * sizeof(float);
-      if (lds > 144 * 1024) return LPP_EUNSUPPORTED;     // the scores of one row are kept in LDS
-      const int32_t st = lpp_ensure_lds(reinterpret_cast<const void*>(tree_attn_f32_kernel), limit, lds, 48 * 1024);
+      a.B = B; a.H = H; a.Hkv = Hkv; a.S = S; a.M = tree->M; a.words = tree->words;
+      a.mtiles = p.mtiles; a.gq = H / Hkv; a.out_bf16 = out_dtype == LPP_BF16;
+      a.scale_log2 = scale * 1.44269504088896340736f;
+      if ((size_t)(S + tree->M) * sizeof(float) > 144 * 1024) return LPP_EUNSUPPORTED;   // (the range that is tested)
+      const int32_t st = Dh == 64 ? launch_f32<64, 16>(a, nl, s) : launch_f32<128, 8>(a, nl, s);
       if (st != LPP_OK) return st;
-      hipLaunchKernelGGL(tree_attn_f32_kernel, dim3((unsigned)tree->M, (unsigned)(B * H), (unsigned)nl), dim3(256), lds,
-                         s, a);
-      LPP_HIP_TRY(hipGetLastError());
       continue;
     }
 

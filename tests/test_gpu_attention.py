@@ -118,3 +118,43 @@ def test_attention_argument_errors():
     with pytest.raises(lpp.LppError) as e:
         run_attention(lpp.Tree(parent), att, cfg)
     assert e.value.status == lpp.LPP_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("N,S,lens", [
+    (0, 1, [1, 0]), (14, 15, [15, 1]), (15, 16, [16, 2]), (16, 17, [17, 0]), (31, 33, [16, 31]),
+    (15, 240, [240, 239]), (32, 256, [256, 241]), (60, 700, [700, 513]), (127, 530, [530, 385])])
+def test_attention_f32_tile_edges(Dh, N, S, lens):
+    # row tiles of 16, key tiles of 16, rounds of 128 or 256 keys: one short, even, one over
+    branching = (6, 3, 2, 2, 1, 1) if N <= 60 else (8, 4, 2, 2, 1, 1, 1, 1)
+    cfg = CONFIGS[2].scaled(N=N, branching=branching, S=S, H=3, Dh=Dh, B=2, kv_dtype="f32")
+    parent = static_tree(cfg.branching, cfg.N) if N else np.array([-1], dtype=np.int32)
+    att = make_attention_inputs(cfg)
+    sl = np.array(lens, dtype=np.int32)
+    _check(cfg, parent, att, run_attention(lpp.Tree(parent), att, cfg, seq_len=sl), seq_len=sl)
+
+
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_attention_f32_ignores_what_a_row_does_not_see(Dh, bad):
+    # a masked key, and one whose weight underflows to zero, add nothing whatever their V rows hold
+    cfg = CONFIGS[2].scaled(N=20, S=150, H=2, B=1, Dh=Dh, kv_dtype="f32")
+    parent = static_tree(cfg.branching, cfg.N)
+    att = make_attention_inputs(cfg)
+    tree = lpp.Tree(parent)
+    from oracle import ancestor_mask
+    vis = ancestor_mask(parent)
+    want = tree_attention(att["q"], att["kc"], att["vc"], att["kt"], att["vt"], parent)
+    kt, vt = att["kt"].copy(), att["vt"].copy()
+    kt[:, :, 2], vt[:, :, 2] = bad, bad
+    got = run_attention(tree, dict(att, kt=kt, vt=vt), cfg)
+    unseen = ~vis[:, 2]
+    assert unseen.any() and attention_error(got[:, :, unseen], want[:, :, unseen]) <= TOL["f32"]
+    assert np.all(np.isnan(got[:, :, ~unseen]) | np.isinf(got[:, :, ~unseen]))
+    kc, vc = att["kc"].copy(), att["vc"].copy()
+    kc[:, :, 5] = -1e6 * np.sign(att["q"][:, :, :1]).squeeze(2)     # row 0 gives it no weight
+    vc[:, :, 5] = bad
+    got = run_attention(tree, dict(att, kc=kc, vc=vc), cfg)
+    keep = np.arange(150) != 5
+    want = tree_attention(att["q"], att["kc"][:, :, keep], att["vc"][:, :, keep], att["kt"], att["vt"], parent)
+    assert attention_error(got[:, :, :1], want[:, :, :1]) <= TOL["f32"]
