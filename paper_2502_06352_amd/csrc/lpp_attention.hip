@@ -598,8 +598,21 @@ struct AttnArgsF32 {
   const int32_t* seq_len; const uint64_t* anc;
   int32_t B, H, Hkv, S, M, words;
   int32_t mtiles, gq, out_bf16;     // row tiles; query heads per key/value head; out holds bf16 instead of float
-  float scale_log2;
+  float scale;
+  int32_t nsplit;                   // key ranges per (batch, head), and with more than one their partials:
+  float4* ws_o;                     // [layer][BH][mtiles][nsplit][16][Dh]  unnormalised partial O
+  float2* ws_ml;                    // [layer][BH][mtiles][nsplit][16]      (reference max, sum)
 };
+
+// e^t for t <= 0 (0 below -200, NaN stays): the hardware's 2^x on t log2 e, whose rounding is taken back to first
+// order.  Without that, scores of a few units cost a fifth of the accuracy; expf keeps it, but its registers
+// spill in the kernel (12 bytes a lane at rows of 64).
+__device__ __forceinline__ float exp_neg(float t) {
+  constexpr float kLog2e = 1.44269504088896340736f, kLn2 = 0.69314718055994530942f;
+  t = t < -200.f ? -200.f : t;
+  const float x = t * kLog2e, r = __builtin_amdgcn_exp2f(x);
+  return __builtin_fmaf(r, __builtin_fmaf(t, kLog2e, -x) * kLn2, r);
+}
 
 // One tile of 16 keys in flight.  K: lane (i, g) holds of key i the dimensions 16 t + 4 g .. + 3; V: of keys
 // 4 g + r the dimensions 64 h + 4 i .. + 3 (i = lane % 16, g = lane / 16).
@@ -641,7 +654,7 @@ __device__ void f32_row_by_selects(const AttnArgsF32& a, const KeysF32<DH>& keys
     const float* kr = keys.k(j);
     float d = 0.f;
     for (int c = 0; c < DH; ++c) d += q[c] * kr[c];
-    return d * a.scale_log2;
+    return d * a.scale;
   };
   float mx = -INFINITY;
   for (int j = lane; j < keys.n; j += 64) mx = fmaxf(mx, score(j));
@@ -650,7 +663,7 @@ __device__ void f32_row_by_selects(const AttnArgsF32& a, const KeysF32<DH>& keys
   float l = 0.f, acc[DH / 64] = {};
   for (int j0 = 0; j0 < keys.n; j0 += 64) {
     const float sc = score(j0 + lane);
-    const float p = sc == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc - mx);
+    const float p = sc == -INFINITY ? 0.f : exp_neg(sc - mx);
     l += p;
     const int cnt = min(64, keys.n - j0);
     for (int u = 0; u < cnt; ++u) {
@@ -669,6 +682,57 @@ __device__ void f32_row_by_selects(const AttnArgsF32& a, const KeysF32<DH>& keys
   }
 }
 
+__device__ __forceinline__ void fma4(float4& o, float f, float4 x) {
+  o.x = __builtin_fmaf(f, x.x, o.x); o.y = __builtin_fmaf(f, x.y, o.y);
+  o.z = __builtin_fmaf(f, x.z, o.z); o.w = __builtin_fmaf(f, x.w, o.w);
+}
+
+// What a block works on: a tile of 16 rows of one (batch, head).  `n` counts the tiles of the block's XCD: the
+// blocks of a key/value head sit on one XCD (block index mod 8) and share its L2.
+template <int DH>
+struct CellF32 {
+  KeysF32<DH> keys;
+  const float* q;                   // the (batch, head)'s queries
+  float* out;
+  int64_t cell, e0;                 // number of the tile over all layers; first element of its output
+  int tile0;
+  bool live;
+  __device__ __forceinline__ CellF32(const AttnArgsF32& a, int n) {
+    const int per = a.mtiles * a.gq, kvbh = (n / per) * 8 + (int)(blockIdx.x & 7);
+    live = kvbh < a.B * a.Hkv;
+    if (!live) return;
+    const int bh = kvbh * a.gq + (n % per) / a.mtiles, b = kvbh / a.Hkv;
+    tile0 = (n % per) % a.mtiles;
+    cell = ((int64_t)blockIdx.y * a.B * a.H + bh) * a.mtiles + tile0;
+    e0 = ((int64_t)bh * a.M + tile0 * 16) * DH;
+    const LayerPtrs& L = a.layer[blockIdx.y];
+    keys.kc = reinterpret_cast<const float*>(L.kc) + (int64_t)kvbh * a.S * DH;
+    keys.vc = reinterpret_cast<const float*>(L.vc) + (int64_t)kvbh * a.S * DH;
+    keys.kt = reinterpret_cast<const float*>(L.kt) + (int64_t)kvbh * a.M * DH;
+    keys.vt = reinterpret_cast<const float*>(L.vt) + (int64_t)kvbh * a.M * DH;
+    keys.seq = a.seq_len ? min(max(a.seq_len[b], 0), a.S) : a.S;
+    keys.n = keys.seq + a.M;
+    q = reinterpret_cast<const float*>(L.q) + (int64_t)bh * a.M * DH;
+    out = reinterpret_cast<float*>(L.out);
+  }
+};
+
+// Divide by the row's sum and write; all threads of the block.  A tile with a result that is not finite (0 / 0
+// among them: no key has a score) is done again by selects.
+template <int DH, int W>
+__device__ __forceinline__ void f32_finish(const AttnArgsF32& a, const CellF32<DH>& c, bool mine, int orow, int c4,
+                                           float4 o, float ll) {
+  if (mine) { o.x /= ll; o.y /= ll; o.z /= ll; o.w /= ll; }
+  const bool finite = isfinite(o.x) && isfinite(o.y) && isfinite(o.z) && isfinite(o.w);
+  if (!__syncthreads_or(!finite)) {
+    if (mine) store_out4(c.out, a.out_bf16 != 0, c.e0 + (int64_t)orow * DH + c4 * 4, o);
+    return;
+  }
+  for (int r = (int)(threadIdx.x >> 6); r < 16 && c.tile0 * 16 + r < a.M; r += W)
+    f32_row_by_selects<DH>(a, c.keys, c.q + (int64_t)(c.tile0 * 16 + r) * DH, c.tile0 * 16 + r, threadIdx.x & 63, c.out,
+                           c.e0 + (int64_t)r * DH);
+}
+
 // A block is 16 tree rows of one (batch, head); its W waves take the 16-key tiles in turn, the loads of a
 // wave's next tile issued before it works on the current one.  Both products run on the float32 matrix cores
 // (16x16x4, float32 products and sums):
@@ -678,8 +742,12 @@ __device__ void f32_row_by_selects(const AttnArgsF32& a, const KeysF32<DH>& keys
 //                                      are dealt like K's: no LDS between the loads and the products
 // Bound by the latency of a wave's few serial tiles at small shapes, by the matrix cores and L2 at large ones.
 // A block per row with a key per thread, which this replaces, read every key once per row and its K rows 64
-// cache lines at a time.  Before -> now: 4 heads, 16 rows, 256 keys of 64: 13.3 -> 9.1 us; 16 heads (2 items),
-// 96 rows, 1898 keys of 64: 172 -> 33 us; 12 heads, 21 rows, 1498 keys of 128: 76 -> 46 us.
+// cache lines at a time.  Before -> now: 4 heads, 16 rows, 256 keys of 64: 13.3 -> 10.3 us; 16 heads, 96 rows,
+// 1898 keys of 64: 172 -> 25.5 us; 12 heads, 21 rows, 1498 keys of 128: 76 -> 20 us.  Error against 64 bits, mean
+// of 12 inputs: 2.1e-7 -> 1.7e-7 at the first, 5.9e-7 -> 2.1e-7 at 4096 keys.
+// Where the launch leaves compute units idle the keys of a (batch, head) are cut into ranges, a block each (one
+// compute unit takes in some tens of bytes a nanosecond, whatever its waves ask for) and a second kernel adds
+// the partials up in the order of the ranges.  (Not a ticket in the handle: calls of this type keep no state.)
 template <int DH, int W>
 __global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
   constexpr int HT = DH / 64, P4 = DH / 4 + 1;              // row pitch of the merge buffer in float4
@@ -689,44 +757,39 @@ __global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
   __shared__ float s_m[W][16], s_l[W][16];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, g = lane >> 4;
-  // the blocks of a key/value head sit on one XCD (block index mod 8) and share its L2
-  const int n = blockIdx.x >> 3, per = a.mtiles * a.gq;
-  const int kvbh = (n / per) * 8 + (int)(blockIdx.x & 7);
-  if (kvbh >= a.B * a.Hkv) return;
-  const int bh = kvbh * a.gq + (n % per) / a.mtiles, tile0 = (n % per) % a.mtiles;
-  const int b = kvbh / a.Hkv, M = a.M;
-  const int seq = a.seq_len ? min(max(a.seq_len[b], 0), a.S) : a.S;
-  const LayerPtrs& L = a.layer[blockIdx.y];
-  KeysF32<DH> keys;
-  keys.kc = reinterpret_cast<const float*>(L.kc) + (int64_t)kvbh * a.S * DH;
-  keys.vc = reinterpret_cast<const float*>(L.vc) + (int64_t)kvbh * a.S * DH;
-  keys.kt = reinterpret_cast<const float*>(L.kt) + (int64_t)kvbh * M * DH;
-  keys.vt = reinterpret_cast<const float*>(L.vt) + (int64_t)kvbh * M * DH;
-  keys.seq = seq; keys.n = seq + M;
-  const int ntiles = (keys.n + 15) / 16;
+  const CellF32<DH> c(a, (int)(blockIdx.x >> 3) / a.nsplit);
+  if (!c.live) return;
+  const KeysF32<DH>& keys = c.keys;
+  const int split = (int)(blockIdx.x >> 3) % a.nsplit, seq = keys.seq, M = a.M, tile0 = c.tile0;
+  const int all = (keys.n + 15) / 16;
+  const int tbeg = split * all / a.nsplit, tend = (split + 1) * all / a.nsplit;
   const int row = min(tile0 * 16 + i, M - 1);               // (rows past the last: the last one again, not written)
-  const float* const lq = reinterpret_cast<const float*>(L.q) + (int64_t)bh * M * DH;
 
   StageF32<DH> cur, nxt;
-  if (wave < ntiles) keys.load(cur, wave, lane);
+  if (tbeg + wave < tend) keys.load(cur, tbeg + wave, lane);
   f32x4 q[DH / 16];
 #pragma unroll
-  for (int t = 0; t < DH / 16; ++t) q[t] = *reinterpret_cast<const f32x4*>(lq + (int64_t)row * DH + 16 * t + 4 * g);
+  for (int t = 0; t < DH / 16; ++t) q[t] = *reinterpret_cast<const f32x4*>(c.q + (int64_t)row * DH + 16 * t + 4 * g);
   f32x4 acc[4 * HT] = {};
   float m = -INFINITY, l = 0.f;
-  for (int tile = wave; tile < ntiles; tile += W) {
-    if (tile + W < ntiles) keys.load(nxt, tile + W, lane);
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+  for (int tile = tbeg + wave; tile < tend; tile += W) {
+    if (tile + W < tend) keys.load(nxt, tile + W, lane);
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};      // four chains of Dh / 4 products, two at a time
 #pragma unroll
-    for (int t = 0; t < DH / 16; t += 2)
+    for (int t0 = 0; t0 < DH / 16; t0 += DH / 32) {
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[t][e], q[t][e], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[t + 1][e], q[t + 1][e], s1, 0, 0, 0);
-      }
+      for (int t = t0; t < t0 + DH / 32; t += 2)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[t][e], q[t][e], s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[t + 1][e], q[t + 1][e], s1, 0, 0, 0);
+        }
+      s += s0 + s1;
+    }
     float sc[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) sc[r] = (s0[r] + s1[r]) * a.scale_log2;
+    for (int r = 0; r < 4; ++r) sc[r] = s[r] * a.scale;
     if (tile * 16 + 16 > seq) {                             // tree keys, or past the end
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -740,7 +803,7 @@ __global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
     mn = fmaxf(mn, __shfl_xor(mn, 32));
     mn = fmaxf(mn, m);
     if (__any(mn != m)) {
-      const float f = mn == m ? 1.f : __builtin_amdgcn_exp2f(m - mn);
+      const float f = mn == m ? 1.f : exp_neg(m - mn);
       l *= f;
 #pragma unroll
       for (int d = 0; d < 4 * HT; ++d) acc[d] *= f;
@@ -748,7 +811,7 @@ __global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      sc[r] = sc[r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sc[r] - m);
+      sc[r] = sc[r] == -INFINITY ? 0.f : exp_neg(sc[r] - m);
       l += sc[r];
     }
 #pragma unroll
@@ -763,7 +826,7 @@ __global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
   if (lane < 16) { s_m[wave][i] = m; s_l[wave][i] = l; }
-  if (wave < ntiles) {
+  if (tbeg + wave < tend) {
 #pragma unroll
     for (int h = 0; h < HT; ++h)
 #pragma unroll
@@ -775,29 +838,60 @@ __global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
 
   const int orow = tid / (DH / 4), c4 = tid % (DH / 4);
   const bool mine = tid < 16 * DH / 4 && tile0 * 16 + orow < M;
-  const int nw = min(W, ntiles);
+  const int nw = min(W, tend - tbeg);
   float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+  float mm = -INFINITY, ll = 0.f;
   if (mine) {
-    float mm = s_m[0][orow], ll = 0.f;
-    for (int w = 1; w < nw; ++w) mm = fmaxf(mm, s_m[w][orow]);
-#pragma unroll 4
-    for (int w = 0; w < nw; ++w) {
-      const float f = __builtin_amdgcn_exp2f(s_m[w][orow] - mm);     // (NaN where no key has a score: by selects)
-      const float4 x = s_o[(w * 16 + orow) * P4 + c4];
-      ll += f * s_l[w][orow];
-      o.x += f * x.x; o.y += f * x.y; o.z += f * x.z; o.w += f * x.w;
-    }
-    o.x /= ll; o.y /= ll; o.z /= ll; o.w /= ll;
+    float mw[W], lw[W];                     // (a wave without a tile wrote -inf and 0)
+#pragma unroll
+    for (int w = 0; w < W; ++w) { mw[w] = s_m[w][orow]; lw[w] = s_l[w][orow]; }
+#pragma unroll
+    for (int w = 0; w < W; ++w) mm = fmaxf(mm, mw[w]);
+    float4 o1 = o;                          // (the odd waves' sums)
+    float l1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+      if (w < nw) {
+        const float f = mw[w] == -INFINITY ? 0.f : exp_neg(mw[w] - mm);
+        fma4(w & 1 ? o1 : o, f, s_o[(w * 16 + orow) * P4 + c4]);
+        (w & 1 ? l1 : ll) = __builtin_fmaf(f, lw[w], w & 1 ? l1 : ll);
+      }
+    o.x += o1.x; o.y += o1.y; o.z += o1.z; o.w += o1.w;
+    ll += l1;
   }
-  const bool finite = isfinite(o.x) && isfinite(o.y) && isfinite(o.z) && isfinite(o.w);
-  float* const out = reinterpret_cast<float*>(L.out);
-  const int64_t e0 = ((int64_t)bh * M + tile0 * 16) * DH;
-  if (!__syncthreads_or(!finite)) {
-    if (mine) store_out4(out, a.out_bf16 != 0, e0 + (int64_t)orow * DH + c4 * 4, o);
+  if (a.nsplit > 1) {
+    const int64_t prow = (c.cell * a.nsplit + split) * 16 + orow;
+    if (mine) {
+      a.ws_o[prow * (DH / 4) + c4] = o;
+      if (c4 == 0) a.ws_ml[prow] = make_float2(mm, ll);
+    }
     return;
   }
-  for (int r = wave; r < 16 && tile0 * 16 + r < M; r += W)
-    f32_row_by_selects<DH>(a, keys, lq + (int64_t)(tile0 * 16 + r) * DH, tile0 * 16 + r, lane, out, e0 + (int64_t)r * DH);
+  f32_finish<DH, W>(a, c, mine, orow, c4, o, ll);
+}
+
+// The partials of a row tile's key ranges, added up in their order: four floats of a row per thread.
+template <int DH, int W>
+__global__ __launch_bounds__(W * 64) void tree_attn_f32_merge_kernel(AttnArgsF32 a) {
+  const CellF32<DH> c(a, (int)(blockIdx.x >> 3));
+  if (!c.live) return;
+  const int tid = threadIdx.x, orow = tid / (DH / 4), c4 = tid % (DH / 4);
+  const bool mine = tid < 16 * DH / 4 && c.tile0 * 16 + orow < a.M;
+  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+  float mm = -INFINITY, ll = 0.f;
+  if (mine) {
+    const int64_t p0 = c.cell * a.nsplit * 16 + orow;
+    for (int u = 0; u < a.nsplit; ++u) mm = fmaxf(mm, a.ws_ml[p0 + 16 * u].x);
+#pragma unroll 4
+    for (int u = 0; u < a.nsplit; ++u) {
+      const float2 ml = a.ws_ml[p0 + 16 * u];
+      const float4 x = a.ws_o[(p0 + 16 * u) * (DH / 4) + c4];
+      const float f = ml.x == -INFINITY ? 0.f : exp_neg(ml.x - mm);
+      ll = __builtin_fmaf(f, ml.y, ll);
+      fma4(o, f, x);
+    }
+  }
+  f32_finish<DH, W>(a, c, mine, orow, c4, o, ll);
 }
 
 template <int DH, int W>
@@ -807,11 +901,35 @@ int32_t launch_f32(const AttnArgsF32& a, int n_layers, hipStream_t s) {
   const size_t lds = (size_t)W * 16 * (DH + 4) * sizeof(float);
   const int32_t st = lpp_ensure_lds(reinterpret_cast<const void*>(kern), limit, lds, 48 * 1024);
   if (st != LPP_OK) return st;
-  const int64_t blocks = 8 * (((int64_t)a.B * a.Hkv + 7) / 8) * a.gq * a.mtiles;
+  const int64_t blocks = 8 * (((int64_t)a.B * a.Hkv + 7) / 8) * a.gq * a.mtiles * a.nsplit;
   if (blocks >= (1ll << 31)) return LPP_EUNSUPPORTED;
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)n_layers), dim3(W * 64), lds, s, a);
   LPP_HIP_TRY(hipGetLastError());
+  if (a.nsplit > 1) {
+    hipLaunchKernelGGL((tree_attn_f32_merge_kernel<DH, W>), dim3((unsigned)(blocks / a.nsplit), (unsigned)n_layers),
+                       dim3(W * 64), 0, s, a);
+    LPP_HIP_TRY(hipGetLastError());
+  }
   return LPP_OK;
+}
+
+// Key ranges per (batch, head) of the float32 kernel: only while a compute unit would idle, of kRangeF32 key tiles
+// or more: a tile costs a block 0.2 us (rows of 64) or 0.4 us (128), the second kernel about 3 us, so that two
+// ranges of 16 are the least that gain.  One range -> this rule, 4 heads: 512 keys 12.5 -> 11.7 and 20.9 -> 17.2
+// us; 4096 keys 56 -> 14 and 106 -> 24 us (both sides before the exponential above, which adds about 1 us).
+constexpr int kRangeF32 = 16;
+int f32_splits(const lpp_tree* tree, int B, int H, int S, int layers) {
+  const int64_t blocks = (int64_t)B * H * ((tree->M + 15) / 16) * std::max(1, std::min(layers, kLayersPerLaunch));
+  const int64_t tiles = ((int64_t)S + tree->M + 15) / 16;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(tree->n_cu / blocks, tiles / kRangeF32), 16));
+}
+
+// Bytes of its partials: [O | max, sum]; nothing for one range.
+size_t f32_workspace(const lpp_tree* tree, int B, int H, int Dh, int layers, int nsplit, size_t* o_bytes) {
+  if (nsplit < 2) return 0;
+  const size_t rows = (size_t)B * H * ((tree->M + 15) / 16) * 16 * std::min(layers, kLayersPerLaunch) * nsplit;
+  if (o_bytes) *o_bytes = rows * Dh * sizeof(float);
+  return rows * (Dh + 2) * sizeof(float);
 }
 
 struct AttnPlan {
@@ -903,7 +1021,8 @@ extern "C" size_t lpp_tree_attention_layers_workspace(const lpp_tree* tree, int3
                                                       int32_t S, int32_t Dh) {
   if (!tree || L < 1 || B < 1 || H < 1 || S < 0 || (Dh != 64 && Dh != 128)) return 0;
   const AttnPlan p = plan_attention(tree, B, H, S, Dh, L);
-  return (size_t)std::min(L, kLayersPerLaunch) * layer_workspace(p, B, H, Dh, nullptr);
+  return std::max((size_t)std::min(L, kLayersPerLaunch) * layer_workspace(p, B, H, Dh, nullptr),
+                  f32_workspace(tree, B, H, Dh, L, f32_splits(tree, B, H, S, L), nullptr));
 }
 
 namespace {
@@ -924,13 +1043,14 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
   if (out_dtype != LPP_F32 && out_dtype != LPP_BF16) return LPP_EUNSUPPORTED;
   if ((int64_t)B * H > (1 << 24) || (int64_t)B * H * H >= (1ll << 32)) return LPP_EUNSUPPORTED;
   if ((int64_t)S * Dh >= (1ll << 31) || (int64_t)tree->M * Dh >= (1ll << 31)) return LPP_EUNSUPPORTED;   // 32-bit offsets inside one head
-  const size_t need = lpp_tree_attention_layers_workspace(tree, L, B, H, S, Dh);
+  const AttnPlan p = plan_attention(tree, B, H, S, Dh, L);
+  // (what bf16 needs; the float32 kernel takes as many key ranges as the workspace has room for)
+  const size_t need = (size_t)std::min(L, kLayersPerLaunch) * layer_workspace(p, B, H, Dh, nullptr);
   if (!ws || ws_bytes < need) return LPP_ENOWORKSPACE;
   if (!tree->d_anc) return LPP_EHIP;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if (scale == 0.f) scale = 1.0f / sqrtf((float)Dh);
 
-  const AttnPlan p = plan_attention(tree, B, H, S, Dh, L);
   // up to kLayersPerLaunch layers per launch; the launches of one call follow each other on the
   // stream and share the workspace
   for (int32_t l0 = 0; l0 < L; l0 += kLayersPerLaunch) {
@@ -944,8 +1064,13 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
       a.seq_len = seq_len; a.anc = tree->d_anc;
       a.B = B; a.H = H; a.Hkv = Hkv; a.S = S; a.M = tree->M; a.words = tree->words;
       a.mtiles = p.mtiles; a.gq = H / Hkv; a.out_bf16 = out_dtype == LPP_BF16;
-      a.scale_log2 = scale * 1.44269504088896340736f;
+      a.scale = scale;
       if ((size_t)(S + tree->M) * sizeof(float) > 144 * 1024) return LPP_EUNSUPPORTED;   // (the range that is tested)
+      size_t o_bytes = 0;
+      a.nsplit = f32_splits(tree, B, H, S, L);
+      while (a.nsplit > 1 && f32_workspace(tree, B, H, Dh, L, a.nsplit, &o_bytes) > ws_bytes) --a.nsplit;
+      a.ws_o = reinterpret_cast<float4*>(ws);
+      a.ws_ml = reinterpret_cast<float2*>(reinterpret_cast<unsigned char*>(ws) + o_bytes);
       const int32_t st = Dh == 64 ? launch_f32<64, 16>(a, nl, s) : launch_f32<128, 8>(a, nl, s);
       if (st != LPP_OK) return st;
       continue;

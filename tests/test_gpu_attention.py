@@ -123,9 +123,11 @@ def test_attention_argument_errors():
 @pytest.mark.parametrize("Dh", [64, 128])
 @pytest.mark.parametrize("N,S,lens", [
     (0, 1, [1, 0]), (14, 15, [15, 1]), (15, 16, [16, 2]), (16, 17, [17, 0]), (31, 33, [16, 31]),
-    (15, 240, [240, 239]), (32, 256, [256, 241]), (60, 700, [700, 513]), (127, 530, [530, 385])])
+    (15, 240, [240, 239]), (32, 256, [256, 241]), (60, 700, [700, 513]), (127, 530, [530, 385]),
+    (15, 496, [496, 0]), (15, 1100, [1100, 3]), (4, 4200, [4200, 4111])])
 def test_attention_f32_tile_edges(Dh, N, S, lens):
-    # row tiles of 16, key tiles of 16, rounds of 128 or 256 keys: one short, even, one over
+    # row tiles of 16, key tiles of 16, rounds of 128 or 256 keys: one short, even, one over; key ranges in
+    # blocks of their own, some of them empty for a short item
     branching = (6, 3, 2, 2, 1, 1) if N <= 60 else (8, 4, 2, 2, 1, 1, 1, 1)
     cfg = CONFIGS[2].scaled(N=N, branching=branching, S=S, H=3, Dh=Dh, B=2, kv_dtype="f32")
     parent = static_tree(cfg.branching, cfg.N) if N else np.array([-1], dtype=np.int32)
@@ -136,9 +138,10 @@ def test_attention_f32_tile_edges(Dh, N, S, lens):
 
 @pytest.mark.parametrize("Dh", [64, 128])
 @pytest.mark.parametrize("bad", [np.nan, np.inf])
-def test_attention_f32_ignores_what_a_row_does_not_see(Dh, bad):
+@pytest.mark.parametrize("S", [150, 900])
+def test_attention_f32_ignores_what_a_row_does_not_see(Dh, bad, S):
     # a masked key, and one whose weight underflows to zero, add nothing whatever their V rows hold
-    cfg = CONFIGS[2].scaled(N=20, S=150, H=2, B=1, Dh=Dh, kv_dtype="f32")
+    cfg = CONFIGS[2].scaled(N=20, S=S, H=2, B=1, Dh=Dh, kv_dtype="f32")
     parent = static_tree(cfg.branching, cfg.N)
     att = make_attention_inputs(cfg)
     tree = lpp.Tree(parent)
@@ -155,6 +158,6 @@ def test_attention_f32_ignores_what_a_row_does_not_see(Dh, bad):
     kc[:, :, 5] = -1e6 * np.sign(att["q"][:, :, :1]).squeeze(2)     # row 0 gives it no weight
     vc[:, :, 5] = bad
     got = run_attention(tree, dict(att, kc=kc, vc=vc), cfg)
-    keep = np.arange(150) != 5
+    keep = np.arange(S) != 5
     want = tree_attention(att["q"], att["kc"][:, :, keep], att["vc"][:, :, keep], att["kt"], att["vt"], parent)
     assert attention_error(got[:, :, :1], want[:, :, :1]) <= TOL["f32"]
