@@ -42,6 +42,7 @@
 #include <type_traits>
 
 #include "lpp_internal.h"
+#include "lpp_knn_list.h"
 
 namespace {
 
@@ -301,7 +302,8 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   const double unit = FIXED ? limb_unit(st.mabs) : 1.0 / kHalfScale;
   // one step of the histogram's argument: products of scaled halves, or of upper limbs (2^32 unit^2)
   const float to_sim = (float)(FIXED ? unit * unit * 4294967296.0 : unit * unit);
-  const bool finite = top > 0.f && top < INFINITY && (FIXED || st.mabs * kHalfScale < 65504.0f);
+  // (far below 1e-30 the bound on the error would itself be rounded)
+  const bool finite = top > 1e-30f && top < INFINITY && (FIXED || st.mabs * kHalfScale < 65504.0f);
   const float bscale = finite ? (kSampleBins / 2) * to_sim / top : 0.f;
 
   if (!a.take_all) {
@@ -393,7 +395,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   // ---- the row's plan (lane = row)
   RowPlan p;
   const int vb = a.vmask_bits;
-  const float qmax = (float)((1u << vb) - 2u);
+  const uint32_t qmax = (1u << vb) - 2u;
   const bool all = a.take_all || !finite;
   float thr, hi;
   if (all) {
@@ -422,7 +424,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   e += norm * st.norm * 1e-9f;
   float range = hi - thr;
   // below the bin's edge by more than the test at the end asks of the (k-1)-th entry
-  const float slack = 2.2f * e + 6.0f * range / qmax;
+  const float slack = 2.2f * e + (6.0f + 2.0f * (float)list_rounding(qmax)) * range / (float)qmax;
   thr -= slack;
   range += slack;
   p.flags = (all ? kAll : 0) | (st.nan > 0.f ? kAnyNan : 0) | (finite ? 0 : kNoList);
@@ -430,8 +432,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   p.a = (float)((double)qmax / ((double)range / uu));
   if (FIXED) p.thr_u = (int)fmin(fmax(floor((double)thr / uu), -1073741824.0), 1073741823.0);
   else p.thr = (float)((double)thr / uu);
-  // (values are floors of products rounded by less than a tenth)
-  p.E = (int)fmin(floor(2.002 * (double)e * (double)qmax / (double)range + 0.2) + 1.0, 1073741824.0);
+  p.E = list_margin(e, range, qmax);
   if (row >= a.V || !finite) {                              // nothing passes
     p.a = 0.f;
     if (FIXED) p.thr_u = 1 << 30;
@@ -460,7 +461,7 @@ __device__ __forceinline__ void emit_window(const KnnArgs& a, uint32_t mask, con
     if (mask != 0u) {
       const uint32_t s = __builtin_clz(mask), hi = s >> 2, lo = s & 3;
       mask &= ~(0x80000000u >> s);
-      const uint32_t v = min(value(mine[hi * 256 + lo]), qmax);
+      const uint32_t v = value(mine[hi * 256 + lo], qmax);
       const uint32_t code = __umul24(hi, tile_step) + code0;
       if (at < end) a.cand[at] = (v << a.ib) | code | lo;
       ++at;
@@ -519,7 +520,7 @@ __global__ __launch_bounds__(kCollectMaxWaves * 64) void knn_collect_f16_kernel(
     const int n = __popc(mask);
     const int base = n > 0 ? atomicAdd(&s_cnt[l16], n) : 0;
     emit_window(a, mask, parked, (uint32_t)(t0 * 16 + 4 * g4), (uint32_t)(16 * step), lane, list + base,
-                row < a.V ? a.cap - base : 0, [&](uint32_t v) { return (uint32_t)(__uint_as_float(v) * p.a); });
+                row < a.V ? a.cap - base : 0, [&](uint32_t v, uint32_t qmax) { return list_value(__uint_as_float(v), p.a, qmax); });
   }
   __syncthreads();
   if (threadIdx.x < 16 && blockIdx.x * 16 + threadIdx.x < a.V) a.cnt[blockIdx.x * 16 + threadIdx.x] = s_cnt[threadIdx.x];
@@ -633,7 +634,7 @@ __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(K
       const int base = out[n] + (g4 > 0 ? c1 : 0) + (g4 > 1 ? c2 : 0) + (g4 > 2 ? c3 : 0);
       emit_window(a, m, reinterpret_cast<const uint32_t*>(s_park[wave][n]), code0, (uint32_t)(16 * a.splits), lane, list[n] + base,
                   (qtile + n) * 16 + l16 < a.V ? a.cap_split - base : 0,
-                  [&](uint32_t v) { return (uint32_t)((float)(int)v * scale[n]); });
+                  [&](uint32_t v, uint32_t qmax) { return list_value((float)(int)v, scale[n], qmax); });
       out[n] += c1 + c2 + c3 + c4;
       fail[n] = 0;
     }

@@ -51,3 +51,14 @@ def test_knn_near_ties_inside_the_rounding_of_the_similarities(D):
     g = np.random.default_rng(D)
     E = np.repeat(_unit(g, 250, D).astype(np.float64), 10, axis=0) + 3e-8 * g.standard_normal((2500, D))
     _check((E / np.linalg.norm(E, axis=1, keepdims=True)).astype(np.float32), 25)
+
+
+@pytest.mark.parametrize("V,D", [(120, 250), (250, 256), (500, 200)])
+def test_knn_order_below_the_fixed_point_unit(V, D):
+    # flat rows +-c whose entries differ by a few units of the last place of a float: the fixed-point image, and
+    # the 24 to 23 value bits of so few codes, cannot tell them apart, the float64 keys must
+    g = np.random.default_rng(V + D)
+    c = np.float32(1.0 / np.sqrt(D))
+    sign = np.where(g.random((4, D)) < 0.5, -1.0, 1.0)[g.integers(0, 4, size=V)]
+    E = (sign * c * (1.0 + 2.0 ** -24 * g.integers(-3, 4, size=(V, D)))).astype(np.float32)
+    _check(E, V // 2)
