@@ -97,7 +97,8 @@ int32_t lpp_tree_set_walk_patience(lpp_tree* tree, int32_t rounds);
  *   neigh  [device] int32 [V, k] out; row x = B_k(x), nearest first, x itself in
  *          slot 0.  Order is by the similarity evaluated in float64 (the D
  *          products added one after the other in index order), ties to the lower
- *          index -- a deterministic, machine-independent result.
+ *          index -- a deterministic, machine-independent result.  A similarity that is NaN comes after
+ *          every other.
  * One-time per codebook.  Errors: LPP_EINVAL (null, V < 1, D < 1, k < 1, k > V),
  * LPP_EUNSUPPORTED (k > LPP_MAX_K, D > 256, V > 65536), LPP_ENOWORKSPACE, LPP_EHIP.
  * Rows are filtered by similarities of bounded error (rows of up to 16 floats: pairs of halves, so

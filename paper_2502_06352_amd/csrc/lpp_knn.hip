@@ -671,7 +671,10 @@ __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(K
 
 // ------------------------------------------------------------------------------------------ ranking
 
+// A key as an integer of the same order.  NaN comes last, behind -inf: a code that holds one is nobody's
+// neighbour while there are others, on every path.
 __device__ __forceinline__ uint64_t orderable(double x) {
+  if (x != x) return 1ull;
   const uint64_t u = (uint64_t)__double_as_longlong(x);
   return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
 }

@@ -62,3 +62,13 @@ def test_knn_order_below_the_fixed_point_unit(V, D):
     sign = np.where(g.random((4, D)) < 0.5, -1.0, 1.0)[g.integers(0, 4, size=V)]
     E = (sign * c * (1.0 + 2.0 ** -24 * g.integers(-3, 4, size=(V, D)))).astype(np.float32)
     _check(E, V // 2)
+
+
+@pytest.mark.parametrize("V,D,k", [(1000, 8, 40), (1000, 8, 1000), (1500, 8, 40), (1500, 8, 1500), (700, 40, 30), (700, 40, 700)])
+def test_knn_codes_that_hold_a_nan_come_last(V, D, k):
+    # on every path: rows of zeros tie everywhere and take the exact one, k = V has to list the NaN codes
+    g = np.random.default_rng(V + D)
+    E = _unit(g, V, D)
+    E[[7, V // 2], D // 2] = np.nan
+    E[[3, 11, V - 2]] = 0.0
+    _check(E, k, np.unique(np.concatenate([[3, 7, 11, V // 2, V - 2], g.choice(V, size=100)])))
