@@ -643,45 +643,6 @@ struct KeysF32 {
   }
 };
 
-// Rows whose result is not finite: a masked key, or one whose weight underflows, contributes an exact 0
-// whatever its V row holds, which a product of matrices does not give.  A wave per row, two passes.
-template <int DH>
-__device__ void f32_row_by_selects(const AttnArgsF32& a, const KeysF32<DH>& keys, const float* q, int m, int lane,
-                                   float* out, int64_t e) {
-  auto score = [&](int j) {
-    const int t = j - keys.seq;
-    if (j >= keys.n || (t >= 0 && !((a.anc[(int64_t)m * a.words + (t >> 6)] >> (t & 63)) & 1ull))) return -INFINITY;
-    const float* kr = keys.k(j);
-    float d = 0.f;
-    for (int c = 0; c < DH; ++c) d += q[c] * kr[c];
-    return d * a.scale;
-  };
-  float mx = -INFINITY;
-  for (int j = lane; j < keys.n; j += 64) mx = fmaxf(mx, score(j));
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-  float l = 0.f, acc[DH / 64] = {};
-  for (int j0 = 0; j0 < keys.n; j0 += 64) {
-    const float sc = score(j0 + lane);
-    const float p = sc == -INFINITY ? 0.f : exp_neg(sc - mx);
-    l += p;
-    const int cnt = min(64, keys.n - j0);
-    for (int u = 0; u < cnt; ++u) {
-      const float pu = __shfl(p, u);
-      const float* vr = keys.v(j0 + u);
-#pragma unroll
-      for (int h = 0; h < DH / 64; ++h) acc[h] += pu != 0.f ? pu * vr[lane + 64 * h] : 0.f;
-    }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o);
-#pragma unroll
-  for (int h = 0; h < DH / 64; ++h) {
-    if (a.out_bf16) reinterpret_cast<__bf16*>(out)[e + lane + 64 * h] = (__bf16)(acc[h] / l);
-    else out[e + lane + 64 * h] = acc[h] / l;
-  }
-}
-
 __device__ __forceinline__ void fma4(float4& o, float f, float4 x) {
   o.x = __builtin_fmaf(f, x.x, o.x); o.y = __builtin_fmaf(f, x.y, o.y);
   o.z = __builtin_fmaf(f, x.z, o.z); o.w = __builtin_fmaf(f, x.w, o.w);
@@ -717,20 +678,148 @@ struct CellF32 {
   }
 };
 
-// Divide by the row's sum and write; all threads of the block.  A tile with a result that is not finite (0 / 0
-// among them: no key has a score) is done again by selects.
+// Scores of a tile: lane (i, g) holds those of tree row i with keys 4 g + r, -inf where the row does not see the key.
+// row: that tree row.
+template <int DH>
+__device__ __forceinline__ void f32_scores(const AttnArgsF32& a, const StageF32<DH>& st, const f32x4 (&q)[DH / 16], int tile,
+                                           int row, int g, int seq, float (&sc)[4]) {
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};      // four chains of Dh / 4 products, two at a time
+#pragma unroll
+  for (int t0 = 0; t0 < DH / 16; t0 += DH / 32) {
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = t0; t < t0 + DH / 32; t += 2)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(st.k[t][e], q[t][e], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(st.k[t + 1][e], q[t + 1][e], s1, 0, 0, 0);
+      }
+    s += s0 + s1;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) sc[r] = s[r] * a.scale;
+  if (tile * 16 + 16 > seq) {                             // tree keys, or past the end
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int t = tile * 16 + 4 * g + r - seq;
+      const uint64_t w = t >= 0 && t < a.M ? a.anc[(int64_t)row * a.words + (t >> 6)] >> (t & 63) : (uint64_t)(t < 0);
+      if (!(w & 1ull)) sc[r] = -INFINITY;
+    }
+  }
+}
+
+// x, as something the compiler does not know: what is formed from it is formed here, and takes no registers
+// (which the loop over the keys has none to spare of) before.
+__device__ __forceinline__ int formed_anew(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// A wave's accumulators [4 HT] to the merge buffer's row (wave, i), row pitch P4.
+template <int DH>
+__device__ __forceinline__ void f32_park(float4* s_o, int P4, int wave, int lane, const f32x4 (&acc)[DH / 16]) {
+  const int i = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int h = 0; h < DH / 64; ++h)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      s_o[(wave * 16 + i) * P4 + 16 * h + 4 * g + r] =
+          make_float4(acc[4 * h][r], acc[4 * h + 1][r], acc[4 * h + 2][r], acc[4 * h + 3][r]);
+}
+
+// Divide by the row's sum and write; all threads of the block.  A key that a row does not see, or whose weight
+// underflows, adds an exact 0 whatever its V row holds, which a product of matrices does not give: where a
+// result is not finite the tile is done again, now with the rows' maxima (mm) known.  V is then multiplied with its
+// infinities and NaN as zeros, and in tiles that hold any they are counted, by a product with "the key has a
+// weight", and put where they belong.  One more pass over the keys, by one block per row tile (a second tile in
+// flight gains nothing: a compute unit takes in what it can).  With a NaN in one V row, key by key in
+// a block per row -> key by key in a wave per row -> so: 4 heads, 16 rows, 256 keys of 64: 13.3 -> 128 -> 17.8 us;
+// 16 heads, 96 rows, 1898 keys: 197 -> 866 -> 56; 12 heads, 21 rows, 1498 keys of 128: 76 -> 1556 -> 65; 8 heads on 2
+// shared ones, 27 rows, 1024 keys of 128: 46 -> 1075 -> 50.
 template <int DH, int W>
-__device__ __forceinline__ void f32_finish(const AttnArgsF32& a, const CellF32<DH>& c, bool mine, int orow, int c4,
-                                           float4 o, float ll) {
+__device__ __forceinline__ void f32_finish(const AttnArgsF32& a, const CellF32<DH>& c, float4* s_o, bool mine, int orow, int c4,
+                                           float4 o, float mm, float ll) {
+  constexpr int HT = DH / 64, P4 = DH / 4 + 1;
+  __shared__ float s_mx[16], s_sum[W][16];
+  __shared__ __align__(16) int s_again[W];
+  const int tid = formed_anew(threadIdx.x);
   if (mine) { o.x /= ll; o.y /= ll; o.z /= ll; o.w /= ll; }
   const bool finite = isfinite(o.x) && isfinite(o.y) && isfinite(o.z) && isfinite(o.w);
-  if (!__syncthreads_or(!finite)) {
-    if (mine) store_out4(c.out, a.out_bf16 != 0, c.e0 + (int64_t)orow * DH + c4 * 4, o);
-    return;
+  if (c4 == 0 && tid < 16 * DH / 4) s_mx[orow] = mm;
+  const int odd_wave = __any(!finite) ? 1 : 0;
+  if ((tid & 63) == 0) s_again[tid >> 6] = odd_wave;
+  __syncthreads();
+  int again = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) again |= s_again[w];
+  if (__builtin_amdgcn_readfirstlane(again)) {
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), i = lane & 15, g = lane >> 4;
+    const int row = min(c.tile0 * 16 + i, a.M - 1), all = (c.keys.n + 15) / 16;
+    const float mx = s_mx[min(i, a.M - 1 - c.tile0 * 16)];
+    f32x4 q[DH / 16], acc[4 * HT] = {};
+#pragma unroll
+    for (int t = 0; t < DH / 16; ++t) q[t] = *reinterpret_cast<const f32x4*>(c.q + (int64_t)row * DH + 16 * t + 4 * g);
+    float l = 0.f;
+    for (int tile = wave; tile < all; tile += W) {
+      StageF32<DH> st;
+      c.keys.load(st, tile, lane);
+      float sc[4], has[4];
+      f32_scores<DH>(a, st, q, tile, row, g, c.keys.seq, sc);
+      bool odd = false;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        sc[r] = sc[r] == -INFINITY ? 0.f : exp_neg(sc[r] - mx);
+        has[r] = sc[r] != 0.f ? 1.f : 0.f;
+        l += sc[r];
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int h = 0; h < HT; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float v = st.v[r][h][e];
+            odd = odd || !isfinite(v);
+            acc[4 * h + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(isfinite(v) ? v : 0.f, sc[r], acc[4 * h + e], 0, 0, 0);
+          }
+      if (__any(odd)) {
+#pragma unroll
+        for (int h = 0; h < HT; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            f32x4 n = {0.f, 0.f, 0.f, 0.f};              // of the 16 keys: +inf count 1, -inf 32, NaN 33
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float v = st.v[r][h][e];
+              const float count = isfinite(v) ? 0.f : (v > 0.f ? 1.f : (v < 0.f ? 32.f : 33.f));
+              n = __builtin_amdgcn_mfma_f32_16x16x4f32(count, has[r], n, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int x = (int)n[r];
+              if (x & 31) acc[4 * h + e][r] += INFINITY;
+              if (x >> 5) acc[4 * h + e][r] -= INFINITY;              // (both: NaN)
+            }
+          }
+      }
+    }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (lane < 16) s_sum[wave][i] = l;
+    f32_park<DH>(s_o, P4, wave, lane, acc);
+    __syncthreads();
+    if (mine && !finite) {
+      o = make_float4(0.f, 0.f, 0.f, 0.f);
+      ll = 0.f;
+#pragma unroll 1
+      for (int w = 0; w < W; ++w) {
+        fma4(o, 1.f, s_o[(w * 16 + orow) * P4 + c4]);
+        ll += s_sum[w][orow];
+      }
+      o.x /= ll; o.y /= ll; o.z /= ll; o.w /= ll;
+    }
   }
-  for (int r = (int)(threadIdx.x >> 6); r < 16 && c.tile0 * 16 + r < a.M; r += W)
-    f32_row_by_selects<DH>(a, c.keys, c.q + (int64_t)(c.tile0 * 16 + r) * DH, c.tile0 * 16 + r, threadIdx.x & 63, c.out,
-                           c.e0 + (int64_t)r * DH);
+  if (mine) store_out4(c.out, a.out_bf16 != 0, c.e0 + (int64_t)orow * DH + c4 * 4, o);
 }
 
 // A block is 16 tree rows of one (batch, head); its W waves take the 16-key tiles in turn, the loads of a
@@ -774,30 +863,8 @@ __global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
   float m = -INFINITY, l = 0.f;
   for (int tile = tbeg + wave; tile < tend; tile += W) {
     if (tile + W < tend) keys.load(nxt, tile + W, lane);
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};      // four chains of Dh / 4 products, two at a time
-#pragma unroll
-    for (int t0 = 0; t0 < DH / 16; t0 += DH / 32) {
-      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = t0; t < t0 + DH / 32; t += 2)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[t][e], q[t][e], s0, 0, 0, 0);
-          s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.k[t + 1][e], q[t + 1][e], s1, 0, 0, 0);
-        }
-      s += s0 + s1;
-    }
     float sc[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) sc[r] = s[r] * a.scale;
-    if (tile * 16 + 16 > seq) {                             // tree keys, or past the end
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int t = tile * 16 + 4 * g + r - seq;
-        const uint64_t w = t >= 0 && t < M ? a.anc[(int64_t)row * a.words + (t >> 6)] >> (t & 63) : (uint64_t)(t < 0);
-        if (!(w & 1ull)) sc[r] = -INFINITY;
-      }
-    }
+    f32_scores<DH>(a, cur, q, tile, row, g, seq, sc);
     float mn = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
     mn = fmaxf(mn, __shfl_xor(mn, 16));
     mn = fmaxf(mn, __shfl_xor(mn, 32));
@@ -825,19 +892,13 @@ __global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
   }
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
-  if (lane < 16) { s_m[wave][i] = m; s_l[wave][i] = l; }
-  if (tbeg + wave < tend) {
-#pragma unroll
-    for (int h = 0; h < HT; ++h)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        s_o[(wave * 16 + i) * P4 + 16 * h + 4 * g + r] =
-            make_float4(acc[4 * h][r], acc[4 * h + 1][r], acc[4 * h + 2][r], acc[4 * h + 3][r]);
-  }
+  const int tid2 = formed_anew(tid), lane2 = tid2 & 63;
+  if (lane2 < 16) { s_m[wave][lane2] = m; s_l[wave][lane2] = l; }
+  if (tbeg + wave < tend) f32_park<DH>(s_o, P4, wave, lane2, acc);
   __syncthreads();
 
-  const int orow = tid / (DH / 4), c4 = tid % (DH / 4);
-  const bool mine = tid < 16 * DH / 4 && tile0 * 16 + orow < M;
+  const int orow = tid2 / (DH / 4), c4 = tid2 % (DH / 4);
+  const bool mine = tid2 < 16 * DH / 4 && tile0 * 16 + orow < M;
   const int nw = min(W, tend - tbeg);
   float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
   float mm = -INFINITY, ll = 0.f;
@@ -867,12 +928,13 @@ __global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
     }
     return;
   }
-  f32_finish<DH, W>(a, c, mine, orow, c4, o, ll);
+  f32_finish<DH, W>(a, c, s_o, mine, orow, c4, o, mm, ll);
 }
 
 // The partials of a row tile's key ranges, added up in their order: four floats of a row per thread.
 template <int DH, int W>
 __global__ __launch_bounds__(W * 64) void tree_attn_f32_merge_kernel(AttnArgsF32 a) {
+  extern __shared__ __align__(16) unsigned char s_f32[];    // (for tiles that are done again)
   const CellF32<DH> c(a, (int)(blockIdx.x >> 3));
   if (!c.live) return;
   const int tid = threadIdx.x, orow = tid / (DH / 4), c4 = tid % (DH / 4);
@@ -891,7 +953,7 @@ __global__ __launch_bounds__(W * 64) void tree_attn_f32_merge_kernel(AttnArgsF32
       fma4(o, f, x);
     }
   }
-  f32_finish<DH, W>(a, c, mine, orow, c4, o, ll);
+  f32_finish<DH, W>(a, c, reinterpret_cast<float4*>(s_f32), mine, orow, c4, o, mm, ll);
 }
 
 template <int DH, int W>
@@ -906,8 +968,11 @@ int32_t launch_f32(const AttnArgsF32& a, int n_layers, hipStream_t s) {
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks, (unsigned)n_layers), dim3(W * 64), lds, s, a);
   LPP_HIP_TRY(hipGetLastError());
   if (a.nsplit > 1) {
-    hipLaunchKernelGGL((tree_attn_f32_merge_kernel<DH, W>), dim3((unsigned)(blocks / a.nsplit), (unsigned)n_layers),
-                       dim3(W * 64), 0, s, a);
+    static LppLdsLimit merge_limit;
+    auto merge = tree_attn_f32_merge_kernel<DH, W>;
+    const int32_t mst = lpp_ensure_lds(reinterpret_cast<const void*>(merge), merge_limit, lds, 48 * 1024);
+    if (mst != LPP_OK) return mst;
+    hipLaunchKernelGGL(merge, dim3((unsigned)(blocks / a.nsplit), (unsigned)n_layers), dim3(W * 64), lds, s, a);
     LPP_HIP_TRY(hipGetLastError());
   }
   return LPP_OK;

@@ -5,11 +5,12 @@ Tolerance (relative to |want| + the row's max |want|): 1e-4 for fp32 inputs,
 matrix cores)."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2502_06352_amd as lpp
 from oracle import tree_attention
 from workloads import CONFIGS, static_tree, make_attention_inputs
-from gpu_common import run_attention, attention_error
+from gpu_common import DEV, dev, run_attention, attention_error
 
 pytestmark = pytest.mark.gpu
 TOL = {"f32": 1e-4, "bf16": 2e-2}
@@ -161,3 +162,57 @@ def test_attention_f32_ignores_what_a_row_does_not_see(Dh, bad, S):
     keep = np.arange(S) != 5
     want = tree_attention(att["q"], att["kc"][:, :, keep], att["vc"][:, :, keep], att["kt"], att["vt"], parent)
     assert attention_error(got[:, :, :1], want[:, :, :1]) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("S", [150, 1100])
+def test_attention_f32_puts_infinities_where_they_belong(Dh, S):
+    # V rows with infinities of either sign and NaN, seen by all rows (cache) or by some (tree): every element of
+    # the output is what a sum over the keys its row sees gives, and what holds none stays as it was
+    cfg = CONFIGS[2].scaled(N=20, S=S, H=2, B=1, Dh=Dh, kv_dtype="f32")
+    parent = static_tree(cfg.branching, cfg.N)
+    att = make_attention_inputs(cfg)
+    tree = lpp.Tree(parent)
+    from oracle import ancestor_mask
+    vis = ancestor_mask(parent)
+    clean = run_attention(tree, att, cfg)
+    vc, vt = att["vc"].copy(), att["vt"].copy()
+    vc[0, 0, 7, 3], vc[0, 0, S - 1, 4], vc[0, 0, 40, 5], vc[0, 0, 41, 5] = np.inf, -np.inf, np.inf, -np.inf
+    vt[0, 1, 2, 6], vt[0, 1, 5, 6], vt[0, 1, 1, Dh - 1] = np.inf, -np.inf, np.nan
+    got = run_attention(tree, dict(att, vc=vc, vt=vt), cfg)
+    want = clean.astype(np.float64)
+    want[0, 0, :, 3], want[0, 0, :, 4], want[0, 0, :, 5] = np.inf, -np.inf, np.nan
+    want[0, 1, vis[:, 2], 6] = np.inf
+    want[0, 1, vis[:, 5], 6] = np.where(vis[vis[:, 5], 2], np.nan, -np.inf)
+    want[0, 1, vis[:, 1], Dh - 1] = np.nan
+    odd = ~np.isfinite(want)
+    assert np.array_equal(got[odd], want[odd], equal_nan=True)
+    # (an element that shares its 16 bytes with one of these is summed in another order)
+    assert attention_error(np.where(odd, 0, got), np.where(odd, 0, want)) <= 1e-5
+
+
+def test_attention_f32_costs_two_passes_where_a_masked_key_holds_nan():
+    # 96 rows of 16 heads on 1898 keys, the last row's V a NaN: 56 us against 24; done key by key it took 866
+    cfg = CONFIGS[2].scaled(N=95, branching=(8, 4, 2, 2, 1, 1, 1, 1), S=1898, H=16, B=1, kv_dtype="f32")
+    parent = static_tree(cfg.branching, cfg.N)
+    att = make_attention_inputs(cfg)
+    tree = lpp.Tree(parent)
+    t = {n: dev(att[n]) for n in ("q", "kc", "vc", "kt", "vt")}
+    out = torch.empty((1, cfg.H, cfg.M, cfg.Dh), device=DEV)
+    ws = torch.empty(lpp.lpp_tree_attention_workspace(tree, 1, cfg.H, cfg.S, cfg.Dh), dtype=torch.uint8, device=DEV)
+
+    def least():
+        best = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                lpp.lpp_tree_attention(tree, lpp.LPP_F32, t["q"], t["kc"], t["vc"], t["kt"], t["vt"], None, 1, cfg.H, cfg.S,
+                                       cfg.Dh, 0.0, out, ws)
+            b.record()
+            torch.cuda.synchronize()
+            best.append(a.elapsed_time(b))
+        return min(best)
+    plain = least()
+    t["vt"][:, :, -1] = float("nan")
+    assert least() < 6 * plain
