@@ -70,22 +70,28 @@ def lib() -> C.CDLL:
     L.lpp_relaxed_verify_workspace.argtypes = [vp, i32, i32, i32]
     L.lpp_relaxed_verify.restype = i32
     L.lpp_relaxed_verify.argtypes = [vp, vp, vp, i64, i32, i32, i32, vp, vp, i32, i32, f32, vp, vp,
-                                     vp, vp, sz, vp]
+                                     C.POINTER(VerifyOut), vp, sz, vp]
     L.lpp_relaxed_verify_static.restype = i32
     L.lpp_relaxed_verify_static.argtypes = [vp, vp, vp, i64, i32, i32, i32, vp, vp, i32, i32, f32, vp, vp,
-                                            vp, vp]
+                                            C.POINTER(VerifyOut), vp]
     L.lpp_relaxed_verify_additive.restype = i32
     L.lpp_relaxed_verify_additive.argtypes = L.lpp_relaxed_verify.argtypes
     L.lpp_relaxed_verify_sampled.restype = i32
     L.lpp_relaxed_verify_sampled.argtypes = [vp, vp, vp, f32, i32, vp, i64, i32, i32, i32, vp, vp, i32, i32, f32, vp, vp,
-                                             vp, vp, sz, vp]
+                                             C.POINTER(VerifyOut), vp, sz, vp]
     L.lpp_relaxed_verify_opts.restype = i32
     L.lpp_relaxed_verify_opts.argtypes = [vp, vp, vp, i64, i32, i32, i32, vp, vp, i32, i32, vp, vp, vp,
-                                          vp, vp, sz, vp]
+                                          C.POINTER(VerifyOut), vp, sz, vp]
     L.lpp_commit_kv.restype = i32
     L.lpp_commit_kv.argtypes = [vp, i32, vp, vp, vp, vp, vp, i32, i32, i32, i32, vp, vp, vp, vp]
     L.lpp_probe_stream_read.restype = i32
     L.lpp_probe_stream_read.argtypes = [vp, sz, vp, i32, vp]
+    # (the wrappers below pass lpp_verify_out as packed bytes, through function objects of their own: who calls
+    # lib() directly keeps the typed argument)
+    for name in ("", "_static", "_additive", "_sampled", "_opts"):
+        f, g = getattr(L, "lpp_relaxed_verify" + name), L["lpp_relaxed_verify" + name]
+        g.restype, g.argtypes = f.restype, [vp if t is C.POINTER(VerifyOut) else t for t in f.argtypes]
+        setattr(L, "verify_packed" + name, g)
     _lib = L
     return L
 
@@ -227,10 +233,10 @@ def lpp_relaxed_verify(tree: Tree, target_logits, drafter_logits, ldv: int, voca
                        B: int, tokens, neigh, kstride: int, k: int, lam: float, u_accept, u_final,
                        out: dict, ws, stream=None) -> None:
     """``out`` maps lpp_verify_out field names to tensors (missing / None = not wanted)."""
-    _check(lib().lpp_relaxed_verify(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv, vocab_offset,
-                                    V, B, _ptr(tokens), _ptr(neigh), kstride, k, lam, _ptr(u_accept),
-                                    _ptr(u_final), _verify_out(out), _ptr(ws),
-                                    _bytes(ws), _stream(stream)),
+    _check(lib().verify_packed(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv, vocab_offset,
+                               V, B, _ptr(tokens), _ptr(neigh), kstride, k, lam, _ptr(u_accept),
+                               _ptr(u_final), _verify_out(out), _ptr(ws),
+                               _bytes(ws), _stream(stream)),
            "lpp_relaxed_verify")
 
 
@@ -238,9 +244,9 @@ def lpp_relaxed_verify_static(tree: Tree, target_logits, drafter_logits, ldv: in
                               B: int, tokens, neigh, kstride: int, k: int, lam: float, u_accept, u_final,
                               out: dict, stream=None) -> None:
     """As lpp_relaxed_verify, without a workspace: the library's static device array holds the walk words."""
-    _check(lib().lpp_relaxed_verify_static(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv, vocab_offset,
-                                           V, B, _ptr(tokens), _ptr(neigh), kstride, k, lam, _ptr(u_accept),
-                                           _ptr(u_final), _verify_out(out), _stream(stream)),
+    _check(lib().verify_packed_static(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv, vocab_offset,
+                                      V, B, _ptr(tokens), _ptr(neigh), kstride, k, lam, _ptr(u_accept),
+                                      _ptr(u_final), _verify_out(out), _stream(stream)),
            "lpp_relaxed_verify_static")
 
 
@@ -248,10 +254,10 @@ def lpp_relaxed_verify_additive(tree: Tree, target_logits, drafter_logits, ldv: 
                                 B: int, tokens, neigh, kstride: int, k: int, delta: float, u_accept, u_final,
                                 out: dict, ws, stream=None) -> None:
     """As lpp_relaxed_verify, under the additive bound ``sum_A r < delta``."""
-    _check(lib().lpp_relaxed_verify_additive(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv,
-                                             vocab_offset, V, B, _ptr(tokens), _ptr(neigh), kstride, k, delta,
-                                             _ptr(u_accept), _ptr(u_final), _verify_out(out), _ptr(ws),
-                                             _bytes(ws), _stream(stream)),
+    _check(lib().verify_packed_additive(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv,
+                                        vocab_offset, V, B, _ptr(tokens), _ptr(neigh), kstride, k, delta,
+                                        _ptr(u_accept), _ptr(u_final), _verify_out(out), _ptr(ws),
+                                        _bytes(ws), _stream(stream)),
            "lpp_relaxed_verify_additive")
 
 
@@ -271,10 +277,10 @@ def lpp_relaxed_verify_opts(tree: Tree, target_logits, drafter_logits, ldv: int,
                             siblings: int = 0, uncond_logits=None, cfg_scale: float = 0.0, top_k: int = 0) -> None:
     """lpp_relaxed_verify with the bound, the choice of A, the sibling scheme and the front end as options."""
     opts = VerifyOptions(bound, bound_value, rule, siblings, _ptr(uncond_logits), cfg_scale, top_k)
-    _check(lib().lpp_relaxed_verify_opts(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv, vocab_offset,
-                                         V, B, _ptr(tokens), _ptr(neigh), kstride, k, C.byref(opts),
-                                         _ptr(u_accept), _ptr(u_final), _verify_out(out), _ptr(ws),
-                                         _bytes(ws), _stream(stream)),
+    _check(lib().verify_packed_opts(tree.handle, _ptr(target_logits), _ptr(drafter_logits), ldv, vocab_offset,
+                                    V, B, _ptr(tokens), _ptr(neigh), kstride, k, C.byref(opts),
+                                    _ptr(u_accept), _ptr(u_final), _verify_out(out), _ptr(ws),
+                                    _bytes(ws), _stream(stream)),
            "lpp_relaxed_verify_opts")
 
 
@@ -290,11 +296,11 @@ def lpp_relaxed_verify_sampled(tree: Tree, cond_logits, uncond_logits, cfg_scale
                                kstride: int, k: int, lam: float, u_accept, u_final, out: dict, ws,
                                stream=None) -> None:
     """As lpp_relaxed_verify, with guidance and top-k applied to the target rows inside the kernel."""
-    _check(lib().lpp_relaxed_verify_sampled(tree.handle, _ptr(cond_logits), _ptr(uncond_logits), cfg_scale, top_k,
-                                            _ptr(drafter_logits), ldv, vocab_offset, V, B, _ptr(tokens),
-                                            _ptr(neigh), kstride, k, lam, _ptr(u_accept), _ptr(u_final),
-                                            _verify_out(out), _ptr(ws),
-                                            _bytes(ws), _stream(stream)),
+    _check(lib().verify_packed_sampled(tree.handle, _ptr(cond_logits), _ptr(uncond_logits), cfg_scale, top_k,
+                                       _ptr(drafter_logits), ldv, vocab_offset, V, B, _ptr(tokens),
+                                       _ptr(neigh), kstride, k, lam, _ptr(u_accept), _ptr(u_final),
+                                       _verify_out(out), _ptr(ws),
+                                       _bytes(ws), _stream(stream)),
            "lpp_relaxed_verify_sampled")
 
 

@@ -191,3 +191,16 @@ def test_variant_entry_points_validate_like_the_plain_ones(L):
                            None) == lpp.LPP_EUNSUPPORTED
     assert L.lpp_commit_kv(None, lpp.LPP_BF16, FAKE, FAKE, FAKE, FAKE, FAKE, 1, 2, 64, 64, FAKE, FAKE, None,
                            None) == lpp.LPP_EINVAL
+
+
+def test_verify_out_is_a_typed_argument_for_callers_of_the_library_itself(L):
+    # a structure, by reference or as it is; nothing else (a null tree: nothing is enqueued)
+    before = [None, FAKE, FAKE, 64, 0, 64, 1, FAKE, FAKE, 4, 4, 2.0, FAKE, FAKE]
+    vo = VerifyOut(accept_len=FAKE, path=FAKE, final_token=FAKE)
+    for f in (L.lpp_relaxed_verify, L.lpp_relaxed_verify_additive):
+        for x in (vo, C.byref(vo), C.pointer(vo), None):
+            assert f(*before, x, FAKE, 1 << 20, None) == lpp.LPP_EINVAL
+        for x in (C.byref(C.c_int32()), b"bytes", 7):
+            with pytest.raises(C.ArgumentError):
+                f(*before, x, FAKE, 1 << 20, None)
+    assert L.lpp_relaxed_verify_static(*before, vo, None) == lpp.LPP_EINVAL
