@@ -3,9 +3,11 @@ short rows, every number of contraction steps, the sample's strides, one wave / 
 row, lists that take every code, rows that fall through to the exact path.  Bit-exact against the oracle."""
 import numpy as np
 import pytest
+import torch
 
+import paper_2502_06352_amd as lpp
 from oracle import build_neighbours
-from gpu_common import run_knn
+from gpu_common import DEV, dev, run_knn
 
 pytestmark = pytest.mark.gpu
 
@@ -72,3 +74,37 @@ def test_knn_codes_that_hold_a_nan_come_last(V, D, k):
     E[[7, V // 2], D // 2] = np.nan
     E[[3, 11, V - 2]] = 0.0
     _check(E, k, np.unique(np.concatenate([[3, 7, 11, V // 2, V - 2], g.choice(V, size=100)])))
+
+
+def _least_ms(E, k):
+    """Least time of one build, device time, of a few."""
+    V, D = E.shape
+    e = dev(E)
+    neigh = torch.empty((V, k), dtype=torch.int32, device=DEV)
+    ws = torch.empty(lpp.lpp_build_neighbours_workspace(V, D, k), dtype=torch.uint8, device=DEV)
+    best = []
+    for _ in range(6):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        lpp.lpp_build_neighbours(e, k, neigh, ws)
+        b.record()
+        torch.cuda.synchronize()
+        best.append(a.elapsed_time(b))
+    return min(best)
+
+
+@pytest.mark.parametrize("V,D,k", [(1024, 8, 16), (16384, 8, 100), (8192, 256, 100), (8192, 256, 1000)])
+def test_knn_rows_without_an_order_cost_nothing(V, D, k):
+    # a code that holds a NaN, and every twentieth code zeros: 1.0 to 13 ms when such rows took the exact path (or
+    # ordered a thousand equal keys: 0.6 ms); as long as any other codebook now
+    g = np.random.default_rng(3)
+    E = _unit(g, V, D)
+    plain = _least_ms(E, k)
+    if V > 1024:
+        nan = E.copy()
+        nan[5, D - 1] = np.nan
+        assert _least_ms(nan, k) < 2 * plain
+    E[::20] = 0.0
+    E[40, 1] = -0.0
+    _check(E, k, np.array([0, 1, 20, 40, V - 4, V - 1]))
+    assert _least_ms(E, k) < 2.5 * plain
