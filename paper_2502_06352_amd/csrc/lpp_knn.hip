@@ -53,6 +53,8 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kShortRow = 16;                 // rows of up to this many floats: fp32 similarities
 constexpr int kDirectCodes = 1024;            // codebooks of short rows up to this size: one kernel
+constexpr int kLaterCodes = 4096;             // (see the rule at the end of this file)
+constexpr int kLaterFloats = 1 << 20;
 constexpr int kSampleCodes = 4096;            // codes a row's threshold is estimated from
 constexpr int kSampleBins = 1024;             // bins of the estimate, [-|e_i| max|e_j|, +]
 constexpr int kSampleThreads = 1024;
@@ -73,6 +75,8 @@ struct RowPlan {
 };
 constexpr int kAll = 1, kAnyNan = 2, kNoList = 4, kFlat = 8;
 constexpr int kMaxSplits = 16;                // segments of a long row's list
+constexpr int kUnits = 256;                   // compute units of the card these kernels are for
+constexpr size_t kMostLds = 150 * 1024;       // dynamic LDS of a block, static arrays beside it
 
 struct KnnArgs {
   const float* E;
@@ -96,6 +100,7 @@ struct KnnArgs {
   RowPlan* plan;        // [Vp]
   int32_t* cnt;         // [V][splits]
   uint32_t* cand;       // [V][cap]
+  int32_t* redo;        // [1 + V]: rows that take the exact path, their number first
   int32_t* neigh;       // [V][k]
 };
 
@@ -142,6 +147,7 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = threadIdx.x % G;
   const bool vec = (a.D & 3) == 0 && (reinterpret_cast<uintptr_t>(a.E) & 15) == 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.redo[0] = 0;
   float mx[4] = {0.f, 0.f, 0.f, 0.f};
   for (int row = blockIdx.x * (kStatThreads / G) + threadIdx.x / G; row < a.V; row += gridDim.x * (kStatThreads / G)) {
     const float* src = a.E + (int64_t)row * a.D;
@@ -713,6 +719,42 @@ __device__ __forceinline__ uint64_t exact_key(const double* ei, const Rows& R, i
   return orderable(acc);
 }
 
+// exact_key of U codes side by side, 64 bytes of each at a time: their chains do not wait for each other's loads.
+template <int U>
+__device__ __forceinline__ void exact_keys(const double* ei, const Rows& R, const int (&j)[U], uint64_t (&K)[U]) {
+  if (!R.quads) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) K[u] = exact_key(ei, R, j[u]);
+    return;
+  }
+  double acc[U] = {};
+  const float* ej[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) ej[u] = R.p + (int64_t)j[u] * R.pitch;
+  for (int t0 = 0; t0 < R.D; t0 += 16) {
+    f32x4 v[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (t0 + 4 * c < R.D) v[u][c] = *reinterpret_cast<const f32x4*>(ej[u] + t0 + 4 * c);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (t0 + 4 * c < R.D) {
+        const f64x2 e0 = *reinterpret_cast<const f64x2*>(ei + t0 + 4 * c), e1 = *reinterpret_cast<const f64x2*>(ei + t0 + 4 * c + 2);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          acc[u] = __builtin_fma(e0[0], (double)v[u][c][0], acc[u]);
+          acc[u] = __builtin_fma(e0[1], (double)v[u][c][1], acc[u]);
+          acc[u] = __builtin_fma(e1[0], (double)v[u][c][2], acc[u]);
+          acc[u] = __builtin_fma(e1[1], (double)v[u][c][3], acc[u]);
+        }
+      }
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) K[u] = orderable(acc[u]);
+}
+
 // (key desc, idx asc) "a goes before b"
 __device__ __forceinline__ bool before(uint64_t ka, uint32_t ia, uint64_t kb, uint32_t ib) {
   return ka > kb || (ka == kb && ia < ib);
@@ -1047,40 +1089,90 @@ __device__ void bucket_rank(const uint64_t* skey, const uint16_t* sidx, int n, i
   }
 }
 
-// Exact path of one row over all V codes: radix select of the kk-th largest key.  Rare and slow.
-template <int NTHR>
+// LDS of the exact path in a block of `threads`, in bytes; keys: those of all codes are kept there.
+size_t exact_lds(int V, int PD, int kk, int threads, bool keys) {
+  return (size_t)PD * 8 + lpp_align_up((size_t)kk, threads) * 16 + 2 * 16 * 8 + 260 * 4 + (keys ? (size_t)V * 8 : 0);
+}
+
+// Exact path of one row over all V codes: radix select of the kk-th largest key.  KEEP: the keys are formed once
+// and kept in LDS, not formed again in each of nine passes.  U: how many a thread forms side by side (rows of
+// more than 16 floats: two; one takes fewer registers).
+template <int NTHR, bool KEEP, int U>
 __device__ void exact_row(const Rows& R, int V, int i, int kk, unsigned char* smem, int* s_w, int32_t* out, int tid) {
   const int lane = tid & 63, wv = tid >> 6;
-  const int P = (kk + 1023) & ~1023;
+  const int P = (kk + NTHR - 1) / NTHR * NTHR;
   double* eid = reinterpret_cast<double*>(smem);            // (already there)
   uint64_t* skey = reinterpret_cast<uint64_t*>(eid + ((R.D + 3) & ~3));
   uint32_t* cur = reinterpret_cast<uint32_t*>(skey + P);
   uint16_t* sidx = reinterpret_cast<uint16_t*>(cur + P);
   uint16_t* ord = sidx + P;
   uint64_t* s_red = reinterpret_cast<uint64_t*>(ord + P);   // [2 NTHR / 64]
-  int* s_hist = reinterpret_cast<int*>(s_red + 2 * NTHR / 64);
+  int* s_hist = reinterpret_cast<int*>(s_red + 2 * 16);
   int* s_misc = s_hist + 256;
+  uint64_t* kept = reinterpret_cast<uint64_t*>(s_misc + 4);
+  // keys of the codes j0 + u NTHR + tid (of the last one again past the end)
+  auto form = [&](int j0, uint64_t (&K)[U]) {
+    int j[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) j[u] = min(j0 + u * NTHR + tid, V - 1);
+    if (U == 1) K[0] = exact_key(eid, R, j[0]);
+    else exact_keys<U>(eid, R, j, K);
+  };
+  if (KEEP)                                                 // (every thread reads back what it wrote itself)
+    for (int j0 = 0; j0 < V; j0 += U * NTHR) {
+      uint64_t K[U];
+      form(j0, K);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (j0 + u * NTHR + tid < V) kept[j0 + u * NTHR + tid] = K[u];
+    }
+  auto keys = [&](int j0, uint64_t (&K)[U]) {
+    if (!KEEP) form(j0, K);
+#pragma unroll
+    for (int u = 0; KEEP && u < U; ++u) K[u] = kept[min(j0 + u * NTHR + tid, V - 1)];
+  };
   uint64_t prefix = 0ull;
   int need = kk;
   for (int byte = 7; byte >= 0; --byte) {
     __syncthreads();
     for (int t = tid; t < 256; t += NTHR) s_hist[t] = 0;
     __syncthreads();
-    for (int j = tid; j < V; j += NTHR) {
-      if (j == i) continue;
-      const uint64_t K = exact_key(eid, R, j);
-      const bool match = byte == 7 || (K >> (8 * (byte + 1))) == (prefix >> (8 * (byte + 1)));
-      if (match) atomicAdd(&s_hist[(int)((K >> (8 * byte)) & 255ull)], 1);
+    for (int j0 = 0; j0 < V; j0 += U * NTHR) {
+      uint64_t K[U];
+      keys(j0, K);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = j0 + u * NTHR + tid;
+        const bool match = j < V && j != i && (byte == 7 || (K[u] >> (8 * (byte + 1))) == (prefix >> (8 * (byte + 1))));
+        const int digit = (int)((K[u] >> (8 * byte)) & 255ull);
+        // (the bytes of keys that brought a row here are mostly the same: those of the wave's first in one add)
+        const unsigned long long in = __ballot(match);
+        if (in) {
+          const int first = __builtin_ctzll(in), d0 = __builtin_amdgcn_readlane(digit, first);
+          const unsigned long long same = __ballot(match && digit == d0);
+          if (lane == first) atomicAdd(&s_hist[d0], __popcll(same));
+          else if (match && digit != d0) atomicAdd(&s_hist[digit], 1);
+        }
+      }
     }
     __syncthreads();
-    if (tid == 0) {
-      int cum = 0, bsel = 0;
-      for (int bkt = 255; bkt >= 0; --bkt) {
-        if (cum + s_hist[bkt] >= need) { bsel = bkt; break; }
-        cum += s_hist[bkt];
+    if (wv == 0) {                                          // lane: four bins, from the top
+      int c[4], local = 0;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) { c[b] = s_hist[255 - 4 * lane - b]; local += c[b]; }
+      int above = local;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(above, o);
+        if (lane >= o) above += t;
       }
-      s_misc[0] = bsel;
-      s_misc[1] = need - cum;
+      above -= local;
+      if (above < need && above + local >= need) {
+        int b = 0;
+        for (; b < 3 && above + c[b] < need; ++b) above += c[b];
+        s_misc[0] = 255 - 4 * lane - b;
+        s_misc[1] = need - above;
+      }
     }
     __syncthreads();
     prefix |= (uint64_t)s_misc[0] << (8 * byte);
@@ -1092,40 +1184,40 @@ __device__ void exact_row(const Rows& R, int V, int i, int kk, unsigned char* sm
   __syncthreads();
   if (tid == 0) { s_misc[2] = 0; s_misc[3] = 0; }
   __syncthreads();
-  for (int j0 = 0; j0 < V; j0 += NTHR) {
-    const int j = j0 + tid;
-    uint64_t K = 0ull;
-    bool gt = false, eq = false;
-    if (j < V && j != i) {
-      K = exact_key(eid, R, j);
-      gt = K > prefix;
-      eq = K == prefix;
+  for (int j0 = 0; j0 < V; j0 += U * NTHR) {
+    uint64_t K[U];
+    keys(j0, K);
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + u * NTHR + tid;
+      const uint64_t key = U == 2 && u == 1 ? K[U - 1] : K[0];
+      const bool other = j < V && j != i, gt = other && key > prefix, eq = other && key == prefix;
+      if (gt) {
+        const int pos = atomicAdd(&s_misc[2], 1);
+        skey[pos] = key; sidx[pos] = (uint16_t)j;
+      }
+      // ordered compaction of the ties (ascending index)
+      const unsigned long long bal = __ballot(eq);
+      if (lane == 0) s_hist[wv] = __popcll(bal);
+      __syncthreads();
+      int base = s_misc[3];
+      for (int w = 0; w < wv; ++w) base += s_hist[w];
+      const int rank = base + __popcll(bal & ((1ull << lane) - 1ull));
+      if (eq && rank < need) { skey[n_gt + rank] = key; sidx[n_gt + rank] = (uint16_t)j; }
+      __syncthreads();
+      if (tid == 0) {
+        int t = 0;
+        for (int w = 0; w < NTHR / 64; ++w) t += s_hist[w];
+        s_misc[3] += t;
+      }
+      __syncthreads();
     }
-    if (gt) {
-      const int pos = atomicAdd(&s_misc[2], 1);
-      skey[pos] = K; sidx[pos] = (uint16_t)j;
-    }
-    // ordered compaction of the ties (ascending index)
-    const unsigned long long bal = __ballot(eq);
-    if (lane == 0) s_hist[wv] = __popcll(bal);
-    __syncthreads();
-    int base = s_misc[3];
-    for (int w = 0; w < wv; ++w) base += s_hist[w];
-    const int rank = base + __popcll(bal & ((1ull << lane) - 1ull));
-    if (eq && rank < need) { skey[n_gt + rank] = K; sidx[n_gt + rank] = (uint16_t)j; }
-    __syncthreads();
-    if (tid == 0) {
-      int t = 0;
-      for (int w = 0; w < NTHR / 64; ++w) t += s_hist[w];
-      s_misc[3] += t;
-    }
-    __syncthreads();
   }
   bucket_rank<NTHR>(skey, sidx, kk, P, cur, ord, s_red, s_w, kk, out, tid);
 }
 
-// One block per row: NTHR threads, EPT list words each in registers.
-template <int NTHR, int EPT, bool STAGED>
+// One block per row: NTHR threads, EPT list words each in registers.  A row that its list does not decide takes the
+// exact path here, or (LATER) in a launch of its own.
+template <int NTHR, int EPT, bool STAGED, bool LATER>
 __global__ __launch_bounds__(NTHR) void knn_rank_kernel(KnnArgs a, RankShape sh) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_w[20];
@@ -1134,10 +1226,6 @@ __global__ __launch_bounds__(NTHR) void knn_rank_kernel(KnnArgs a, RankShape sh)
   if (tid == 0) out[0] = i;
   if (kk == 0) return;
   const RowPlan p = a.plan[i];
-  if (p.flags & kFlat) {                                    // uniform
-    for (int t = tid; t < kk; t += NTHR) out[1 + t] = t < i ? t : t + 1;
-    return;
-  }
   const uint32_t* list = a.cand + (int64_t)i * a.cap;
   const uint32_t mask = (1u << a.ib) - 1u;
   uint32_t w[EPT], on = 0;
@@ -1189,13 +1277,40 @@ __global__ __launch_bounds__(NTHR) void knn_rank_kernel(KnnArgs a, RankShape sh)
     on |= keep ? 1u << u : 0u;
     w[u] = ~w[u];
   }
+  if (p.flags & kFlat) {                                    // uniform (here: the loads above do not wait for the plan)
+    for (int t = tid; t < kk; t += NTHR) out[1 + t] = t < i ? t : t + 1;
+    return;
+  }
   const Rows R{a.Ep, a.PD, a.D, true};
   if (!over && !(p.flags & kNoList)) {
     if (rank_row<NTHR, EPT, STAGED>(w, on, a.ib, a.vmask_bits, p.E, (p.flags & kAll) != 0, kk, R, sh, smem, s_w, out, tid)) return;
   }
-  __threadfence();                                          // (what was written of the row is written again by other lanes)
-  __syncthreads();
-  exact_row<NTHR>(R, a.V, i, kk, smem, s_w, out, tid);
+  // (what was written of the row is written again)
+  if constexpr (LATER) {
+    if (tid == 0) a.redo[1 + atomicAdd(a.redo, 1)] = i;
+  } else {
+    __threadfence();
+    __syncthreads();
+    exact_row<NTHR, false, STAGED ? 2 : 1>(R, a.V, i, kk, smem, s_w, out, tid);
+  }
+}
+
+// The rows that no list decides, one after the other by blocks of 16 waves: 0.02 to 0.1 ms a row (D = 8), 0.3 ms
+// (D = 256); inside the ranking's blocks it is 0.4 to 0.9 ms and 2 to 9 ms.
+constexpr int kExactThreads = 1024;
+template <bool KEEP>
+__global__ __launch_bounds__(kExactThreads) void knn_exact_kernel(KnnArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int s_w[20];
+  const int n = a.redo[0];
+  for (int r = blockIdx.x; r < n; r += gridDim.x) {
+    const int i = a.redo[1 + r];
+    double* eid = reinterpret_cast<double*>(smem);
+    for (int d = threadIdx.x; d < a.PD; d += kExactThreads) eid[d] = (double)a.Ep[(int64_t)i * a.PD + d];
+    __syncthreads();
+    exact_row<kExactThreads, KEEP, KEEP ? 2 : 1>(Rows{a.Ep, a.PD, a.D, true}, a.V, i, a.k - 1, smem, s_w, a.neigh + (int64_t)i * a.k, threadIdx.x);
+    __syncthreads();
+  }
 }
 
 // Small codebooks of short rows: one block per row forms the row's similarities with every code
@@ -1285,15 +1400,15 @@ __global__ __launch_bounds__(kDirectThreads) void knn_direct_kernel(KnnArgs a, R
   const Rows R{a.E, D, D, quads};
   if (range < INFINITY && rank_row<kDirectThreads, EPT, false>(w, on, a.ib, a.vmask_bits, E, true, kk, R, sh, smem, s_w, out, tid))
     return;
-  __threadfence();                                          // (as in knn_rank_kernel)
+  __threadfence();                                          // (what was written of the row is written again by other lanes)
   __syncthreads();
-  exact_row<kDirectThreads>(R, V, i, kk, smem, s_w, out, tid);
+  exact_row<kDirectThreads, false, 1>(R, V, i, kk, smem, s_w, out, tid);
 }
 
 // -------------------------------------------------------------------------------------------- host
 
 struct KnnLayout {
-  size_t o_ep, o_ef, o_es, o_norms, o_l1, o_part, o_plan, o_cnt, o_cand, total;
+  size_t o_ep, o_ef, o_es, o_norms, o_l1, o_part, o_plan, o_cnt, o_redo, o_cand, total;
   int32_t PD, KS, Vp, cap, ib, vb, stride, ns, m, take_all, splits, cap_split;
 };
 
@@ -1321,7 +1436,7 @@ KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   L.cap = L.take_all ? L.Vp : (int32_t)std::min<size_t>(L.Vp, lpp_align_up((size_t)(expect + 5.0 * dev) + 64 + V / 256, 64));
   // long rows: blocks of 128 queries by `splits` shares of the code tiles, two blocks per compute unit
   const int ntiles = (V + 15) / 16, groups = L.Vp / 128;
-  L.splits = L.KS ? std::max(1, std::min({512 / groups, ntiles, kMaxSplits})) : 1;
+  L.splits = L.KS ? std::max(1, std::min({2 * kUnits / groups, ntiles, kMaxSplits})) : 1;
   L.cap_split = L.cap;
   if (L.splits > 1) {
     const int tiles = (ntiles + L.splits - 1) / L.splits;
@@ -1340,18 +1455,14 @@ KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   L.o_part = take((size_t)kStatBlocks * sizeof(float4));
   L.o_plan = take((size_t)L.Vp * sizeof(RowPlan));
   L.o_cnt = take((size_t)V * L.splits * sizeof(int32_t));
+  L.o_redo = take((size_t)(V + 1) * sizeof(int32_t));
   L.o_cand = take((size_t)V * entries * sizeof(uint32_t));
   L.total = o;
   return L;
 }
 
-// LDS of one row's ranking or of its exact path, whichever is larger
-size_t rank_lds(int P, int NB, int PD, int kk) {
-  const size_t rank = (size_t)PD * 8 + (size_t)NB * 4 + (size_t)P * 8 + (size_t)P * 2;
-  const size_t PX = lpp_align_up((size_t)kk, 1024);
-  const size_t exact = (size_t)PD * 8 + PX * 16 + 2 * 16 * 8 + 260 * 4;
-  return std::max(rank, exact);
-}
+// LDS of one row's ranking
+size_t rank_lds(int P, int NB, int PD) { return (size_t)PD * 8 + (size_t)NB * 4 + (size_t)P * 8 + (size_t)P * 2; }
 
 template <bool FIXED, int N>
 int32_t launch_sample(const KnnArgs& a, hipStream_t s) {
@@ -1371,7 +1482,7 @@ int32_t launch_collect_f16(const KnnArgs& a, hipStream_t s) {
   if (st != LPP_OK) return st;
   // a block per 16 queries: as many waves as give every compute unit 18 (8 KB of LDS each), 16 at most
   const int blocks = (a.V + 15) / 16;
-  const int waves = std::max(4, std::min(kCollectMaxWaves, 256 * 18 / blocks));
+  const int waves = std::max(4, std::min(kCollectMaxWaves, kUnits * 18 / blocks));
   const size_t lds = (size_t)waves * 8192;
   auto kern = knn_collect_f16_kernel<N>;
   static LppLdsLimit limit;
@@ -1394,17 +1505,34 @@ int32_t launch_collect_i8(const KnnArgs& a, hipStream_t s) {
   return LPP_OK;
 }
 
-template <int NTHR, bool STAGED>
+// Every key of a row in LDS where they fit (16384 codes and k = 1000, or 8192 and 4096).
+template <bool KEEP>
+int32_t launch_exact_as(const KnnArgs& a, hipStream_t s) {
+  const size_t lds = exact_lds(a.V, a.PD, a.k - 1, kExactThreads, KEEP);
+  auto kern = knn_exact_kernel<KEEP>;
+  static LppLdsLimit limit;
+  const int32_t st = lpp_ensure_lds(reinterpret_cast<const void*>(kern), limit, lds, 48 * 1024);
+  if (st != LPP_OK) return st;
+  hipLaunchKernelGGL(kern, dim3((unsigned)std::min(a.V, kUnits)), dim3(kExactThreads), lds, s, a);
+  LPP_HIP_TRY(hipGetLastError());
+  return LPP_OK;
+}
+int32_t launch_exact(const KnnArgs& a, hipStream_t s) {
+  return exact_lds(a.V, a.PD, a.k - 1, kExactThreads, true) <= kMostLds ? launch_exact_as<true>(a, s) : launch_exact_as<false>(a, s);
+}
+
+template <int NTHR, bool STAGED, bool LATER>
 int32_t launch_rank(const KnnArgs& a, RankShape sh, hipStream_t s) {
-  const size_t lds = rank_lds(sh.P, 1 << sh.lognb, a.PD, a.k - 1);
-  if (lds > 150 * 1024) return LPP_EUNSUPPORTED;
-  auto kern = knn_rank_kernel<NTHR, 8, STAGED>;
+  const size_t own = rank_lds(sh.P, 1 << sh.lognb, a.PD);
+  const size_t lds = LATER ? own : std::max(own, exact_lds(a.V, a.PD, a.k - 1, NTHR, false));
+  if (lds > kMostLds) return LPP_EUNSUPPORTED;
+  auto kern = knn_rank_kernel<NTHR, 8, STAGED, LATER>;
   static LppLdsLimit limit;
   const int32_t st = lpp_ensure_lds(reinterpret_cast<const void*>(kern), limit, lds, 48 * 1024);
   if (st != LPP_OK) return st;
   hipLaunchKernelGGL(kern, dim3((unsigned)a.V), dim3(NTHR), lds, s, a, sh);
   LPP_HIP_TRY(hipGetLastError());
-  return LPP_OK;
+  return LATER && a.k > 1 ? launch_exact(a, s) : LPP_OK;
 }
 
 }  // namespace
@@ -1441,13 +1569,14 @@ extern "C" int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, in
   a.plan = reinterpret_cast<RowPlan*>(w + L.o_plan);
   a.cnt = reinterpret_cast<int32_t*>(w + L.o_cnt);
   a.cand = reinterpret_cast<uint32_t*>(w + L.o_cand);
+  a.redo = reinterpret_cast<int32_t*>(w + L.o_redo);
   a.neigh = neigh;
   auto log2_up = [](int x) { int l = 0; while ((1 << l) < x) ++l; return l; };
 
   if (D <= kShortRow && V <= kDirectCodes) {
     // values need no more than the float's bits; the key buffer over counters and scattered words wants NB >= P
     const RankShape sh{kDirectCodes, log2_up(kDirectCodes)};
-    const size_t lds = rank_lds(sh.P, 1 << sh.lognb, L.PD, k - 1);
+    const size_t lds = std::max(rank_lds(sh.P, 1 << sh.lognb, L.PD), exact_lds(V, L.PD, k - 1, kDirectThreads, false));
     hipLaunchKernelGGL(knn_direct_kernel, dim3((unsigned)V), dim3(kDirectThreads), lds, s, a, sh);
     LPP_HIP_TRY(hipGetLastError());
     return LPP_OK;
@@ -1476,15 +1605,21 @@ extern "C" int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, in
   // a list of up to eight words per thread: one wave for short lists (a block of four would mostly wait for
   // its barriers), four for the usual ones
   const bool staged = D > kShortRow;
-  if (L.cap <= 512) {
-    const RankShape sh{L.cap, std::max(8, log2_up(L.cap))};
-    return staged ? launch_rank<64, true>(a, sh, s) : launch_rank<64, false>(a, sh, s);
-  }
-  if (L.cap <= 2048) {
-    const RankShape sh{L.cap, std::max(10, log2_up(L.cap))};
-    return staged ? launch_rank<256, true>(a, sh, s) : launch_rank<256, false>(a, sh, s);
-  }
+  // Rows that fall through (heavy ties, infinities, norms far apart) in a launch of their own, which costs 2 us
+  // whether there are any or not: where one such row would cost many times that in a ranking block (codebooks of 2^20
+  // numbers of long rows), and where one wave ranks a row of a large codebook, whose blocks then hold the LDS of a
+  // list only.  900 equal codes among 8192 x 256, k = 16, 300, 1000: 13.9, 28.4, 15.8 ms -> 1.4, 1.9, 3.4; all else
+  // equal, 8192 x 256: k = 16 195 -> 182 us, 100 223 -> 202, 300 266.5 -> 268.4, 1000 316.8 -> 318.4; 16384 x 8:
+  // k = 16 116 -> 99, 100 131 -> 114 us.  2048 x 8, k = 16: 23.6 us without, 25.8 with.
+  const bool later = staged ? (int64_t)V * D > kLaterFloats : L.cap <= 512 && V > kLaterCodes;
+  auto rank = [&](auto threads, int least) {
+    constexpr int NTHR = decltype(threads)::value;
+    const RankShape sh{L.cap, std::max(least, log2_up(L.cap))};
+    if (staged) return later ? launch_rank<NTHR, true, true>(a, sh, s) : launch_rank<NTHR, true, false>(a, sh, s);
+    return later ? launch_rank<NTHR, false, true>(a, sh, s) : launch_rank<NTHR, false, false>(a, sh, s);
+  };
+  if (L.cap <= 512) return rank(std::integral_constant<int, 64>(), 8);
+  if (L.cap <= 2048) return rank(std::integral_constant<int, 256>(), 10);
   if (L.cap > 8192) return LPP_EUNSUPPORTED;
-  const RankShape sh{L.cap, std::max(12, log2_up(L.cap))};
-  return staged ? launch_rank<1024, true>(a, sh, s) : launch_rank<1024, false>(a, sh, s);
+  return rank(std::integral_constant<int, 1024>(), 12);
 }

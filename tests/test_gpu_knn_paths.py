@@ -108,3 +108,25 @@ def test_knn_rows_without_an_order_cost_nothing(V, D, k):
     E[40, 1] = -0.0
     _check(E, k, np.array([0, 1, 20, 40, V - 4, V - 1]))
     assert _least_ms(E, k) < 2.5 * plain
+
+
+@pytest.mark.parametrize("V,D,k", [(1025, 16, 1025), (2000, 3, 900), (20000, 8, 40), (16384, 8, 1000), (8192, 20, 4096), (3000, 130, 12)])
+def test_knn_exact_path_of_every_row(V, D, k):
+    # one infinite entry: no bound on any row's similarities.  With the keys kept in LDS, and too many for it.
+    g = np.random.default_rng(V + k)
+    E = _unit(g, V, D)
+    E[V // 3] = E[V // 5]
+    E[7, 1] = np.inf
+    _check(E, k, np.unique(np.concatenate([[0, 7, V // 3, V - 1], g.choice(V, size=40)])))
+
+
+@pytest.mark.parametrize("V,D,k,most", [(16384, 8, 100, 7), (8192, 256, 16, 20), (8192, 256, 300, 20), (8192, 256, 1000, 20)])
+def test_knn_rows_that_fall_through_share_the_chip(V, D, k, most):
+    # 900 codes that are the same: their lists overflow.  1.3 to 28 ms when they took the exact path in the blocks
+    # that rank (11, 73, 106 and 50 times a codebook without)
+    g = np.random.default_rng(4)
+    E = _unit(g, V, D)
+    plain = _least_ms(E, k)
+    E[g.permutation(V)[:900]] = E[0]
+    _check(E, k, g.choice(V, size=60))
+    assert _least_ms(E, k) < most * plain
