@@ -10,13 +10,15 @@
 //            8-bit limbs, in matrix-core fragment order
 //   sample   per row: histogram of its similarities with a hashed, stratified sample of
 //            about 4096 codes; the threshold is the sample's quantile at which, five
-//            standard deviations of the sample's share allowed, k - 1 codes lie above
+//            standard deviations of the sample's share allowed, k - 1 codes lie above (short rows: its
+//            bin looked at again in 1024 parts where a few codes far longer than the rest crowd the others into it)
 //   collect  the dense V x V contraction on the matrix cores, once: every code above the
 //            row's threshold is appended to its list as one 32-bit word, similarity
 //            (fixed point) over code index
 //   rank     per row: the list is sorted by its approximate similarities (value buckets in
-//            LDS); runs of entries whose similarities differ by less than twice the bound on
+//            LDS); entries whose similarities differ by less than twice the bound on
 //            their error are ordered by their exact float64 keys, everything else already is
+//   exact    rows that their list does not decide, over all codes (a launch of its own where that pays)
 // Small codebooks of short rows (V <= kDirectCodes, D <= 16) take one kernel that does all of it.
 //
 // Why the list is enough: an outsider's similarity is at most threshold + e, e bounding the error of
@@ -27,7 +29,10 @@
 //
 // The approximate similarities and their bound e:
 //   rows of up to 16 floats: x = h + l in halves of 11 bits, h h' + l h' + h l' on the f16 matrix
-//   cores; what is left out is below 3 2^-22 |e_i| |e_j|, the sums are rounded by 2^-23 each.
+//   cores; what is left out is below 3 2^-22 |e_i| |e_j|.  The products are exact in float32; that each of
+//   the 32 N additions is off by at most 2^-23 of |e_i| |e_j| is how the matrix cores are taken to add, not
+//   something their documents promise.  The halves are of 4096 x, or of 4 x in codebooks with entries from 16 on;
+//   from 16376 on every row takes the exact path.
 //   longer rows: x = q D + d with a 24-bit integer q = 2^16 a + 2^8 b + c (a, b, c signed 8-bit
 //   limbs), |d| <= D / 2, D = largest magnitude / (127 2^16).  All limb products but c c are summed
 //   exactly in int32 by the i8 matrix cores (eight MFMA 16x16x64 per 64 dimensions), so the only
@@ -46,12 +51,18 @@
 
 namespace {
 
+// x, as something the compiler does not know: what is formed from it is formed here, and takes no registers before.
+__device__ __forceinline__ int formed_anew(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kShortRow = 16;                 // rows of up to this many floats: fp32 similarities
+constexpr int kShortRow = 16;                 // rows of up to this many floats: pairs of halves
 constexpr int kDirectCodes = 1024;            // codebooks of short rows up to this size: one kernel
 constexpr int kLaterCodes = 4096;             // (see the rule at the end of this file)
 constexpr int kLaterFloats = 1 << 20;
@@ -60,7 +71,8 @@ constexpr int kSampleBins = 1024;             // bins of the estimate, [-|e_i| m
 constexpr int kSampleThreads = 1024;
 constexpr int kCollectWaves = 4;              // (long rows) waves per block
 constexpr int kStatBlocks = 128, kStatThreads = 1024;
-constexpr float kHalfScale = 4096.0f;         // short rows as halves: largest entry 15.9
+constexpr float kHalfScale = 4096.0f;         // short rows as halves: entries below 15.9
+constexpr float kWideScale = 4.0f;            // ... of codebooks with larger ones: below 16376
 constexpr float kLimbRange = 8323072.0f;      // 127 * 2^16: the largest |q|
 
 // What the collecting kernel needs of a row: a code passes where d = similarity - thr is not negative, and
@@ -71,9 +83,9 @@ struct RowPlan {
   union { float thr; int32_t thr_u; };
   int32_t E;
   int32_t flags;                              // kAll: every code passes; kAnyNan: some code holds a NaN; kNoList: exact path;
-                                              // kFlat: its similarities are all the same
+                                              // kFlat: its similarities are all the same; kWide: halves of kWideScale
 };
-constexpr int kAll = 1, kAnyNan = 2, kNoList = 4, kFlat = 8;
+constexpr int kAll = 1, kAnyNan = 2, kNoList = 4, kFlat = 8, kWide = 16;
 constexpr int kMaxSplits = 16;                // segments of a long row's list
 constexpr int kUnits = 256;                   // compute units of the card these kernels are for
 constexpr size_t kMostLds = 150 * 1024;       // dynamic LDS of a block, static arrays beside it
@@ -88,12 +100,15 @@ struct KnnArgs {
   int32_t vmask_bits;   // value bits
   int32_t stride, ns, m;   // sample: one of every `stride` codes, ns in all, threshold at its m-th largest
   int32_t take_all;     // the list takes every code
+  int32_t most;         // sampled codes above a threshold, at which the list is likely to overflow
   int32_t splits, cap_split;   // (long rows) segments of a row's list, one per block that collects for it, and their size
   int32_t statblocks;
   float* Ep;            // [V][PD]
   i32x4* Ef;            // long rows: [Vp/16][KS][3 limbs][64 lanes] fragments
                         // short rows: [Vp][2 N] pieces of 8 halves, the upper ones, then the lower ones
   i32x4* Es;            // the sample's codes, packed: long rows [ns/16][KS][64 lanes] upper limbs, short rows [ns][2 N]
+  i32x4* Ew;            // short rows: Ef and Es of the halves of kWideScale
+  i32x4* Ews;
   float* norms;         // [V]
   float* l1;            // [V]
   float4* part;         // [kStatBlocks]: max norm, max |x|, max 1-norm, any NaN
@@ -128,6 +143,8 @@ __device__ __forceinline__ Stats reduce_stats(const KnnArgs& a, int lane) {
   for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
     for (int q = 0; q < 4; ++q) v[q] = fmaxf(v[q], __shfl_xor(v[q], o));
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v[q] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v[q])));
   return Stats{v[0], v[1], v[2], v[3]};
 }
 
@@ -167,19 +184,23 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
       }
       if (d < a.PD) *reinterpret_cast<f32x4*>(dst + d) = f32x4{v[0], v[1], v[2], v[3]};
       if (G == 4) {
-        // 4096 x = h + l + rest: two halves of 11 bits each (rest: at most 2^-24 of it, or 2^-25)
+        // scale x = h + l + rest: two halves of 11 bits each (rest: at most 2^-24 of it, or 2^-25).  Both scales:
+        // which one holds is known when all rows have been here.
         typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-        f16x4 h, l;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float x = v[e] * kHalfScale;
-          h[e] = (_Float16)x;
-          l[e] = (_Float16)(x - (float)h[e]);
-        }
         const int n8 = a.D > 8 ? 2 : 1;                     // pieces of 8 halves per part
-        put_halves(a.Ef, row, n8, d, h, l);
         const int j = sample_slot(a, row);
-        if (j >= 0) put_halves(a.Es, j, n8, d, h, l);
+#pragma unroll
+        for (int wide = 0; wide < 2; ++wide) {
+          f16x4 h, l;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float x = v[e] * (wide ? kWideScale : kHalfScale);
+            h[e] = (_Float16)x;
+            l[e] = (_Float16)(x - (float)h[e]);
+          }
+          put_halves(wide ? a.Ew : a.Ef, row, n8, d, h, l);
+          if (j >= 0) put_halves(wide ? a.Ews : a.Es, j, n8, d, h, l);
+        }
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -298,104 +319,136 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   extern __shared__ __align__(16) uint32_t s_hist[];      // [kSampleBins][16]
   constexpr int SEG = kSampleThreads / 16, SW = kSampleBins / SEG;   // segments of the bins, bins of each
   __shared__ int s_seg[kSampleThreads / 64][16];           // counts of a wave's segments, per row
-  __shared__ int s_top[16], s_bin[16];
+  __shared__ int s_top[16], s_bin[16], s_fine[16], s_crowded[17];   // [16]: any row
   constexpr int W = kSampleThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
   const int row0 = blockIdx.x * 16, row = row0 + l16, rowc = min(row, a.V - 1);
   const Stats st = reduce_stats(a, lane);
-  const float norm = a.norms[rowc];
+  const float norm = a.norms[rowc], l1 = a.l1[rowc];
   const float top = norm * st.norm * 1.0001f;              // |similarity| stays below
-  const double unit = FIXED ? limb_unit(st.mabs) : 1.0 / kHalfScale;
+  const bool wide = !FIXED && st.mabs * kHalfScale >= 65504.0f;
+  const float hscale = wide ? kWideScale : kHalfScale;
+  const double unit = FIXED ? limb_unit(st.mabs) : 1.0 / hscale;
   // one step of the histogram's argument: products of scaled halves, or of upper limbs (2^32 unit^2)
   const float to_sim = (float)(FIXED ? unit * unit * 4294967296.0 : unit * unit);
   // (far below 1e-30 the bound on the error would itself be rounded)
-  const bool finite = top > 1e-30f && top < INFINITY && (FIXED || st.mabs * kHalfScale < 65504.0f);
-  const float bscale = finite ? (kSampleBins / 2) * to_sim / top : 0.f;
+  const bool finite = top > 1e-30f && top < INFINITY && (FIXED || st.mabs * hscale < 65504.0f);
 
   if (!a.take_all) {
-    for (int i = tid; i < kSampleBins * 4; i += kSampleThreads) reinterpret_cast<uint4*>(s_hist)[i] = make_uint4(0, 0, 0, 0);
-    if (tid < 16) { s_top[tid] = 0; s_bin[tid] = 0; }
-    __syncthreads();
+    if (tid < 17) { s_top[tid & 15] = 0; s_bin[tid & 15] = 0; s_crowded[tid] = 0; }
     const int ntiles = (a.ns + 15) / 16;
-    auto add = [&](float v) {
-      const uint32_t bin = min((uint32_t)__builtin_fmaf(v, bscale, kSampleBins / 2), kSampleBins - 1u);   // (negative, NaN: 0)
+    float per_bin = finite ? (kSampleBins / 2) * to_sim / top : 0.f, middle = kSampleBins / 2;
+    auto add = [&](float v, int l16) {
+      const uint32_t bin = min((uint32_t)__builtin_fmaf(v, per_bin, middle), kSampleBins - 1u);   // (negative, NaN: 0)
       atomicAdd(&s_hist[bin * 16 + l16], 1u);
     };
     // (codes past the sample's end are not counted)
-    auto count = [&](float x0, float x1, float x2, float x3, int t) {
+    auto count = [&](float x0, float x1, float x2, float x3, int t, int l16, int g4) {
       const float x[4] = {x0, x1, x2, x3};
       if ((t + 1) * 16 <= a.ns) {                          // uniform
 #pragma unroll
-        for (int r = 0; r < 4; ++r) add(x[r]);
+        for (int r = 0; r < 4; ++r) add(x[r], l16);
       } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (t * 16 + 4 * g4 + r < a.ns) add(x[r]);
+          if (t * 16 + 4 * g4 + r < a.ns) add(x[r], l16);
       }
     };
     constexpr int U = FIXED && N >= 3 ? 1 : (FIXED && N == 2 ? 2 : 4);
-    if constexpr (FIXED) {
-      i32x4 q[N];
+    auto sweep = [&](int tid) {
+      const int l16 = tid & 15, g4 = (tid >> 4) & 3;
+      auto clear = [&]() {
+        for (int i = tid; i < kSampleBins * 4; i += kSampleThreads) reinterpret_cast<uint4*>(s_hist)[i] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+      };
+      if constexpr (FIXED) {
+        clear();
+        i32x4 q[N];
 #pragma unroll
-      for (int ks = 0; ks < N; ++ks) q[ks] = a.Ef[((int64_t)(blockIdx.x * N + ks) * 3) * 64 + lane];
-      for (int t0 = wave; t0 < ntiles; t0 += W * U) {
-        i32x4 f[U][N];
+        for (int ks = 0; ks < N; ++ks) q[ks] = a.Ef[((int64_t)(blockIdx.x * N + ks) * 3) * 64 + (g4 * 16 + l16)];
+        for (int t0 = wave; t0 < ntiles; t0 += W * U) {
+          i32x4 f[U][N];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+          for (int u = 0; u < U; ++u)
 #pragma unroll
-          for (int ks = 0; ks < N; ++ks) f[u][ks] = a.Es[(min(t0 + W * u, ntiles - 1) * N + ks) * 64 + lane];
+            for (int ks = 0; ks < N; ++ks) f[u][ks] = a.Es[(min(t0 + W * u, ntiles - 1) * N + ks) * 64 + (g4 * 16 + l16)];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          i32x4 acc = {0, 0, 0, 0};
+          for (int u = 0; u < U; ++u) {
+            i32x4 acc = {0, 0, 0, 0};
 #pragma unroll
-          for (int ks = 0; ks < N; ++ks) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[u][ks], q[ks], acc, 0, 0, 0);
-          if (t0 + W * u < ntiles) count((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3], t0 + W * u);
+            for (int ks = 0; ks < N; ++ks) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[u][ks], q[ks], acc, 0, 0, 0);
+            if (t0 + W * u < ntiles) count((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3], t0 + W * u, l16, g4);
+          }
+        }
+      } else {
+        const i32x4* const sampled = wide ? a.Ews : a.Es;
+        HalfOperand<N> q, f[U];
+        auto load = [&](int t0) {
+#pragma unroll
+          for (int u = 0; u < U; ++u) f[u].load_code(sampled + (int64_t)min((t0 + W * u) * 16 + l16, a.ns - 1) * 2 * N, g4);
+        };
+        q.load_query((wide ? a.Ew : a.Ef) + (int64_t)min(row0 + l16, a.V - 1) * 2 * N, g4);
+        clear();
+        for (int t0 = wave; t0 < ntiles; t0 += W * U) {
+          load(t0);
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const f32x4 acc = f[u].times(q, f32x4{0.f, 0.f, 0.f, 0.f});
+            if (t0 + W * u < ntiles) count(acc[0], acc[1], acc[2], acc[3], t0 + W * u, l16, g4);
+          }
         }
       }
-    } else {
-      HalfOperand<N> q;
-      q.load_query(a.Ef + (int64_t)rowc * 2 * N, g4);
-      for (int t0 = wave; t0 < ntiles; t0 += W * U) {
-        HalfOperand<N> f[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) f[u].load_code(a.Es + (int64_t)min((t0 + W * u) * 16 + l16, a.ns - 1) * 2 * N, g4);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const f32x4 acc = f[u].times(q, f32x4{0.f, 0.f, 0.f, 0.f});
-          if (t0 + W * u < ntiles) count(acc[0], acc[1], acc[2], acc[3], t0 + W * u);
-        }
-      }
-    }
-    __syncthreads();
-    // thread (row, segment of bins): its count, then the segment the m-th largest lies in.  A wave
+    };
+    // thread (row, segment of bins): its count, then the segment the target-th largest lies in.  A wave
     // holds four segments of every row: sums over the waves go through LDS, inside a wave over lanes.
-    const int hr = tid & 15, seg = tid >> 4;
-    int local = 0, high = -1;
+    auto search = [&](int target, int* s_found, bool first, int tid) {
+      const int hr = tid & 15, seg = tid >> 4, g4 = seg & 3;
+      int local = 0, high = -1;
 #pragma unroll
-    for (int i = 0; i < SW; ++i) {
-      const uint32_t c = s_hist[(seg * SW + i) * 16 + hr];
-      local += (int)c;
-      if (c) high = SW * seg + i;
-    }
-    int above = 0;                                         // counts of the segments above mine
-    {
-      const int x1 = __shfl_down(local, 16), x2 = __shfl_down(local, 32), x3 = __shfl_down(local, 48);
-      above = (g4 < 3 ? x1 : 0) + (g4 < 2 ? x2 : 0) + (g4 < 1 ? x3 : 0);
-      if (g4 == 0) s_seg[wave][hr] = above + local;
-    }
-    if (high >= 0) atomicMax(&s_top[hr], high);
-    __syncthreads();
-    for (int w = wave + 1; w < W; ++w) above += s_seg[w][hr];
-    if (above < a.m && a.m <= above + local) {
-      int i = SW - 1;
-      for (; i > 0; --i) {
-        above += (int)s_hist[(seg * SW + i) * 16 + hr];
-        if (above >= a.m) break;
+      for (int i = 0; i < SW; ++i) {
+        const uint32_t c = s_hist[(seg * SW + i) * 16 + hr];
+        local += (int)c;
+        if (c) high = SW * seg + i;
       }
-      s_bin[hr] = SW * seg + i;
-    }
+      int above = 0;                                       // counts of the segments above mine
+      {
+        const int x1 = __shfl_down(local, 16), x2 = __shfl_down(local, 32), x3 = __shfl_down(local, 48);
+        above = (g4 < 3 ? x1 : 0) + (g4 < 2 ? x2 : 0) + (g4 < 1 ? x3 : 0);
+        if (g4 == 0) s_seg[wave][hr] = above + local;
+      }
+      if (first && high >= 0) atomicMax(&s_top[hr], high);
+      __syncthreads();
+      for (int w = wave + 1; w < W; ++w) above += s_seg[w][hr];
+      if (above < target && target <= above + local) {
+        int i = SW - 1;
+        for (;; --i) {
+          above += (int)s_hist[(seg * SW + i) * 16 + hr];
+          if (i == 0 || above >= target) break;
+        }
+        s_found[hr] = SW * seg + i;
+        // (bin 0 holds what lies below the range as well: no use looking closer)
+        if (!FIXED && first && finite && above > a.most && s_found[hr] > 0) s_crowded[hr] = s_crowded[16] = 1;
+      }
+      __syncthreads();
+    };
+    sweep(tid);
     __syncthreads();
+    search(a.m, s_bin, true, tid);
+    // So many codes in the threshold's bin that some list would overflow (a few codes far longer than the others
+    // stretch the bins, or a row has many near its largest): that bin once more, in as many parts.  The list's
+    // values then end where its upper eighth begins, what lies above is ordered by keys.  16384 x 8, k = 16, 100,
+    // 1000, one code of length 300: 7.0, 7.1, 6.2 ms on the exact path -> 0.13, 0.16, 0.62; 16384 x 2: k = 16 3.2 ->
+    // 0.16 ms.  (Long rows: their upper limbs would not tell the parts apart.)
+    if (!FIXED && __builtin_amdgcn_readfirstlane(s_crowded[16])) {
+      const int t = formed_anew(tid);                      // (nothing of it is kept in registers before)
+      search(max(a.m / 8, 1), s_top, false, t);
+      per_bin *= kSampleBins;
+      middle = (float)(kSampleBins / 2 - s_bin[t & 15]) * kSampleBins;
+      sweep(t);
+      __syncthreads();
+      search(a.m, s_fine, false, t);
+    }
   }
   if (tid >= 16) return;
 
@@ -411,7 +464,8 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   } else {
     // (bin 0 also holds what lies below the range)
     const float width = top / (kSampleBins / 2);
-    thr = s_bin[tid] > 0 ? (float)(s_bin[tid] - kSampleBins / 2) * width : -top;
+    const float fine = !FIXED && s_crowded[tid] ? (float)s_fine[tid] / kSampleBins : 0.f;
+    thr = s_bin[tid] > 0 ? ((float)(s_bin[tid] - kSampleBins / 2) + fine) * width : -top;
     hi = (float)(s_top[tid] + 1 - kSampleBins / 2) * width;
     hi = fminf(hi + 0.125f * (hi - thr), top);
     hi = fmaxf(hi, thr + 0.25f * width);
@@ -421,12 +475,12 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   if (FIXED) {
     const double u = unit;
     const double trunc = 3.0 * 16777216.0 * u * u;         // cut low parts: below three units of the value kept
-    e = (float)(0.5005 * u * ((double)a.l1[rowc] + (double)st.l1) * 1.001 + a.D * u * u + trunc);
+    e = (float)(0.5005 * u * ((double)l1 + (double)st.l1) * 1.001 + a.D * u * u + trunc);
   } else {
     // 32 N products on top of the threshold, each sum rounded by 2^-23; l l' and what the halves leave of
     // each number: 3 2^-22, or 2^-25 of the scaled number
     e = (float)(32 * N + 6) * 1.1920929e-07f * (norm * st.norm + fabsf(thr)) * 1.001f + 7.2e-07f * norm * st.norm +
-        2.9802322e-08f / kHalfScale * (a.l1[rowc] + st.l1) * 1.001f + 1e-30f;
+        2.9802322e-08f / hscale * (l1 + st.l1) * 1.001f + 1e-30f;
   }
   e += norm * st.norm * 1e-9f;
   float range = hi - thr;
@@ -438,8 +492,9 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   // similarity is the same, the lowest codes are its neighbours.  (On the exact path a wave took 0.8 to 9 ms for
   // such a row.  One NaN: 987 -> 137 us at 16384 x 8, k = 100, 9692 -> 218 us at 8192 x 256; a twentieth of zeros:
   // 1518 -> 134 us and 11.8 ms -> 212 us.)
-  const bool flat = norm != norm || (a.l1[rowc] == 0.f && st.norm < INFINITY && !(st.nan > 0.f));
-  p.flags = (all ? kAll : 0) | (st.nan > 0.f ? kAnyNan : 0) | (finite ? 0 : kNoList) | (flat ? kFlat : 0);
+  const bool flat = norm != norm || (l1 == 0.f && st.norm < INFINITY && !(st.nan > 0.f));
+  p.flags = (all ? kAll : 0) | (st.nan > 0.f ? kAnyNan : 0) | (finite ? 0 : kNoList) | (flat ? kFlat : 0) |
+            (wide ? kWide : 0);
   const double uu = FIXED ? unit * unit * 16777216.0 : unit * unit;      // real value of one unit of d
   p.a = (float)((double)qmax / ((double)range / uu));
   if (FIXED) p.thr_u = (int)fmin(fmax(floor((double)thr / uu), -1073741824.0), 1073741823.0);
@@ -496,7 +551,8 @@ __global__ __launch_bounds__(kCollectMaxWaves * 64) void knn_collect_f16_kernel(
   const int ntiles = (a.V + 15) >> 4;
   const float c0 = -p.thr;
   HalfOperand<N> q;
-  q.load_query(a.Ef + (int64_t)rowc * 2 * N, g4);
+  const i32x4* const Ef = __builtin_amdgcn_readfirstlane(p.flags) & kWide ? a.Ew : a.Ef;
+  q.load_query(Ef + (int64_t)rowc * 2 * N, g4);
   if (threadIdx.x < 16) s_cnt[threadIdx.x] = 0;
   __syncthreads();
   uint32_t* const parked = s_park + wave * (T * 256);
@@ -504,7 +560,7 @@ __global__ __launch_bounds__(kCollectMaxWaves * 64) void knn_collect_f16_kernel(
   const int step = blockDim.x >> 6;
   // (tile numbers past the end are clamped: read again, not used; rows V .. Vp - 1 are there, whatever
   // they hold: their codes are dropped when the list is ranked)
-  const i32x4* const lane_row = a.Ef + l16 * 2 * N;
+  const i32x4* const lane_row = Ef + l16 * 2 * N;
   auto load = [&](HalfOperand<N> (&f)[4], int t0) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) f[u].load_code(lane_row + (int64_t)min(t0 + step * u, ntiles - 1) * (32 * N), g4);
@@ -984,25 +1040,22 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int ib, int vb, 
     }
   }
   __syncthreads();
-  // inside a run of entries whose neighbours differ by at most E the keys decide; runs do not mix
+  // the keys decide between entries that differ by at most E; all others are in order
   for (int f = tid; f < m; f += NTHR) {
     const int p = todo[f];
     const uint32_t x = sorted[p];
     const uint64_t K = key[p];
     const uint32_t I = ~x & mask;
     int at = p;
-    int v = (int)(x >> ib);
+    const int v = (int)(x >> ib);
     for (int s = p - 1; s >= 0; --s) {
       const uint32_t y = sorted[s];
       if (v - (int)(y >> ib) > E) break;
-      v = (int)(y >> ib);
       at -= before(key[s], ~y & mask, K, I) ? 0 : 1;
     }
-    v = (int)(x >> ib);
     for (int s = p + 1; s < kept; ++s) {
       const uint32_t y = sorted[s];
       if ((int)(y >> ib) - v > E) break;
-      v = (int)(y >> ib);
       at += before(key[s], ~y & mask, K, I) ? 1 : 0;
     }
     if (at < kk) out[1 + at] = (int32_t)I;
@@ -1408,8 +1461,8 @@ __global__ __launch_bounds__(kDirectThreads) void knn_direct_kernel(KnnArgs a, R
 // -------------------------------------------------------------------------------------------- host
 
 struct KnnLayout {
-  size_t o_ep, o_ef, o_es, o_norms, o_l1, o_part, o_plan, o_cnt, o_redo, o_cand, total;
-  int32_t PD, KS, Vp, cap, ib, vb, stride, ns, m, take_all, splits, cap_split;
+  size_t o_ep, o_ef, o_es, o_ew, o_ews, o_norms, o_l1, o_part, o_plan, o_cnt, o_redo, o_cand, total;
+  int32_t PD, KS, Vp, cap, ib, vb, stride, ns, m, take_all, most, splits, cap_split;
 };
 
 KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
@@ -1434,6 +1487,7 @@ KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   L.take_all = expect >= 0.75 * V;
   // (the last term: the threshold is the lower edge of a bin, whose codes are all taken)
   L.cap = L.take_all ? L.Vp : (int32_t)std::min<size_t>(L.Vp, lpp_align_up((size_t)(expect + 5.0 * dev) + 64 + V / 256, 64));
+  L.most = L.m + (int)std::max(0.0, (L.cap - expect) / (2.0 * L.stride));
   // long rows: blocks of 128 queries by `splits` shares of the code tiles, two blocks per compute unit
   const int ntiles = (V + 15) / 16, groups = L.Vp / 128;
   L.splits = L.KS ? std::max(1, std::min({2 * kUnits / groups, ntiles, kMaxSplits})) : 1;
@@ -1450,6 +1504,8 @@ KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   const int n8 = D > 8 ? 2 : 1;
   L.o_ef = take(L.KS ? (size_t)(L.Vp / 16) * L.KS * 3 * 64 * 16 : (size_t)L.Vp * 2 * n8 * 16);
   L.o_es = take(L.KS ? (size_t)((L.ns + 15) / 16) * L.KS * 64 * 16 : (size_t)L.ns * 2 * n8 * 16);
+  L.o_ew = take(L.KS ? 0 : (size_t)L.Vp * 2 * n8 * 16);
+  L.o_ews = take(L.KS ? 0 : (size_t)L.ns * 2 * n8 * 16);
   L.o_norms = take((size_t)V * sizeof(float));
   L.o_l1 = take((size_t)V * sizeof(float));
   L.o_part = take((size_t)kStatBlocks * sizeof(float4));
@@ -1559,10 +1615,12 @@ extern "C" int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, in
   unsigned char* w = reinterpret_cast<unsigned char*>(ws);
   KnnArgs a;
   a.E = E; a.V = V; a.D = D; a.k = k; a.PD = L.PD; a.Vp = L.Vp; a.cap = L.cap; a.ib = L.ib; a.vmask_bits = L.vb;
-  a.stride = L.stride; a.ns = L.ns; a.m = L.m; a.take_all = L.take_all; a.splits = L.splits; a.cap_split = L.cap_split;
+  a.stride = L.stride; a.ns = L.ns; a.m = L.m; a.take_all = L.take_all; a.most = L.most; a.splits = L.splits; a.cap_split = L.cap_split;
   a.Ep = reinterpret_cast<float*>(w + L.o_ep);
   a.Ef = reinterpret_cast<i32x4*>(w + L.o_ef);
   a.Es = reinterpret_cast<i32x4*>(w + L.o_es);
+  a.Ew = reinterpret_cast<i32x4*>(w + L.o_ew);
+  a.Ews = reinterpret_cast<i32x4*>(w + L.o_ews);
   a.norms = reinterpret_cast<float*>(w + L.o_norms);
   a.l1 = reinterpret_cast<float*>(w + L.o_l1);
   a.part = reinterpret_cast<float4*>(w + L.o_part);

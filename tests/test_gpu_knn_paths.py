@@ -130,3 +130,36 @@ def test_knn_rows_that_fall_through_share_the_chip(V, D, k, most):
     E[g.permutation(V)[:900]] = E[0]
     _check(E, k, g.choice(V, size=60))
     assert _least_ms(E, k) < most * plain
+
+
+def _uneven(g, V, D, kind):
+    E = _unit(g, V, D)
+    if kind == "spread":
+        E *= g.uniform(0.2, 3.0, size=(V, 1)).astype(np.float32)
+    elif kind == "tiny":                                    # the lower halves are denormal
+        E *= np.float32(1e-4)
+    elif kind == "third":
+        E[::3] *= np.float32(0.003)
+    elif kind == "few":                                     # 20 codes of length 900: beyond the first scale's 16
+        E[g.permutation(V)[:20]] *= np.float32(900)
+    else:                                                   # one code with one large entry
+        E[5] = 0
+        E[5, D - 1] = float(kind)
+    return E
+
+
+# short rows that are not unit vectors: both scales of the halves (entries below and from 16), the second look at a
+# crowded bin, and beyond both (20000: the exact path); long rows with entries far below the largest
+@pytest.mark.parametrize("kind", ["spread", "tiny", "third", "few", "15.9", "16", "20", "-300", "16376", "20000"])
+@pytest.mark.parametrize("V,D,k", [(1500, 8, 40), (9000, 16, 300), (5000, 3, 900), (2000, 64, 60)])
+def test_knn_rows_of_other_lengths(V, D, k, kind):
+    g = np.random.default_rng(V)
+    E = _uneven(g, V, D, kind)
+    _check(E, k, np.unique(np.concatenate([[0, 3, 5, V - 1], g.choice(V, size=60)])))
+
+
+@pytest.mark.parametrize("kind,k", [("20", 16), ("20", 1000), ("300", 100), ("few", 16)])
+def test_knn_a_few_large_codes_keep_the_lists(kind, k):
+    # 7.2 ms for every row on the exact path where an entry of 16 or more was beyond the halves' range
+    g = np.random.default_rng(6)
+    assert _least_ms(_uneven(g, 16384, 8, kind), k) < 6 * _least_ms(_unit(g, 16384, 8), k)
