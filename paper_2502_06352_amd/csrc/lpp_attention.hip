@@ -983,6 +983,8 @@ int32_t launch_f32(const AttnArgsF32& a, int n_layers, hipStream_t s) {
 // ranges of 16 are the least that gain.  One range -> this rule, 4 heads: 512 keys 12.5 -> 11.7 and 20.9 -> 17.2
 // us; 4096 keys 56 -> 14 and 106 -> 24 us (both sides before the exponential above, which adds about 1 us).
 constexpr int kRangeF32 = 16;
+// Keys of a row, at most: no need of the kernel's (it keeps no scores), but what lpp.h states and the tests cover.
+constexpr int64_t kMostKeysF32 = 36864;
 int f32_splits(const lpp_tree* tree, int B, int H, int S, int layers) {
   const int64_t blocks = (int64_t)B * H * ((tree->M + 15) / 16) * std::max(1, std::min(layers, kLayersPerLaunch));
   const int64_t tiles = ((int64_t)S + tree->M + 15) / 16;
@@ -1130,7 +1132,7 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
       a.B = B; a.H = H; a.Hkv = Hkv; a.S = S; a.M = tree->M; a.words = tree->words;
       a.mtiles = p.mtiles; a.gq = H / Hkv; a.out_bf16 = out_dtype == LPP_BF16;
       a.scale = scale;
-      if ((size_t)(S + tree->M) * sizeof(float) > 144 * 1024) return LPP_EUNSUPPORTED;   // (the range that is tested)
+      if ((int64_t)S + tree->M > kMostKeysF32) return LPP_EUNSUPPORTED;
       size_t o_bytes = 0;
       a.nsplit = f32_splits(tree, B, H, S, L);
       while (a.nsplit > 1 && f32_workspace(tree, B, H, Dh, L, a.nsplit, &o_bytes) > ws_bytes) --a.nsplit;

@@ -106,3 +106,50 @@ def test_layers_ragged_lengths_bf16_out_and_errors():
                                                                              v_tree=None, out=one)],
                                       None, 1, 4, 4, 64, 64, 0.0, one)
     assert e.value.status == lpp.LPP_EINVAL
+
+
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("L,Hkv,seq", [(1, 2, [1100, 333]), (3, 4, None), (3, 1, [0, 1099]), (17, 2, None)])
+@pytest.mark.parametrize("out_dtype", [lpp.LPP_F32, lpp.LPP_BF16])
+def test_layers_float32_keys_in_ranges(Dh, L, Hkv, seq, out_dtype):
+    # 1100 keys in two to four ranges (17 layers: two launches that share the partials): shared heads, ragged
+    # lengths, bf16 output; 21 rows, so the second row tile is a short one
+    cfg = CONFIGS[2].scaled(N=20, S=1100, H=4, B=2 if seq else 1, Dh=Dh, kv_dtype="f32")
+    parent = static_tree(cfg.branching, cfg.N)
+    atts = [_layer_inputs(cfg, Hkv, l) for l in range(L)]
+    got = _run_layers(lpp.Tree(parent), atts, cfg, Hkv, out_dtype=out_dtype, seq_len=seq)
+    tol = 1e-4 if out_dtype == lpp.LPP_F32 else 2.0 ** -8       # (half a unit of bf16's last place)
+    for l in range(L):
+        for b in range(cfg.B):
+            n = seq[b] if seq else cfg.S
+            want = tree_attention(atts[l]["q"][b:b + 1], atts[l]["kc"][b:b + 1, :, :n], atts[l]["vc"][b:b + 1, :, :n],
+                                  atts[l]["kt"][b:b + 1], atts[l]["vt"][b:b + 1], parent)
+            assert attention_error(got[l][b:b + 1], want) <= tol, (l, b)
+
+
+@pytest.mark.parametrize("Dh", [64, 128])
+def test_float32_takes_fewer_ranges_for_a_smaller_workspace(Dh):
+    # every size that is accepted gives the result and leaves what lies behind it alone
+    cfg = CONFIGS[2].scaled(N=20, S=4000, H=4, B=1, Dh=Dh, kv_dtype="f32")
+    parent = static_tree(cfg.branching, cfg.N)
+    tree = lpp.Tree(parent)
+    att = _layer_inputs(cfg, cfg.H, 0)
+    want = tree_attention(att["q"], att["kc"], att["vc"], att["kt"], att["vt"], parent)
+    t = {n: dev(att[n]) for n in ("q", "kc", "vc", "kt", "vt")}
+    full = lpp.lpp_tree_attention_workspace(tree, 1, cfg.H, cfg.S, Dh)
+    least = 0
+    for part in range(1, 33):
+        size = full * part // 32 // 16 * 16
+        ws = torch.full((full + 256,), 0x5A, dtype=torch.uint8, device=DEV)
+        out = torch.full((1, cfg.H, cfg.M, Dh), float("nan"), device=DEV)
+        try:
+            lpp.lpp_tree_attention(tree, lpp.LPP_F32, t["q"], t["kc"], t["vc"], t["kt"], t["vt"], None, 1, cfg.H, cfg.S,
+                                   Dh, 0.0, out, ws[:size])
+        except lpp.LppError as e:
+            assert e.status == lpp.LPP_ENOWORKSPACE and least == 0
+            continue
+        least = least or part
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0x5A).all())
+        assert attention_error(out.cpu().numpy(), want) <= 1e-4, part
+    assert 1 <= least < 32
