@@ -1417,22 +1417,23 @@ __global__ __launch_bounds__(kDirectThreads) void knn_direct_kernel(KnnArgs a, R
     hi = fmaxf(hi, __shfl_xor(hi, o));
     maxn2 = fmaxf(maxn2, __shfl_xor(maxn2, o));
   }
-  // a row of zeros, every similarity zero (none a NaN): the lowest codes (1024 x 8, 30 % zeros: 1072 -> 9 us)
-  bool flat = true;
-#pragma unroll
-  for (int u = 0; u < EPT; ++u) flat = flat && sim[u] == 0.f;
-#pragma unroll
-  for (int d = 0; d < kShortRow; ++d) flat = flat && q[d] == 0.f;
-  if (!__any(!flat)) maxn2 = -1.f;
   if (lane == 0) { s_m[0][wv] = lo; s_m[1][wv] = hi; s_m[2][wv] = maxn2; }
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < W; ++w) { lo = fmaxf(lo, s_m[0][w]); hi = fmaxf(hi, s_m[1][w]); maxn2 = fmaxf(maxn2, s_m[2][w]); }
-  if (maxn2 < 0.f) {                                        // uniform: every wave's
-    for (int t = tid; t < kk; t += kDirectThreads) out[1 + t] = t < i ? t : t + 1;
-    return;
-  }
   lo = -lo;
+  if (__builtin_expect(hi == 0.f && lo == 0.f, 0)) {        // uniform
+    // a row of zeros, no similarity a NaN: the lowest codes (1024 x 8, 30 % zeros: 1072 -> 9 us)
+    bool other = false;
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) other = other || sim[u] != 0.f;
+#pragma unroll 1
+    for (int d = 0; d < D; ++d) other = other || eid[d] != 0.0;
+    if (!__syncthreads_or(other)) {
+      for (int t = tid; t < kk; t += kDirectThreads) out[1 + t] = t < i ? t : t + 1;
+      return;
+    }
+  }
   float n2 = 0.f;
 #pragma unroll
   for (int d = 0; d < kShortRow; ++d) n2 = __builtin_fmaf(q[d], q[d], n2);
