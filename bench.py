@@ -415,11 +415,12 @@ def main():
     knn = None
     if knn_ms:
         knn_flops = 2.0 * V * V * cfg.D             # the method's contraction: every pair of codes once
-        knn = {"ms": knn_ms, "mfma_dtype": "f32" if cfg.D <= 16 else "bf16 filter, float64 keys",
+        knn = {"ms": knn_ms, "mfma_dtype": "f16 pairs of halves, float64 keys" if cfg.D <= 16 else "i8 limbs (24-bit fixed point), float64 keys",
                "contraction_TFLOPs": knn_flops / (knn_ms * 1e-3) / 1e12,
                "frac_of_fp32_mfma_peak": knn_flops / (knn_ms * 1e-3) / 1e12 / FP32_MFMA_PEAK_TFLOPS,
-               "note": "one-time per codebook; whole build (select, float64 re-rank, ordering) against the 2 V^2 D "
-                       "flops of the definition; sweeps beyond the first are not counted as work"}
+               "note": "one-time per codebook; whole build (sample, one filtered contraction, ranking) against the 2 V^2 D "
+                       "flops of the definition, priced at the float32 matrix peak although no float32 product "
+                       "is formed; the several products per pair are not counted as work"}
 
     # ---- CPU baseline: the float64 numpy oracle, as it stands, on this host: once held to one
     # thread, once with the host's threading

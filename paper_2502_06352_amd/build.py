@@ -13,7 +13,10 @@ SOURCES = ["lpp_tree.hip", "lpp_verify.hip", "lpp_attention.hip", "lpp_knn.hip",
 FLAGS = ["-O3", "-ffp-contract=off", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          # matrix results in vector registers: every kernel here works on them right away, and out of the
-         # accumulation registers each value costs a copy
+         # accumulation registers each value costs a copy.  Measured for what it reaches beside the neighbour build:
+         # bf16 attention with long heads in several layers (<128, 2, 1, 4>: 3245 instructions instead of 4186)
+         # 30.3 -> 29.6 us (4 items, 16 heads, 1024 keys, 4 layers), 109.2 -> 108.1 (16 layers, 4 shared heads);
+         # 24 such calls 0 to 2 % faster, none slower; float32 attention equal with and without over 16 calls
          "-mllvm", "-amdgpu-mfma-vgpr-form",
          "-Wall", "-Wno-unused-function", "-Wno-unknown-attributes", "-Wno-unused-command-line-argument"]
 

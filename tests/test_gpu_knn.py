@@ -87,7 +87,8 @@ def test_knn_unnormalised_rows_still_exact():
     E = (g.standard_normal((900, 8)) * g.uniform(0.2, 3.0, size=(900, 1))).astype(np.float32)
     got = run_knn(E, 100)
     _check_rows(E, 100, got, np.arange(900))
-    # rows of more than 16 floats go through the bfloat16 filter, whose margin grows with the norms
+    # rows of more than 16 floats go through the fixed-point filter, whose unit is the largest entry's
+    # (short rows of larger codebooks: test_knn_rows_of_other_lengths)
     E = g.standard_normal((700, 40))
     E = (E / np.linalg.norm(E, axis=1, keepdims=True) * g.uniform(0.5, 1.6, size=(700, 1))).astype(np.float32)
     got = run_knn(E, 60)
@@ -95,8 +96,8 @@ def test_knn_unnormalised_rows_still_exact():
 
 
 def test_knn_long_rows_near_ties_below_bfloat16_resolution():
-    # Codes that differ from each other by far less than a bfloat16 rounding (1e-4 against 4e-3):
-    # the filter cannot tell them apart, the float64 keys must.  Clusters of 12 around 150 centres.
+    # Codes that differ from each other by far less than a bfloat16 rounding (1e-4 against 4e-3), which the
+    # sample's 8-bit image cannot tell apart.  Clusters of 12 around 150 centres.
     g = np.random.default_rng(7)
     centres = g.standard_normal((150, 64))
     E = np.repeat(centres, 12, axis=0) + 1e-4 * g.standard_normal((1800, 64))
