@@ -163,3 +163,39 @@ def test_knn_a_few_large_codes_keep_the_lists(kind, k):
     # 7.2 ms for every row on the exact path where an entry of 16 or more was beyond the halves' range
     g = np.random.default_rng(6)
     assert _least_ms(_uneven(g, 16384, 8, kind), k) < 6 * _least_ms(_unit(g, 16384, 8), k)
+
+
+@pytest.mark.parametrize("V,D", [(5000, 8), (4200, 256)])
+def test_knn_graph_replays_with_and_without_rows_that_fall_through(V, D):
+    # the number of rows left to the exact launch is cleared by every build: a captured one, replayed on codebooks
+    # with some, with all and with none, and eager builds in between on the same workspace
+    k = 20
+    g = np.random.default_rng(V)
+    some, every, none = _unit(g, V, D), _unit(g, V, D), _unit(g, V, D)
+    some[g.permutation(V)[:700]] = some[0]
+    every[9, 1] = np.inf
+    books = [dev(E) for E in (some, every, none)]
+    e = torch.empty_like(books[0])
+    neigh = torch.empty((V, k), dtype=torch.int32, device=DEV)
+    ws = torch.empty(lpp.lpp_build_neighbours_workspace(V, D, k), dtype=torch.uint8, device=DEV)
+    want = []
+    for b in books:
+        e.copy_(b)
+        lpp.lpp_build_neighbours(e, k, neigh, ws)
+        torch.cuda.synchronize()
+        want.append(neigh.clone())
+    rows = np.array([0, 9, V - 1])
+    for E, w in zip((some, every, none), want):
+        assert np.array_equal(w.cpu().numpy()[rows], build_neighbours(E, k, rows=rows))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        lpp.lpp_build_neighbours(e, k, neigh, ws)
+    for i in (0, 2, 1, 1, 2, 0):
+        e.copy_(books[i])
+        neigh.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(neigh, want[i]), i
+        lpp.lpp_build_neighbours(books[(i + 1) % 3], k, neigh, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(neigh, want[(i + 1) % 3])
