@@ -319,7 +319,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   extern __shared__ __align__(16) uint32_t s_hist[];      // [kSampleBins][16]
   constexpr int SEG = kSampleThreads / 16, SW = kSampleBins / SEG;   // segments of the bins, bins of each
   __shared__ int s_seg[kSampleThreads / 64][16];           // counts of a wave's segments, per row
-  __shared__ int s_top[16], s_bin[16], s_fine[16], s_crowded[17];   // [16]: any row
+  __shared__ int s_top[16], s_upper[16], s_bin[16], s_fine[16], s_crowded[17];   // [16]: any row
   constexpr int W = kSampleThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
@@ -437,12 +437,12 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
     search(a.m, s_bin, true, tid);
     // So many codes in the threshold's bin that some list would overflow (a few codes far longer than the others
     // stretch the bins, or a row has many near its largest): that bin once more, in as many parts.  The list's
-    // values then end where its upper eighth begins, what lies above is ordered by keys.  16384 x 8, k = 16, 100,
+    // values then end where its upper eighth begins, what lies above is ordered by keys (only of the rows that asked).  16384 x 8, k = 16, 100,
     // 1000, one code of length 300: 7.0, 7.1, 6.2 ms on the exact path -> 0.13, 0.16, 0.62; 16384 x 2: k = 16 3.2 ->
     // 0.16 ms.  (Long rows: their upper limbs would not tell the parts apart.)
     if (!FIXED && __builtin_amdgcn_readfirstlane(s_crowded[16])) {
       const int t = formed_anew(tid);                      // (nothing of it is kept in registers before)
-      search(max(a.m / 8, 1), s_top, false, t);
+      search(max(a.m / 8, 1), s_upper, false, t);
       per_bin *= kSampleBins;
       middle = (float)(kSampleBins / 2 - s_bin[t & 15]) * kSampleBins;
       sweep(t);
@@ -466,7 +466,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
     const float width = top / (kSampleBins / 2);
     const float fine = !FIXED && s_crowded[tid] ? (float)s_fine[tid] / kSampleBins : 0.f;
     thr = s_bin[tid] > 0 ? ((float)(s_bin[tid] - kSampleBins / 2) + fine) * width : -top;
-    hi = (float)(s_top[tid] + 1 - kSampleBins / 2) * width;
+    hi = (float)((!FIXED && s_crowded[tid] ? s_upper[tid] : s_top[tid]) + 1 - kSampleBins / 2) * width;
     hi = fminf(hi + 0.125f * (hi - thr), top);
     hi = fmaxf(hi, thr + 0.25f * width);
   }
