@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   __shared__ int s_top[16], s_upper[16], s_bin[16], s_fine[16], s_crowded[17];   // [16]: any row
   constexpr int W = kSampleThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l16 = lane & 15, g4 = lane >> 4;
+  const int l16 = lane & 15;
   const int row0 = blockIdx.x * 16, row = row0 + l16, rowc = min(row, a.V - 1);
   const Stats st = reduce_stats(a, lane);
   const float norm = a.norms[rowc], l1 = a.l1[rowc];
