@@ -17,7 +17,8 @@
 //            (fixed point) over code index
 //   rank     per row: the list is sorted by its approximate similarities (value buckets in
 //            LDS); entries whose similarities differ by less than twice the bound on
-//            their error are ordered by their exact float64 keys, everything else already is
+//            their error are ordered by their exact float64 keys (long rows: by float64 sums in any order where these
+//            are far enough apart), everything else already is
 //   exact    rows that their list does not decide, over all codes (a launch of its own where that pays)
 // Small codebooks of short rows (V <= kDirectCodes, D <= 16) take one kernel that does all of it.
 //
@@ -86,6 +87,9 @@ struct RowPlan {
                                               // kFlat: its similarities are all the same; kWide: halves of kWideScale
 };
 constexpr int kAll = 1, kAnyNan = 2, kNoList = 4, kFlat = 8, kWide = 16;
+// Rows of up to this many floats: a thread forms an entry's key, a chain that short costs less than the sums and their
+// comparison (4096 x 64, k = 300: 59 us either way, every code four times: 91 us and 162).
+constexpr int kChainFloats = 64;
 constexpr int kMaxSplits = 16;                // segments of a long row's list
 constexpr int kUnits = 256;                   // compute units of the card these kernels are for
 constexpr size_t kMostLds = 150 * 1024;       // dynamic LDS of a block, static arrays beside it
@@ -111,8 +115,12 @@ struct KnnArgs {
   i32x4* Ews;
   float* norms;         // [V]
   float* l1;            // [V]
+  int32_t* seen;        // (long rows) [1 << 32 - seen_shift] codes by their 1-norm
+  int32_t* twin;        // (long rows) [V] a code that is the same, one for all of them
+  int32_t seen_shift;
   float4* part;         // [kStatBlocks]: max norm, max |x|, max 1-norm, any NaN
   RowPlan* plan;        // [Vp]
+  float* top;           // [Vp] what a row's similarities stay below (long rows)
   int32_t* cnt;         // [V][splits]
   uint32_t* cand;       // [V][cap]
   int32_t* redo;        // [1 + V]: rows that take the exact path, their number first
@@ -154,6 +162,11 @@ __device__ __forceinline__ int sample_slot(const KnnArgs& a, int code) {
   const int j = code / a.stride;
   const uint32_t off = (((uint32_t)j * 2654435761u) >> 15) & (uint32_t)(a.stride - 1);
   return j < a.ns && code == j * a.stride + (int)off ? j : -1;
+}
+
+// Place of a code in `seen`, by its 1-norm: codes that are the same share it.
+__device__ __forceinline__ uint32_t seen_slot(const KnnArgs& a, float l1) {
+  return (__float_as_uint(l1) * 2654435761u) >> a.seen_shift;
 }
 
 // G lanes per row, 16 bytes per lane and step.
@@ -217,6 +230,7 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
     }
     const float n = sqrtf(ss);
     if (sub == 0) { a.norms[row] = n; a.l1[row] = sa; }
+    if (G > 4 && sub == 0 && sa > 0.f) a.seen[seen_slot(a, sa)] = row;   // (any of the codes that share the place)
     // (a row that holds a NaN has a NaN norm and takes no part in the maxima)
     const bool bad = !(n == n);
     mx[0] = fmaxf(mx[0], n);
@@ -335,6 +349,18 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   // (far below 1e-30 the bound on the error would itself be rounded)
   const bool finite = top > 1e-30f && top < INFINITY && (FIXED || st.mabs * hscale < 65504.0f);
 
+  // A code that is the same as this one, the same for all of them, or the code itself.  (seen holds what was written to
+  // the place last, and rubbish where nothing was: what counts is that the numbers are the same.)
+  if (FIXED && tid >= kSampleThreads - 16 && row < a.V) {
+    const int r = a.seen[seen_slot(a, l1)];
+    bool same = l1 > 0.f && r >= 0 && r < a.V && r != row && a.l1[r] == l1;
+#pragma unroll 1
+    for (int d = 0; same && d < a.PD; d += 4) {
+      const i32x4 x = *reinterpret_cast<const i32x4*>(a.Ep + (int64_t)row * a.PD + d), y = *reinterpret_cast<const i32x4*>(a.Ep + (int64_t)r * a.PD + d);
+      same = x[0] == y[0] && x[1] == y[1] && x[2] == y[2] && x[3] == y[3];
+    }
+    a.twin[row] = same ? r : row;
+  }
   if (!a.take_all) {
     if (tid < 17) { s_top[tid & 15] = 0; s_bin[tid & 15] = 0; s_crowded[tid] = 0; }
     const int ntiles = (a.ns + 15) / 16;
@@ -507,6 +533,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   }
   if (!(e < INFINITY)) p.E = 1 << 30;
   a.plan[row] = p;
+  if (FIXED) a.top[row] = top;
 }
 
 // What both collecting kernels do with the similarities they form: a lane holds four of one row per
@@ -754,6 +781,7 @@ struct Rows {
   const float* p;
   int32_t pitch, D;
   bool quads;
+  const int32_t* twin;                                      // (long rows) codes that are the same have the same here
 };
 
 // exact key of the pair (row i held in LDS as doubles, code j): float64 FMA chain in index order
@@ -811,6 +839,25 @@ __device__ __forceinline__ void exact_keys(const double* ei, const Rows& R, cons
   for (int u = 0; u < U; ++u) K[u] = orderable(acc[u]);
 }
 
+__device__ __forceinline__ double key_value(uint64_t K) {
+  const uint64_t u = (K >> 63) ? (K & 0x7FFFFFFFFFFFFFFFull) : ~K;
+  return __longlong_as_double((long long)u);
+}
+
+// Sum over the 16 lanes of a DPP row; all of them return it.
+__device__ __forceinline__ double add_over_16(double x) {
+#define LPP_ROR(n)                                                                                                  \
+  {                                                                                                                 \
+    const uint64_t b = (uint64_t)__double_as_longlong(x);                                                           \
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x120 + n, 0xf, 0xf, false);       \
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), 0x120 + n, 0xf, 0xf, false); \
+    x += __longlong_as_double((long long)((uint64_t)hi << 32 | lo));                                                \
+  }
+  LPP_ROR(8) LPP_ROR(4) LPP_ROR(2) LPP_ROR(1)
+#undef LPP_ROR
+  return x;
+}
+
 // (key desc, idx asc) "a goes before b"
 __device__ __forceinline__ bool before(uint64_t ka, uint32_t ia, uint64_t kb, uint32_t ib) {
   return ka > kb || (ka == kb && ia < ib);
@@ -858,7 +905,7 @@ struct RankShape { int32_t P, lognb; };
 // only before it by its key: neither can move anything among the first kk.)
 template <int NTHR, int EPT, bool STAGED>
 __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int ib, int vb, int E, bool all, int kk, const Rows& R,
-                         RankShape sh, unsigned char* smem, int* s_w, int32_t* out, int tid) {
+                         float top, RankShape sh, unsigned char* smem, int* s_w, int32_t* out, int tid) {
   const int NB = 1 << sh.lognb;
   double* eid = reinterpret_cast<double*>(smem);
   uint32_t* bucket = reinterpret_cast<uint32_t*>(eid + ((R.D + 3) & ~3));
@@ -874,6 +921,9 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int ib, int vb, 
 
   for (int i = tid; i < NB / 4; i += NTHR) reinterpret_cast<uint4*>(bucket)[i] = make_uint4(0, 0, 0, 0);
   if (tid == 0) { s_w[kTodo] = 0; s_w[kKept] = 0; s_w[kCrowded] = 0; }
+  __shared__ uint32_t s_same[STAGED ? NTHR * EPT / 32 : 1];  // (long rows) bit p: sorted entry p is the same code as the one before it
+  if (STAGED)
+    for (int i = tid; i < NTHR * EPT / 32; i += NTHR) s_same[i] = 0;
   __syncthreads();
   uint32_t pos[EPT];
 #pragma unroll
@@ -985,52 +1035,72 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int ib, int vb, 
   // rounding of the threshold)
   if (!all && (int)(~sorted[kk - 1] >> ib) <= E + 2) return false;      // uniform
   const int m = s_w[kTodo];
+  // the first of the entries up to p, and the one behind those from p on, that are the same code
+  auto run_start = [&](int p) {
+    uint32_t w = (uint32_t)p >> 5, first = ~s_same[w] & (0xFFFFFFFFu >> (31 - (p & 31)));       // (entry 0 is never set)
+    while (!first) first = ~s_same[--w];
+    return (int)(32 * w) + 31 - __builtin_clz(first);
+  };
+  auto run_end = [&](int p) {
+    int w = p + 1 >> 5;
+    uint32_t next = w < NTHR * EPT / 32 ? ~s_same[w] & (0xFFFFFFFFu << (p + 1 & 31)) : 1u;
+    while (!next) next = ++w < NTHR * EPT / 32 ? ~s_same[w] : 1u;
+    return 32 * w + __builtin_ctz(next);
+  };
   if (STAGED) {
-    // rows of more than 16 floats: a wave takes 64 entries (there are 50 or so as a rule), stages 16
-    // floats of their rows at a time through LDS (whole 64-byte segments, four steps of them in flight) and
-    // every lane runs the chain of its own
-    constexpr int CH = 16, PITCH = CH + 4, DEEP = 4, TILES = NTHR >= 128 ? 2 : 1;
-    __shared__ __align__(16) float s_tile[TILES][64 * PITCH];
-    if (wv < TILES) {
-      float* tile = s_tile[wv];
-      for (int base = wv * 64; base < m; base += TILES * 64) {
-        const int p = todo[min(base + lane, m - 1)];
-        const int jown = (int)(~sorted[p] & mask), col = (lane & 3) * 4;
-        const float* r[4];
+    // Long rows (up to kChainFloats the key is formed by a thread): 16 lanes an entry, four floats of its row each per step,
+    // their sums added across the lanes.  Such a sum and the key, which adds the same exact products in index order, are
+    // each off by at most D 2^-53 of the products' magnitudes (those by the norms' product): where two sums are further
+    // apart than `apart`, twice what both together come to, the keys have the same order.  The few entries with a
+    // closer one get their key.  Bound by waiting for the rows, of which few are in L2: what counts is the waves
+    // in flight.  (A lane an entry, its row's pieces through 10 KB of LDS and 64 registers, left four blocks to a compute
+    // unit and two of a block's four waves at work; now six blocks: 8192 x 256, k = 1000: the build 316 -> 269 us, 5000 x 96,
+    // k = 2500: the build 403 -> 268.  The four chains of four lanes going round them, exact at once: 146 us.)
+    // A code that is the same as the one before it in the order has that one's key.  (Every code four times, 8192 x 256,
+    // k = 1000, the build: 0.96 ms before, 1.64 with all sums and keys formed, 0.93 so; 64 times 1.61, 2.11, 0.92.)
+    auto follows = [&](int p) {
+      const bool yes = p > 0 && (sorted[p - 1] ^ sorted[p]) >> ib == 0 && R.twin[~sorted[p - 1] & mask] == R.twin[~sorted[p] & mask];
+      if (yes) atomicOr(&s_same[p >> 5], 1u << (p & 31));
+      return yes;
+    };
+    const int l16 = lane & 15;
+    bool again = false;
+    if (R.D <= kChainFloats) {
+      for (int f = tid; f < m; f += NTHR) {
+        const int p = todo[f];
+        if (follows(p)) again = true;
+        else key[p] = exact_key(eid, R, (int)(~sorted[p] & mask));
+      }
+    } else {
+      for (int f = tid >> 4; f < m; f += NTHR / 16) {
+        const int p = todo[f];
+        if (follows(p)) { again = true; continue; }
+        const float* r = R.p + (int64_t)(~sorted[p] & mask) * R.pitch;
+        f32x4 x[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) r[q] = R.p + (int64_t)__shfl(jown, 16 * q + (lane >> 2)) * R.pitch + col;
-        f32x4 x[DEEP][4];
-        auto fetch = [&](f32x4 (&y)[4], int st) {
+        for (int st = 0; st < 4; ++st)
+          if (64 * st < R.D) x[st] = 64 * st + 4 * l16 < R.pitch ? *reinterpret_cast<const f32x4*>(r + 64 * st + 4 * l16) : f32x4{0.f, 0.f, 0.f, 0.f};
+        double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) y[q] = st + col < R.pitch ? *reinterpret_cast<const f32x4*>(r[q] + st) : f32x4{0.f, 0.f, 0.f, 0.f};
-        };
-#pragma unroll
-        for (int d = 0; d < DEEP; ++d) fetch(x[d], d * CH);
-        double acc = 0.0;
-        for (int st0 = 0; st0 < R.D; st0 += DEEP * CH) {
-#pragma unroll
-          for (int d = 0; d < DEEP; ++d) {
-            const int st = st0 + d * CH;
-            if (st >= R.D) break;                           // uniform
-#pragma unroll
-            for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(tile + (16 * q + (lane >> 2)) * PITCH + col) = x[d][q];
-            wave_lds_sync();
-            fetch(x[d], st + DEEP * CH);
-#pragma unroll
-            for (int t = 0; t < CH; t += 4) {
-              if (st + t >= R.D) break;                     // uniform
-              const f32x4 v = *reinterpret_cast<const f32x4*>(tile + lane * PITCH + t);
-              const double* eq = eid + st + t;
-              const f64x2 e0 = *reinterpret_cast<const f64x2*>(eq), e1 = *reinterpret_cast<const f64x2*>(eq + 2);
-              acc = __builtin_fma(e0[0], (double)v[0], acc);
-              acc = __builtin_fma(e0[1], (double)v[1], acc);
-              acc = __builtin_fma(e1[0], (double)v[2], acc);
-              acc = __builtin_fma(e1[1], (double)v[3], acc);
-            }
-            wave_lds_sync();
+        for (int st = 0; st < 4; ++st)
+          if (64 * st < R.D) {                                // uniform
+            // (the row's floats out of LDS each time: in registers they cost more, in waves, than the reads do)
+            const double* e = eid + min(64 * st + 4 * l16, R.pitch - 4);
+            const f64x2 e0 = *reinterpret_cast<const f64x2*>(e), e1 = *reinterpret_cast<const f64x2*>(e + 2);
+            s0 = __builtin_fma(e0[0], (double)x[st][0], s0);
+            s1 = __builtin_fma(e0[1], (double)x[st][1], s1);
+            s0 = __builtin_fma(e1[0], (double)x[st][2], s0);
+            s1 = __builtin_fma(e1[1], (double)x[st][3], s1);
           }
-        }
-        if (base + lane < m) key[p] = orderable(acc);
+        s0 = add_over_16(s0 + s1);
+        if (l16 == 0) key[p] = orderable(s0);
+      }
+    }
+    if (__syncthreads_or(again)) {
+      for (int f = tid; f < m; f += NTHR) {
+        const int p = todo[f];
+        const int q = run_start(p);
+        if (q != p) key[p] = key[q];
       }
     }
   } else {
@@ -1041,31 +1111,48 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int ib, int vb, 
   }
   __syncthreads();
   // the keys decide between entries that differ by at most E; all others are in order
-  for (int f = tid; f < m; f += NTHR) {
-    const int p = todo[f];
+  const double apart = STAGED && R.D > kChainFloats ? 8.4 * 1.1102230246251565e-16 * R.D * (double)top : -1.0;
+  auto place = [&](int p, bool sums) {                      // false: closer to some other than its sum tells
     const uint32_t x = sorted[p];
-    const uint64_t K = key[p];
+    const uint64_t K = key[p], lo = orderable(key_value(K) - apart), hi = orderable(key_value(K) + apart);
     const uint32_t I = ~x & mask;
-    int at = p;
     const int v = (int)(x >> ib);
-    for (int s = p - 1; s >= 0; --s) {
+    // (the entries of one value lie by descending index: a run of the same code is turned round)
+    const int beg = STAGED ? run_start(p) : p, end = STAGED ? run_end(p) : p + 1;
+    bool clear = true;
+    int at = beg + end - 1 - p;
+    for (int s = beg - 1; s >= 0; --s) {
       const uint32_t y = sorted[s];
       if (v - (int)(y >> ib) > E) break;
-      at -= before(key[s], ~y & mask, K, I) ? 0 : 1;
+      const uint64_t L = key[s];
+      clear = clear && (L < lo || L > hi);
+      at -= before(L, ~y & mask, K, I) ? 0 : 1;
     }
-    for (int s = p + 1; s < kept; ++s) {
+    for (int s = end; s < kept; ++s) {
       const uint32_t y = sorted[s];
       if ((int)(y >> ib) - v > E) break;
-      at += before(key[s], ~y & mask, K, I) ? 1 : 0;
+      const uint64_t L = key[s];
+      clear = clear && (L < lo || L > hi);
+      at += before(L, ~y & mask, K, I) ? 1 : 0;
     }
-    if (at < kk) out[1 + at] = (int32_t)I;
+    clear = clear || !STAGED || !sums || apart < 0.0;
+    if (clear && at < kk) out[1 + at] = (int32_t)I;
+    return clear;
+  };
+  bool unclear = false;
+  for (int f = tid; f < m; f += NTHR)
+    if (!place(todo[f], true)) { todo[f] |= 0x8000; unclear = true; }
+  if (STAGED && __syncthreads_or(unclear)) {
+    for (int f = tid; f < m; f += NTHR)
+      if (todo[f] & 0x8000) {
+        const int p = todo[f] & 0x7FFF;
+        key[p] = exact_key(eid, R, (int)(~sorted[p] & mask));
+      }
+    __syncthreads();
+    for (int f = tid; f < m; f += NTHR)
+      if (todo[f] & 0x8000) place(todo[f] & 0x7FFF, false);
   }
   return true;
-}
-
-__device__ __forceinline__ double key_value(uint64_t K) {
-  const uint64_t u = (K >> 63) ? (K & 0x7FFFFFFFFFFFFFFFull) : ~K;
-  return __longlong_as_double((long long)u);
 }
 
 // Rank of each of the n entries of (skey, sidx) in the order (key desc, idx asc), without a
@@ -1271,7 +1358,7 @@ __device__ void exact_row(const Rows& R, int V, int i, int kk, unsigned char* sm
 // One block per row: NTHR threads, EPT list words each in registers.  A row that its list does not decide takes the
 // exact path here, or (LATER) in a launch of its own.
 template <int NTHR, int EPT, bool STAGED, bool LATER>
-__global__ __launch_bounds__(NTHR) void knn_rank_kernel(KnnArgs a, RankShape sh) {
+__global__ __launch_bounds__(NTHR, 8) void knn_rank_kernel(KnnArgs a, RankShape sh) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_w[20];
   const int tid = threadIdx.x, i = blockIdx.x, kk = a.k - 1;
@@ -1334,9 +1421,10 @@ __global__ __launch_bounds__(NTHR) void knn_rank_kernel(KnnArgs a, RankShape sh)
     for (int t = tid; t < kk; t += NTHR) out[1 + t] = t < i ? t : t + 1;
     return;
   }
-  const Rows R{a.Ep, a.PD, a.D, true};
+  const Rows R{a.Ep, a.PD, a.D, true, a.twin};
   if (!over && !(p.flags & kNoList)) {
-    if (rank_row<NTHR, EPT, STAGED>(w, on, a.ib, a.vmask_bits, p.E, (p.flags & kAll) != 0, kk, R, sh, smem, s_w, out, tid)) return;
+    if (rank_row<NTHR, EPT, STAGED>(w, on, a.ib, a.vmask_bits, p.E, (p.flags & kAll) != 0, kk, R,
+                                   STAGED ? a.top[i] : 0.f, sh, smem, s_w, out, tid)) return;
   }
   // (what was written of the row is written again)
   if constexpr (LATER) {
@@ -1361,7 +1449,7 @@ __global__ __launch_bounds__(kExactThreads) void knn_exact_kernel(KnnArgs a) {
     double* eid = reinterpret_cast<double*>(smem);
     for (int d = threadIdx.x; d < a.PD; d += kExactThreads) eid[d] = (double)a.Ep[(int64_t)i * a.PD + d];
     __syncthreads();
-    exact_row<kExactThreads, KEEP, KEEP ? 2 : 1>(Rows{a.Ep, a.PD, a.D, true}, a.V, i, a.k - 1, smem, s_w, a.neigh + (int64_t)i * a.k, threadIdx.x);
+    exact_row<kExactThreads, KEEP, KEEP ? 2 : 1>(Rows{a.Ep, a.PD, a.D, true, a.twin}, a.V, i, a.k - 1, smem, s_w, a.neigh + (int64_t)i * a.k, threadIdx.x);
     __syncthreads();
   }
 }
@@ -1451,8 +1539,8 @@ __global__ __launch_bounds__(kDirectThreads) void knn_direct_kernel(KnnArgs a, R
     on |= c < V && c != i && sim[u] == sim[u] ? 1u << u : 0u;      // (a code that holds a NaN is no neighbour)
   }
   __syncthreads();
-  const Rows R{a.E, D, D, quads};
-  if (range < INFINITY && rank_row<kDirectThreads, EPT, false>(w, on, a.ib, a.vmask_bits, E, true, kk, R, sh, smem, s_w, out, tid))
+  const Rows R{a.E, D, D, quads, nullptr};
+  if (range < INFINITY && rank_row<kDirectThreads, EPT, false>(w, on, a.ib, a.vmask_bits, E, true, kk, R, 0.f, sh, smem, s_w, out, tid))
     return;
   __threadfence();                                          // (what was written of the row is written again by other lanes)
   __syncthreads();
@@ -1462,9 +1550,11 @@ __global__ __launch_bounds__(kDirectThreads) void knn_direct_kernel(KnnArgs a, R
 // -------------------------------------------------------------------------------------------- host
 
 struct KnnLayout {
-  size_t o_ep, o_ef, o_es, o_ew, o_ews, o_norms, o_l1, o_part, o_plan, o_cnt, o_redo, o_cand, total;
-  int32_t PD, KS, Vp, cap, ib, vb, stride, ns, m, take_all, most, splits, cap_split;
+  size_t o_ep, o_ef, o_es, o_ew, o_ews, o_norms, o_l1, o_seen, o_twin, o_part, o_plan, o_top, o_cnt, o_redo, o_cand, total;
+  int32_t PD, KS, Vp, cap, ib, vb, stride, ns, m, take_all, most, splits, cap_split, seen_shift;
 };
+
+int log2_up(int x) { int l = 0; while ((1 << l) < x) ++l; return l; }
 
 KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   KnnLayout L;
@@ -1509,8 +1599,12 @@ KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   L.o_ews = take(L.KS ? 0 : (size_t)L.ns * 2 * n8 * 16);
   L.o_norms = take((size_t)V * sizeof(float));
   L.o_l1 = take((size_t)V * sizeof(float));
+  L.seen_shift = 32 - log2_up(std::max(V, 1024)) - 2;
+  L.o_seen = take(L.KS ? sizeof(int32_t) << (32 - L.seen_shift) : 0);
+  L.o_twin = take(L.KS ? (size_t)V * sizeof(int32_t) : 0);
   L.o_part = take((size_t)kStatBlocks * sizeof(float4));
   L.o_plan = take((size_t)L.Vp * sizeof(RowPlan));
+  L.o_top = take(L.KS ? (size_t)L.Vp * sizeof(float) : 0);
   L.o_cnt = take((size_t)V * L.splits * sizeof(int32_t));
   L.o_redo = take((size_t)(V + 1) * sizeof(int32_t));
   L.o_cand = take((size_t)V * entries * sizeof(uint32_t));
@@ -1624,13 +1718,16 @@ extern "C" int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, in
   a.Ews = reinterpret_cast<i32x4*>(w + L.o_ews);
   a.norms = reinterpret_cast<float*>(w + L.o_norms);
   a.l1 = reinterpret_cast<float*>(w + L.o_l1);
+  a.seen = reinterpret_cast<int32_t*>(w + L.o_seen);
+  a.twin = reinterpret_cast<int32_t*>(w + L.o_twin);
+  a.seen_shift = L.seen_shift;
   a.part = reinterpret_cast<float4*>(w + L.o_part);
   a.plan = reinterpret_cast<RowPlan*>(w + L.o_plan);
+  a.top = reinterpret_cast<float*>(w + L.o_top);
   a.cnt = reinterpret_cast<int32_t*>(w + L.o_cnt);
   a.cand = reinterpret_cast<uint32_t*>(w + L.o_cand);
   a.redo = reinterpret_cast<int32_t*>(w + L.o_redo);
   a.neigh = neigh;
-  auto log2_up = [](int x) { int l = 0; while ((1 << l) < x) ++l; return l; };
 
   if (D <= kShortRow && V <= kDirectCodes) {
     // values need no more than the float's bits; the key buffer over counters and scattered words wants NB >= P

@@ -199,3 +199,23 @@ def test_knn_graph_replays_with_and_without_rows_that_fall_through(V, D):
         lpp.lpp_build_neighbours(books[(i + 1) % 3], k, neigh, ws)
         torch.cuda.synchronize()
         assert torch.equal(neigh, want[(i + 1) % 3])
+
+
+@pytest.mark.parametrize("kind", ["copies", "permuted"])
+@pytest.mark.parametrize("V,D,k", [(1200, 17, 90), (1200, 64, 90), (1200, 65, 90), (2000, 128, 300), (1500, 253, 900), (4500, 256, 120)])
+def test_knn_long_rows_the_same_or_the_same_sum(V, D, k, kind):
+    # copies: codes six times over, in any order, some of them one unit of the last place off in one number.
+    # permuted: codes of the same numbers in another order, seen from rows of equal numbers: the sums are the same, the
+    # keys, added in index order, are not; 17 and 64 floats form keys at once
+    g = np.random.default_rng(V + D)
+    if kind == "copies":
+        E = _unit(g, V // 6 + 1, D)[np.arange(V) // 6]
+        i = np.flatnonzero(np.arange(V) % 6 == 5)
+        E[i, i % D] = np.nextafter(E[i, i % D], np.float32(2))
+        E = E[g.permutation(V)]
+    else:
+        E = _unit(g, 40, D)[np.arange(V) % 40]
+        E = g.permuted(E, axis=1)
+        E[::7] = np.float32(1.0 / np.sqrt(D))
+        E[3::7] = np.where(np.arange(D) < D // 2, np.float32(0.7), np.float32(0.7) * np.float32(1 + 2.0 ** -23)) / np.float32(np.sqrt(D))
+    _check(E, k, None if V <= 2000 else np.unique(np.concatenate([[0, 3, 5, V - 1], g.choice(V, size=200)])))
