@@ -87,8 +87,9 @@ struct RowPlan {
                                               // kFlat: its similarities are all the same; kWide: halves of kWideScale
 };
 constexpr int kAll = 1, kAnyNan = 2, kNoList = 4, kFlat = 8, kWide = 16;
-// Rows of up to this many floats: a thread forms an entry's key, a chain that short costs less than the sums and their
-// comparison (4096 x 64, k = 300: 59 us either way, every code four times: 91 us and 162).
+// Rows of up to this many floats, more of a list's entries than an eighth of the threads being near ties: a thread forms an
+// entry's key, a chain that short costs less than the sums and their comparison (every code four times, 4096 x 64,
+// k = 300: 91 us and 162).  Few entries: the chain's loads in turn cost more (2000 x 64, k = 50: 37.4 us and 36.2).
 constexpr int kChainFloats = 64;
 constexpr int kMaxSplits = 16;                // segments of a long row's list
 constexpr int kUnits = 256;                   // compute units of the card these kernels are for
@@ -349,18 +350,6 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   // (far below 1e-30 the bound on the error would itself be rounded)
   const bool finite = top > 1e-30f && top < INFINITY && (FIXED || st.mabs * hscale < 65504.0f);
 
-  // A code that is the same as this one, the same for all of them, or the code itself.  (seen holds what was written to
-  // the place last, and rubbish where nothing was: what counts is that the numbers are the same.)
-  if (FIXED && tid >= kSampleThreads - 16 && row < a.V) {
-    const int r = a.seen[seen_slot(a, l1)];
-    bool same = l1 > 0.f && r >= 0 && r < a.V && r != row && a.l1[r] == l1;
-#pragma unroll 1
-    for (int d = 0; same && d < a.PD; d += 4) {
-      const i32x4 x = *reinterpret_cast<const i32x4*>(a.Ep + (int64_t)row * a.PD + d), y = *reinterpret_cast<const i32x4*>(a.Ep + (int64_t)r * a.PD + d);
-      same = x[0] == y[0] && x[1] == y[1] && x[2] == y[2] && x[3] == y[3];
-    }
-    a.twin[row] = same ? r : row;
-  }
   if (!a.take_all) {
     if (tid < 17) { s_top[tid & 15] = 0; s_bin[tid & 15] = 0; s_crowded[tid] = 0; }
     const int ntiles = (a.ns + 15) / 16;
@@ -369,16 +358,20 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
       const uint32_t bin = min((uint32_t)__builtin_fmaf(v, per_bin, middle), kSampleBins - 1u);   // (negative, NaN: 0)
       atomicAdd(&s_hist[bin * 16 + l16], 1u);
     };
-    // (codes past the sample's end are not counted)
+    // (codes past the sample's end are not counted, nor is the row itself: where it is in the sample its own similarity,
+    // often far above the others, would stretch the list's values over a range that holds nobody: 8192 x 256, k = 1000,
+    // half the rows: buckets of 15 entries instead of 3)
+    const int own_tile = row0 / a.stride >> 4;             // (16 rows from a multiple of 16 on: one tile of the sample)
     auto count = [&](float x0, float x1, float x2, float x3, int t, int l16, int g4) {
       const float x[4] = {x0, x1, x2, x3};
-      if ((t + 1) * 16 <= a.ns) {                          // uniform
+      if ((t + 1) * 16 <= a.ns && !(FIXED && t == own_tile)) {   // uniform
 #pragma unroll
         for (int r = 0; r < 4; ++r) add(x[r], l16);
       } else {
+        const int own = FIXED ? sample_slot(a, row0 + l16) : -1;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (t * 16 + 4 * g4 + r < a.ns) add(x[r], l16);
+          if (t * 16 + 4 * g4 + r < a.ns && t * 16 + 4 * g4 + r != own) add(x[r], l16);
       }
     };
     constexpr int U = FIXED && N >= 3 ? 1 : (FIXED && N == 2 ? 2 : 4);
@@ -475,6 +468,20 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
       __syncthreads();
       search(a.m, s_fine, false, t);
     }
+  }
+  // A code that is the same as this one, the same for all of them, or the code itself.  (seen holds what was written to
+  // the place last, and rubbish where nothing was: what counts is that the numbers are the same.)
+  if (FIXED && wave == 1) {
+    const int r = a.seen[seen_slot(a, l1)];
+    int same = l1 > 0.f && r >= 0 && r < a.V && r != row && a.l1[min(max(r, 0), a.V - 1)] == l1;
+#pragma unroll 1
+    for (int d = lane >> 4 << 2; same && d < a.PD; d += 16) {
+      const i32x4 x = *reinterpret_cast<const i32x4*>(a.Ep + (int64_t)rowc * a.PD + d), y = *reinterpret_cast<const i32x4*>(a.Ep + (int64_t)r * a.PD + d);
+      same = x[0] == y[0] && x[1] == y[1] && x[2] == y[2] && x[3] == y[3];
+    }
+    same &= __shfl_xor(same, 16);
+    same &= __shfl_xor(same, 32);
+    if (lane < 16 && row < a.V) a.twin[row] = same ? r : row;
   }
   if (tid >= 16) return;
 
@@ -1047,8 +1054,9 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int ib, int vb, 
     while (!next) next = ++w < NTHR * EPT / 32 ? ~s_same[w] : 1u;
     return 32 * w + __builtin_ctz(next);
   };
+  const bool chain = R.D <= kChainFloats && m > NTHR / 8;   // uniform
   if (STAGED) {
-    // Long rows (up to kChainFloats the key is formed by a thread): 16 lanes an entry, four floats of its row each per step,
+    // Long rows: 16 lanes an entry, four floats of its row each per step,
     // their sums added across the lanes.  Such a sum and the key, which adds the same exact products in index order, are
     // each off by at most D 2^-53 of the products' magnitudes (those by the norms' product): where two sums are further
     // apart than `apart`, twice what both together come to, the keys have the same order.  The few entries with a
@@ -1065,7 +1073,7 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int ib, int vb, 
     };
     const int l16 = lane & 15;
     bool again = false;
-    if (R.D <= kChainFloats) {
+    if (chain) {
       for (int f = tid; f < m; f += NTHR) {
         const int p = todo[f];
         if (follows(p)) again = true;
@@ -1111,7 +1119,7 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int ib, int vb, 
   }
   __syncthreads();
   // the keys decide between entries that differ by at most E; all others are in order
-  const double apart = STAGED && R.D > kChainFloats ? 8.4 * 1.1102230246251565e-16 * R.D * (double)top : -1.0;
+  const double apart = STAGED && !chain ? 8.4 * 1.1102230246251565e-16 * R.D * (double)top : -1.0;
   auto place = [&](int p, bool sums) {                      // false: closer to some other than its sum tells
     const uint32_t x = sorted[p];
     const uint64_t K = key[p], lo = orderable(key_value(K) - apart), hi = orderable(key_value(K) + apart);
@@ -1357,8 +1365,10 @@ __device__ void exact_row(const Rows& R, int V, int i, int kk, unsigned char* sm
 
 // One block per row: NTHR threads, EPT list words each in registers.  A row that its list does not decide takes the
 // exact path here, or (LATER) in a launch of its own.
+// (Waves a SIMD asked for: what the LDS leaves room for; with the exact path of long rows inside, 64 registers are not
+// enough, and scratch memory would cost every launch 1 us.)
 template <int NTHR, int EPT, bool STAGED, bool LATER>
-__global__ __launch_bounds__(NTHR, 8) void knn_rank_kernel(KnnArgs a, RankShape sh) {
+__global__ __launch_bounds__(NTHR, LATER || !STAGED ? 8 : 6) void knn_rank_kernel(KnnArgs a, RankShape sh) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_w[20];
   const int tid = threadIdx.x, i = blockIdx.x, kk = a.k - 1;
