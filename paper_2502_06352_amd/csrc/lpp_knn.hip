@@ -544,85 +544,98 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
 }
 
 // What both collecting kernels do with the similarities they form: a lane holds four of one row per
-// code tile, less the row's threshold (which the sums start from).  It parks them in LDS as they are (one
-// 16-byte write, nothing else leaves the registers) and shifts their sign bits into a mask, one
-// instruction each.  After a window of tiles the lanes take the clear bits of their masks and write
-// the list words.  (With one LDS write per similarity, to a ring that only moved on where a
+// code tile, less the row's threshold (which the sums start from).  It parks them in LDS as they are
+// and shifts their sign bits into a mask, one instruction each.  After a window of tiles the lanes take the clear bits
+// of their masks and write the list words.  (With one LDS write per similarity, to a ring that only moved on where a
 // similarity passed, the kernel was bound by issuing those writes.)
 __device__ __forceinline__ uint32_t shift_in_sign(uint32_t mask, int d) { return __builtin_amdgcn_alignbit(mask, (uint32_t)d, 31); }
 
-// mask: bit 31 - s set where similarity s of the window passes; tile s >> 2, parked at [tile][lane][s & 3].
-// `at`: where the lane's entries go in cand, `room` of them at most.
-template <typename Value>
-__device__ __forceinline__ void emit_window(const KnnArgs& a, uint32_t mask, const uint32_t* parked, uint32_t code0, uint32_t tile_step,
-                                            int lane, uint32_t at, int room, Value value) {
-  const uint32_t* mine = parked + lane * 4;
-  const uint32_t end = at + (uint32_t)max(room, 0), qmax = (1u << a.vmask_bits) - 2u;
+// mask: bit 31 - s set where similarity s of the window passes; word(s): its list word.  The lane's words go to cand
+// from `at` on, which is in the list (a list that overflows is not used, nor written to).
+// A word at a time: a store's lanes lie in as many places as there are lanes, which take the address unit a cycle or
+// more each, 21 us of 79 at 16384 x 8, k = 1000.  One where their number is odd, then two, then four at a time: 4 us.
+template <typename Word>
+__device__ __forceinline__ void emit_window(uint32_t* cand, uint32_t at, uint32_t mask, Word word) {
+  typedef uint32_t words2 __attribute__((ext_vector_type(2), aligned(4)));
+  typedef uint32_t words4 __attribute__((ext_vector_type(4), aligned(4)));
+  auto take = [&]() {
+    const uint32_t s = __builtin_clz(mask);
+    mask &= ~(0x80000000u >> s);
+    return word(s);
+  };
+  const int n = __popc(mask);
+  if (n & 1) cand[at++] = take();
+  if (n & 2) {
+    const uint32_t x = take(), y = take();
+    *reinterpret_cast<words2*>(cand + at) = words2{x, y};
+    at += 2;
+  }
   while (__any(mask != 0u)) {
     if (mask != 0u) {
-      const uint32_t s = __builtin_clz(mask), hi = s >> 2, lo = s & 3;
-      mask &= ~(0x80000000u >> s);
-      const uint32_t v = value(mine[hi * 256 + lo], qmax);
-      const uint32_t code = __umul24(hi, tile_step) + code0;
-      if (at < end) a.cand[at] = (v << a.ib) | code | lo;
-      ++at;
+      const uint32_t x = take(), y = take(), z = take(), w = take();
+      *reinterpret_cast<words4*>(cand + at) = words4{x, y, z, w};
+      at += 4;
     }
   }
 }
 
-// Short rows: a block owns 16 queries, its waves (as many as fill the chip) take the code tiles (16
-// codes) in turn.
+// Short rows: a block owns 16 queries, its waves (as many as fill the chip) take windows of 128 codes in turn, eight
+// MFMA tiles.  Which code a tile's row is, is free: lane (l16, g4) gets the similarities of the 32 consecutive codes from
+// 32 g4 on, so that slot s of its window is code s, parked at [s][lane] (no two lanes of a read in one bank), and an
+// entry's code, its place in LDS and its list word are an instruction or two each.  (Tiles of 16 consecutive codes: 17
+// vector instructions an entry instead of 14; 16384 x 8, k = 1000: 79 -> 77 us, 58 with what emit_window does.)
 constexpr int kCollectMaxWaves = 16;
+constexpr int kWindowCodes = 128;
 template <int N>
 __global__ __launch_bounds__(kCollectMaxWaves * 64) void knn_collect_f16_kernel(KnnArgs a) {
-  constexpr int T = 8;                                     // tiles per window: 32 similarities, 32 bits
-  extern __shared__ __align__(16) uint32_t s_park[];       // [wave][T][64 lanes][4]
+  constexpr int T = kWindowCodes / 16;                     // tiles per window: 32 similarities a lane, 32 bits
+  extern __shared__ __align__(16) uint32_t s_park[];       // [wave][32][64 lanes]
   __shared__ int s_cnt[16];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
   const int row = blockIdx.x * 16 + l16, rowc = min(row, a.V - 1);
   const RowPlan p = a.plan[row];
-  const int ntiles = (a.V + 15) >> 4;
+  const int windows = a.Vp / kWindowCodes;                 // (rows V .. Vp - 1 are there, whatever they hold)
   const float c0 = -p.thr;
   HalfOperand<N> q;
   const i32x4* const Ef = __builtin_amdgcn_readfirstlane(p.flags) & kWide ? a.Ew : a.Ef;
   q.load_query(Ef + (int64_t)rowc * 2 * N, g4);
   if (threadIdx.x < 16) s_cnt[threadIdx.x] = 0;
   __syncthreads();
-  uint32_t* const parked = s_park + wave * (T * 256);
-  const uint32_t list = (uint32_t)rowc * (uint32_t)a.cap;
-  const int step = blockDim.x >> 6;
-  // (tile numbers past the end are clamped: read again, not used; rows V .. Vp - 1 are there, whatever
-  // they hold: their codes are dropped when the list is ranked)
-  const i32x4* const lane_row = Ef + l16 * 2 * N;
-  auto load = [&](HalfOperand<N> (&f)[4], int t0) {
+  uint32_t* const parked = s_park + wave * (T * 256) + lane;
+  const uint32_t list = (uint32_t)rowc * (uint32_t)a.cap, qmax = (1u << a.vmask_bits) - 2u;
+  const int step = blockDim.x >> 6, room = row < a.V ? a.cap : 0;
+  const i32x4* const lane_row = Ef + (32 * (l16 >> 2) + (l16 & 3)) * 2 * N;
+  auto load = [&](HalfOperand<N> (&f)[4], int w, int h) {  // (past the end: the last window again, not used)
+    const i32x4* const first = lane_row + (int64_t)min(w, windows - 1) * (kWindowCodes * 2 * N);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) f[u].load_code(lane_row + (int64_t)min(t0 + step * u, ntiles - 1) * (32 * N), g4);
+    for (int u = 0; u < 4; ++u) f[u].load_code(first + (h + u) * 8 * N, g4);
   };
   HalfOperand<N> f[4];
-  load(f, wave);
-  for (int t0 = wave; t0 < ntiles; t0 += step * T) {
+  load(f, wave, 0);
+  for (int w = wave; w < windows; w += step) {
     uint32_t fail = 0;
 #pragma unroll
     for (int h = 0; h < T; h += 4) {
       f32x4 acc[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) acc[u] = f[u].times(q, f32x4{c0, c0, c0, c0});
-      load(f, t0 + step * (h + 4));
+      load(f, h + 4 < T ? w : w + step, h + 4 < T ? h + 4 : 0);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        *reinterpret_cast<f32x4*>(parked + ((h + u) * 64 + lane) * 4) = acc[u];
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) fail = shift_in_sign(fail, __float_as_int(acc[u][r]));
-      }
+        for (int r = 0; r < 4; ++r) {
+          parked[((h + u) * 4 + r) * 64] = __float_as_uint(acc[u][r]);
+          fail = shift_in_sign(fail, __float_as_int(acc[u][r]));
+        }
     }
-    // tiles past the end: their bits are the last ones
-    uint32_t mask = ~fail;
-    if (t0 + step * (T - 1) >= ntiles) mask &= ~(0xFFFFFFFFu >> (4 * ((ntiles - t0 + step - 1) / step)));      // uniform
+    const int code0 = w * kWindowCodes + 32 * g4;
+    uint32_t mask = ~fail;                                 // (codes past the end are not there)
+    if (w == windows - 1) mask &= code0 + 32 <= a.V ? 0xFFFFFFFFu : (code0 < a.V ? ~(0xFFFFFFFFu >> (a.V - code0)) : 0u);
     const int n = __popc(mask);
     const int base = n > 0 ? atomicAdd(&s_cnt[l16], n) : 0;
-    emit_window(a, mask, parked, (uint32_t)(t0 * 16 + 4 * g4), (uint32_t)(16 * step), lane, list + base,
-                row < a.V ? a.cap - base : 0, [&](uint32_t v, uint32_t qmax) { return list_value(__uint_as_float(v), p.a, qmax); });
+    emit_window(a.cand, list + (uint32_t)base, base + n > room ? 0u : mask,
+                [&](uint32_t s) { return (list_value(__uint_as_float(parked[s * 64]), p.a, qmax) << a.ib) | (code0 + s); });
   }
   __syncthreads();
   if (threadIdx.x < 16 && blockIdx.x * 16 + threadIdx.x < a.V) a.cnt[blockIdx.x * 16 + threadIdx.x] = s_cnt[threadIdx.x];
@@ -726,7 +739,8 @@ __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(K
   // the window that ends with the block's tile number i - 1
   auto emit = [&](int i) {
     const int i0 = (i - 1) / T * T, have = i - i0;
-    const uint32_t code0 = (uint32_t)((split + i0 * a.splits) * 16 + 4 * g4);
+    const uint32_t code0 = (uint32_t)((split + i0 * a.splits) * 16 + 4 * g4), tile_step = (uint32_t)(16 * a.splits);
+    const uint32_t qmax = (1u << a.vmask_bits) - 2u;
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
       // the four lanes of a row put their entries one after the other
@@ -734,9 +748,11 @@ __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(K
       const int cnt = __popc(m);
       const int c1 = __shfl(cnt, l16), c2 = __shfl(cnt, l16 + 16), c3 = __shfl(cnt, l16 + 32), c4 = __shfl(cnt, l16 + 48);
       const int base = out[n] + (g4 > 0 ? c1 : 0) + (g4 > 1 ? c2 : 0) + (g4 > 2 ? c3 : 0);
-      emit_window(a, m, reinterpret_cast<const uint32_t*>(s_park[wave][n]), code0, (uint32_t)(16 * a.splits), lane, list[n] + base,
-                  (qtile + n) * 16 + l16 < a.V ? a.cap_split - base : 0,
-                  [&](uint32_t v, uint32_t qmax) { return list_value((float)(int)v, scale[n], qmax); });
+      const int* const mine = reinterpret_cast<const int*>(s_park[wave][n] + lane);
+      emit_window(a.cand, list[n] + (uint32_t)base, (qtile + n) * 16 + l16 < a.V && base + cnt <= a.cap_split ? m : 0u, [&](uint32_t s) {
+        const uint32_t hi = s >> 2, lo = s & 3;
+        return (list_value((float)mine[hi * 256 + lo], scale[n], qmax) << a.ib) | (__umul24(hi, tile_step) + code0) | lo;
+      });
       out[n] += c1 + c2 + c3 + c4;
       fail[n] = 0;
     }
@@ -1366,9 +1382,10 @@ __device__ void exact_row(const Rows& R, int V, int i, int kk, unsigned char* sm
 // One block per row: NTHR threads, EPT list words each in registers.  A row that its list does not decide takes the
 // exact path here, or (LATER) in a launch of its own.
 // (Waves a SIMD asked for: what the LDS leaves room for; with the exact path of long rows inside, 64 registers are not
-// enough, and scratch memory would cost every launch 1 us.)
+// enough, and scratch memory would cost every launch 1 us: blocks of 16 waves gain more by running in pairs, 5000 x 96,
+// k = 2500: 314 -> 230 us.)
 template <int NTHR, int EPT, bool STAGED, bool LATER>
-__global__ __launch_bounds__(NTHR, LATER || !STAGED ? 8 : 6) void knn_rank_kernel(KnnArgs a, RankShape sh) {
+__global__ __launch_bounds__(NTHR, LATER || !STAGED || NTHR == 1024 ? 8 : 6) void knn_rank_kernel(KnnArgs a, RankShape sh) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_w[20];
   const int tid = threadIdx.x, i = blockIdx.x, kk = a.k - 1;
