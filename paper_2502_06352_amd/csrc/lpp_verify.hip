@@ -33,8 +33,8 @@
 //        neighbours that would break the bound instead of stopping at the first one (wave 0 walks
 //        the gathered values 64 at a time), and siblings that are distinct draws (a rejected token
 //        leaves p, which is rescaled by 1 / (1 - p(x^))).
-// STAG   the build for a grid that is resident at once (one row per compute unit): rows hold
-//        their logit loads back by chain length, and the walk is done by a wave of the longest
+// STAG   the builds for a grid that is resident at once (one row per compute unit): rows hold
+//        their logit loads back by chain length (not with FRONT), and the walk is done by a wave of the longest
 //        row's block beside that row's draw (collect_and_walk).
 // The additive bound of the earlier LANTERN method is a run-time choice of the cap.
 #include <limits.h>
@@ -1259,25 +1259,27 @@ int32_t relaxed_verify_impl(int32_t additive, int32_t skip, int32_t norepl, bool
   TreeTab tt;
   static_assert(sizeof(tt.rowinfo) == sizeof(tree->rowinfo), "the handle holds the kernel's row table");
   memcpy(tt.rowinfo, tree->rowinfo, sizeof(tt.rowinfo));
-  // Whole grid resident at once (one block per compute unit, the plain step only): rows hold their
-  // loads back by chain length and the walk needs no tickets (see the kernel).  With more blocks
-  // than compute units the launch order, most children first, already staggers the rows; with a
-  // front end every row has a long stretch of its own before its chain, which waits would only
-  // push back.
+  // Whole grid resident at once (one block per compute unit): rows hold their loads back by chain length and the walk
+  // needs no tickets (see the kernel).  With more blocks than compute units the launch order, most children first,
+  // already staggers the rows; with a front end every row has a long stretch of its own before its chain, which waits
+  // would only push back: no waits, but the walk all the same.  With tickets -> so: distinct siblings, 4 items, 61 rows of
+  // 16384: 22.8 -> 20.7 us, skip rule 38.8 -> 35.5; guidance and top-k, 1 item, 61 rows of 8192: 21.4 -> 20.7.
   a.n_parents = tree->n_parents;
   a.wait_parent = a.wait_leaf = 0;
   // (The walk by a resident block assumes that all B * M blocks of the launch are on the device at
   // once: one block per compute unit, the device not shared with other work meanwhile.  If that
   // does not hold the walk may give up, which lpp_tree_walk_status reports.)
-  const bool stag = (int64_t)B * tree->M <= std::min<int32_t>(tree->n_cu, LPP_MAX_ROWS) && !front && !alt && tree->d_mail != nullptr;
+  const bool stag = (int64_t)B * tree->M <= std::min<int32_t>(tree->n_cu, LPP_MAX_ROWS) && tree->d_mail != nullptr;
   if (stag) {
     // Tuned on MI355X (256 compute units): a row waits for 0.8 of the time the memory system needs,
     // at kStaggerBytesPerSecond, for the bytes asked for ahead of it (measured best: 0.7 .. 0.9).
     constexpr double kStagger = 0.8, kStaggerBytesPerSecond = 5.0e12;
     // one logit row of every item, in 1/256 of the kernel's sleep unit (1024 clocks)
     const double ticks_per_row = (double)B * V * 4.0 / kStaggerBytesPerSecond * (tree->clock_khz * 1.0e3) / 1024.0 * 256.0 * kStagger;
-    a.wait_parent = (int32_t)(2.0 * ticks_per_row);
-    a.wait_leaf = (int32_t)ticks_per_row;
+    if (!front) {
+      a.wait_parent = (int32_t)(2.0 * ticks_per_row);
+      a.wait_leaf = (int32_t)ticks_per_row;
+    }
     // the other rows' words reach the walking block through the tree's mail words, not the workspace
     a.ws_decision = tree->d_mail;
     a.ws_final = tree->d_mail + LPP_MAX_ROWS;
@@ -1293,14 +1295,14 @@ int32_t relaxed_verify_impl(int32_t additive, int32_t skip, int32_t norepl, bool
   };
   const bool al = aligned16(target_logits) && aligned16(drafter_logits) && aligned16(uncond_logits);
   int32_t st;
-#define LPP_DISPATCH2(T, N, ALT)                                                                            \
-  st = front ? (al ? launch_rows<T, N, true, true, ALT, false>(a, tt, s) : launch_rows<T, N, false, true, ALT, false>(a, tt, s))   \
-             : (al ? launch_rows<T, N, true, false, ALT, false>(a, tt, s) : launch_rows<T, N, false, false, ALT, false>(a, tt, s))
-#define LPP_DISPATCH(T, N)                                     \
-  do {                                                         \
-    if (stag) {                                                \
-      st = al ? launch_rows<T, N, true, false, false, true>(a, tt, s) : launch_rows<T, N, false, false, false, true>(a, tt, s); \
-    } else if (alt) { LPP_DISPATCH2(T, N, true); } else { LPP_DISPATCH2(T, N, false); } \
+#define LPP_DISPATCH3(T, N, FRONT, ALT, STAG) \
+  st = al ? launch_rows<T, N, true, FRONT, ALT, STAG>(a, tt, s) : launch_rows<T, N, false, FRONT, ALT, STAG>(a, tt, s)
+#define LPP_DISPATCH2(T, N, FRONT, ALT) \
+  do { if (stag) { LPP_DISPATCH3(T, N, FRONT, ALT, true); } else { LPP_DISPATCH3(T, N, FRONT, ALT, false); } } while (0)
+#define LPP_DISPATCH(T, N)                                                                                      \
+  do {                                                                                                          \
+    if (front) { if (alt) LPP_DISPATCH2(T, N, true, true); else LPP_DISPATCH2(T, N, true, false); }             \
+    else { if (alt) LPP_DISPATCH2(T, N, false, true); else LPP_DISPATCH2(T, N, false, false); }                 \
   } while (0)
   if (V <= 2048) LPP_DISPATCH(512, 1);
   else if (V <= 4096) LPP_DISPATCH(512, 2);
@@ -1309,6 +1311,7 @@ int32_t relaxed_verify_impl(int32_t additive, int32_t skip, int32_t norepl, bool
   else LPP_DISPATCH(1024, 8);
 #undef LPP_DISPATCH
 #undef LPP_DISPATCH2
+#undef LPP_DISPATCH3
   if (st != LPP_OK) return st;
   if (!fused_walk) {
     hipLaunchKernelGGL(walk_kernel, dim3((unsigned)B), dim3(64), 0, s, a);

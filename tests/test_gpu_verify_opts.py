@@ -134,3 +134,38 @@ def test_opts_everything_at_once_front_end_skip_rule_distinct_siblings(additive,
                          rule="skip", siblings="without_replacement")
     print(f"front end + skip + distinct, additive={additive}: {rep}", flush=True)
     assert rep["nodes"] > 0 and rep["near_tie_decisions"] <= 2
+
+
+@pytest.mark.parametrize("idx", [1, 3])
+def test_opts_builds_take_turns_on_one_handle(idx):
+    # with every row's block resident the walk goes through the handle's words whatever the options: the builds in
+    # turn on one handle, with other inputs each, give what each gives on a handle of its own; a walk that gives up
+    # says so and harms no later call of another build
+    cfg = CONFIGS[idx]
+    parent = static_tree(cfg.branching, cfg.N)
+    E = make_codebook(cfg)
+    skip, distinct, front = dict(rule=lpp.LPP_RULE_SKIP), dict(siblings=lpp.LPP_SIBLINGS_DISTINCT), dict(top_k=cfg.V // 8)
+    builds = [None, skip, distinct, front, dict(**front, **distinct), dict(**front, **skip, **distinct)]
+    xs = [make_verify_inputs(cfg, parent, rho=0.8, salt=s) for s in range(len(builds))]
+    neigh = sparse_neighbour_table(E, cfg.k, np.concatenate([x["tokens"][:, 1:].ravel() for x in xs]), cfg.V)
+
+    def call(tree, i):
+        return run_verify(tree, xs[i], neigh, cfg.V, cfg.vocab_offset, cfg.ldv, cfg.k, cfg.lam, opts=builds[i])
+
+    want = [call(lpp.Tree(parent), i) for i in range(len(builds))]
+    tree = lpp.Tree(parent)
+    for i in (0, 1, 2, 3, 4, 5, 3, 1, 0, 5, 2):
+        got = call(tree, i)
+        for n in got:
+            assert np.array_equal(got[n], want[i][n], equal_nan=True), (i, n)
+    for i in range(len(builds)):
+        tree.set_walk_patience(-1)
+        got = call(tree, i)
+        assert np.all(got["accept_len"] == -1) and np.all(got["final_token"] == -1) and np.all(got["path"] == -1), i
+        assert np.array_equal(got["decision"], want[i]["decision"])
+        tree.set_walk_patience(1 << 19)
+        j = (i + 2) % len(builds)
+        got = call(tree, j)
+        for n in got:
+            assert np.array_equal(got[n], want[j][n], equal_nan=True), (i, j, n)
+    assert tree.walk_gave_up() == len(builds) * cfg.B
