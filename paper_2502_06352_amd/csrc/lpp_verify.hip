@@ -350,10 +350,13 @@ __device__ __forceinline__ int hist_slot(int b) {
   return (r << 6) + (((b >> 5) + r) & 63);
 }
 
-// The bin of the top-k front end's histogram (its first nb bins) that holds the need-th key from the top, the keys
+// The bin of the top-k front end's histogram that holds the need-th key from the top, the keys
 // above it and its own; every wave finds it for itself.  Lane l counts bins 2047 - 32 l and the 31 below, a scan over the
 // lanes finds the group, and the group's bins, a lane each, the bin.  (Scans through LDS permutes and the group's bins one
 // after the other in one lane: 21.1 -> 19.1 us a call at 61 rows of 8192, top-k 2000.)
+// Every lane reads, of 2048 bins that are all there: where the lanes parted for the read, the builds for V > 16384,
+// which spill, had registers of lanes 32 .. 63 left out of their spills (the compiler put the stores ahead of the
+// instruction that brings the lanes back).
 __device__ __forceinline__ int wave_inclusive_scan_int(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
   v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
@@ -363,19 +366,16 @@ __device__ __forceinline__ int wave_inclusive_scan_int(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
   return v;
 }
-__device__ __forceinline__ void find_bin(const uint32_t* hist, int nb, int need, int lane, int& bin, int& above, int& inbin) {
+__device__ __forceinline__ void find_bin(const uint32_t* hist, int need, int lane, int& bin, int& above, int& inbin) {
   int local = 0;
 #pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    const int b = 2047 - 32 * lane - i;
-    local += b < nb ? (int)hist[hist_slot(b)] : 0;
-  }
+  for (int i = 0; i < 32; ++i) local += (int)hist[hist_slot(2047 - 32 * lane - i)];
   const int incl = wave_inclusive_scan_int(local);
   const unsigned long long groups = __ballot(incl >= need);
   const int g = __builtin_amdgcn_readfirstlane(groups ? __ffsll((long long)groups) - 1 : 63);
-  const int before = __builtin_amdgcn_readlane(incl - local, g), b = 2047 - 32 * g - (lane & 31);
-  const int mine = lane < 32 && b < nb ? (int)hist[hist_slot(b)] : 0;
-  const int run = before + wave_inclusive_scan_int(mine);
+  const int before = __builtin_amdgcn_readlane(incl - local, g);
+  const int mine = (int)hist[hist_slot(2047 - 32 * g - (lane & 31))];
+  const int run = before + wave_inclusive_scan_int(mine);     // (lanes 0 .. 31 count; the others go over the bins again)
   const unsigned long long bins = __ballot(run >= need) & 0xFFFFFFFFull;
   const int l = __builtin_amdgcn_readfirstlane(bins ? __ffsll((long long)bins) - 1 : 31);
   bin = max(2047 - 32 * g - l, 0);
@@ -619,7 +619,7 @@ __global__ __launch_bounds__(NT, (STAG || ALT || FRONT || NT > 512) ? 1 : 4) voi
         }
         lds_barrier();
         int bstar, above, inbin;
-        find_bin(hist, 2048, a.top_k, lane, bstar, above, inbin);
+        find_bin(hist, a.top_k, lane, bstar, above, inbin);
         const int need = a.top_k - above;                        // rank inside bin bstar, from the top
         if (inbin <= kCand) {                                    // uniform
 #pragma unroll
@@ -659,7 +659,7 @@ __global__ __launch_bounds__(NT, (STAG || ALT || FRONT || NT > 512) ? 1 : 4) voi
             }
           lds_barrier();
           int found, above, inbin;
-          find_bin(hist, nb, need, lane, found, above, inbin);
+          find_bin(hist, need, lane, found, above, inbin);      // (bins from nb on are empty)
           prefix |= (uint32_t)found << shift;
           need -= above;
           lds_barrier();            // the histogram is cleared again (or handed over to r) after this

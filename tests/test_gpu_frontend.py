@@ -76,6 +76,16 @@ def test_sampled_verify_switches():
     assert rep["nodes"] > 0
 
 
+@pytest.mark.parametrize("B", [1, 5])                     # every row's block resident at once, and not
+@pytest.mark.parametrize("V,off", [(20000, 0), (32768, 0), (20001, 3)])
+def test_sampled_verify_widest_rows(V, off, B):
+    # these builds keep registers in scratch memory (V = 20000, 4 items: one drafted token's A of the 240 was wrong)
+    cfg = CONFIGS[3].scaled(V=V, ldv=V + off, vocab_offset=off, B=B, k=300)
+    for guide in (False, True):
+        rep, got = _run(cfg, 3.0, 2000, guide=guide)
+        assert rep["nodes"] > 0 and rep["near_tie_decisions"] <= 2 and rep["nagg_ties"] <= 2
+
+
 def test_sampled_verify_argument_errors():
     cfg = CONFIGS[1]
     parent = static_tree(cfg.branching, cfg.N)
