@@ -70,9 +70,11 @@ int32_t lpp_tree_info(const lpp_tree* tree, int32_t* M, int32_t* depth,
 
 /* The walk of lpp_relaxed_verify, in all its forms, when all B * M row blocks of a launch fit the device at once
  * (one per compute unit) is done by one of the item's row blocks, which waits, with a bound, for the other
- * rows' results (see lpp_relaxed_verify).  That presumes the launch's blocks are all resident
+ * rows' results (see lpp_relaxed_verify).  That goes best while the launch's blocks are all resident
  * together: the stream's kernel has the device to itself (no compute-unit mask, no long kernel of
- * another stream or process in the way).  If the wait ever runs out, the item's accept_len, path and
+ * another stream or process in the way).  If the wait ever runs out, a call with a front end, the skip rule or
+ * distinct siblings hands the walk to the row that finishes last: its results are the same.  The other calls
+ * presume that the blocks are resident: the item's accept_len, path and
  * final_token are -1 for that call, and for that call only: the rows' results carry the number of
  * their call, so whatever arrives late is not taken for a later call's.  A caller checks
  * accept_len[b] < 0 (lpp_commit_kv commits nothing but the root for such an item) or asks:
@@ -82,7 +84,8 @@ int32_t lpp_tree_info(const lpp_tree* tree, int32_t* M, int32_t* depth,
  *   lpp_tree_walk_reset    enqueues on `stream` the kernel that sets that count (and the handle's other
  *                          walk words) back to zero; never needed for correctness.
  *   lpp_tree_set_walk_patience   rounds (about 0.5 us each) the walking block waits: default and maximum
- *                          2^19; -1 makes the walk give up at once (for tests of the caller's handling).
+ *                          2^19 (calls that hand the walk over: 2^8); -1 makes the walk give up at once (for
+ *                          tests of the caller's handling).
  * Errors: LPP_EINVAL (null, rounds < -1), LPP_EHIP (host-only handle, copy or launch failed).
  */
 int32_t lpp_tree_walk_status(const lpp_tree* tree, int32_t* gave_up);
@@ -218,7 +221,8 @@ int32_t lpp_tree_attention_layers(const lpp_tree* tree, int32_t dtype, int32_t o
  * its row blocks, which waits for the others' results; that wait is bounded, and nobody waits
  * for that block.  Should it ever run out (it cannot unless the other blocks of the launch do
  * not run), accept_len[b], path[b, :] and final_token[b] of that call are set to -1 (later calls
- * are not affected); lpp_tree_walk_status counts such walks.
+ * are not affected); lpp_tree_walk_status counts such walks.  (lpp_relaxed_verify_sampled and
+ * _opts with a front end, the skip rule or distinct siblings: never; there the walk is handed over.)
  */
 typedef struct lpp_verify_out {
   int32_t* accept_len;     /* [device] [B]        number of accepted drafted nodes            */

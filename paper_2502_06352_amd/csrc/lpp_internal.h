@@ -36,11 +36,12 @@ struct lpp_tree {
   int32_t* d_counters = nullptr;   // [2 * LPP_COUNTER_SLOTS]: verify, then attention
   // verify with the whole grid resident: words the rows leave for the block that walks
   // ([LPP_MAX_ROWS] decisions, [LPP_MAX_ROWS] draws, each tagged with its call; then the number
-  // of walks that gave up)
+  // of walks that gave up; then, per item, the call whose walk was handed over)
   int32_t* d_mail = nullptr;       // [kMailWords], zero when the handle is made
 };
 constexpr int kMailGaveUp = 2 * LPP_MAX_ROWS;
-constexpr int kMailWords = 2 * LPP_MAX_ROWS + 1;
+constexpr int kMailHanded = kMailGaveUp + 1;
+constexpr int kMailWords = kMailHanded + LPP_MAX_ROWS;
 
 #define LPP_COUNTER_SLOTS 4096
 

@@ -254,7 +254,8 @@ __device__ __forceinline__ void walk_wave(const int32_t* word, const int32_t* fi
 // in `mail` (device-scope stores), this wave asks for them until none is missing and walks as
 // above.  Nobody waits for this block, so the wait ends as soon as the other blocks have run; it
 // is bounded all the same (`spin_limit` rounds of loads): when the bound is hit the item's
-// accept_len, path and final token are set to -1 and the count in mail[kMailGaveUp] goes up.
+// accept_len, path and final token are set to -1 and the count in mail[kMailGaveUp] goes up (HAND: the
+// walk is handed over to the other rows instead, see walk_if_complete).  False: the bound was hit.
 //
 // Words carry a tag in their upper bits (kMailTagShift) that changes from call to call, so a
 // word that arrives after its call's walk gave up is not taken for the next call's, and nothing
@@ -285,7 +286,8 @@ __device__ __forceinline__ void mail_fetch(MailRound& r, const int32_t* mail, in
     r.f[q] = __hip_atomic_load(&mail[LPP_MAX_ROWS + nodebase + ic], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
-__device__ __forceinline__ void collect_and_walk(MailRound r, int32_t* mail, uint32_t tagw, int64_t nodebase, int M,
+template <bool HAND>
+__device__ __forceinline__ bool collect_and_walk(MailRound r, int32_t* mail, uint32_t tagw, int64_t nodebase, int M,
                                                  int depth, int P, int spin_limit, int lane, const int* s_own,
                                                  int* s_next, int* s_fin, int* s_end, int32_t* accept_len,
                                                  int32_t* path, int32_t* final_token) {
@@ -316,13 +318,15 @@ __device__ __forceinline__ void collect_and_walk(MailRound r, int32_t* mail, uin
   }
   if (!ok) {
     if (lane == 0) {
-      __hip_atomic_fetch_add(&mail[kMailGaveUp], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      for (int i = 0; i < depth; ++i) path[i] = -1;
-      *accept_len = -1;
-      *final_token = -1;
       *s_end = -1;
+      if (!HAND) {
+        __hip_atomic_fetch_add(&mail[kMailGaveUp], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int i = 0; i < depth; ++i) path[i] = -1;
+        *accept_len = -1;
+        *final_token = -1;
+      }
     }
-    return;
+    return false;
   }
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
@@ -338,6 +342,52 @@ __device__ __forceinline__ void collect_and_walk(MailRound r, int32_t* mail, uin
     if (cur != P) *final_token = s_fin[cur];      // (ended on this block's own row: its draw is with wave 0)
     *s_end = cur;
   }
+  return true;
+}
+
+// The wave's device-scope stores so far have completed: every compute unit sees them.
+__device__ __forceinline__ void stores_done() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// A walk handed over: the block that was to walk has left its own words in the mail too and then this call's tag in
+// the item's kMailHanded word.  It and every row that sees the tag there, its own words completed before it looked,
+// comes here; a row that looked too early is seen by the others.  So whoever completes its words last finds all of
+// them (others may as well), and of those who do one changes the word and walks.  (A word changed 1023 calls ago
+// holds the same tag, but is not taken for a fresh one.)
+__device__ __forceinline__ void walk_if_complete(int32_t* mail, int item, uint32_t tagw, int64_t nodebase, int M, int depth,
+                                                 int lane, int* s_next, int* s_fin, int32_t* accept_len, int32_t* path,
+                                                 int32_t* final_token) {
+  constexpr int Q = LPP_MAX_ROWS / 64;
+  MailRound r;
+  mail_fetch(r, mail, nodebase, M, lane);
+  bool missing = false;
+  int wd[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = lane + 64 * q;
+    missing = missing || (i < M && ((uint32_t)r.f[q] & ~kMailPayload) != tagw) ||
+              (i >= 1 && i < M && ((uint32_t)r.w[q] & ~kMailPayload) != tagw);
+    wd[q] = i >= 1 && i < M ? (int)((uint32_t)r.w[q] & kMailPayload) : 0;
+  }
+  if (__ballot(missing)) return;
+  int mine = 0;
+  if (lane == 0)
+    mine = __hip_atomic_exchange(&mail[kMailHanded + item], (int)(tagw | 1u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)tagw;
+  if (!__builtin_amdgcn_readfirstlane(mine)) return;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = lane + 64 * q;
+    if (i < M) {
+      s_fin[i] = (int)((uint32_t)r.f[q] & kMailPayload);
+      s_next[i] = INT_MAX;
+    }
+  }
+  wave_lds_sync();
+  const int cur = follow_accepted(wd, M, depth, lane, s_next, accept_len, path);
+  if (lane == 0) *final_token = s_fin[cur];
 }
 
 // Where bin b of the top-k front end's 2048-bin histogram is kept in LDS.  The search reads it with
@@ -430,6 +480,7 @@ __global__ __launch_bounds__(NT, (STAG || ALT || FRONT || NT > 512) ? 1 : 4) voi
   constexpr int PASS = 2 * NT;             // neighbour slots per pass
   constexpr int MAXP = (LPP_MAX_K + PASS - 1) / PASS;
   constexpr int ZC = NT * NCH * 4;         // index of a cell of r_lds that always holds 0
+  constexpr bool HAND = STAG && (FRONT || ALT);   // a walk that gives up is handed over to the other rows
   extern __shared__ __align__(16) unsigned char smem[];
   float* r_lds = reinterpret_cast<float*>(smem);                              // current r, then the zero cell
   uint32_t* s_neigh = reinterpret_cast<uint32_t*>(r_lds + ZC + 4);            // [nstage][NT] pairs of 16-bit slots
@@ -1031,9 +1082,7 @@ __global__ __launch_bounds__(NT, (STAG || ALT || FRONT || NT > 512) ? 1 : 4) voi
     // the row's ticket, which it does after the barrier below
     tagw = STAG ? next_tag(last_word) : 0u;
     write_children(64 * w, min(nchild - 64 * w, 64));
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    stores_done();
   }
   if (STAG && walker && tid < nchild) {
     // the walking block's own children: their words go to the wave that walks through LDS
@@ -1044,12 +1093,13 @@ __global__ __launch_bounds__(NT, (STAG || ALT || FRONT || NT > 512) ? 1 : 4) voi
   if (w != 0) {
     if (!(STAG && walker)) return;
     tagw = STAG ? next_tag(last_word) : 0u;
+    bool walked = true;
     if (w == 1)
-      collect_and_walk(mail_first, a.ws_decision, tagw, nodebase, a.M, a.depth, P, a.spin_limit, lane, s_mail,
+      walked = collect_and_walk<HAND>(mail_first, a.ws_decision, tagw, nodebase, a.M, a.depth, P, a.spin_limit, lane, s_mail,
                        s_mail + LPP_MAX_ROWS, s_mail + 2 * LPP_MAX_ROWS, s_mail + 3 * LPP_MAX_ROWS, a.accept_len + b,
                        a.path + (int64_t)b * a.depth, a.final_token + b);
     // (the walking block's own word is read by nobody but itself, next call: it keeps the tags in step)
-    if (w == 1 && lane == 0) a.ws_final[nodebase + P] = (int)tagw;
+    if (w == 1 && lane == 0 && !(HAND && !walked)) a.ws_final[nodebase + P] = (int)tagw;
     lds_barrier();           // (met by wave 0 once it holds the draw)
     return;
   }
@@ -1132,17 +1182,36 @@ __global__ __launch_bounds__(NT, (STAG || ALT || FRONT || NT > 512) ? 1 : 4) voi
     if (!STAG && a.counters) {
       // every store of this row's decisions and draw was issued by this wave: once they have
       // completed they are visible device-wide, and only then the ticket is taken
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      stores_done();
       ticket = __hip_atomic_fetch_add(&a.counters[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
   if (STAG) {
+    int end = 0;
     if (walker) {
       lds_barrier();         // the walk is done
-      if (lane == 0 && s_mail[3 * LPP_MAX_ROWS] == P) a.final_token[b] = x;
+      end = __builtin_amdgcn_readfirstlane(s_mail[3 * LPP_MAX_ROWS]);
+      if (lane == 0 && end == P) a.final_token[b] = x;
     }
+    if (!HAND || (walker && end >= 0)) return;
+    if (walker) {            // the walk gave up: hand it over
+      for (int i = lane; i < a.M; i += 64)
+        if (s_mail[i] != -1)
+          __hip_atomic_store(&a.ws_decision[nodebase + i], (int)(tagw | (uint32_t)s_mail[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (lane == 0)
+        __hip_atomic_store(&a.ws_final[nodebase + P], (int)(tagw | (uint32_t)x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      stores_done();
+      if (lane == 0)
+        __hip_atomic_store(&a.ws_decision[kMailHanded + b], (int)tagw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      stores_done();
+    } else {
+      stores_done();
+      const int word = __hip_atomic_load(&a.ws_decision[kMailHanded + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__builtin_amdgcn_readfirstlane(word) != (int)tagw) return;
+    }
+    int* s_walk = reinterpret_cast<int*>(smem);     // r is dead
+    walk_if_complete(a.ws_decision, b, tagw, nodebase, a.M, a.depth, lane, s_walk, s_walk + a.M, a.accept_len + b,
+                     a.path + (int64_t)b * a.depth, a.final_token + b);
     return;
   }
   if (!a.counters) return;
@@ -1268,8 +1337,10 @@ int32_t relaxed_verify_impl(int32_t additive, int32_t skip, int32_t norepl, bool
     a.ws_final = tree->d_mail + LPP_MAX_ROWS;
     a.counters = nullptr;
     fused_walk = true;
-    // about 0.5 us a round: a quarter of a second before the walk gives up (see collect_and_walk)
-    a.spin_limit = tree->walk_patience;
+    // about 0.5 us a round: a quarter of a second before the walk gives up (see collect_and_walk), and no longer than
+    // the slowest rows take (45 us at V = 16384) where it is only handed over
+    constexpr int32_t kHandOverRounds = 256;
+    a.spin_limit = front || alt ? std::min(tree->walk_patience, kHandOverRounds) : tree->walk_patience;
   }
 
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);

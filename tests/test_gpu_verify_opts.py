@@ -140,7 +140,8 @@ def test_opts_everything_at_once_front_end_skip_rule_distinct_siblings(additive,
 def test_opts_builds_take_turns_on_one_handle(idx):
     # with every row's block resident the walk goes through the handle's words whatever the options: the builds in
     # turn on one handle, with other inputs each, give what each gives on a handle of its own; a walk that gives up
-    # says so and harms no later call of another build
+    # says so (the plain step) or is handed over to another row (calls with options, whose walks never end without a
+    # result), and harms no later call of another build
     cfg = CONFIGS[idx]
     parent = static_tree(cfg.branching, cfg.N)
     E = make_codebook(cfg)
@@ -161,11 +162,43 @@ def test_opts_builds_take_turns_on_one_handle(idx):
     for i in range(len(builds)):
         tree.set_walk_patience(-1)
         got = call(tree, i)
-        assert np.all(got["accept_len"] == -1) and np.all(got["final_token"] == -1) and np.all(got["path"] == -1), i
-        assert np.array_equal(got["decision"], want[i]["decision"])
+        if builds[i] is None:
+            assert np.all(got["accept_len"] == -1) and np.all(got["final_token"] == -1) and np.all(got["path"] == -1)
+            assert np.array_equal(got["decision"], want[i]["decision"])
+        else:
+            for n in got:
+                assert np.array_equal(got[n], want[i][n], equal_nan=True), (i, n)
         tree.set_walk_patience(1 << 19)
         j = (i + 2) % len(builds)
         got = call(tree, j)
         for n in got:
             assert np.array_equal(got[n], want[j][n], equal_nan=True), (i, j, n)
-    assert tree.walk_gave_up() == len(builds) * cfg.B
+    assert tree.walk_gave_up() == cfg.B
+
+
+# (wide: a root with more than 64 children, whose words several waves write; alone: no row but the root)
+@pytest.mark.parametrize("shape", ["B1", "B4", "wide", "alone"])
+@pytest.mark.parametrize("opts", [dict(siblings=lpp.LPP_SIBLINGS_DISTINCT), dict(top_k=300),
+                                  dict(rule=lpp.LPP_RULE_SKIP, siblings=lpp.LPP_SIBLINGS_DISTINCT, top_k=300)])
+def test_opts_a_walk_that_gives_up_is_handed_over(shape, opts):
+    # however early the walking block gives up (at once, after a few rounds, while the last rows finish), call after
+    # call on one handle, with the full wait in between: every output as without
+    cfg = CONFIGS[1].scaled(V=2000, ldv=2000, k=50) if shape in ("wide", "alone") else CONFIGS[3].scaled(B=int(shape[1]))
+    parent = {"wide": np.array([-1] + [0] * 100 + list(range(1, 101)), dtype=np.int32), "alone": np.array([-1], dtype=np.int32)}.get(
+        shape, static_tree(cfg.branching, cfg.N))
+    cfg = cfg.scaled(N=len(parent) - 1)
+    x = make_verify_inputs(cfg, parent, rho=0.8)
+    neigh = sparse_neighbour_table(make_codebook(cfg), cfg.k, x["tokens"].ravel(), cfg.V)
+    tree = lpp.Tree(parent)
+
+    def call():
+        return run_verify(tree, x, neigh, cfg.V, cfg.vocab_offset, cfg.ldv, cfg.k, cfg.lam, opts=opts)
+
+    want = call()
+    assert np.all(want["accept_len"] >= 0)
+    for rounds in (-1, 0, 1, 2, 4, 8, 12, 16, 20, 24, 28, 32, -1, 1 << 19, -1, 3, 1 << 19):
+        tree.set_walk_patience(rounds)
+        got = call()
+        for n in got:
+            assert np.array_equal(got[n], want[n], equal_nan=True), (rounds, n)
+    assert tree.walk_gave_up() == 0
