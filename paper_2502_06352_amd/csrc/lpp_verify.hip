@@ -436,7 +436,8 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, int need, int lan
 // Sum (max), in wave order, of one float per wave held in LDS; every wave
 // computes the same value the same way.
 // WIDE: two broadcast reads and seven additions, a shorter chain than the row shifts (for the
-// build that has eight registers to spare).
+// build that has eight registers to spare, of the plain step: calls with options add in one order whatever their
+// batch, so that an item's bits do not depend on it).
 template <int NW, bool WIDE = false>
 __device__ __forceinline__ float combine_sum(const float* s_w, int lane) {
   if (WIDE && NW == 8) {
@@ -1003,7 +1004,7 @@ __global__ __launch_bounds__(NT, (STAG || ALT || FRONT || NT > 512) ? 1 : 4) voi
     z = wave_sum(z);
     if (lane == 0) s_z[ci & 1][w] = z;
     lds_barrier();
-    z = combine_sum<NW, STAG>(s_z[ci & 1], lane);
+    z = combine_sum<NW, STAG && !HAND>(s_z[ci & 1], lane);
     rt_nx = r_lds[t_nx];
     v0_nx = r_lds[pk_nx & 0xFFFFu];
     v1_nx = r_lds[pk_nx >> 16];

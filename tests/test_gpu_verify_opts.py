@@ -202,3 +202,18 @@ def test_opts_a_walk_that_gives_up_is_handed_over(shape, opts):
         for n in got:
             assert np.array_equal(got[n], want[n], equal_nan=True), (rounds, n)
     assert tree.walk_gave_up() == 0
+
+
+@pytest.mark.parametrize("opts", [dict(siblings=lpp.LPP_SIBLINGS_DISTINCT), dict(rule=lpp.LPP_RULE_SKIP), dict(top_k=2000),
+                                  dict(rule=lpp.LPP_RULE_SKIP, siblings=lpp.LPP_SIBLINGS_DISTINCT, top_k=2000)])
+@pytest.mark.parametrize("V,off", [(16384, 0), (5003, 3), (20000, 0)])
+def test_opts_an_item_does_not_depend_on_its_batch(V, off, opts):
+    # 4 items of 61 rows are resident at once, 5 are not: another build, the same bits
+    cfg = CONFIGS[3].scaled(B=5, V=V, vocab_offset=off, ldv=V + off, k=700)
+    parent = static_tree(cfg.branching, cfg.N)
+    x = make_verify_inputs(cfg, parent, rho=0.8)
+    neigh = sparse_neighbour_table(make_codebook(cfg), cfg.k, x["tokens"][:, 1:], V)
+    tree = lpp.Tree(parent)
+    five, four = [run_verify(tree, {n: t[:B] for n, t in x.items()}, neigh, V, off, cfg.ldv, cfg.k, cfg.lam, opts=opts) for B in (5, 4)]
+    for n in four:
+        assert np.array_equal(four[n], five[n][:4], equal_nan=True), n
