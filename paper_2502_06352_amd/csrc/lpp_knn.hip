@@ -471,17 +471,22 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   }
   // A code that is the same as this one, the same for all of them, or the code itself.  (seen holds what was written to
   // the place last, and rubbish where nothing was: what counts is that the numbers are the same.)
-  if (FIXED && wave == 1) {
-    const int r = a.seen[seen_slot(a, l1)];
-    int same = l1 > 0.f && r >= 0 && r < a.V && r != row && a.l1[min(max(r, 0), a.V - 1)] == l1;
-#pragma unroll 1
-    for (int d = lane >> 4 << 2; same && d < a.PD; d += 16) {
-      const i32x4 x = *reinterpret_cast<const i32x4*>(a.Ep + (int64_t)rowc * a.PD + d), y = *reinterpret_cast<const i32x4*>(a.Ep + (int64_t)r * a.PD + d);
-      same = x[0] == y[0] && x[1] == y[1] && x[2] == y[2] && x[3] == y[3];
+  if (FIXED && wave >= 1 && wave <= 8) {                   // a row to 32 lanes, wave 0 has the plans to make (to four lanes: 14.0 us, not 11.1, at 1024 codes four times)
+    const int own = row0 + 2 * (wave - 1) + (lane >> 5), c = min(own, a.V - 1), d = 4 * (lane & 31);
+    const float sum = a.l1[c];
+    const int r = a.seen[seen_slot(a, sum)];
+    bool same = sum > 0.f && r >= 0 && r < a.V && r != own && a.l1[min(max(r, 0), a.V - 1)] == sum;
+    if (same) {
+      const float* const x = a.Ep + (int64_t)c * a.PD;
+      const float* const y = a.Ep + (int64_t)r * a.PD;
+      i32x4 differ = {0, 0, 0, 0};
+#pragma unroll
+      for (int h = 0; h < 256; h += 128)
+        if (d + h < a.PD) differ |= *reinterpret_cast<const i32x4*>(x + d + h) ^ *reinterpret_cast<const i32x4*>(y + d + h);
+      same = (differ[0] | differ[1] | differ[2] | differ[3]) == 0;
     }
-    same &= __shfl_xor(same, 16);
-    same &= __shfl_xor(same, 32);
-    if (lane < 16 && row < a.V) a.twin[row] = same ? r : row;
+    const bool all_same = (uint32_t)(__ballot(same) >> (lane & 32)) == 0xFFFFFFFFu;
+    if (d == 0 && own < a.V) a.twin[own] = all_same ? r : own;
   }
   if (tid >= 16) return;
 
@@ -942,11 +947,11 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib
   const int drop = 32 - min(sh.lognb, vb);                  // bucket number: the value's upper bits
   const uint32_t mask = (1u << ib) - 1u;
   const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  enum { kTodo = 16, kKept, kLast, kCrowded };
+  enum { kTodo = 16, kKept, kLast, kCrowded, kFollow };
   constexpr int SIDE = 8;                                   // largest bucket the transposition rounds sort
 
   for (int i = tid; i < NB / 4; i += NTHR) reinterpret_cast<uint4*>(bucket)[i] = make_uint4(0, 0, 0, 0);
-  if (tid == 0) { s_w[kTodo] = 0; s_w[kKept] = 0; s_w[kCrowded] = 0; }
+  if (tid == 0) { s_w[kTodo] = 0; s_w[kKept] = 0; s_w[kCrowded] = 0; s_w[kFollow] = 0; }
   __shared__ uint32_t s_same[STAGED ? NTHR * EPT / 32 : 1];  // (long rows) bit p: sorted entry p is the same code as the one before it
   if (STAGED)
     for (int i = tid; i < NTHR * EPT / 32; i += NTHR) s_same[i] = 0;
@@ -1043,18 +1048,38 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib
       x1 = min(hi, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)lo, 0x130, 0xf, 0xf, false));
       x0 = max(lo, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x138, 0xf, 0xf, false));
     }
-    const int prev = (int)((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x1, 0x138, 0xf, 0xf, false) >> ib);
+    const uint32_t px = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x1, 0x138, 0xf, 0xf, false);
+    const int prev = (int)(px >> ib);
     const int next = (int)((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x0, 0x130, 0xf, 0xf, false) >> ib);
     const int v0 = (int)(x0 >> ib), v1 = (int)(x1 >> ib);
     const bool mid = p + 1 < kept && v1 - v0 <= E;
     const bool near0 = (p > 0 && v0 - prev <= E) || mid, near1 = mid || (p + 2 < kept && next - v1 <= E);
+    // (long rows) entries that are the same code as the one before them go to the other end of the list, in which the
+    // others then stand close: a block's turns at them are full ones
+    auto put = [&](int q, bool follows) {
+      if (STAGED && follows) {
+        todo[sh.P - 1 - atomicAdd(&s_w[kFollow], 1)] = (uint16_t)q;
+        atomicOr(&s_same[q >> 5], 1u << (q & 31));
+      } else {
+        todo[atomicAdd(&s_w[kTodo], 1)] = (uint16_t)q;
+      }
+    };
     if (lane >= SIDE / 2 && lane < 64 - SIDE / 2 && p < kept) {
+      bool follows0 = false, follows1 = false;
+      if (STAGED) {
+        const bool even0 = near0 && p > 0 && (px ^ x0) >> ib == 0, even1 = near1 && (x0 ^ x1) >> ib == 0;
+        if (even0 || even1) {
+          const int t0 = R.twin[~x0 & mask];
+          follows0 = even0 && R.twin[~px & mask] == t0;
+          follows1 = even1 && R.twin[~x1 & mask] == t0;
+        }
+      }
       sorted[p] = x0;
-      if (near0) todo[atomicAdd(&s_w[kTodo], 1)] = (uint16_t)p;
+      if (near0) put(p, follows0);
       else if (p < kk) out[1 + p] = (int32_t)(~x0 & mask);
       if (p + 1 < kept) {
         sorted[p + 1] = x1;
-        if (near1) todo[atomicAdd(&s_w[kTodo], 1)] = (uint16_t)(p + 1);
+        if (near1) put(p + 1, follows1);
         else if (p + 1 < kk) out[2 + p] = (int32_t)(~x1 & mask);
       }
     }
@@ -1063,7 +1088,8 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib
   // an outsider lies below the threshold, value 0, and may be off by as much as any entry (and by the
   // rounding of the threshold)
   if (!all && (int)(~sorted[kk - 1] >> ib) <= E + 2) return false;      // uniform
-  const int m = s_w[kTodo];
+  const int m = s_w[kTodo], mf = STAGED ? s_w[kFollow] : 0;
+  auto follower = [&](int f) { return (int)todo[sh.P - 1 - f] & 0x7FFF; };
   // the first of the entries up to p, and the one behind those from p on, that are the same code
   auto run_start = [&](int p) {
     uint32_t w = (uint32_t)p >> 5, first = ~s_same[w] & (0xFFFFFFFFu >> (31 - (p & 31)));       // (entry 0 is never set)
@@ -1071,12 +1097,12 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib
     return (int)(32 * w) + 31 - __builtin_clz(first);
   };
   auto run_end = [&](int p) {
-    int w = p + 1 >> 5;
-    uint32_t next = w < NTHR * EPT / 32 ? ~s_same[w] & (0xFFFFFFFFu << (p + 1 & 31)) : 1u;
+    int w = (p + 1) >> 5;
+    uint32_t next = w < NTHR * EPT / 32 ? ~s_same[w] & (0xFFFFFFFFu << ((p + 1) & 31)) : 1u;
     while (!next) next = ++w < NTHR * EPT / 32 ? ~s_same[w] : 1u;
     return 32 * w + __builtin_ctz(next);
   };
-  const bool chain = R.D <= kChainFloats && m > NTHR / 8;   // uniform
+  const bool chain = R.D <= kChainFloats && m + mf > NTHR / 8;      // uniform
   if (STAGED) {
     // Long rows: 16 lanes an entry, four floats of its row each per step,
     // their sums added across the lanes.  Such a sum and the key, which adds the same exact products in index order, are
@@ -1086,25 +1112,18 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib
     // in flight.  (A lane an entry, its row's pieces through 10 KB of LDS and 64 registers, left four blocks to a compute
     // unit and two of a block's four waves at work; now six blocks: 8192 x 256, k = 1000: the build 316 -> 269 us, 5000 x 96,
     // k = 2500: the build 403 -> 268.  The four chains of four lanes going round them, exact at once: 146 us.)
-    // A code that is the same as the one before it in the order has that one's key.  (Every code four times, 8192 x 256,
-    // k = 1000, the build: 0.96 ms before, 1.64 with all sums and keys formed, 0.93 so; 64 times 1.61, 2.11, 0.92.)
-    auto follows = [&](int p) {
-      const bool yes = p > 0 && (sorted[p - 1] ^ sorted[p]) >> ib == 0 && R.twin[~sorted[p - 1] & mask] == R.twin[~sorted[p] & mask];
-      if (yes) atomicOr(&s_same[p >> 5], 1u << (p & 31));
-      return yes;
-    };
+    // A code that is the same as the one before it in the order has that one's key and takes no part here.  (Every code
+    // four times, the build: 8192 x 256, k = 1000: 0.94 ms with the look for them in the loop below, a lane in 16 asking, 0.50
+    // so; 64 times 1.17 and 0.69; 1024 x 256, k = 100, four times: 83 us and 58.)
     const int l16 = lane & 15;
-    bool again = false;
     if (chain) {
       for (int f = tid; f < m; f += NTHR) {
         const int p = todo[f];
-        if (follows(p)) again = true;
-        else key[p] = exact_key(eid, R, (int)(~sorted[p] & mask));
+        key[p] = exact_key(eid, R, (int)(~sorted[p] & mask));
       }
     } else {
       for (int f = tid >> 4; f < m; f += NTHR / 16) {
         const int p = todo[f];
-        if (follows(p)) { again = true; continue; }
         const float* r = R.p + (int64_t)(~sorted[p] & mask) * R.pitch;
         f32x4 x[4];
 #pragma unroll
@@ -1126,12 +1145,9 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib
         if (l16 == 0) key[p] = orderable(s0);
       }
     }
-    if (__syncthreads_or(again)) {
-      for (int f = tid; f < m; f += NTHR) {
-        const int p = todo[f];
-        const int q = run_start(p);
-        if (q != p) key[p] = key[q];
-      }
+    if (mf > 0) {                                           // uniform
+      __syncthreads();
+      for (int f = tid; f < mf; f += NTHR) key[follower(f)] = key[run_start(follower(f))];
     }
   } else {
     for (int f = tid; f < m; f += NTHR) {
@@ -1169,9 +1185,12 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib
     if (clear && at < kk) out[1 + at] = (int32_t)I;
     return clear;
   };
+  // (what a run's first entry is told holds for all of it)
   bool unclear = false;
-  for (int f = tid; f < m; f += NTHR)
-    if (!place(todo[f], true)) { todo[f] |= 0x8000; unclear = true; }
+  for (int f = tid; f < m + mf; f += NTHR) {
+    uint16_t& t = todo[f < m ? f : sh.P - 1 - (f - m)];
+    if (!place(t, true)) { t |= 0x8000; unclear = true; }
+  }
   if (STAGED && __syncthreads_or(unclear)) {
     for (int f = tid; f < m; f += NTHR)
       if (todo[f] & 0x8000) {
@@ -1179,8 +1198,14 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib
         key[p] = exact_key(eid, R, (int)(~sorted[p] & mask));
       }
     __syncthreads();
-    for (int f = tid; f < m; f += NTHR)
-      if (todo[f] & 0x8000) place(todo[f] & 0x7FFF, false);
+    if (mf > 0) {
+      for (int f = tid; f < mf; f += NTHR) key[follower(f)] = key[run_start(follower(f))];
+      __syncthreads();
+    }
+    for (int f = tid; f < m + mf; f += NTHR) {
+      const int t = todo[f < m ? f : sh.P - 1 - (f - m)];
+      if (t & 0x8000) place(t & 0x7FFF, false);
+    }
   }
   return true;
 }
@@ -1393,7 +1418,7 @@ __device__ void exact_row(const Rows& R, int V, int i, int kk, unsigned char* sm
 template <int NTHR, int EPT, bool STAGED, bool LATER>
 __global__ __launch_bounds__(NTHR, LATER || !STAGED || NTHR == 1024 ? 8 : 6) void knn_rank_kernel(KnnArgs a, RankShape sh) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_w[20];
+  __shared__ int s_w[24];
   const int tid = threadIdx.x, i = blockIdx.x, kk = a.k - 1;
   int32_t* out = a.neigh + (int64_t)i * a.k;
   if (tid == 0) out[0] = i;
@@ -1476,7 +1501,7 @@ constexpr int kExactThreads = 1024;
 template <bool KEEP>
 __global__ __launch_bounds__(kExactThreads) void knn_exact_kernel(KnnArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_w[20];
+  __shared__ int s_w[24];
   const int n = a.redo[0];
   for (int r = blockIdx.x; r < n; r += gridDim.x) {
     const int i = a.redo[1 + r];
@@ -1494,7 +1519,7 @@ constexpr int kDirectThreads = 256;
 __global__ __launch_bounds__(kDirectThreads) void knn_direct_kernel(KnnArgs a, RankShape sh) {
   constexpr int EPT = kDirectCodes / kDirectThreads, W = kDirectThreads / 64;
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_w[20];
+  __shared__ int s_w[24];
   __shared__ float s_m[3][W];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, i = blockIdx.x, kk = a.k - 1;
   const int D = a.D, V = a.V;

@@ -219,3 +219,12 @@ def test_knn_long_rows_the_same_or_the_same_sum(V, D, k, kind):
         E[::7] = np.float32(1.0 / np.sqrt(D))
         E[3::7] = np.where(np.arange(D) < D // 2, np.float32(0.7), np.float32(0.7) * np.float32(1 + 2.0 ** -23)) / np.float32(np.sqrt(D))
     _check(E, k, None if V <= 2000 else np.unique(np.concatenate([[0, 3, 5, V - 1], g.choice(V, size=200)])))
+
+
+@pytest.mark.parametrize("V,D,k,most", [(1024, 256, 100, 1.85), (8192, 256, 1000, 2.7)])
+def test_knn_every_code_four_times(V, D, k, most):
+    # 1.5 and 1.9 times a codebook without copies; 2.2 and 3.5 where a lane in 16 looked for them between the sums
+    g = np.random.default_rng(8)
+    E = _unit(g, V // 4, D)[g.permutation(V) // 4]
+    _check(E, k, g.choice(V, size=60))
+    assert _least_ms(E, k) < most * _least_ms(_unit(g, V, D), k)
