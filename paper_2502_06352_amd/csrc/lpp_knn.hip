@@ -121,7 +121,7 @@ struct KnnArgs {
   int32_t seen_shift;
   float4* part;         // [kStatBlocks]: max norm, max |x|, max 1-norm, any NaN
   RowPlan* plan;        // [Vp]
-  float* top;           // [Vp] what a row's similarities stay below (long rows)
+  float* reach;         // [Vp] what the magnitudes of a row's products with any code add up to at most (long rows)
   int32_t* cnt;         // [V][splits]
   uint32_t* cand;       // [V][cap]
   int32_t* redo;        // [1 + V]: rows that take the exact path, their number first
@@ -545,7 +545,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   }
   if (!(e < INFINITY)) p.E = 1 << 30;
   a.plan[row] = p;
-  if (FIXED) a.top[row] = top;
+  if (FIXED) a.reach[row] = l1 * st.mabs;                   // (not the norms: squares of small numbers vanish in them)
 }
 
 // What both collecting kernels do with the similarities they form: a lane holds four of one row per
@@ -936,7 +936,7 @@ struct RankShape { int32_t P, lognb; };
 // only before it by its key: neither can move anything among the first kk.)
 template <int NTHR, int EPT, bool STAGED>
 __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib, int vb, int E, bool all, int kk, const Rows& R,
-                         float top, RankShape sh, unsigned char* smem, int* s_w, int32_t* out, int tid) {
+                         float reach, RankShape sh, unsigned char* smem, int* s_w, int32_t* out, int tid) {
   const int NB = 1 << sh.lognb;
   double* eid = reinterpret_cast<double*>(smem);
   uint32_t* bucket = reinterpret_cast<uint32_t*>(eid + ((R.D + 3) & ~3));
@@ -1106,8 +1106,8 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib
   if (STAGED) {
     // Long rows: 16 lanes an entry, four floats of its row each per step,
     // their sums added across the lanes.  Such a sum and the key, which adds the same exact products in index order, are
-    // each off by at most D 2^-53 of the products' magnitudes (those by the norms' product): where two sums are further
-    // apart than `apart`, twice what both together come to, the keys have the same order.  The few entries with a
+    // each off by at most D 2^-53 of the products' magnitudes: where two sums are further
+    // apart than `apart` (key_margin), the keys have the same order.  The few entries with a
     // closer one get their key.  Bound by waiting for the rows, of which few are in L2: what counts is the waves
     // in flight.  (A lane an entry, its row's pieces through 10 KB of LDS and 64 registers, left four blocks to a compute
     // unit and two of a block's four waves at work; now six blocks: 8192 x 256, k = 1000: the build 316 -> 269 us, 5000 x 96,
@@ -1157,7 +1157,7 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib
   }
   __syncthreads();
   // the keys decide between entries that differ by at most E; all others are in order
-  const double apart = STAGED && !chain ? 8.4 * 1.1102230246251565e-16 * R.D * (double)top : -1.0;
+  const double apart = STAGED && !chain ? key_margin(reach, R.D) : -1.0;
   auto place = [&](int p, bool sums) {                      // false: closer to some other than its sum tells
     const uint32_t x = sorted[p];
     const uint64_t K = key[p], lo = orderable(key_value(K) - apart), hi = orderable(key_value(K) + apart);
@@ -1483,7 +1483,7 @@ __global__ __launch_bounds__(NTHR, LATER || !STAGED || NTHR == 1024 ? 8 : 6) voi
   const Rows R{a.Ep, a.PD, a.D, true, a.twin};
   if (!over && !(p.flags & kNoList)) {
     if (rank_row<NTHR, EPT, STAGED>(w, on, n, a.ib, a.vmask_bits, p.E, (p.flags & kAll) != 0, kk, R,
-                                   STAGED ? a.top[i] : 0.f, sh, smem, s_w, out, tid)) return;
+                                   STAGED ? a.reach[i] : 0.f, sh, smem, s_w, out, tid)) return;
   }
   // (what was written of the row is written again)
   if constexpr (LATER) {
@@ -1609,7 +1609,7 @@ __global__ __launch_bounds__(kDirectThreads) void knn_direct_kernel(KnnArgs a, R
 // -------------------------------------------------------------------------------------------- host
 
 struct KnnLayout {
-  size_t o_ep, o_ef, o_es, o_ew, o_ews, o_norms, o_l1, o_seen, o_twin, o_part, o_plan, o_top, o_cnt, o_redo, o_cand, total;
+  size_t o_ep, o_ef, o_es, o_ew, o_ews, o_norms, o_l1, o_seen, o_twin, o_part, o_plan, o_reach, o_cnt, o_redo, o_cand, total;
   int32_t PD, KS, Vp, cap, ib, vb, stride, ns, m, take_all, most, splits, cap_split, seen_shift;
 };
 
@@ -1663,7 +1663,7 @@ KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   L.o_twin = take(L.KS ? (size_t)V * sizeof(int32_t) : 0);
   L.o_part = take((size_t)kStatBlocks * sizeof(float4));
   L.o_plan = take((size_t)L.Vp * sizeof(RowPlan));
-  L.o_top = take(L.KS ? (size_t)L.Vp * sizeof(float) : 0);
+  L.o_reach = take(L.KS ? (size_t)L.Vp * sizeof(float) : 0);
   L.o_cnt = take((size_t)V * L.splits * sizeof(int32_t));
   L.o_redo = take((size_t)(V + 1) * sizeof(int32_t));
   L.o_cand = take((size_t)V * entries * sizeof(uint32_t));
@@ -1782,7 +1782,7 @@ extern "C" int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, in
   a.seen_shift = L.seen_shift;
   a.part = reinterpret_cast<float4*>(w + L.o_part);
   a.plan = reinterpret_cast<RowPlan*>(w + L.o_plan);
-  a.top = reinterpret_cast<float*>(w + L.o_top);
+  a.reach = reinterpret_cast<float*>(w + L.o_reach);
   a.cnt = reinterpret_cast<int32_t*>(w + L.o_cnt);
   a.cand = reinterpret_cast<uint32_t*>(w + L.o_cand);
   a.redo = reinterpret_cast<int32_t*>(w + L.o_redo);

@@ -24,4 +24,10 @@ __host__ __device__ inline int32_t list_margin(double e, double range, uint32_t 
   return m < 1073741823.0 ? (int32_t)m + 1 : 1 << 30;                 // (also where m is NaN)
 }
 
+// Float64 sums of the D products of two pairs (a row with two codes), in any order, that differ by more than this: added
+// in index order they have the same order.  Each of the four sums is off by at most D 2^-53 of the magnitudes added,
+// which `reach`, the row's 1-norm times the largest magnitude of the codebook, bounds: 4 D 2^-53, and as much again in
+// hand, of which 5 % are for the rounding of `reach` itself (its D float32 additions and a product).
+__host__ __device__ inline double key_margin(float reach, int32_t D) { return 8.4 * 1.1102230246251565e-16 * D * (double)reach; }
+
 #endif  // LPP_KNN_LIST_H_
