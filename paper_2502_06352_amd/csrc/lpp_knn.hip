@@ -116,7 +116,8 @@ struct KnnArgs {
   i32x4* Ews;
   float* norms;         // [V]
   float* l1;            // [V]
-  int32_t* seen;        // (long rows) [1 << 32 - seen_shift] codes by their 1-norm
+  uint32_t* hash;       // (long rows) [V] of a code's numbers and their order
+  int32_t* seen;        // (long rows) [2][1 << 32 - seen_shift] codes by their hash, in one place and in another
   int32_t* twin;        // (long rows) [V] a code that is the same, one for all of them
   int32_t seen_shift;
   float4* part;         // [kStatBlocks]: max norm, max |x|, max 1-norm, any NaN
@@ -165,9 +166,34 @@ __device__ __forceinline__ int sample_slot(const KnnArgs& a, int code) {
   return j < a.ns && code == j * a.stride + (int)off ? j : -1;
 }
 
-// Place of a code in `seen`, by its 1-norm: codes that are the same share it.
-__device__ __forceinline__ uint32_t seen_slot(const KnnArgs& a, float l1) {
-  return (__float_as_uint(l1) * 2654435761u) >> a.seen_shift;
+// One number more in a lane's share of the hash of a code (no products, which issue at a quarter of the rate).
+__device__ __forceinline__ uint32_t hash_in(uint32_t h, float x) {
+  h ^= __float_as_uint(x);
+  h += h << 10;
+  return h ^ __builtin_amdgcn_alignbit(h, h, 6);
+}
+// The hash of a code held by G lanes: the last of them returns it.
+template <int G>
+__device__ __forceinline__ uint32_t hash_end(uint32_t h) {
+  h = (h ^ h >> 15) * 2246822519u;
+  h ^= h >> 13;
+  h += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0x128, 0xf, 0xf, false);       // row_ror:8, 4, 2, 1
+  h += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0x124, 0xf, 0xf, false);
+  h += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0x122, 0xf, 0xf, false);
+  h += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0x121, 0xf, 0xf, false);
+  if (G == 64) {
+    h += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0x142, 0xa, 0xf, false);     // row_bcast:15 into rows 1 and 3
+    h += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0x143, 0xc, 0xf, false);     // row_bcast:31 into rows 2 and 3
+  }
+  return h;
+}
+
+// The two places of a code in `seen`; its copies are found unless other codes took both.  (One place, and a group of 64
+// copies whose place another code took: 8192 x 256, k = 100 280 us instead of 232.  By the 1-norm instead of a hash, codes of one
+// set of numbers with their signs turned shared a place: 8192 x 256, each four times, k = 1000 1.68 ms and now 0.43.)
+__device__ __forceinline__ uint32_t seen_slot(const KnnArgs& a, uint32_t hash) { return hash >> a.seen_shift; }
+__device__ __forceinline__ uint32_t other_slot(const KnnArgs& a, uint32_t hash) {
+  return (1u << (32 - a.seen_shift)) + (hash * 2654435761u >> a.seen_shift);
 }
 
 // G lanes per row, 16 bytes per lane and step.
@@ -184,6 +210,7 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
     const float* src = a.E + (int64_t)row * a.D;
     float* dst = a.Ep + (int64_t)row * a.PD;
     float ss = 0.f, sa = 0.f, mb = 0.f;
+    uint32_t hash = (uint32_t)(sub + 1) * 2246822519u;
     // (short rows: whole pieces of eight halves, zero past the row)
     const int dend = G == 4 ? (a.D > 8 ? 16 : 8) : a.PD;
     for (int d = 4 * sub; d < dend; d += 4 * G) {
@@ -218,6 +245,7 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
+        if (G > 4) hash = hash_in(hash, v[e]);
         ss += v[e] * v[e];
         sa += fabsf(v[e]);
         mb = fmaxf(mb, fabsf(v[e]));
@@ -231,7 +259,8 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
     }
     const float n = sqrtf(ss);
     if (sub == 0) { a.norms[row] = n; a.l1[row] = sa; }
-    if (G > 4 && sub == 0 && sa > 0.f) a.seen[seen_slot(a, sa)] = row;   // (any of the codes that share the place)
+    if (G > 4) hash = hash_end<G>(hash);
+    if (G > 4 && sub == G - 1) a.hash[row] = hash;
     // (a row that holds a NaN has a NaN norm and takes no part in the maxima)
     const bool bad = !(n == n);
     mx[0] = fmaxf(mx[0], n);
@@ -270,6 +299,11 @@ __global__ __launch_bounds__(256) void knn_limb_kernel(KnnArgs a) {
   const int row = tile * 16 + (lane & 15), d0 = ks * 64 + (lane >> 4) * 16;
   const double inv = 1.0 / limb_unit(st.mabs);
   const bool ok = row < a.V && a.norms[min(row, a.V - 1)] == a.norms[min(row, a.V - 1)];
+  if (ks == 0 && lane < 16 && row < a.V && a.l1[row] > 0.f) {          // (any of the codes that share a place)
+    const uint32_t hash = a.hash[row];
+    a.seen[seen_slot(a, hash)] = row;
+    a.seen[other_slot(a, hash)] = row;
+  }
   uint32_t limb[3][4];
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
@@ -471,11 +505,15 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   }
   // A code that is the same as this one, the same for all of them, or the code itself.  (seen holds what was written to
   // the place last, and rubbish where nothing was: what counts is that the numbers are the same.)
-  if (FIXED && wave >= 1 && wave <= 8) {                   // a row to 32 lanes, wave 0 has the plans to make (to four lanes: 14.0 us, not 11.1, at 1024 codes four times)
+  // A row to 32 lanes; wave 0 has the plans to make.  (To four lanes: 14.0 us, not 11.1, 1024 x 256, each code four times.)
+  if (FIXED && wave >= 1 && wave <= 8) {
     const int own = row0 + 2 * (wave - 1) + (lane >> 5), c = min(own, a.V - 1), d = 4 * (lane & 31);
-    const float sum = a.l1[c];
-    const int r = a.seen[seen_slot(a, sum)];
-    bool same = sum > 0.f && r >= 0 && r < a.V && r != own && a.l1[min(max(r, 0), a.V - 1)] == sum;
+    const uint32_t hash = a.hash[c];
+    const int r1 = a.seen[seen_slot(a, hash)], r2 = a.seen[other_slot(a, hash)];
+    auto holds = [&](int r) { return r >= 0 && r < a.V && a.hash[min(max(r, 0), a.V - 1)] == hash; };
+    const bool first = holds(r1), second = holds(r2);
+    const int r = first ? r1 : r2;
+    bool same = (first || second) && r != own && a.l1[c] > 0.f;
     if (same) {
       const float* const x = a.Ep + (int64_t)c * a.PD;
       const float* const y = a.Ep + (int64_t)r * a.PD;
@@ -1609,7 +1647,7 @@ __global__ __launch_bounds__(kDirectThreads) void knn_direct_kernel(KnnArgs a, R
 // -------------------------------------------------------------------------------------------- host
 
 struct KnnLayout {
-  size_t o_ep, o_ef, o_es, o_ew, o_ews, o_norms, o_l1, o_seen, o_twin, o_part, o_plan, o_reach, o_cnt, o_redo, o_cand, total;
+  size_t o_ep, o_ef, o_es, o_ew, o_ews, o_norms, o_l1, o_hash, o_seen, o_twin, o_part, o_plan, o_reach, o_cnt, o_redo, o_cand, total;
   int32_t PD, KS, Vp, cap, ib, vb, stride, ns, m, take_all, most, splits, cap_split, seen_shift;
 };
 
@@ -1658,8 +1696,9 @@ KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   L.o_ews = take(L.KS ? 0 : (size_t)L.ns * 2 * n8 * 16);
   L.o_norms = take((size_t)V * sizeof(float));
   L.o_l1 = take((size_t)V * sizeof(float));
+  L.o_hash = take(L.KS ? (size_t)V * sizeof(uint32_t) : 0);
   L.seen_shift = 32 - log2_up(std::max(V, 1024)) - 2;
-  L.o_seen = take(L.KS ? sizeof(int32_t) << (32 - L.seen_shift) : 0);
+  L.o_seen = take(L.KS ? sizeof(int32_t) << (33 - L.seen_shift) : 0);
   L.o_twin = take(L.KS ? (size_t)V * sizeof(int32_t) : 0);
   L.o_part = take((size_t)kStatBlocks * sizeof(float4));
   L.o_plan = take((size_t)L.Vp * sizeof(RowPlan));
@@ -1777,6 +1816,7 @@ extern "C" int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, in
   a.Ews = reinterpret_cast<i32x4*>(w + L.o_ews);
   a.norms = reinterpret_cast<float*>(w + L.o_norms);
   a.l1 = reinterpret_cast<float*>(w + L.o_l1);
+  a.hash = reinterpret_cast<uint32_t*>(w + L.o_hash);
   a.seen = reinterpret_cast<int32_t*>(w + L.o_seen);
   a.twin = reinterpret_cast<int32_t*>(w + L.o_twin);
   a.seen_shift = L.seen_shift;

@@ -228,3 +228,15 @@ def test_knn_every_code_four_times(V, D, k, most):
     E = _unit(g, V // 4, D)[g.permutation(V) // 4]
     _check(E, k, g.choice(V, size=60))
     assert _least_ms(E, k) < most * _least_ms(_unit(g, V, D), k)
+
+
+@pytest.mark.parametrize("k,most", [(100, 1.5), (1000, 3.0)])
+def test_knn_copies_among_codes_of_one_norm(k, most):
+    # one set of numbers with signs of each code's own, four times over: all 1-norms are the same, bit for bit.  1.2 and
+    # 1.8 times a codebook without copies; 1.9 and 6.5 where copies were looked for by 1-norm
+    V, D = 8192, 256
+    g = np.random.default_rng(9)
+    E = _unit(g, 1, D) * np.where(g.random((V // 4, D)) < 0.5, -1, 1).astype(np.float32)
+    E = np.ascontiguousarray(E[g.permutation(V) // 4])
+    _check(E, k, g.choice(V, size=60))
+    assert _least_ms(E, k) < most * _least_ms(_unit(g, V, D), k)
