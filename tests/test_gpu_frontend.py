@@ -14,12 +14,15 @@ from gpu_common import DEV, dev, compare_verify, sparse_neighbour_table
 pytestmark = pytest.mark.gpu
 
 
-def _run(cfg, scale, top_k, guide=True, salt=0):
+def _run(cfg, scale, top_k, guide=True, salt=0, edit=None, everything=False):
+    """edit: changes a set of logit rows.  everything: the skip rule and distinct siblings behind the front end."""
     parent = static_tree(cfg.branching, cfg.N)
     tree = lpp.Tree(parent)
     x = make_verify_inputs(cfg, parent, rho=0.8, salt=salt)
     y = make_verify_inputs(cfg, parent, rho=0.0, salt=salt + 100)      # an unrelated row set: the null-conditioned rows
     cond, uncond = x["target_logits"], y["target_logits"]
+    if edit is not None:
+        cond, uncond = edit(cond), edit(uncond)
     B, M = x["tokens"].shape
     V, off, k = cfg.V, cfg.vocab_offset, cfg.k
     neigh = sparse_neighbour_table(make_codebook(cfg), k, x["tokens"][:, 1:], V)
@@ -33,16 +36,23 @@ def _run(cfg, scale, top_k, guide=True, salt=0):
            "q_tok": torch.zeros((B, M), device=DEV), "p_tok": torch.zeros((B, M), device=DEV),
            "final_tok_all": torch.full((B, M), -7, dtype=torch.int32, device=DEV)}
     ws = torch.empty(lpp.lpp_relaxed_verify_workspace(tree, B, V, k), dtype=torch.uint8, device=DEV)
-    lpp.lpp_relaxed_verify_sampled(tree, dev(cond), dev(uncond) if guide else None, scale, top_k,
-                                   dev(x["drafter_logits"]), cfg.ldv, off, V, B, dev(x["tokens"]), dev(neigh),
-                                   neigh.shape[1], k, cfg.lam, dev(x["u_accept"]), dev(x["u_final"]), out, ws)
+    null = dev(uncond) if guide else None
+    args = (dev(x["drafter_logits"]), cfg.ldv, off, V, B, dev(x["tokens"]), dev(neigh), neigh.shape[1], k)
+    if everything:
+        lpp.lpp_relaxed_verify_opts(tree, dev(cond), *args, dev(x["u_accept"]), dev(x["u_final"]), out, ws,
+                                    bound=lpp.LPP_BOUND_MULTIPLICATIVE, bound_value=cfg.lam, rule=lpp.LPP_RULE_SKIP,
+                                    siblings=lpp.LPP_SIBLINGS_DISTINCT, uncond_logits=null, cfg_scale=scale, top_k=top_k)
+    else:
+        lpp.lpp_relaxed_verify_sampled(tree, dev(cond), null, scale, top_k, *args, cfg.lam, dev(x["u_accept"]),
+                                       dev(x["u_final"]), out, ws)
     torch.cuda.synchronize()
     got = {n: t.cpu().numpy() for n, t in out.items()}
     filt = sampling_frontend(cond, uncond if guide else cond, scale if guide else 0.0, top_k, off, V)
     if not guide:
         assert np.array_equal(sampling_frontend(cond, cond, 3.0, 0, off, V)[:, :, off:off + V], cond[:, :, off:off + V])
     xx = dict(x, target_logits=filt)
-    rep = compare_verify(parent, xx, neigh, V, off, k, cfg.lam, got)
+    rep = compare_verify(parent, xx, neigh, V, off, k, cfg.lam, got, rule="skip" if everything else "prefix",
+                         siblings="without_replacement" if everything else "with_replacement")
     # survivors: drafted tokens the filter removed have q = 0 exactly, the others do not
     tok_logit = np.take_along_axis(filt[:, :, off:off + V][:, [int(p) if p >= 0 else 0 for p in parent]],
                                    x["tokens"][:, :, None].astype(np.int64), axis=2)[:, :, 0]
@@ -83,6 +93,45 @@ def test_sampled_verify_widest_rows(V, off, B):
     cfg = CONFIGS[3].scaled(V=V, ldv=V + off, vocab_offset=off, B=B, k=300)
     for guide in (False, True):
         rep, got = _run(cfg, 3.0, 2000, guide=guide)
+        assert rep["nodes"] > 0 and rep["near_tie_decisions"] <= 2 and rep["nagg_ties"] <= 2
+
+
+@pytest.mark.parametrize("everything", [False, True])
+@pytest.mark.parametrize("V,off,top_k", [(16384, 0, 2000), (8192, 4, 300), (5003, 3, 1000), (3000, 0, 500), (1027, 1, 200)])
+def test_sampled_verify_more_rows_than_compute_units(V, off, top_k, everything):
+    # 305 rows: the walk goes by tickets, in every width of the kernel
+    cfg = CONFIGS[3].scaled(V=V, ldv=V + off, vocab_offset=off, B=5, k=min(700, V // 2))
+    for guide in (False, True):
+        rep, got = _run(cfg, 3.0, top_k, guide=guide, everything=everything)
+        assert rep["nodes"] > 0 and rep["near_tie_decisions"] <= 2
+        assert rep["nagg_ties"] <= (rep["nodes"] // 100 + 2 if everything else 2)
+
+
+def _rounded(l):                      # a few dozen values, hundreds of equal keys each: the k-th largest lies among them
+    return (np.round(l * 2) / 2).astype(np.float32)
+
+
+def _outlier(l):                      # one logit stretches the bins until one or two of them hold the rest of the row
+    l = l.copy()
+    l[:, :, 37] = -1e4
+    return l
+
+
+def _few_finite(l):                   # fewer finite logits than top_k: the k-th largest is -inf, nothing is removed
+    l = l.copy()
+    l[:, :, np.arange(l.shape[2]) % 8 != 5] = -np.inf
+    return l
+
+
+@pytest.mark.parametrize("B", [1, 5])                     # every row's block resident at once, and not
+@pytest.mark.parametrize("V,off,top_k", [(16384, 0, 2500), (5003, 3, 700)])
+@pytest.mark.parametrize("edit", [_rounded, _outlier, _few_finite])
+def test_sampled_verify_crowded_bins(edit, V, off, top_k, B):
+    # more than 256 keys in the threshold's bin: the exact search over the keys' bits.  (A bound of 2.7, not 3: no sums
+    # of equal probabilities that meet it)
+    cfg = CONFIGS[3].scaled(V=V, ldv=V + off, vocab_offset=off, B=B, k=300, lam=2.7)
+    for guide in (False, True) if edit is not _few_finite else (False,):
+        rep, got = _run(cfg, 3.0, top_k, guide=guide, edit=edit)
         assert rep["nodes"] > 0 and rep["near_tie_decisions"] <= 2 and rep["nagg_ties"] <= 2
 
 

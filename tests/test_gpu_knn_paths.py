@@ -202,7 +202,8 @@ def test_knn_graph_replays_with_and_without_rows_that_fall_through(V, D):
 
 
 @pytest.mark.parametrize("kind", ["copies", "permuted"])
-@pytest.mark.parametrize("V,D,k", [(1200, 17, 90), (1200, 64, 90), (1200, 65, 90), (2000, 128, 300), (1500, 253, 900), (4500, 256, 120)])
+@pytest.mark.parametrize("V,D,k", [(1200, 17, 90), (1200, 64, 90), (1200, 65, 90), (2000, 128, 300), (1500, 253, 900), (4500, 256, 120),
+                                   (5000, 96, 2500), (8192, 256, 2100)])
 def test_knn_long_rows_the_same_or_the_same_sum(V, D, k, kind):
     # copies: codes six times over, in any order, some of them one unit of the last place off in one number.
     # permuted: codes of the same numbers in another order, seen from rows of equal numbers: the sums are the same, the

@@ -87,6 +87,15 @@ def test_opts_distinct_siblings_repeated_token_and_ragged_vocab():
     _case(cfg, 0.5, skip=True, distinct=True, lam=4.0)
 
 
+@pytest.mark.parametrize("skip,distinct", [(True, False), (False, True)])
+@pytest.mark.parametrize("V,off", [(16384, 0), (8192, 4), (5003, 3), (3001, 0), (1027, 1), (20001, 3)])
+def test_opts_more_rows_than_compute_units(V, off, skip, distinct):
+    # 305 rows: the walk goes by tickets, in every width of the kernel
+    rep, _, _ = _case(CONFIGS[3].scaled(V=V, ldv=V + off, vocab_offset=off, B=5, k=min(700, V // 2)), 0.8, skip=skip, distinct=distinct)
+    assert rep["nodes"] > 0 and rep["near_tie_decisions"] <= 2
+    assert rep["nagg_ties"] <= (rep["nodes"] // 100 + 2 if skip else 2)
+
+
 def test_opts_argument_errors():
     cfg = CONFIGS[1]
     parent = static_tree(cfg.branching, cfg.N)
