@@ -1322,7 +1322,20 @@ int32_t relaxed_verify_impl(int32_t additive, int32_t skip, int32_t norepl, bool
   // (The walk by a resident block assumes that all B * M blocks of the launch are on the device at
   // once: one block per compute unit, the device not shared with other work meanwhile.  If that
   // does not hold the walk may give up, which lpp_tree_walk_status reports.)
-  const bool stag = (int64_t)B * tree->M <= std::min<int32_t>(tree->n_cu, LPP_MAX_ROWS) && tree->d_mail != nullptr;
+  auto aligned16 = [&](const float* p) {
+    return p == nullptr || ((reinterpret_cast<uintptr_t>(p + vocab_offset) % 16 == 0) && (ldv % 4 == 0) && (V % 4 == 0));
+  };
+  const bool al = aligned16(target_logits) && aligned16(drafter_logits) && aligned16(uncond_logits);
+  // The builds for rows beyond 16384 keep registers in scratch memory, and for some options the resident grid's keeps more:
+  // tickets there.  61 rows an item, tickets and resident grid: distinct siblings alone, rows on 16 bytes, 20000: 1 to 3
+  // items 32.0 us and 32.6, 33.3 and 33.9, 33.8 and 34.4 (4: 35.8 and 35.2; 32768: 37.9 and 35.7); guidance on rows that
+  // do not start there, 17001: 1, 2, 4 items 46.7 and 46.7, 54.4 and 56.4, 67.6 and 71.9 (with top-k 71.1 and 66.4, 78.0
+  // and 77.1, 87.4 and 90.1), with the skip rule 75.6 and 79.1, 97.1 and 100.1, 111.5 and 118.1; with distinct siblings
+  // only 74.2 and 73.6, 98.2 and 94.2, 115.8 and 118.0.  Without guidance such rows gain by 2 to 42 %.
+  const int64_t rows = (int64_t)B * tree->M;
+  const bool ticketed = V > 16384 && (front ? uncond_logits != nullptr && !al && (skip || (!norepl && rows > 64))
+                                            : norepl && !skip && al && rows <= 192);
+  const bool stag = rows <= std::min<int32_t>(tree->n_cu, LPP_MAX_ROWS) && tree->d_mail != nullptr && !ticketed;
   if (stag) {
     // Tuned on MI355X (256 compute units): a row waits for 0.8 of the time the memory system needs,
     // at kStaggerBytesPerSecond, for the bytes asked for ahead of it (measured best: 0.7 .. 0.9).
@@ -1345,10 +1358,6 @@ int32_t relaxed_verify_impl(int32_t additive, int32_t skip, int32_t norepl, bool
   }
 
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  auto aligned16 = [&](const float* p) {
-    return p == nullptr || ((reinterpret_cast<uintptr_t>(p + vocab_offset) % 16 == 0) && (ldv % 4 == 0) && (V % 4 == 0));
-  };
-  const bool al = aligned16(target_logits) && aligned16(drafter_logits) && aligned16(uncond_logits);
   int32_t st;
 #define LPP_DISPATCH3(T, N, FRONT, ALT, STAG) \
   st = al ? launch_rows<T, N, true, FRONT, ALT, STAG>(a, tt, s) : launch_rows<T, N, false, FRONT, ALT, STAG>(a, tt, s)

@@ -107,6 +107,18 @@ def test_sampled_verify_more_rows_than_compute_units(V, off, top_k, everything):
         assert rep["nagg_ties"] <= (rep["nodes"] // 100 + 2 if everything else 2)
 
 
+@pytest.mark.parametrize("B", [1, 2])                     # the resident grid, and tickets where guidance is the faster so
+@pytest.mark.parametrize("everything", [False, True])
+def test_sampled_verify_guided_wide_rows_off_sixteen_bytes(everything, B):
+    cfg = CONFIGS[3].scaled(V=17001, ldv=17001, B=B, k=300)
+    # (all tokens kept, guidance leaves probabilities down to 1e-20 of the largest: whether the skip rule takes such a
+    # neighbour once the sum is at the cap is decided below float32's resolution, 43 ties of 115 nodes)
+    for top_k in (2000,) if everything else (0, 2000):
+        rep, got = _run(cfg, 3.0, top_k, everything=everything)
+        assert rep["nodes"] > 0 and rep["near_tie_decisions"] <= 2
+        assert rep["nagg_ties"] <= (rep["nodes"] // 100 + 2 if everything else 2)
+
+
 def _rounded(l):                      # a few dozen values, hundreds of equal keys each: the k-th largest lies among them
     return (np.round(l * 2) / 2).astype(np.float32)
 

@@ -96,6 +96,13 @@ def test_opts_more_rows_than_compute_units(V, off, skip, distinct):
     assert rep["nagg_ties"] <= (rep["nodes"] // 100 + 2 if skip else 2)
 
 
+@pytest.mark.parametrize("B", [1, 3, 4])                  # tickets, tickets, the resident grid: where one is the faster
+@pytest.mark.parametrize("V", [20000, 32768])
+def test_opts_distinct_siblings_of_wide_rows(V, B):
+    rep, _, _ = _case(CONFIGS[3].scaled(V=V, ldv=V, B=B, k=300), 0.8, distinct=True)
+    assert rep["nodes"] > 0 and rep["near_tie_decisions"] <= 2 and rep["nagg_ties"] <= 2
+
+
 def test_opts_argument_errors():
     cfg = CONFIGS[1]
     parent = static_tree(cfg.branching, cfg.N)
