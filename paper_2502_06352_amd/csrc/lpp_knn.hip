@@ -293,14 +293,15 @@ __device__ __forceinline__ double limb_unit(float mabs) {
 // One lane per (tile of 16 codes, step of 64 dimensions, fragment lane): 16 dimensions of one code.
 template <int KS>
 __global__ __launch_bounds__(256) void knn_limb_kernel(KnnArgs a) {
-  const Stats st = reduce_stats(a, threadIdx.x & 63);
   const int idx = blockIdx.x * 256 + threadIdx.x;            // (the grid covers Vp/16 * KS * 64 lanes exactly)
   const int lane = idx & 63, ks = (idx >> 6) % KS, tile = (idx >> 6) / KS;
   const int row = tile * 16 + (lane & 15), d0 = ks * 64 + (lane >> 4) * 16;
+  const uint32_t hash = a.hash[min(row, a.V - 1)];
+  const float l1 = a.l1[min(row, a.V - 1)];
+  const Stats st = reduce_stats(a, threadIdx.x & 63);
   const double inv = 1.0 / limb_unit(st.mabs);
   const bool ok = row < a.V && a.norms[min(row, a.V - 1)] == a.norms[min(row, a.V - 1)];
-  if (ks == 0 && lane < 16 && row < a.V && a.l1[row] > 0.f) {          // (any of the codes that share a place)
-    const uint32_t hash = a.hash[row];
+  if (ks == 0 && lane < 16 && row < a.V && l1 > 0.f) {       // (any of the codes that share a place)
     a.seen[seen_slot(a, hash)] = row;
     a.seen[other_slot(a, hash)] = row;
   }
@@ -373,7 +374,11 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15;
   const int row0 = blockIdx.x * 16, row = row0 + l16, rowc = min(row, a.V - 1);
+  // (for the look at the row's copies below, by waves 1 .. 8: asked for now)
+  const int own = min(max(row0 + 2 * (wave - 1) + (lane >> 5), 0), a.V - 1);
+  const uint32_t own_hash = FIXED ? a.hash[own] : 0u;
   const Stats st = reduce_stats(a, lane);
+  const int seen1 = FIXED ? a.seen[seen_slot(a, own_hash)] : 0, seen2 = FIXED ? a.seen[other_slot(a, own_hash)] : 0;
   const float norm = a.norms[rowc], l1 = a.l1[rowc];
   const float top = norm * st.norm * 1.0001f;              // |similarity| stays below
   const bool wide = !FIXED && st.mabs * kHalfScale >= 65504.0f;
@@ -507,15 +512,13 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   // the place last, and rubbish where nothing was: what counts is that the numbers are the same.)
   // A row to 32 lanes; wave 0 has the plans to make.  (To four lanes: 14.0 us, not 11.1, 1024 x 256, each code four times.)
   if (FIXED && wave >= 1 && wave <= 8) {
-    const int own = row0 + 2 * (wave - 1) + (lane >> 5), c = min(own, a.V - 1), d = 4 * (lane & 31);
-    const uint32_t hash = a.hash[c];
-    const int r1 = a.seen[seen_slot(a, hash)], r2 = a.seen[other_slot(a, hash)];
-    auto holds = [&](int r) { return r >= 0 && r < a.V && a.hash[min(max(r, 0), a.V - 1)] == hash; };
-    const bool first = holds(r1), second = holds(r2);
-    const int r = first ? r1 : r2;
-    bool same = (first || second) && r != own && a.l1[c] > 0.f;
+    const int d = 4 * (lane & 31);
+    auto holds = [&](int r) { return r >= 0 && r < a.V && a.hash[min(max(r, 0), a.V - 1)] == own_hash; };
+    const bool first = holds(seen1), second = holds(seen2);
+    const int r = first ? seen1 : seen2;
+    bool same = (first || second) && r != own && a.l1[own] > 0.f;
     if (same) {
-      const float* const x = a.Ep + (int64_t)c * a.PD;
+      const float* const x = a.Ep + (int64_t)own * a.PD;
       const float* const y = a.Ep + (int64_t)r * a.PD;
       i32x4 differ = {0, 0, 0, 0};
 #pragma unroll
@@ -524,7 +527,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
       same = (differ[0] | differ[1] | differ[2] | differ[3]) == 0;
     }
     const bool all_same = (uint32_t)(__ballot(same) >> (lane & 32)) == 0xFFFFFFFFu;
-    if (d == 0 && own < a.V) a.twin[own] = all_same ? r : own;
+    if (d == 0) a.twin[own] = all_same ? r : own;           // (rows past the end: the last one's again)
   }
   if (tid >= 16) return;
 
