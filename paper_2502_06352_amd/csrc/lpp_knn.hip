@@ -992,7 +992,8 @@ __device__ bool rank_row(const uint32_t (&w)[EPT], uint32_t on, int have, int ib
   constexpr int SIDE = 8;                                   // largest bucket the transposition rounds sort
 
   for (int i = tid; i < NB / 4; i += NTHR) reinterpret_cast<uint4*>(bucket)[i] = make_uint4(0, 0, 0, 0);
-  if (tid == 0) { s_w[kTodo] = 0; s_w[kKept] = 0; s_w[kCrowded] = 0; s_w[kFollow] = 0; }
+  if (tid == 0) { s_w[kTodo] = 0; s_w[kKept] = 0; s_w[kCrowded] = 0; }
+  if (STAGED && tid == 0) s_w[kFollow] = 0;
   __shared__ uint32_t s_same[STAGED ? NTHR * EPT / 32 : 1];  // (long rows) bit p: sorted entry p is the same code as the one before it
   if (STAGED)
     for (int i = tid; i < NTHR * EPT / 32; i += NTHR) s_same[i] = 0;
@@ -1459,7 +1460,7 @@ __device__ void exact_row(const Rows& R, int V, int i, int kk, unsigned char* sm
 template <int NTHR, int EPT, bool STAGED, bool LATER>
 __global__ __launch_bounds__(NTHR, LATER || !STAGED || NTHR == 1024 ? 8 : 6) void knn_rank_kernel(KnnArgs a, RankShape sh) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_w[24];
+  __shared__ int s_w[STAGED ? 24 : 20];
   const int tid = threadIdx.x, i = blockIdx.x, kk = a.k - 1;
   int32_t* out = a.neigh + (int64_t)i * a.k;
   if (tid == 0) out[0] = i;
@@ -1542,7 +1543,7 @@ constexpr int kExactThreads = 1024;
 template <bool KEEP>
 __global__ __launch_bounds__(kExactThreads) void knn_exact_kernel(KnnArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_w[24];
+  __shared__ int s_w[20];
   const int n = a.redo[0];
   for (int r = blockIdx.x; r < n; r += gridDim.x) {
     const int i = a.redo[1 + r];
@@ -1560,7 +1561,7 @@ constexpr int kDirectThreads = 256;
 __global__ __launch_bounds__(kDirectThreads) void knn_direct_kernel(KnnArgs a, RankShape sh) {
   constexpr int EPT = kDirectCodes / kDirectThreads, W = kDirectThreads / 64;
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_w[24];
+  __shared__ int s_w[20];
   __shared__ float s_m[3][W];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, i = blockIdx.x, kk = a.k - 1;
   const int D = a.D, V = a.V;
