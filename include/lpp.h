@@ -68,8 +68,8 @@ int32_t lpp_tree_destroy(lpp_tree* tree);
 int32_t lpp_tree_info(const lpp_tree* tree, int32_t* M, int32_t* depth,
                       int32_t* n_parents, int32_t* max_children);
 
-/* The walk of lpp_relaxed_verify, in all its forms, when all B * M row blocks of a launch fit the device at once
- * (one per compute unit) is done by one of the item's row blocks, which waits, with a bound, for the other
+/* The walk of lpp_relaxed_verify, in all its forms but for some options on rows beyond 16384 tokens, when all B * M
+ * row blocks of a launch fit the device at once (one per compute unit) is done by one of the item's row blocks, which waits, with a bound, for the other
  * rows' results (see lpp_relaxed_verify).  That goes best while the launch's blocks are all resident
  * together: the stream's kernel has the device to itself (no compute-unit mask, no long kernel of
  * another stream or process in the way).  If the wait ever runs out, a call with a front end, the skip rule or

@@ -39,7 +39,7 @@
 //   exactly in int32 by the i8 matrix cores (eight MFMA 16x16x64 per 64 dimensions), so the only
 //   errors are the quantisation, D/2 (|e_i|_1 + |e_j|_1), and a few units of the last place kept.
 //   This is far tighter than what can be proved for fp32 accumulation of the same rows, at four times
-//   its rate; at unit rows of 256 floats about one entry in twenty needs its float64 key.
+//   its rate; at unit rows of 256 floats about one entry in twenty needs a float64 sum, hardly one its key.
 #include <limits.h>
 #include <math.h>
 
@@ -693,7 +693,7 @@ __global__ __launch_bounds__(kCollectMaxWaves * 64) void knn_collect_f16_kernel(
 // chunks' loads in flight while one is worked on.  Two blocks per compute unit.  The code tiles are
 // dealt to `splits` blocks, each with a segment of its own in a row's list: where an entry goes is
 // known without asking anybody (a counter per row in memory makes the wave wait for it, and the other
-// three for that wave at the next barrier).  8192 rows of 256: 134 us, matrix cores busy 46 % of it (the
+// three for that wave at the next barrier).  8192 rows of 256: 130 us, matrix cores busy 42 % of it (the
 // similarities alone, in bf16 and twice over, took 259 us and told less).
 template <int KS>
 __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(KnnArgs a) {
