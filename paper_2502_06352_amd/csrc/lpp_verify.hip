@@ -896,6 +896,10 @@ __global__ __launch_bounds__(NT, (STAG || ALT || FRONT || NT > 512) ? 1 : 4) voi
           s_val[2 * tid + 1] = v1;
           lds_barrier();
           if (w == 0) {
+            // (Where the turns below, a few hundred bytes of code that one wave goes through in series, lie among the
+            // pieces of 32 bytes counts: sixteen bytes behind one, the other half and none, 61 rows: of 2767 25.3 us, 26.7
+            // and, as it came, 26.6; of 8192 26.1, 27.6, 26.7; of 16384 31.6, 33.2, 33.0; distinct siblings are the same.)
+            asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
             for (int c = 0; c < PASS / 64; ++c) {
               const int slot = ps * PASS + 64 * c + lane;
               if (ps * PASS + 64 * c >= k) break;                       // uniform
