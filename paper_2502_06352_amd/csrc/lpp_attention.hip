@@ -31,6 +31,9 @@
 
 #include "lpp_internal.h"
 
+#ifndef LIVEMIN
+#define LIVEMIN 5
+#endif
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -51,30 +54,39 @@ struct LayerPtrs {
 };
 
 struct AttnArgs {
-  LayerPtrs layer[kLayersPerLaunch];
-  int32_t n_layers;
-  uint32_t blocks_per_layer, rc_bpl;  // (a multiple of 8: every layer maps to the XCDs the same way)
-  int64_t layer_rows;                // partial rows per layer in ws_o / ws_ml
-  int32_t layer_counters;            // counters per layer
+  // (what every block needs to find its place lies together: one line of the scalar cache)
+  uint32_t whole;                    // units (layer, head, row range) that one block each takes (a multiple of 8); those behind them are split
+  uint32_t blocks_per_layer, rc_bpl; // units of a layer (a multiple of 8: every layer maps to the XCDs the same way)
+  int32_t nsplit; uint32_t rc_nsplit;   // key ranges of a split unit
+  int32_t msplits; uint32_t rc_msplits; // row ranges of a head.  rc_d: ceil(2^32 / d): n / d = mulhi(n, rc) while n d < 2^32
+  int32_t gq; uint32_t rc_gq;        // query heads per key/value head (H = Hkv * gq)
+  int32_t H; uint32_t rc_H;
+  int32_t KVBH, S, M, words;         // KVBH: batch * key/value heads
+  int32_t out_bf16;                  // out holds bf16 instead of float
   const int32_t* seq_len;
   const uint64_t* anc;
-  int32_t B, H, S, M, words;
-  int32_t Hkv, gq;                   // key/value heads and query heads per key/value head (H = Hkv * gq)
-  int32_t out_bf16;                  // out holds bf16 instead of float
-  int32_t nsplit, msplits, mtiles;   // mtiles = ceil(M / 16)
-  uint32_t rc_perbh, rc_msplits, rc_H, rc_nsplit, rc_gq;   // ceil(2^32 / d): n / d = mulhi(n, rc) while n d < 2^32
   float scale_log2;                  // scale * log2(e)
-  float* ws_o;                       // [BH][nsplit][mtiles*16][Dh]   unnormalised partial O
-  float* ws_ml;                      // [BH][nsplit][mtiles*16][2]    (reference max in log2 units, sum)
-  uint32_t ws_o_bytes, ws_ml_bytes;  // sizes of the two (each below 2^31 when `counters` is set)
-  int32_t* counters;                 // [BH * msplits] zero between calls, or null: separate merge kernel
+  uint32_t ws_o_bytes, ws_ml_bytes;  // sizes of the two, each below 2^31
+  float* ws_o;                       // [split unit][nsplit][rows of a block][Dh]   unnormalised partial O
+  float* ws_ml;                      // [split unit][nsplit][rows of a block][2]    (reference max in log2 units, sum)
+  int32_t* counters;                 // [split unit] zero between calls
+  int32_t n_layers;
+  LayerPtrs layer[kLayersPerLaunch];
 };
+
+// x, as something the compiler does not know: what is formed from it is formed here, and takes no registers
+// (which the loops over the keys have none to spare of) before.
+__device__ __forceinline__ int formed_anew(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
 
 // n / d for wave-uniform operands through the host's reciprocal: scalar multiplies, no division
 __device__ __forceinline__ uint32_t div_rc(uint32_t n, uint32_t d, uint32_t rc) {
   const uint32_t q = (uint32_t)(((uint64_t)n * rc) >> 32);   // (rc = 0 for d = 1)
   return rc == 0 ? n : q;
 }
+__device__ __forceinline__ uint4 ld16(const char* p) { return *reinterpret_cast<const uint4*>(p); }
 __device__ __forceinline__ uint4 ld16(const uint16_t* p) {
   return *reinterpret_cast<const uint4*>(p);
 }
@@ -129,7 +141,7 @@ struct Stage {
 // rows [rw NT 16, (rw + 1) NT 16).  The RW waves that share a key group load it independently; the
 // second read is served by the compute unit's own cache.
 template <int DH, int NT, int RW, int KW>
-__global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 ? 3 : 2) : 1)) void tree_attn_bf16_kernel(AttnArgs a) {
+__global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 ? (NT == 1 ? 4 : 3) : 2) : 1)) void tree_attn_bf16_kernel(AttnArgs a) {
   static_assert(RW == 1, "a block is one row range; its waves split the keys");
   constexpr int W = RW * KW;
   constexpr int KS = DH / 32;        // contraction steps of Q K^T
@@ -142,6 +154,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
   constexpr int WROWS = NT * 16;     // rows of a wave
   constexpr int ROWS = RW * WROWS;   // rows of the block
   constexpr int OPITCH = DH + 4;     // floats per row of the merge buffer
+  constexpr bool kLean = DH != 64 || NT >= 5;   // no registers for a third stage
   // merge slots: one per wave if that fits where the V tiles were (or in 12 KB per wave), else half as many
   constexpr int MS = (KW * NT * 16 * (DH + 4) * 4 <= (KW * 2 * VTILE > KW * 12 * 1024 ? KW * 2 * VTILE : KW * 12 * 1024)) ? KW : KW / 2;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -151,30 +164,39 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
   const int l16 = lane & 15, g4 = lane >> 4;
   const int kw = wave % KW, rw = wave / KW;
 
-  // block -> (batch*head, key split, row split); all blocks of one key/value head (every row range
+  // block -> unit = (layer, batch*head, row range) and key range; all blocks of one key/value head (every row range
   // and every query head that reads it) share an XCD and follow each other in launch order
-  const uint32_t lyr = div_rc(blockIdx.x, a.blocks_per_layer, a.rc_bpl);
-  const uint32_t bid = blockIdx.x - lyr * a.blocks_per_layer;
+  // (Every argument is asked for at once, then the layer's pointers and the item's length, and no branch up to the first
+  // loads: left to the compiler, the scalar loads wait for each other four times, a few tenths of a microsecond each.)
+  uint32_t whole = a.whole, bpl = a.blocks_per_layer, rc_bpl = a.rc_bpl, rc_nsplit = a.rc_nsplit, rc_msplits = a.rc_msplits;
+  uint32_t rc_gq = a.rc_gq, rc_H = a.rc_H;
+  int ranges = a.nsplit, msplits = a.msplits, gq = a.gq, H = a.H, KVBH = a.KVBH, S = a.S, M = a.M;
+  asm("" : "+s"(whole), "+s"(bpl), "+s"(rc_bpl), "+s"(rc_nsplit), "+s"(rc_msplits), "+s"(rc_gq), "+s"(rc_H), "+s"(ranges), "+s"(msplits),
+           "+s"(gq), "+s"(H), "+s"(KVBH), "+s"(S), "+s"(M) : "s"(a.words), "s"(a.anc), "s"(a.seq_len), "s"(a.scale_log2));
+  const uint32_t behind = blockIdx.x - whole, bslot = behind >> 3;
+  const uint32_t bunit = div_rc(bslot, (uint32_t)ranges, rc_nsplit);              // among the split units of this XCD
+  const bool is_split = blockIdx.x >= whole;
+  const uint32_t unit = is_split ? whole + bunit * 8 + (behind & 7) : blockIdx.x;
+  const int split = is_split ? (int)(bslot - bunit * (uint32_t)ranges) : 0, nsplit = is_split ? ranges : 1;
+  const uint32_t lyr = div_rc(unit, bpl, rc_bpl);
+  const uint32_t bid = unit - lyr * bpl;
   const LayerPtrs& L = a.layer[lyr];
   const uint32_t xcd = bid & 7, slot = bid >> 3;
-  const uint32_t per_bh = (uint32_t)(a.nsplit * a.msplits);
-  const uint32_t hq = div_rc(slot, per_bh, a.rc_perbh), hr = slot - hq * per_bh;
-  const uint32_t kvq = div_rc(hq, (uint32_t)a.gq, a.rc_gq), qg = hq - kvq * (uint32_t)a.gq;
-  const int KVBH = a.B * a.Hkv;
-  // (no early exit for the padding blocks of the last XCD round: a branch here would keep every
-  // later argument load behind it; they redo the last head's work and write nothing)
+  const uint32_t hq = div_rc(slot, (uint32_t)msplits, rc_msplits);
+  const int ms = (int)(slot - hq * (uint32_t)msplits);
+  const uint32_t kvq = div_rc(hq, (uint32_t)gq, rc_gq), qg = hq - kvq * (uint32_t)gq;
+  // (no early exit for the padding blocks of the last XCD round: they redo the last head's work and write nothing)
   const bool live = (int)(kvq * 8 + xcd) < KVBH;
   const int kvbh = min((int)(kvq * 8 + xcd), KVBH - 1);     // batch * Hkv + key/value head
-  const int bh = kvbh * a.gq + (int)qg;                     // batch * H + query head
-  const int split = (int)div_rc(hr, (uint32_t)a.msplits, a.rc_msplits), ms = (int)hr - split * a.msplits;
-  const int b = (int)div_rc((uint32_t)bh, (uint32_t)a.H, a.rc_H);
-  const int M = a.M, S = a.S;
+  const int bh = kvbh * gq + (int)qg;                       // batch * H + query head
+  const int b = (int)div_rc((uint32_t)bh, (uint32_t)H, rc_H);
   const int m0 = ms * ROWS + rw * WROWS;       // first row of this wave
-  int seq = S;
-  if (a.seq_len) seq = min(max(a.seq_len[b], 0), S);     // (everything below depends on it anyway)
+  int len = *(a.seq_len ? a.seq_len + b : reinterpret_cast<const int32_t*>(a.anc));          // (no lengths: something that can be read)
+  asm("" : "+s"(len) : "s"(L.q), "s"(L.kc), "s"(L.vc), "s"(L.kt), "s"(L.vt));
+  const int seq = a.seq_len ? min(max(len, 0), S) : S;
   const int GC = (seq + 31) >> 5, GT = (M + 31) >> 5, G = GC + GT;
-  const int gbeg = (int)div_rc((uint32_t)(split * G), (uint32_t)a.nsplit, a.rc_nsplit);
-  const int gend = (int)div_rc((uint32_t)((split + 1) * G), (uint32_t)a.nsplit, a.rc_nsplit);
+  const int gbeg = (int)div_rc((uint32_t)(split * G), (uint32_t)nsplit, is_split ? rc_nsplit : 0u);
+  const int gend = (int)div_rc((uint32_t)((split + 1) * G), (uint32_t)nsplit, is_split ? rc_nsplit : 0u);
   const uint16_t* kc = reinterpret_cast<const uint16_t*>(L.kc) + (int64_t)kvbh * S * DH;
   const uint16_t* vc = reinterpret_cast<const uint16_t*>(L.vc) + (int64_t)kvbh * S * DH;
   const uint16_t* kt = reinterpret_cast<const uint16_t*>(L.kt) + (int64_t)kvbh * M * DH;
@@ -185,18 +207,19 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
   // Key groups [0, GF) lie wholly inside the cache: no mask, no bounds.  The others (the ragged
   // end of the cache and the tree keys) go through the general path after them.
   const int GF = seq >> 5;
-  const uint32_t koff = (uint32_t)(l16 * DH + g4 * 8);                      // my K chunk inside a group
-  const uint32_t voff = (uint32_t)((lane / CPR) * DH + (lane % CPR) * 8);   // my V chunks: + p * (64 / CPR) rows
+  // (in bytes, 32 bits: offsets to a wave-uniform pointer)
+  const uint32_t koff = (uint32_t)(l16 * DH + g4 * 8) * 2;                  // my K chunk inside a group
+  const uint32_t voff = (uint32_t)lane * 16;                                // my V chunks: + p * 64 chunks
   auto load_full = [&](Stage<DH>& st, int g) {
-    const uint16_t* Kp = kc + (int64_t)g * (32 * DH);
-    const uint16_t* Vp = vc + (int64_t)g * (32 * DH);
+    const char* Kp = reinterpret_cast<const char*>(kc + (int64_t)g * (32 * DH));
+    const char* Vp = reinterpret_cast<const char*>(vc + (int64_t)g * (32 * DH));
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
-        st.ka[t][ks] = __builtin_bit_cast(bf16x8, ld16(Kp + (koff + (uint32_t)(t * 16 * DH + ks * 32))));
+        st.ka[t][ks] = __builtin_bit_cast(bf16x8, ld16(Kp + koff + (t * 32 * DH + ks * 64)));
 #pragma unroll
-    for (int p = 0; p < VCH; ++p) st.vr[p] = ld16(Vp + (voff + (uint32_t)(p * (64 / CPR) * DH)));
+    for (int p = 0; p < VCH; ++p) st.vr[p] = ld16(Vp + voff + p * 1024);
   };
   // general path: every load is unconditional and in bounds (row index clamped); absent keys are
   // masked out of the scores, and their V rows are zeroed on the way into LDS
@@ -211,13 +234,13 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
       const int row = min(kbase + t * 16 + l16, last);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
-        st.ka[t][ks] = __builtin_bit_cast(bf16x8, ld16(Kp + (uint32_t)(row * DH + ks * 32 + g4 * 8)));
+        st.ka[t][ks] = __builtin_bit_cast(bf16x8, ld16(reinterpret_cast<const char*>(Kp) + ((uint32_t)row * (DH * 2) + g4 * 16) + ks * 64));
     }
 #pragma unroll
     for (int p = 0; p < VCH; ++p) {
       const int c = lane + 64 * p;
       const int row = min(kbase + c / CPR, last);
-      st.vr[p] = ld16(Vp + (uint32_t)(row * DH + (c % CPR) * 8));
+      st.vr[p] = ld16(reinterpret_cast<const char*>(Vp) + ((uint32_t)row * (DH * 2) + (c % CPR) * 16));
     }
   };
 
@@ -228,7 +251,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
     const int m = min(m0 + nt * 16 + l16, M - 1);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      qb[nt][ks] = __builtin_bit_cast(bf16x8, ld16(qh + (uint32_t)(m * DH + ks * 32 + g4 * 8)));
+      qb[nt][ks] = __builtin_bit_cast(bf16x8, ld16(reinterpret_cast<const char*>(qh) + ((uint32_t)m * (DH * 2) + g4 * 16) + ks * 64));
   }
 
   f32x4 oacc[DT][NT], lacc[NT];
@@ -261,19 +284,20 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
     }
   };
 
-  // One key group.  FULL (compile time): all 32 keys present and visible to every row.
-  auto compute_group = [&](const Stage<DH>& st, int g, const uint64_t (&vis)[NT], auto full_tag) {
+  // One key group.  FULL (compile time): all 32 keys present and visible to every row.  Of the wave's tiles the first NL.
+  auto compute_group = [&](const Stage<DH>& st, int g, const uint64_t (&vis)[NT], auto full_tag, auto live_tag) {
     constexpr bool FULL = decltype(full_tag)::value;
+    constexpr int NL = decltype(live_tag)::value;
     const bool is_tree = g >= GC;
     const int kbase = is_tree ? (g - GC) * 32 : g * 32;
     const int limit = is_tree ? M : seq;                       // keys [kbase, limit) exist
 
     // S^T = K Q^T
-    f32x4 sacc[2][NT];
+    f32x4 sacc[2][NL];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
+      for (int nt = 0; nt < NL; ++nt) {
         sacc[t][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
@@ -290,11 +314,11 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
     }
 
     // softmax weights of the group; lane holds keys t*16 + 4*g4 + r of column l16
-    uint32_t bits[NT];
-    float mxl[NT];
+    uint32_t bits[NL];
+    float mxl[NL];
     bool need = false;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+    for (int nt = 0; nt < NL; ++nt) {
       bits[nt] = 0xFFFFFFFFu;
       if (!FULL) {
         const int left = seq - kbase;
@@ -316,7 +340,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
     }
     if (__ballot(need)) {   // some row's reference moves: rare after a wave's first group
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
+      for (int nt = 0; nt < NL; ++nt) {
         float v = mxl[nt];
         v = fmaxf(v, __shfl_xor(v, 16));
         v = fmaxf(v, __shfl_xor(v, 32));
@@ -329,9 +353,9 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
         for (int dt = 0; dt < DT; ++dt) oacc[dt][nt] *= alpha;
       }
     }
-    bf16x8 pb[NT];
+    bf16x8 pb[NL];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+    for (int nt = 0; nt < NL; ++nt) {
       uint32_t pk[4];
 #pragma unroll
       for (int t = 0; t < 2; ++t)
@@ -363,7 +387,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
       const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
       const bf16x8 va = __builtin_bit_cast(bf16x8, make_uint4(l2.x, l2.y, h2.x, h2.y));
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
+      for (int nt = 0; nt < NL; ++nt)
         oacc[dt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb[nt], oacc[dt][nt], 0, 0, 0);
     }
     buf ^= 1;   // the next group writes the other tile while these reads may still be in flight
@@ -375,7 +399,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
   // D - 1 groups are in flight while one is worked on, and a stage is refilled as soon as it has
   // been consumed.  The wave's first general group is fetched before them and worked on while
   // the ring's first loads are in flight.
-  {
+  auto run = [&](auto live) {
     const int h1 = min(gend, GF);                     // full groups: [gbeg, h1)
     const int c0 = max(gbeg, GF);                     // general groups: [c0, gend)
     const uint64_t novis[NT] = {};
@@ -394,31 +418,36 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
       int g = gbeg + kw;
       const int hl = max(h1 - 1, 0);
 #pragma unroll
-      for (int d = 0; d < D; ++d) load_full(st[d], min(g + d * KW, hl));
-      if (pre) { compute_group(cst, gx, vis, kAny); gx += KW; }   // while the ring's loads are in flight
+      for (int d = 0; d < D; ++d)
+        if (!kLean || d < D - 1) load_full(st[d], min(g + d * KW, hl));
+      if (pre) { compute_group(cst, gx, vis, kAny, live); gx += KW; }   // while the ring's loads are in flight
+      if (kLean) load_full(st[D - 1], min(g + (D - 1) * KW, hl));
       // whole rounds of the ring, as long as at least the round's first refill is a group of this
       // wave (a round that would refill nothing is left to the tail below: a wave with D groups or
       // fewer would else spend half of the compute unit's load issue on re-reads nobody uses)
       while (g + D * KW < h1) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-          compute_group(st[d], g, novis, kFull);
+          compute_group(st[d], g, novis, kFull, live);
           load_full(st[d], min(g + D * KW, hl));
           g += KW;
         }
       }
 #pragma unroll
       for (int d = 0; d < D; ++d) {               // what is left: up to D groups, already loaded
-        if (g < h1) compute_group(st[d], g, novis, kFull);
+        if (g < h1) compute_group(st[d], g, novis, kFull, live);
         g += KW;
       }
     }
     for (; gx < gend; gx += KW) {                 // further general groups: rare, not pipelined
       visibility(vis, gx);
       load_any(cst, gx);
-      compute_group(cst, gx, vis, kAny);
+      compute_group(cst, gx, vis, kAny, live);
     }
-  }
+  };
+  // (a block behind an odd number of tiles has none in its last place: 129 rows as 5 + 4)
+  if (NT >= 5 && m0 + (NT - 1) * 16 >= M) run(std::integral_constant<int, (NT > 1 ? NT - 1 : 1)>());
+  else run(std::integral_constant<int, NT>());
 
   // ---- merge the waves of the block (fixed order => run-to-run identical): every wave brings
   // its O to the block's reference maximum and parks it in LDS; the sum over the waves is taken
@@ -478,8 +507,10 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
 
   // ---- write: final rows if this block saw every key, else an unnormalised partial
   constexpr int C4 = DH / 4;
-  const int rows_pad = a.mtiles * 16;
   const int mb = ms * ROWS;                                     // first row of the block
+  // the unit's number among the split ones (all of them: without the padding of the last XCD round)
+  const uint32_t part = whole ? unit - whole : (lyr * (uint32_t)(KVBH * gq) + (uint32_t)bh) * (uint32_t)msplits + (uint32_t)ms;
+  const int64_t part0 = (int64_t)part * nsplit * ROWS;          // first row of its partials
   const __amdgpu_buffer_rsrc_t dev_o = device_buffer(a.ws_o, a.ws_o_bytes), dev_ml = device_buffer(a.ws_ml, a.ws_ml_bytes);
   for (int idx = threadIdx.x; idx < ROWS * C4; idx += W * 64) {
     const int r = idx / C4, c4 = idx % C4;
@@ -492,23 +523,17 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
       v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
     }
     const float bm = s_m[W * ROWS + r], bl = s_l[W * ROWS + r];
-    if (a.nsplit == 1) {
+    if (nsplit == 1) {
       const float inv = 1.0f / bl;
       v.x *= inv; v.y *= inv; v.z *= inv; v.w *= inv;
       store_out4(out, a.out_bf16 != 0, ((int64_t)bh * M + m) * DH + c4 * 4, v);
-    } else {
-      const int64_t prow = lyr * a.layer_rows + ((int64_t)bh * a.nsplit + split) * rows_pad + m;
-      float* dst = a.ws_o + prow * DH + c4 * 4;
-      if (a.counters) {   // read by another block of this launch: stores that are visible device-wide when they complete
-        store_dev(dev_o, (uint32_t)((prow * DH + c4 * 4) * 4), v);
-        if (c4 == 0) store_dev(dev_ml, (uint32_t)(prow * 8), make_float2(bm, bl));
-      } else {
-        *reinterpret_cast<float4*>(dst) = v;
-        if (c4 == 0) { a.ws_ml[prow * 2] = bm; a.ws_ml[prow * 2 + 1] = bl; }
-      }
+    } else {   // read by another block of this launch: stores that are visible device-wide when they complete
+      const int64_t prow = part0 + split * ROWS + r;
+      store_dev(dev_o, (uint32_t)((prow * DH + c4 * 4) * 4), v);
+      if (c4 == 0) store_dev(dev_ml, (uint32_t)(prow * 8), make_float2(bm, bl));
     }
   }
-  if (a.nsplit == 1 || !a.counters || !live) return;
+  if (nsplit == 1 || !live) return;
 
   // ---- the block of this (head, row range) that finishes last adds the splits up, in split order
   // Every wave first waits until its own stores of the partial have completed (a device-scope
@@ -521,9 +546,9 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __syncthreads();
   if (threadIdx.x == 0)
-    s_ticket = __hip_atomic_fetch_add(&a.counters[lyr * a.layer_counters + bh * a.msplits + ms], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_ticket = __hip_atomic_fetch_add(&a.counters[part], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  if (s_ticket != a.nsplit - 1) return;
+  if (s_ticket != nsplit - 1) return;
   for (int idx = threadIdx.x; idx < ROWS * C4; idx += W * 64) {
     const int r = idx / C4, c4 = idx % C4;
     const int m = mb + r;
@@ -531,26 +556,25 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
     // (four splits at a time: all their loads are in flight together)
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float ll = 0.f, mm = kMasked;
-    for (int s0 = 0; s0 < a.nsplit; s0 += 4) {
+    for (int s0 = 0; s0 < nsplit; s0 += 4) {
       float2 ml[4];
       float4 o[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int sp = min(s0 + u, a.nsplit - 1);                // (a split past the end: read again, weight 0)
-        const int64_t prow = lyr * a.layer_rows + ((int64_t)bh * a.nsplit + sp) * rows_pad + m;
+        const int64_t prow = part0 + min(s0 + u, nsplit - 1) * ROWS + r;      // (a split past the end: read again, weight 0)
         ml[u] = load_dev2(dev_ml, (uint32_t)(prow * 8));
         o[u] = load_dev4(dev_o, (uint32_t)((prow * DH + c4 * 4) * 4));
       }
       float nm = mm;
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        if (s0 + u < a.nsplit) nm = fmaxf(nm, ml[u].x);
+        if (s0 + u < nsplit) nm = fmaxf(nm, ml[u].x);
       const float keep = __builtin_amdgcn_exp2f(mm - nm);       // (the first batch: exp2(-huge) = 0 on zeros)
       acc.x *= keep; acc.y *= keep; acc.z *= keep; acc.w *= keep; ll *= keep;
       mm = nm;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const float f = s0 + u < a.nsplit ? __builtin_amdgcn_exp2f(ml[u].x - mm) : 0.f;
+        const float f = s0 + u < nsplit ? __builtin_amdgcn_exp2f(ml[u].x - mm) : 0.f;
         ll += f * ml[u].y;
         acc.x += f * o[u].x; acc.y += f * o[u].y; acc.z += f * o[u].z; acc.w += f * o[u].w;
       }
@@ -560,36 +584,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 && DH == 64 ? (NT == 2 
                make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv));
   }
   if (threadIdx.x == 0)   // ready for the next call
-    __hip_atomic_store(&a.counters[lyr * a.layer_counters + bh * a.msplits + ms], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Finish the softmax across the key splits of one (batch, head): one lane per 4 output floats.
-template <int DH>
-__global__ __launch_bounds__(256) void tree_attn_merge_kernel(AttnArgs a) {
-  constexpr int C4 = DH / 4;
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t total = (int64_t)a.B * a.H * a.M * C4;
-  if (idx >= total) return;
-  const int c4 = (int)(idx % C4);
-  const int64_t row = idx / C4;
-  const int m = (int)(row % a.M);
-  const int64_t bh = row / a.M;
-  const int rows_pad = a.mtiles * 16;
-  const int64_t lbase = (int64_t)blockIdx.y * a.layer_rows;      // this layer's partials
-  float mm = kMasked;
-  for (int s = 0; s < a.nsplit; ++s) mm = fmaxf(mm, a.ws_ml[(lbase + (bh * a.nsplit + s) * rows_pad + m) * 2]);
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  float ll = 0.f;
-  for (int s = 0; s < a.nsplit; ++s) {
-    const int64_t prow = lbase + (bh * a.nsplit + s) * rows_pad + m;
-    const float f = __builtin_amdgcn_exp2f(a.ws_ml[prow * 2] - mm);
-    ll += f * a.ws_ml[prow * 2 + 1];
-    const float4 v = *reinterpret_cast<const float4*>(a.ws_o + prow * DH + c4 * 4);
-    acc.x += f * v.x; acc.y += f * v.y; acc.z += f * v.z; acc.w += f * v.w;
-  }
-  const float inv = 1.0f / ll;
-  store_out4(reinterpret_cast<float*>(a.layer[blockIdx.y].out), a.out_bf16 != 0, row * DH + c4 * 4,
-             make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv));
+    __hip_atomic_store(&a.counters[part], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------- fp32 path
@@ -706,13 +701,6 @@ __device__ __forceinline__ void f32_scores(const AttnArgsF32& a, const StageF32<
       if (!(w & 1ull)) sc[r] = -INFINITY;
     }
   }
-}
-
-// x, as something the compiler does not know: what is formed from it is formed here, and takes no registers
-// (which the loop over the keys has none to spare of) before.
-__device__ __forceinline__ int formed_anew(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
 }
 
 // A wave's accumulators [4 HT] to the merge buffer's row (wave, i), row pitch P4.
@@ -1000,7 +988,8 @@ size_t f32_workspace(const lpp_tree* tree, int B, int H, int Dh, int layers, int
 }
 
 struct AttnPlan {
-  int nt, kw, msplits, nsplit, mtiles;
+  int nt, kw, msplits, nsplit, mtiles, groups;
+  int asked;                        // key ranges that a workspace must have room for (with less than nsplit, fewer are made)
   size_t lds;
 };
 
@@ -1012,6 +1001,8 @@ struct AttnPlan {
 AttnPlan plan_attention(const lpp_tree* tree, int B, int H, int S, int Dh, int layers) {
   AttnPlan p;
   p.mtiles = (tree->M + 15) / 16;
+  const int G = (S + 31) / 32 + (tree->M + 31) / 32;
+  const int64_t n_cu = tree->n_cu, heads = (int64_t)B * H * std::max(1, std::min(layers, kLayersPerLaunch));
   // Up to 64 rows: two tiles per wave and one or two blocks per head (enough blocks to fill the
   // chip at small batch).  More rows: up to five tiles per wave, so that as few blocks as possible
   // stream the same K/V out of L2.
@@ -1021,8 +1012,7 @@ AttnPlan plan_attention(const lpp_tree* tree, int B, int H, int S, int Dh, int l
     // Few heads (a quarter of the compute units or fewer would get a block): one tile per wave and
     // twice the row ranges fill the chip with blocks that need no more key splits than before.
     // (Head size 64 only: measured slower at 128, where a one-tile wave holds as many registers.)
-    if (Dh == 64 && p.nt == 2 &&
-        (int64_t)B * H * p.msplits * std::max(1, std::min(layers, kLayersPerLaunch)) * 4 <= tree->n_cu) {
+    if (Dh == 64 && p.nt == 2 && heads * p.msplits * 4 <= n_cu) {
       p.nt = 1;
       p.msplits = p.mtiles;
     }
@@ -1030,22 +1020,33 @@ AttnPlan plan_attention(const lpp_tree* tree, int B, int H, int S, int Dh, int l
     p.msplits = (p.mtiles + 4) / 5;
     p.nt = (p.mtiles + p.msplits - 1) / p.msplits;
   }
-  const int G = (S + 31) / 32 + (tree->M + 31) / 32;
-  const int64_t blocks_bh = (int64_t)B * H * p.msplits * std::max(1, std::min(layers, kLayersPerLaunch));
-  // Blocks of 8 waves, one per compute unit -- unless the launch has more blocks than compute units
-  // and a wave of a 4-wave block still has two groups or more: then two or three such blocks share
-  // a compute unit and cover each other's fixed latencies (first bytes, in-block merge, write-out)
-  // and stalls, which the waves of one block, in step with each other, cannot.  With three tiles or
-  // more per wave (two waves per SIMD either way) that pays from two rounds of blocks on.
-  p.kw = 8;
-  if (G >= 8 && ((p.nt == 2 && blocks_bh > (int64_t)tree->n_cu) ||
-                 (p.nt >= 3 && Dh == 64 && blocks_bh >= 2 * (int64_t)tree->n_cu)))
-    p.kw = 4;
+  // 33 to 64 rows: all of them in one block where the heads alone are enough blocks, so that K/V leave L2 once: 16 layers of
+  // 4 items x 24 heads, 61 rows, 1024 keys 86.8 -> 75.5 us, 8 layers 52.5 -> 46.5; 2 layers of 4096 keys 55.4 -> 40.9.  Not where
+  // four tiles a wave end in a second round that is short (61 rows, 1024 keys, 288 heads 19.9 -> 22.1 us, 384 heads
+  // 20.3 -> 23.1; 480 heads 29.7 -> 25.7); with fewer heads only on long caches, where the key splits fill the chip better
+  // (46 rows, 4000 keys, 72 heads 22.1 -> 15.2 us; 1300 keys, 96 heads 10.0 -> 10.7).
+  bool whole_heads = false;
+  if (Dh == 64 && (p.mtiles == 3 || p.mtiles == 4) && p.nt == 2 &&
+      (heads * 2 > n_cu ? p.mtiles == 3 || G >= 48 || heads <= n_cu || heads * 4 >= n_cu * 7 : heads * 4 > n_cu && G >= 90)) {
+    p.nt = p.mtiles;
+    p.msplits = 1;
+    whole_heads = true;
+  }
+  const int64_t blocks_bh = heads * p.msplits;
+  // Blocks of 8 waves only where they are so few that every second compute unit would idle.  Blocks of 4 waves
+  // share a compute unit and cover each other's fixed latencies (first bytes, in-block merge, write-out) and stalls, which
+  // the waves of one block, in step with each other, cannot: 12 heads x 12 items x 5 layers, 160 keys: 18.7 -> 9.6 us (14
+  // rows); 32 heads of 128 x 3 items x 12 layers, 100 keys: 44 -> 22.5 (20 rows); 24 heads x 8 items, 160 keys: 19.5 ->
+  // 13.2 (116 rows).  Four tiles a wave on long caches: a block a compute unit, while that is enough for all (24
+  // heads x 2 items x 2 layers, 2700 keys, 116 rows: 21.8 us, 22.8 with blocks of 4 waves).
+  p.kw = blocks_bh * 2 > n_cu && !(p.nt == 4 && blocks_bh <= n_cu && G >= 60) ? 4 : 8;
   int ns = (int)std::min<int64_t>(tree->n_cu / blocks_bh, 1 << 20);   // key splits only while a compute unit would idle
   const int max_ns = G / (2 * p.kw);              // at least two key groups per wave
   if (ns > max_ns) ns = max_ns;
   if (ns < 1) ns = 1;
   p.nsplit = ns;
+  p.asked = whole_heads ? 1 : ns;
+  p.groups = G;
   const int rows = p.nt * 16;
   const size_t vt = (size_t)p.kw * 2 * 32 * (Dh * 2 + 32);
   const int ms = (size_t)p.kw * rows * (Dh + 4) * 4 <= std::max<size_t>(vt, (size_t)p.kw * 12 * 1024) ? p.kw : p.kw / 2;
@@ -1060,21 +1061,35 @@ int32_t launch_bf16(const AttnArgs& a, const AttnPlan& p, hipStream_t s) {
   auto kern = tree_attn_bf16_kernel<DH, NT, RW, KW>;
   const int32_t st = lpp_ensure_lds(reinterpret_cast<const void*>(kern), limit, p.lds, 48 * 1024);
   if (st != LPP_OK) return st;
-  hipLaunchKernelGGL(kern, dim3(a.blocks_per_layer * (unsigned)a.n_layers), dim3(RW * KW * 64), p.lds, s, a);
+  const uint32_t units = a.blocks_per_layer * (uint32_t)a.n_layers;
+  hipLaunchKernelGGL(kern, dim3(a.whole + (units - a.whole) * (uint32_t)a.nsplit), dim3(RW * KW * 64), p.lds, s, a);
   LPP_HIP_TRY(hipGetLastError());
-  if (p.nsplit > 1 && !a.counters) {
-    const int64_t total = (int64_t)a.B * a.H * a.M * (DH / 4);
-    hipLaunchKernelGGL(tree_attn_merge_kernel<DH>, dim3((unsigned)((total + 255) / 256), (unsigned)a.n_layers), dim3(256),
-                       0, s, a);
-    LPP_HIP_TRY(hipGetLastError());
-  }
   return LPP_OK;
 }
 
-size_t layer_workspace(const AttnPlan& p, int B, int H, int Dh, size_t* o_bytes) {
-  const size_t rows = (size_t)B * H * p.nsplit * p.mtiles * 16;
+// Which of a launch's units (layer, head, row range; a block each) are split over several blocks by keys.  A launch
+// of fewer units than compute units: all of them, p.nsplit times.  Otherwise those behind the last full round of
+// compute units, so many times that they fill one more, where that saves more than the merge of the parts costs
+// (about 3 us): 31 rows, 3000 keys, 288 heads 54.0 -> 43.8 us, 384 heads 60.4 -> 56.5; 1024 keys, 288 heads 18.0 -> 16.7, but
+// 384 heads, in two parts, 18.4 -> 21.0.
+struct AttnSplit { int64_t whole; int ns; };
+AttnSplit split_units(const lpp_tree* tree, const AttnPlan& p, int64_t units) {
+  if (p.nsplit > 1) return {0, p.nsplit};
+  const int64_t round = std::max(8, tree->n_cu & ~7), rest = units % round;
+  if (rest == units || rest == 0) return {units, 1};
+  const int ns = (int)std::min<int64_t>(round / rest, p.groups / (2 * p.kw));
+  return p.groups < 32 || ns < (p.groups < 80 ? 4 : 2) ? AttnSplit{units, 1} : AttnSplit{units - rest, ns};
+}
+size_t split_rows(const AttnPlan& p, int64_t split, int ns) { return ns < 2 ? 0 : (size_t)split * ns * p.nt * 16; }
+
+// Bytes of so many partial rows: [O | max, sum].
+size_t partial_bytes(size_t rows, int Dh, size_t* o_bytes) {
   if (o_bytes) *o_bytes = lpp_align_up(rows * Dh * sizeof(float), 256);
   return lpp_align_up(rows * Dh * sizeof(float), 256) + lpp_align_up(rows * 2 * sizeof(float), 256);
+}
+// What a call asks for per layer, at least (with less than it could use, a launch has fewer split units).
+size_t layer_workspace(const AttnPlan& p, int B, int H, int Dh) {
+  return partial_bytes((size_t)B * H * p.asked * p.mtiles * 16, Dh, nullptr);
 }
 
 }  // namespace
@@ -1088,8 +1103,12 @@ extern "C" size_t lpp_tree_attention_layers_workspace(const lpp_tree* tree, int3
                                                       int32_t S, int32_t Dh) {
   if (!tree || L < 1 || B < 1 || H < 1 || S < 0 || (Dh != 64 && Dh != 128)) return 0;
   const AttnPlan p = plan_attention(tree, B, H, S, Dh, L);
-  return std::max((size_t)std::min(L, kLayersPerLaunch) * layer_workspace(p, B, H, Dh, nullptr),
-                  f32_workspace(tree, B, H, Dh, L, f32_splits(tree, B, H, S, L), nullptr));
+  const int nl = std::min(L, kLayersPerLaunch);
+  // (the split units behind the last full round, whatever the number of key/value heads: their blocks are a round at most)
+  const size_t rows = std::max(split_rows(p, (int64_t)nl * B * H * p.msplits, p.nsplit),
+                               p.nsplit > 1 || (int64_t)nl * B * H * p.msplits * 8 < tree->n_cu ? 0 : (size_t)tree->n_cu * p.nt * 16);
+  return std::max({(size_t)nl * layer_workspace(p, B, H, Dh), partial_bytes(rows, Dh, nullptr),
+                   f32_workspace(tree, B, H, Dh, L, f32_splits(tree, B, H, S, L), nullptr)});
 }
 
 namespace {
@@ -1112,7 +1131,7 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
   if ((int64_t)S * Dh >= (1ll << 31) || (int64_t)tree->M * Dh >= (1ll << 31)) return LPP_EUNSUPPORTED;   // 32-bit offsets inside one head
   const AttnPlan p = plan_attention(tree, B, H, S, Dh, L);
   // (what bf16 needs; the float32 kernel takes as many key ranges as the workspace has room for)
-  const size_t need = (size_t)std::min(L, kLayersPerLaunch) * layer_workspace(p, B, H, Dh, nullptr);
+  const size_t need = (size_t)std::min(L, kLayersPerLaunch) * layer_workspace(p, B, H, Dh);
   if (!ws || ws_bytes < need) return LPP_ENOWORKSPACE;
   if (!tree->d_anc) return LPP_EHIP;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
@@ -1150,41 +1169,40 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
     }
     a.n_layers = nl;
     a.seq_len = seq_len; a.anc = tree->d_anc;
-    a.B = B; a.H = H; a.S = S; a.M = tree->M; a.words = tree->words;
-    a.Hkv = Hkv; a.gq = H / Hkv; a.out_bf16 = out_dtype == LPP_BF16;
-    a.nsplit = p.nsplit; a.msplits = p.msplits; a.mtiles = p.mtiles;
+    a.H = H; a.S = S; a.M = tree->M; a.words = tree->words;
+    a.KVBH = B * Hkv; a.gq = H / Hkv; a.out_bf16 = out_dtype == LPP_BF16;
+    a.msplits = p.msplits;
     auto rc = [](uint32_t d) { return d <= 1 ? 0u : (uint32_t)((0x100000000ull + d - 1) / d); };
-    a.rc_perbh = rc((uint32_t)(p.nsplit * p.msplits)); a.rc_msplits = rc((uint32_t)p.msplits);
-    a.rc_H = rc((uint32_t)H); a.rc_nsplit = rc((uint32_t)p.nsplit); a.rc_gq = rc((uint32_t)(H / Hkv));
     a.scale_log2 = scale * 1.44269504088896340736f;
-    const int64_t KVBH = (int64_t)B * Hkv;
-    const int64_t bpl = 8 * ((KVBH + 7) / 8) * (H / Hkv) * p.nsplit * p.msplits;
-    if (bpl * nl >= (1ll << 31)) return LPP_EUNSUPPORTED;
+    const int64_t bpl = 8 * (((int64_t)B * Hkv + 7) / 8) * (H / Hkv) * p.msplits;
+    AttnSplit sp = split_units(tree, p, bpl * nl);
+    size_t o_bytes = 0, ml_bytes = 0;
+    auto partials = [&]() {
+      const int64_t units = sp.whole ? bpl * nl - sp.whole : (int64_t)nl * B * H * p.msplits;
+      const size_t bytes = partial_bytes(split_rows(p, units, sp.ns), Dh, &o_bytes);
+      ml_bytes = bytes - o_bytes;
+      return bytes;
+    };
+    while (partials() > ws_bytes) sp = sp.ns > 2 ? AttnSplit{sp.whole, sp.ns - 1} : AttnSplit{bpl * nl, 1};
+    if (sp.whole + (bpl * nl - sp.whole) * sp.ns >= (1ll << 31)) return LPP_EUNSUPPORTED;
+    a.whole = (uint32_t)sp.whole; a.nsplit = sp.ns;
+    a.rc_msplits = rc((uint32_t)p.msplits); a.rc_H = rc((uint32_t)H); a.rc_nsplit = rc((uint32_t)sp.ns);
+    a.rc_gq = rc((uint32_t)(H / Hkv));
     a.blocks_per_layer = (uint32_t)bpl; a.rc_bpl = rc((uint32_t)bpl);
-    size_t o_layer = 0;
-    const size_t ws_layer = layer_workspace(p, B, H, Dh, &o_layer);
-    (void)ws_layer;
-    a.layer_rows = (int64_t)B * H * p.nsplit * p.mtiles * 16;
-    a.layer_counters = B * H * p.msplits;
-    const size_t o_bytes = (size_t)nl * a.layer_rows * Dh * sizeof(float), ml_bytes = (size_t)nl * a.layer_rows * 2 * sizeof(float);
-    // the in-kernel merge of key splits addresses the partials with 32-bit offsets and needs a
-    // counter per (layer, head, row range)
-    a.counters = ((int64_t)nl * a.layer_counters <= LPP_COUNTER_SLOTS && o_bytes < (1u << 31))
-                     ? tree->d_counters + LPP_COUNTER_SLOTS : nullptr;
-    a.ws_o_bytes = (uint32_t)std::min<size_t>(o_bytes, 0x7FFFFFFFu);
-    a.ws_ml_bytes = (uint32_t)std::min<size_t>(ml_bytes, 0x7FFFFFFFu);
+    a.counters = tree->d_counters + LPP_COUNTER_SLOTS;
+    a.ws_o_bytes = (uint32_t)o_bytes; a.ws_ml_bytes = (uint32_t)ml_bytes;
     a.ws_o = reinterpret_cast<float*>(ws);
-    a.ws_ml = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ws) + (size_t)std::min(L, kLayersPerLaunch) * o_layer);
+    a.ws_ml = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ws) + o_bytes);
 
     int32_t st = LPP_EUNSUPPORTED;
     if (Dh == 64) {
-      if (p.nt == 1) st = launch_bf16<64, 1, 1, 8>(a, p, s);
+      if (p.nt == 1) st = p.kw == 4 ? launch_bf16<64, 1, 1, 4>(a, p, s) : launch_bf16<64, 1, 1, 8>(a, p, s);
       else if (p.nt == 2) st = p.kw == 4 ? launch_bf16<64, 2, 1, 4>(a, p, s) : launch_bf16<64, 2, 1, 8>(a, p, s);
       else if (p.nt == 3) st = p.kw == 4 ? launch_bf16<64, 3, 1, 4>(a, p, s) : launch_bf16<64, 3, 1, 8>(a, p, s);
       else if (p.nt == 4) st = p.kw == 4 ? launch_bf16<64, 4, 1, 4>(a, p, s) : launch_bf16<64, 4, 1, 8>(a, p, s);
       else st = p.kw == 4 ? launch_bf16<64, 5, 1, 4>(a, p, s) : launch_bf16<64, 5, 1, 8>(a, p, s);
     } else {
-      if (p.nt == 1) st = launch_bf16<128, 1, 1, 8>(a, p, s);
+      if (p.nt == 1) st = p.kw == 4 ? launch_bf16<128, 1, 1, 4>(a, p, s) : launch_bf16<128, 1, 1, 8>(a, p, s);
       else if (p.nt == 2) st = p.kw == 4 ? launch_bf16<128, 2, 1, 4>(a, p, s) : launch_bf16<128, 2, 1, 8>(a, p, s);
     }
     if (st != LPP_OK) return st;

@@ -153,3 +153,64 @@ def test_float32_takes_fewer_ranges_for_a_smaller_workspace(Dh):
         assert bool((ws[size:] == 0x5A).all())
         assert attention_error(out.cpu().numpy(), want) <= 1e-4, part
     assert 1 <= least < 32
+
+
+@pytest.mark.parametrize("N,S,B,H,Hkv,Dh,L,ragged", [
+    (45, 100, 12, 24, 24, 64, 1, False),     # three tiles a block, 288 blocks of 4 waves, seven key groups
+    (60, 70, 8, 30, 10, 64, 1, True),        # four
+    (45, 1100, 12, 24, 8, 64, 1, True),      # units behind the last full round of compute units in four parts each
+    (60, 1100, 3, 31, 31, 64, 3, False),     # the same with padding behind each layer's last heads
+    (20, 2600, 11, 30, 30, 128, 1, True),    # in three parts, long rows
+    (60, 3000, 5, 20, 20, 64, 1, True),      # four tiles a block, every head in two parts
+    (128, 50, 6, 24, 24, 64, 1, True),       # 129 rows: five tiles and four
+    (128, 1100, 11, 12, 4, 64, 1, False),    # the same, some of them in parts
+    (12, 70, 12, 24, 24, 64, 1, True), (12, 70, 12, 24, 8, 128, 1, True),      # one tile, blocks of 4 waves
+    (60, 120, 5, 28, 28, 128, 1, True),      # long rows, blocks of 4 waves
+])
+def test_layers_launch_shapes(N, S, B, H, Hkv, Dh, L, ragged):
+    branching = (6, 3, 2, 2, 1, 1) if N <= 60 else (8, 4, 2, 2, 1, 1, 1, 1)
+    cfg = CONFIGS[2].scaled(N=N, branching=branching, S=S, H=H, B=B, Dh=Dh)
+    parent = static_tree(cfg.branching, cfg.N)
+    tree = lpp.Tree(parent)
+    atts = [_layer_inputs(cfg, Hkv, l) for l in range(L)]
+    seq = [(S * (b + 1) // B if b != 1 else 0) for b in range(B)] if ragged else [S] * B
+    got = _run_layers(tree, atts, cfg, Hkv, seq_len=seq if ragged else None)
+    again = _run_layers(tree, atts, cfg, Hkv, seq_len=seq if ragged else None)
+    gq = H // Hkv
+    for l in range(L):
+        assert np.all(np.isfinite(got[l])) and np.array_equal(got[l], again[l])
+        for b in range(B):
+            for h in {(7 * b + l) % H, (H - 1 - b) % H}:
+                k = slice(h // gq, h // gq + 1)
+                want = tree_attention(atts[l]["q"][b:b + 1, h:h + 1], atts[l]["kc"][b:b + 1, k, :seq[b]],
+                                      atts[l]["vc"][b:b + 1, k, :seq[b]], atts[l]["kt"][b:b + 1, k], atts[l]["vt"][b:b + 1, k], parent)
+                assert attention_error(got[l][b:b + 1, h:h + 1], want) <= TOL["bf16"], (l, b, h)
+
+
+@pytest.mark.parametrize("N,S,B,H", [(45, 1100, 12, 24), (60, 3000, 5, 20)])
+def test_bf16_makes_fewer_parts_for_a_smaller_workspace(N, S, B, H):
+    # every size that is accepted gives the result and leaves what lies behind it alone
+    cfg = CONFIGS[2].scaled(N=N, branching=(6, 3, 2, 2, 1, 1), S=S, H=H, B=B)
+    parent = static_tree(cfg.branching, cfg.N)
+    tree = lpp.Tree(parent)
+    att = _layer_inputs(cfg, H, 0)
+    t = {n: bf16_dev(att[n + "_bits"]) for n in ("q", "kc", "vc", "kt", "vt")}
+    full = lpp.lpp_tree_attention_workspace(tree, B, H, S, cfg.Dh)
+    outs = []
+    for part in range(1, 17):
+        size = full * part // 16 // 256 * 256
+        ws = torch.full((full + 256,), 0x5A, dtype=torch.uint8, device=DEV)
+        out = torch.full((B, H, cfg.M, cfg.Dh), float("nan"), device=DEV)
+        try:
+            lpp.lpp_tree_attention(tree, lpp.LPP_BF16, t["q"], t["kc"], t["vc"], t["kt"], t["vt"], None, B, H, S, cfg.Dh, 0.0, out,
+                                   ws[:size])
+        except lpp.LppError as e:
+            assert e.status == lpp.LPP_ENOWORKSPACE and not outs
+            continue
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0x5A).all())
+        outs.append(out.cpu().numpy())
+    assert 1 <= len(outs) < 16
+    want = tree_attention(att["q"][-1:, -1:], att["kc"][-1:, -1:], att["vc"][-1:, -1:], att["kt"][-1:, -1:], att["vt"][-1:, -1:], parent)
+    assert max(attention_error(o[-1:, -1:], want) for o in outs) <= TOL["bf16"]
+    assert max(attention_error(o, outs[-1]) for o in outs) <= 2 * TOL["bf16"]
