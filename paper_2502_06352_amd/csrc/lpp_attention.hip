@@ -81,10 +81,18 @@ __device__ __forceinline__ int formed_anew(int x) {
   return x;
 }
 
-// n / d for wave-uniform operands through the host's reciprocal: scalar multiplies, no division
+// n / d for wave-uniform operands through the host's reciprocal (0: d = 1): scalar multiplies, no division
 __device__ __forceinline__ uint32_t div_rc(uint32_t n, uint32_t d, uint32_t rc) {
   const uint32_t q = (uint32_t)(((uint64_t)n * rc) >> 32);   // (rc = 0 for d = 1)
   return rc == 0 ? n : q;
+}
+// The same, rc = 1 where n d can reach 2^32: divided.
+__device__ __forceinline__ uint32_t div_or_rc(uint32_t n, uint32_t d, uint32_t rc) {
+  return rc == 1 ? n / d : div_rc(n, d, rc);
+}
+// ceil(2^32 / d) as the two take it; n_max: the largest n (div_rc: kept below 2^32 / d by its callers)
+uint32_t reciprocal(uint32_t d, uint64_t n_max = 0) {
+  return d <= 1 ? 0u : (n_max * d >= 0x100000000ull ? 1u : (uint32_t)((0x100000000ull + d - 1) / d));
 }
 __device__ __forceinline__ uint4 ld16(const char* p) { return *reinterpret_cast<const uint4*>(p); }
 __device__ __forceinline__ uint4 ld16(const uint16_t* p) {
@@ -589,12 +597,13 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
 
 // ---------------------------------------------------------------- fp32 path
 struct AttnArgsF32 {
-  LayerPtrs layer[kLayersPerLaunch];     // blockIdx.y picks the layer
   const int32_t* seq_len; const uint64_t* anc;
   int32_t B, H, Hkv, S, M, words;
   int32_t mtiles, gq, out_bf16;     // row tiles; query heads per key/value head; out holds bf16 instead of float
   float scale;
   int32_t nsplit;                   // key ranges per (batch, head), and with more than one their partials:
+  uint32_t rc_nsplit, rc_per, rc_mtiles, rc_Hkv;   // reciprocals (div_rc) of nsplit, mtiles * gq, mtiles and Hkv
+  LayerPtrs layer[kLayersPerLaunch];     // blockIdx.y picks the layer
   float4* ws_o;                     // [layer][BH][mtiles][nsplit][16][Dh]  unnormalised partial O
   float2* ws_ml;                    // [layer][BH][mtiles][nsplit][16]      (reference max, sum)
 };
@@ -653,15 +662,31 @@ struct CellF32 {
   int64_t cell, e0;                 // number of the tile over all layers; first element of its output
   int tile0;
   bool live;
-  __device__ __forceinline__ CellF32(const AttnArgsF32& a, int n) {
-    const int per = a.mtiles * a.gq, kvbh = (n / per) * 8 + (int)(blockIdx.x & 7);
+  // (As in the bf16 kernel: every argument and the layer's pointers are asked for at once, and reciprocals instead of divisions:
+  // 4 heads, 16 rows, 256 keys 10.0 -> 9.6 us.)
+  // parts: blocks per tile (key ranges); part: the block's
+  __device__ __forceinline__ CellF32(const AttnArgsF32& a, bool parts, int& part) {
+    const LayerPtrs& L = a.layer[blockIdx.y];
+    uint32_t mtiles = (uint32_t)a.mtiles, rc_nsplit = a.rc_nsplit, rc_per = a.rc_per, rc_mtiles = a.rc_mtiles, rc_Hkv = a.rc_Hkv;
+    asm("" : "+s"(mtiles), "+s"(rc_nsplit), "+s"(rc_per), "+s"(rc_mtiles), "+s"(rc_Hkv)
+        : "s"(a.seq_len), "s"(a.anc), "s"(a.B), "s"(a.H), "s"(a.Hkv), "s"(a.S), "s"(a.M), "s"(a.words), "s"(a.gq), "s"(a.scale),
+          "s"(a.nsplit), "s"(L.q), "s"(L.kc), "s"(L.vc), "s"(L.kt), "s"(L.vt));
+    uint32_t n = blockIdx.x >> 3;
+    part = 0;
+    if (parts) {
+      const uint32_t t = div_or_rc(n, (uint32_t)a.nsplit, rc_nsplit);
+      part = (int)(n - t * (uint32_t)a.nsplit);
+      n = t;
+    }
+    const uint32_t per = mtiles * (uint32_t)a.gq, heads = div_or_rc(n, per, rc_per), rest = n - heads * per;
+    const int kvbh = (int)heads * 8 + (int)(blockIdx.x & 7);
     live = kvbh < a.B * a.Hkv;
     if (!live) return;
-    const int bh = kvbh * a.gq + (n % per) / a.mtiles, b = kvbh / a.Hkv;
-    tile0 = (n % per) % a.mtiles;
-    cell = ((int64_t)blockIdx.y * a.B * a.H + bh) * a.mtiles + tile0;
+    const uint32_t qg = div_or_rc(rest, mtiles, rc_mtiles);
+    const int bh = kvbh * a.gq + (int)qg, b = (int)div_or_rc((uint32_t)kvbh, (uint32_t)a.Hkv, rc_Hkv);
+    tile0 = (int)(rest - qg * mtiles);
+    cell = ((int64_t)blockIdx.y * a.B * a.H + bh) * (int)mtiles + tile0;
     e0 = ((int64_t)bh * a.M + tile0 * 16) * DH;
-    const LayerPtrs& L = a.layer[blockIdx.y];
     keys.kc = reinterpret_cast<const float*>(L.kc) + (int64_t)kvbh * a.S * DH;
     keys.vc = reinterpret_cast<const float*>(L.vc) + (int64_t)kvbh * a.S * DH;
     keys.kt = reinterpret_cast<const float*>(L.kt) + (int64_t)kvbh * a.M * DH;
@@ -834,12 +859,14 @@ __global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
   __shared__ float s_m[W][16], s_l[W][16];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, g = lane >> 4;
-  const CellF32<DH> c(a, (int)(blockIdx.x >> 3) / a.nsplit);
+  int split;
+  const CellF32<DH> c(a, true, split);
   if (!c.live) return;
   const KeysF32<DH>& keys = c.keys;
-  const int split = (int)(blockIdx.x >> 3) % a.nsplit, seq = keys.seq, M = a.M, tile0 = c.tile0;
+  const int seq = keys.seq, M = a.M, tile0 = c.tile0;
   const int all = (keys.n + 15) / 16;
-  const int tbeg = split * all / a.nsplit, tend = (split + 1) * all / a.nsplit;
+  const int tbeg = (int)div_or_rc((uint32_t)(split * all), (uint32_t)a.nsplit, a.rc_nsplit);
+  const int tend = (int)div_or_rc((uint32_t)((split + 1) * all), (uint32_t)a.nsplit, a.rc_nsplit);
   const int row = min(tile0 * 16 + i, M - 1);               // (rows past the last: the last one again, not written)
 
   StageF32<DH> cur, nxt;
@@ -923,7 +950,8 @@ __global__ __launch_bounds__(W * 64) void tree_attn_f32_kernel(AttnArgsF32 a) {
 template <int DH, int W>
 __global__ __launch_bounds__(W * 64) void tree_attn_f32_merge_kernel(AttnArgsF32 a) {
   extern __shared__ __align__(16) unsigned char s_f32[];    // (for tiles that are done again)
-  const CellF32<DH> c(a, (int)(blockIdx.x >> 3));
+  int none;
+  const CellF32<DH> c(a, false, none);
   if (!c.live) return;
   const int tid = threadIdx.x, orow = tid / (DH / 4), c4 = tid % (DH / 4);
   const bool mine = tid < 16 * DH / 4 && c.tile0 * 16 + orow < a.M;
@@ -1155,6 +1183,11 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
       size_t o_bytes = 0;
       a.nsplit = f32_splits(tree, B, H, S, L);
       while (a.nsplit > 1 && f32_workspace(tree, B, H, Dh, L, a.nsplit, &o_bytes) > ws_bytes) --a.nsplit;
+      const uint64_t tiles = (((uint64_t)B * Hkv + 7) / 8) * a.gq * a.mtiles * a.nsplit;
+      a.rc_nsplit = reciprocal((uint32_t)a.nsplit, std::max<uint64_t>(tiles, (uint64_t)(S + tree->M) * a.nsplit));
+      a.rc_per = reciprocal((uint32_t)(a.mtiles * a.gq), tiles);
+      a.rc_mtiles = reciprocal((uint32_t)a.mtiles, (uint64_t)a.mtiles * a.gq);
+      a.rc_Hkv = reciprocal((uint32_t)Hkv, (uint64_t)B * Hkv);
       a.ws_o = reinterpret_cast<float4*>(ws);
       a.ws_ml = reinterpret_cast<float2*>(reinterpret_cast<unsigned char*>(ws) + o_bytes);
       const int32_t st = Dh == 64 ? launch_f32<64, 16>(a, nl, s) : launch_f32<128, 8>(a, nl, s);
@@ -1172,7 +1205,6 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
     a.H = H; a.S = S; a.M = tree->M; a.words = tree->words;
     a.KVBH = B * Hkv; a.gq = H / Hkv; a.out_bf16 = out_dtype == LPP_BF16;
     a.msplits = p.msplits;
-    auto rc = [](uint32_t d) { return d <= 1 ? 0u : (uint32_t)((0x100000000ull + d - 1) / d); };
     a.scale_log2 = scale * 1.44269504088896340736f;
     const int64_t bpl = 8 * (((int64_t)B * Hkv + 7) / 8) * (H / Hkv) * p.msplits;
     AttnSplit sp = split_units(tree, p, bpl * nl);
@@ -1186,9 +1218,9 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
     while (partials() > ws_bytes) sp = sp.ns > 2 ? AttnSplit{sp.whole, sp.ns - 1} : AttnSplit{bpl * nl, 1};
     if (sp.whole + (bpl * nl - sp.whole) * sp.ns >= (1ll << 31)) return LPP_EUNSUPPORTED;
     a.whole = (uint32_t)sp.whole; a.nsplit = sp.ns;
-    a.rc_msplits = rc((uint32_t)p.msplits); a.rc_H = rc((uint32_t)H); a.rc_nsplit = rc((uint32_t)sp.ns);
-    a.rc_gq = rc((uint32_t)(H / Hkv));
-    a.blocks_per_layer = (uint32_t)bpl; a.rc_bpl = rc((uint32_t)bpl);
+    a.rc_msplits = reciprocal((uint32_t)p.msplits); a.rc_H = reciprocal((uint32_t)H); a.rc_nsplit = reciprocal((uint32_t)sp.ns);
+    a.rc_gq = reciprocal((uint32_t)(H / Hkv));
+    a.blocks_per_layer = (uint32_t)bpl; a.rc_bpl = reciprocal((uint32_t)bpl);
     a.counters = tree->d_counters + LPP_COUNTER_SLOTS;
     a.ws_o_bytes = (uint32_t)o_bytes; a.ws_ml_bytes = (uint32_t)ml_bytes;
     a.ws_o = reinterpret_cast<float*>(ws);
