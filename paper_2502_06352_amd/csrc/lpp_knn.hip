@@ -206,7 +206,9 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
   const bool vec = (a.D & 3) == 0 && (reinterpret_cast<uintptr_t>(a.E) & 15) == 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) a.redo[0] = 0;
   float mx[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int row = blockIdx.x * (kStatThreads / G) + threadIdx.x / G; row < a.V; row += gridDim.x * (kStatThreads / G)) {
+  // (short rows: zeros in the halves of the rows from V on, see CollectQuery)
+  for (int row = blockIdx.x * (kStatThreads / G) + threadIdx.x / G; row < (G == 4 ? a.Vp : a.V); row += gridDim.x * (kStatThreads / G)) {
+    const bool there = G != 4 || row < a.V;
     const float* src = a.E + (int64_t)row * a.D;
     float* dst = a.Ep + (int64_t)row * a.PD;
     float ss = 0.f, sa = 0.f, mb = 0.f;
@@ -215,7 +217,10 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
     const int dend = G == 4 ? (a.D > 8 ? 16 : 8) : a.PD;
     for (int d = 4 * sub; d < dend; d += 4 * G) {
       float v[4];
-      if (vec && d < a.D) {
+      if (!there) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = 0.f;
+      } else if (vec && d < a.D) {
         const f32x4 x = *reinterpret_cast<const f32x4*>(src + d);
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = x[e];
@@ -223,7 +228,7 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = d + e < a.D ? src[d + e] : 0.f;
       }
-      if (d < a.PD) *reinterpret_cast<f32x4*>(dst + d) = f32x4{v[0], v[1], v[2], v[3]};
+      if (there && d < a.PD) *reinterpret_cast<f32x4*>(dst + d) = f32x4{v[0], v[1], v[2], v[3]};
       if (G == 4) {
         // scale x = h + l + rest: two halves of 11 bits each (rest: at most 2^-24 of it, or 2^-25).  Both scales:
         // which one holds is known when all rows have been here.
@@ -239,8 +244,11 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
             h[e] = (_Float16)x;
             l[e] = (_Float16)(x - (float)h[e]);
           }
-          put_halves(wide ? a.Ew : a.Ef, row, n8, d, h, l);
           if (j >= 0) put_halves(wide ? a.Ews : a.Es, j, n8, d, h, l);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)                         // (see CollectQuery; the code is left out when it is ranked)
+            if (v[e] != v[e]) { h[e] = (_Float16)0.f; l[e] = (_Float16)0.f; }
+          put_halves(wide ? a.Ew : a.Ef, row, n8, d, h, l);
         }
       }
 #pragma unroll
@@ -258,7 +266,7 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
       mb = fmaxf(mb, __shfl_xor(mb, o));
     }
     const float n = sqrtf(ss);
-    if (sub == 0) { a.norms[row] = n; a.l1[row] = sa; }
+    if (there && sub == 0) { a.norms[row] = n; a.l1[row] = sa; }
     if (G > 4) hash = hash_end<G>(hash);
     if (G > 4 && sub == G - 1) a.hash[row] = hash;
     // (a row that holds a NaN has a NaN norm and takes no part in the maxima)
@@ -355,6 +363,35 @@ struct HalfOperand {
 #pragma unroll
     for (int i = 0; i < N; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[i], q.x[i], acc, 0, 0, 0);
     return acc;
+  }
+};
+
+// The same for the collecting sweep, whose loads bring 64 bytes a cycle and compute unit whatever is in them: every piece of a
+// code is loaded once, and a second MFMA takes the products with the query's lower parts.  N = 1: an operand holds the
+// pieces of two tiles, h l of the one and h l of the other, against h h 0 0 and l 0 0 0 or 0 0 h h and 0 0 l 0; N = 2:
+// h0 h1 l0 l1 against h0 h1 h0 h1 and l0 l1 0 0.  (A code's numbers meet zeros of another's lane: no NaN is in there, nor in the
+// rows from V on, and where one is infinite all rows take the exact path.)
+template <int N>
+struct CollectQuery {
+  f16x8 h[3 - N], l[3 - N];
+  __device__ __forceinline__ void load(const i32x4* row, int g4) {
+    const i32x4 zero = {0, 0, 0, 0};
+    if (N == 1) {
+      const i32x4 up = row[0], low = row[1];
+#pragma unroll
+      for (int t = 0; t < 3 - N; ++t) {
+        h[t] = __builtin_bit_cast(f16x8, g4 >> 1 == t ? up : zero);
+        l[t] = __builtin_bit_cast(f16x8, g4 == 2 * t ? low : zero);
+      }
+    } else {
+      h[0] = __builtin_bit_cast(f16x8, row[g4 & 1]);
+      l[0] = __builtin_bit_cast(f16x8, g4 >= 2 ? zero : row[2 + g4]);
+    }
+  }
+  __device__ __forceinline__ f32x4 times(f16x8 code, int tile, f32x4 acc) const {
+    const int t = N == 1 ? tile : 0;
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(code, h[t], acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(code, l[t], acc, 0, 0, 0);
   }
 };
 
@@ -643,30 +680,32 @@ __global__ __launch_bounds__(kCollectMaxWaves * 64) void knn_collect_f16_kernel(
   const RowPlan p = a.plan[row];
   const int windows = a.Vp / kWindowCodes;                 // (rows V .. Vp - 1 are there, whatever they hold)
   const float c0 = -p.thr;
-  HalfOperand<N> q;
   const i32x4* const Ef = __builtin_amdgcn_readfirstlane(p.flags) & kWide ? a.Ew : a.Ef;
-  q.load_query(Ef + (int64_t)rowc * 2 * N, g4);
+  CollectQuery<N> q;
+  q.load(Ef + (int64_t)rowc * 2 * N, g4);
   if (threadIdx.x < 16) s_cnt[threadIdx.x] = 0;
   __syncthreads();
   uint32_t* const parked = s_park + wave * (T * 256) + lane;
   const uint32_t list = (uint32_t)rowc * (uint32_t)a.cap, qmax = (1u << a.vmask_bits) - 2u;
   const int step = blockDim.x >> 6, room = row < a.V ? a.cap : 0;
-  const i32x4* const lane_row = Ef + (32 * (l16 >> 2) + (l16 & 3)) * 2 * N;
-  auto load = [&](HalfOperand<N> (&f)[4], int w, int h) {  // (past the end: the last window again, not used)
+  // (N = 1: tiles in pairs, the second one's pieces in the upper 32 lanes)
+  const i32x4* const lane_row = Ef + (32 * (l16 >> 2) + (l16 & 3)) * 2 * N + (N == 1 ? 8 * (g4 >> 1) + (g4 & 1) : g4);
+  constexpr int F = T / 2 * N;                             // pieces per lane and window
+  auto load = [&](f16x8 (&f)[F], int w) {                  // (past the end: the last window again, not used)
     const i32x4* const first = lane_row + (int64_t)min(w, windows - 1) * (kWindowCodes * 2 * N);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) f[u].load_code(first + (h + u) * 8 * N, g4);
+    for (int u = 0; u < F; ++u) f[u] = __builtin_bit_cast(f16x8, first[u * 16]);
   };
-  HalfOperand<N> f[4];
-  load(f, wave, 0);
+  f16x8 f[F], next[F];
+  load(f, wave);
   for (int w = wave; w < windows; w += step) {
+    load(next, w + step);
     uint32_t fail = 0;
 #pragma unroll
     for (int h = 0; h < T; h += 4) {
       f32x4 acc[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) acc[u] = f[u].times(q, f32x4{c0, c0, c0, c0});
-      load(f, h + 4 < T ? w : w + step, h + 4 < T ? h + 4 : 0);
+      for (int u = 0; u < 4; ++u) acc[u] = q.times(f[N == 1 ? (h + u) / 2 : h + u], u & 1, f32x4{c0, c0, c0, c0});
 #pragma unroll
       for (int u = 0; u < 4; ++u)
 #pragma unroll
@@ -678,6 +717,13 @@ __global__ __launch_bounds__(kCollectMaxWaves * 64) void knn_collect_f16_kernel(
     const int code0 = w * kWindowCodes + 32 * g4;
     uint32_t mask = ~fail;                                 // (codes past the end are not there)
     if (w == windows - 1) mask &= code0 + 32 <= a.V ? 0xFFFFFFFFu : (code0 < a.V ? ~(0xFFFFFFFFu >> (a.V - code0)) : 0u);
+    // (the next window's pieces have to be here before the list words are written: loads and stores are counted together,
+    // and a wait behind the stores, whose number differs, would be for all of them)
+#pragma unroll
+    for (int u = 0; u < F; ++u) {
+      f[u] = next[u];
+      asm volatile("" : "+v"(f[u]));
+    }
     const int n = __popc(mask);
     const int base = n > 0 ? atomicAdd(&s_cnt[l16], n) : 0;
     emit_window(a.cand, list + (uint32_t)base, base + n > room ? 0u : mask,
@@ -803,16 +849,22 @@ __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(K
       fail[n] = 0;
     }
   };
+  Chunk n0 = fetch(0), n1 = fetch(1);
   auto work = [&](int c, int b) {
 #pragma unroll
     for (int j = 0; j < CT; ++j) {
       const int i = c * CT + j;
       if (i >= own) break;                                 // uniform
       tile_work(s_code[b] + j * TQ + lane, i);
-      if ((i + 1) % T == 0 || i + 1 == own) emit(i + 1);
+      if ((i + 1) % T == 0 || i + 1 == own) {
+        // (the chunks asked for have to be here before the list words are written: loads and stores are counted together,
+        // and a wait behind the stores, whose number differs, would be for all of them)
+#pragma unroll
+        for (int x = 0; x < PER; ++x) asm volatile("" : "+v"(n0.x[x]), "+v"(n1.x[x]));
+        emit(i + 1);
+      }
     }
   };
-  Chunk n0 = fetch(0), n1 = fetch(1);
   park(n0, 0);
   __syncthreads();
   for (int c = 0; c * CT < own; c += 2) {

@@ -76,6 +76,22 @@ def test_knn_codes_that_hold_a_nan_come_last(V, D, k):
     _check(E, k, np.unique(np.concatenate([[3, 7, 11, V // 2, V - 2], g.choice(V, size=100)])))
 
 
+@pytest.mark.parametrize("V,D,k", [(1030, 8, 40), (2500, 6, 300), (2047, 13, 64), (1100, 16, 1100), (700, 40, 30)])
+def test_knn_does_not_depend_on_what_the_workspace_held(V, D, k):
+    # NaN and infinities in every piece of it, and codes that hold a NaN beside others
+    g = np.random.default_rng(V)
+    E = _unit(g, V, D)
+    E[[5, V - 1], 0] = np.nan
+    want = build_neighbours(E, k)
+    e, ws = dev(E), torch.empty(lpp.lpp_build_neighbours_workspace(V, D, k), dtype=torch.uint8, device=DEV)
+    for fill in (0xFF, 0x7C):
+        ws.fill_(fill)
+        neigh = torch.empty((V, k), dtype=torch.int32, device=DEV)
+        lpp.lpp_build_neighbours(e, k, neigh, ws)
+        rows = np.setdiff1d(np.arange(V), [5, V - 1])
+        assert np.array_equal(neigh.cpu().numpy()[rows], want[rows]), hex(fill)
+
+
 def _least_ms(E, k):
     """Least time of one build, device time, of a few."""
     V, D = E.shape
