@@ -12,7 +12,7 @@
 //            about 4096 codes; the threshold is the sample's quantile at which, five
 //            standard deviations of the sample's share allowed, k - 1 codes lie above (short rows: its
 //            bin looked at again in 1024 parts where a few codes far longer than the rest crowd the others into it)
-//   collect  the dense V x V contraction on the matrix cores, once: every code above the
+//   collect  the dense V x V contraction on the matrix cores, once (long rows: its half, it is symmetric): every code above the
 //            row's threshold is appended to its list as one 32-bit word, similarity
 //            (fixed point) over code index
 //   rank     per row: the list is sorted by its approximate similarities (value buckets in
@@ -91,7 +91,7 @@ constexpr int kAll = 1, kAnyNan = 2, kNoList = 4, kFlat = 8, kWide = 16;
 // entry's key, a chain that short costs less than the sums and their comparison (every code four times, 4096 x 64,
 // k = 300: 91 us and 162).  Few entries: the chain's loads in turn cost more (2000 x 64, k = 50: 37.4 us and 36.2).
 constexpr int kChainFloats = 64;
-constexpr int kMaxSplits = 16;                // segments of a long row's list
+constexpr int kMaxSplits = 16;                // (long rows) blocks that share a group's tiles
 constexpr int kUnits = 256;                   // compute units of the card these kernels are for
 constexpr size_t kMostLds = 150 * 1024;       // dynamic LDS of a block, static arrays beside it
 
@@ -106,7 +106,7 @@ struct KnnArgs {
   int32_t stride, ns, m;   // sample: one of every `stride` codes, ns in all, threshold at its m-th largest
   int32_t take_all;     // the list takes every code
   int32_t most;         // sampled codes above a threshold, at which the list is likely to overflow
-  int32_t splits, cap_split;   // (long rows) segments of a row's list, one per block that collects for it, and their size
+  int32_t splits;       // (long rows) blocks that share the tiles of a group of 128 rows
   int32_t statblocks;
   float* Ep;            // [V][PD]
   i32x4* Ef;            // long rows: [Vp/16][KS][3 limbs][64 lanes] fragments
@@ -123,7 +123,7 @@ struct KnnArgs {
   float4* part;         // [kStatBlocks]: max norm, max |x|, max 1-norm, any NaN
   RowPlan* plan;        // [Vp]
   float* reach;         // [Vp] what the magnitudes of a row's products with any code add up to at most (long rows)
-  int32_t* cnt;         // [V][splits]
+  int32_t* cnt;         // [V] entries of the row's list, or more than `cap` where it overflowed
   uint32_t* cand;       // [V][cap]
   int32_t* redo;        // [1 + V]: rows that take the exact path, their number first
   int32_t* neigh;       // [V][k]
@@ -267,6 +267,7 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
     }
     const float n = sqrtf(ss);
     if (there && sub == 0) { a.norms[row] = n; a.l1[row] = sa; }
+    if (G > 4 && sub == 0) a.cnt[row] = 0;
     if (G > 4) hash = hash_end<G>(hash);
     if (G > 4 && sub == G - 1) a.hash[row] = hash;
     // (a row that holds a NaN has a NaN norm and takes no part in the maxima)
@@ -626,6 +627,13 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   if (FIXED) a.reach[row] = l1 * st.mabs;                   // (not the norms: squares of small numbers vanish in them)
 }
 
+// Groups of 128 codes whose tiles a group's blocks take: itself and those up to half way round; of two that lie opposite
+// the first.  Tiles of block `split` of `splits`.
+__host__ __device__ inline int collect_tiles(int groups, int group, int split, int splits) {
+  const int tiles = 8 * (groups % 2 ? groups / 2 + 1 : groups / 2 + (group < groups / 2 ? 1 : 0));
+  return split < tiles ? (tiles - split + splits - 1) / splits : 0;
+}
+
 // What both collecting kernels do with the similarities they form: a lane holds four of one row per
 // code tile, less the row's threshold (which the sums start from).  It parks them in LDS as they are
 // and shifts their sign bits into a mask, one instruction each.  After a window of tiles the lanes take the clear bits
@@ -736,11 +744,17 @@ __global__ __launch_bounds__(kCollectMaxWaves * 64) void knn_collect_f16_kernel(
 // Long rows, fixed point: a wave owns 32 queries (two B operands, held in registers with all their
 // limbs), a block's four waves 128.  Code tiles come through LDS, fragment by fragment as they lie
 // in memory, one copy for the four waves (each limb fragment read feeds 32 queries), the next two
-// chunks' loads in flight while one is worked on.  Two blocks per compute unit.  The code tiles are
-// dealt to `splits` blocks, each with a segment of its own in a row's list: where an entry goes is
-// known without asking anybody (a counter per row in memory makes the wave wait for it, and the other
-// three for that wave at the next barrier).  8192 rows of 256: 130 us, matrix cores busy 42 % of it (the
-// similarities alone, in bf16 and twice over, took 259 us and told less).
+// chunks' loads in flight while one is worked on.  Two blocks per compute unit.
+// The sums are the same whichever of two codes is the query, so each pair of groups of 128 codes is taken once: a group's
+// blocks take the groups up to half way round from it (their tiles dealt to `splits` blocks), and a window's similarities,
+// parked in LDS, are looked at a second time with a lane per code, 32 queries each, for the lists of the codes.
+// The row's list is one, whoever adds to it: a wave asks for its places with an add in memory and has them when the
+// products of the next tile are done; only then does it write the window's words.
+// (Every pair from both sides, a list in segments, one per block that adds to it: the kernel 115 us at 8192 x 256,
+// k = 1000, 78 of them its products alone, and now 77; the build 236 -> 191, 16384 x 256 696 -> 533, 4096 x 64, k = 300
+// 57.9 -> 51.3, 1024 x 256, k = 100 38.0 -> 36.6.)
+// Bound by the matrix cores, whose rate for 8-bit numbers the card's power limits (products of random numbers alone take
+// 1.35 times what they would at 2.4 GHz, of numbers below 16 1.14 times), then by the windows' masks and words.
 template <int KS>
 __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(KnnArgs a) {
   constexpr int T = 4;                                     // tiles per window: 16 similarities per row and lane
@@ -751,30 +765,33 @@ __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(K
   static_assert(CQ % 64 == 0 && T % CT == 0, "chunks end with windows");
   constexpr int PER = (CQ + NTHR - 1) / NTHR;
   __shared__ i32x4 s_code[2][CQ];
-  __shared__ i32x4 s_park[kCollectWaves][2][T * 64];
+  __shared__ i32x4 s_park[kCollectWaves][2][T * 64];       // [query tile][code tile][lane]: the lane's four codes
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g4 = lane >> 4;
   const int group = blockIdx.x / a.splits, split = blockIdx.x - group * a.splits;
   const int qtile = group * (kCollectWaves * 2) + wave * 2;
-  const int ntiles = (a.V + 15) >> 4;
+  const int ntiles = (a.V + 15) >> 4, alltiles = a.Vp >> 4;
+  const uint32_t qmax = (1u << a.vmask_bits) - 2u;
   const i32x4* const Ef = a.Ef;
-  int start[2], out[2] = {0, 0};                             // out: places of the row's segment taken (by all its lanes)
+  int thr[2];
   float scale[2];
-  uint32_t list[2];
   i32x4 q[2][KS][3];
 #pragma unroll
   for (int n = 0; n < 2; ++n) {
-    const int row = (qtile + n) * 16 + l16;
-    const RowPlan p = a.plan[row];                         // (rows past V: nothing passes)
-    start[n] = -p.thr_u; scale[n] = p.a;
-    list[n] = ((uint32_t)min(row, a.V - 1) * (uint32_t)a.splits + (uint32_t)split) * (uint32_t)a.cap_split;
+    const RowPlan p = a.plan[(qtile + n) * 16 + l16];      // (rows past V: nothing passes)
+    thr[n] = p.thr_u; scale[n] = p.a;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
       for (int l = 0; l < 3; ++l) q[n][ks][l] = Ef[((int64_t)((qtile + n) * KS + ks) * 3 + l) * 64 + lane];
   }
-  // this block's tiles: split + i splits, i = 0 .. own - 1; chunk c holds i = c CT ..
-  const int own = split < ntiles ? (ntiles - split + a.splits - 1) / a.splits : 0;
+  // the group's tiles: its own eight, then those of the groups after it, half way round; of two groups that lie opposite
+  // the first takes the pair.  This block's: split + i splits, i = 0 .. own - 1; chunk c holds i = c CT ..
+  const int own = collect_tiles(a.Vp >> 7, group, split, a.splits);
+  auto tile_at = [&](int i) {
+    const int t = group * 8 + split + i * a.splits;
+    return t < alltiles ? t : t - alltiles;
+  };
   // two chunks' loads are in flight while a third is worked on (past the end: the last tile again, not used)
   struct Chunk { i32x4 x[PER]; };
   auto fetch = [&](int c) {
@@ -782,7 +799,7 @@ __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(K
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int o = min(tid + i * NTHR, CQ - 1);
-      const int t = min(split + (c * CT + o / TQ) * a.splits, ntiles - 1);
+      const int t = tile_at(min(c * CT + o / TQ, own - 1));
       k.x[i] = Ef[(int64_t)t * TQ + o % TQ];
     }
     return k;
@@ -793,13 +810,86 @@ __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(K
       if (CQ % NTHR == 0 || tid + i * NTHR < CQ) s_code[b][tid + i * NTHR] = k.x[i];
   };
   uint32_t fail[2] = {0, 0};
+  // what a window leaves to be written
+  struct Window {
+    uint32_t rows[2], codes;                               // masks: a query's codes, a code's queries
+    int before[2];                                         // entries of the row in the lanes before this one (of four)
+    int at_row, at_code;                                   // places: lane 16 n + l16 holds row l16's of tile n; a code's own lane
+    uint32_t code0;                                        // first code of the lane, without the turn round the end
+    int code, thr;                                         // the code as a row, its plan
+    float scale;
+  } win;
+  const int* const parked = reinterpret_cast<const int*>(s_park[wave]);
+  // The lane's code in a window: tile lane >> 4, code lane & 15 of it, which lane group (lane >> 2) & 3 holds as its number
+  // lane & 3.  Step s of the second look: query tile s >> 4, query (s & 15) ^ (lane >> 2), so that a read's lanes lie in 64 banks.
+  const int turn = lane >> 2;
+  const int* const column = parked + turn * 64 + (lane & 3);
+  auto emit = [&]() {
+    const uint32_t tile_step = (uint32_t)(16 * a.splits);
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      const int base = __shfl(win.at_row, 16 * n + l16) + win.before[n];
+      const int row = min((qtile + n) * 16 + l16, a.V - 1);
+      const int* const mine = parked + n * (T * 256) + lane * 4;
+      emit_window(a.cand, (uint32_t)row * (uint32_t)a.cap + (uint32_t)base, base + __popc(win.rows[n]) <= a.cap ? win.rows[n] : 0u,
+                  [&](uint32_t s) {
+                    const uint32_t hi = s >> 2, lo = s & 3, t = __umul24(hi, tile_step) + win.code0;
+                    return (list_value((float)(mine[hi * 256 + lo] - thr[n]), scale[n], qmax) << a.ib) | min(t, t - (uint32_t)a.Vp) | lo;
+                  });
+    }
+    emit_window(a.cand, (uint32_t)win.code * (uint32_t)a.cap + (uint32_t)win.at_code,
+                win.at_code + __popc(win.codes) <= a.cap ? win.codes : 0u, [&](uint32_t s) {
+                  const uint32_t x = (s ^ (uint32_t)turn) & 15u, n = s >> 4;
+                  return (list_value((float)(column[n * (T * 256) + x * 4] - win.thr), win.scale, qmax) << a.ib) |
+                         ((uint32_t)(qtile * 16) + n * 16 + x);
+                });
+  };
+  // the window that ends with the block's tile number i - 1: its masks, and its places are asked for
+  auto close = [&](int i) {
+    const int i0 = (i - 1) / T * T, have = i - i0;
+    int total[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      // the four lanes of a row put their entries one after the other
+      win.rows[n] = ~fail[n] << (32 - 4 * have);
+      fail[n] = 0;
+      const int cnt = __popc(win.rows[n]);
+      const int c1 = __shfl(cnt, l16), c2 = __shfl(cnt, l16 + 16), c3 = __shfl(cnt, l16 + 32), c4 = __shfl(cnt, l16 + 48);
+      win.before[n] = (g4 > 0 ? c1 : 0) + (g4 > 1 ? c2 : 0) + (g4 > 2 ? c3 : 0);
+      total[n] = c1 + c2 + c3 + c4;
+    }
+    win.code0 = (uint32_t)((group * 8 + split + i0 * a.splits) * 16 + 4 * g4);
+    const int mine = g4 == 0 ? total[0] : (g4 == 1 ? total[1] : 0);
+    win.at_row = 0;
+    if (mine > 0) win.at_row = __hip_atomic_fetch_add(a.cnt + (qtile * 16 + lane), mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the same similarities for the codes' lists (a group with itself has them in both its halves)
+    const int it = i0 + (lane >> 4);
+    const bool there = it < i && split + it * a.splits >= 8;
+    win.codes = 0;
+    if (split + (i - 1) * a.splits >= 8) {                 // uniform
+      uint32_t miss = 0;
+#pragma unroll
+      for (int s = 0; s < 32; ++s)
+        miss = shift_in_sign(miss, column[(s >> 4) * (T * 256) + (((s & 15) ^ turn) * 4)] - win.thr);
+      uint32_t m = ~miss;
+      if ((qtile + 2) * 16 > a.V) {                        // uniform: rows past the end are in nobody's list
+        const int last = a.V - qtile * 16;
+#pragma unroll 1
+        for (int s = 0; s < 32; ++s)
+          if ((s & 16) + ((s & 15) ^ turn) >= last) m &= ~(0x80000000u >> s);
+      }
+      win.codes = there ? m : 0u;
+    }
+    const int cnt = __popc(win.codes);
+    win.at_code = 0;
+    if (cnt > 0) win.at_code = __hip_atomic_fetch_add(a.cnt + win.code, cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  Chunk n0, n1;
+  bool full = false;                                       // uniform: a window waits to be written
   auto tile_work = [&](const i32x4* tile, int i) {         // i: the block's tile number
     i32x4 aa[2], ab[2], bb[2], bc[2];
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      aa[n] = bb[n] = bc[n] = i32x4{0, 0, 0, 0};
-      ab[n] = i32x4{start[n], start[n], start[n], start[n]};
-    }
+    for (int n = 0; n < 2; ++n) aa[n] = ab[n] = bb[n] = bc[n] = i32x4{0, 0, 0, 0};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       const i32x4 fa = tile[(ks * 3 + 0) * 64], fb = tile[(ks * 3 + 1) * 64], fc = tile[(ks * 3 + 2) * 64];
@@ -817,52 +907,46 @@ __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(K
       LPP_LIMB(bb, fc, 0);
 #undef LPP_LIMB
     }
-#pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      i32x4 d;                                             // the similarity less the threshold, in units of 2^24 unit^2 (each below 2^30)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        d[r] = (aa[n][r] << 8) + ab[n][r] + ((bb[n][r] + (bc[n][r] >> 8)) >> 8);
-        fail[n] = shift_in_sign(fail[n], d[r]);
-      }
-      s_park[wave][n][(i % T) * 64 + lane] = d;
-    }
-  };
-  // the window that ends with the block's tile number i - 1
-  auto emit = [&](int i) {
-    const int i0 = (i - 1) / T * T, have = i - i0;
-    const uint32_t code0 = (uint32_t)((split + i0 * a.splits) * 16 + 4 * g4), tile_step = (uint32_t)(16 * a.splits);
-    const uint32_t qmax = (1u << a.vmask_bits) - 2u;
-#pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      // the four lanes of a row put their entries one after the other
-      const uint32_t m = ~fail[n] << (32 - 4 * have);
-      const int cnt = __popc(m);
-      const int c1 = __shfl(cnt, l16), c2 = __shfl(cnt, l16 + 16), c3 = __shfl(cnt, l16 + 32), c4 = __shfl(cnt, l16 + 48);
-      const int base = out[n] + (g4 > 0 ? c1 : 0) + (g4 > 1 ? c2 : 0) + (g4 > 2 ? c3 : 0);
-      const int* const mine = reinterpret_cast<const int*>(s_park[wave][n] + lane);
-      emit_window(a.cand, list[n] + (uint32_t)base, (qtile + n) * 16 + l16 < a.V && base + cnt <= a.cap_split ? m : 0u, [&](uint32_t s) {
-        const uint32_t hi = s >> 2, lo = s & 3;
-        return (list_value((float)mine[hi * 256 + lo], scale[n], qmax) << a.ib) | (__umul24(hi, tile_step) + code0) | lo;
-      });
-      out[n] += c1 + c2 + c3 + c4;
-      fail[n] = 0;
-    }
-  };
-  Chunk n0 = fetch(0), n1 = fetch(1);
-  auto work = [&](int c, int b) {
-#pragma unroll
-    for (int j = 0; j < CT; ++j) {
-      const int i = c * CT + j;
-      if (i >= own) break;                                 // uniform
-      tile_work(s_code[b] + j * TQ + lane, i);
-      if ((i + 1) % T == 0 || i + 1 == own) {
+    if (i % T == 0) {                                      // uniform
+      if (full) {
         // (the chunks asked for have to be here before the list words are written: loads and stores are counted together,
         // and a wait behind the stores, whose number differs, would be for all of them)
 #pragma unroll
         for (int x = 0; x < PER; ++x) asm volatile("" : "+v"(n0.x[x]), "+v"(n1.x[x]));
-        emit(i + 1);
+        emit();
       }
+      win.code = tile_at(min(i + (lane >> 4), own - 1)) * 16 + l16;
+      const RowPlan p = a.plan[win.code];
+      win.thr = p.thr_u;
+      win.scale = p.a;
+    }
+    const bool past = tile_at(i) >= ntiles;                // uniform: no codes there
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      i32x4 d;                                             // the similarity, in units of 2^24 unit^2 (each below 2^30, and so are the thresholds)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        d[r] = (aa[n][r] << 8) + ab[n][r] + ((bb[n][r] + (bc[n][r] >> 8)) >> 8);
+        fail[n] = shift_in_sign(fail[n], d[r] - thr[n]);
+      }
+      if (past) fail[n] |= 15u;
+      s_park[wave][n][(i % T) * 64 + lane] = d;
+    }
+    full = (i + 1) % T == 0 || i + 1 == own;
+    if (full) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");           // (the other lanes' similarities are read)
+      __builtin_amdgcn_wave_barrier();
+      close(i + 1);
+    }
+  };
+  if (own == 0) return;                                    // uniform over the block
+  n0 = fetch(0);
+  n1 = fetch(1);
+  auto work = [&](int c, int b) {
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+      if (c * CT + j >= own) break;                        // uniform
+      tile_work(s_code[b] + j * TQ + lane, c * CT + j);
     }
   };
   park(n0, 0);
@@ -878,11 +962,7 @@ __global__ __launch_bounds__(kCollectWaves * 64, 2) void knn_collect_i8_kernel(K
     park(n0, 0);
     __syncthreads();
   }
-#pragma unroll
-  for (int n = 0; n < 2; ++n) {
-    const int row = (qtile + n) * 16 + l16;
-    if (g4 == 0 && row < a.V) a.cnt[(int64_t)row * a.splits + split] = out[n];
-  }
+  emit();                                                  // (the last window ends with the block's last tile)
 }
 
 // ------------------------------------------------------------------------------------------ ranking
@@ -1521,43 +1601,14 @@ __global__ __launch_bounds__(NTHR, LATER || !STAGED || NTHR == 1024 ? 8 : 6) voi
   const uint32_t* list = a.cand + (int64_t)i * a.cap;
   const uint32_t mask = (1u << a.ib) - 1u;
   uint32_t w[EPT], on = 0;
-  int n;
-  bool over;                                                // uniform: the list does not hold everything it should
+  const int n = a.cnt[i];
+  const bool over = n > a.cap;                              // uniform: the list does not hold everything it should
 #pragma unroll
   for (int u = 0; u < EPT; ++u) w[u] = 0;
-  if constexpr (STAGED) {
-    // the list's segments one after the other: lane s of every wave holds the end of segment s
-    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c = lane < a.splits ? a.cnt[(int64_t)i * a.splits + lane] : 0;
-    list = a.cand + (int64_t)i * a.splits * a.cap_split;
-    int end = c;
 #pragma unroll
-    for (int o = 1; o < kMaxSplits; o <<= 1) {
-      const int t = __shfl_up(end, o);
-      if (lane >= o) end += t;
-    }
-    n = __builtin_amdgcn_readlane(end, kMaxSplits - 1);    // (lanes behind the last segment hold the total as well)
-    over = __any(c > a.cap_split) || n > a.cap;
-    int s = 0, s0 = 0, s1 = __builtin_amdgcn_readlane(end, 0);
-    if (!over)
-#pragma unroll
-      for (int u = 0; u < EPT; ++u) {
-        const int g0 = wv * 64 + u * NTHR, g = g0 + lane;
-        while (s < a.splits && s1 <= g0) { s0 = s1; ++s; s1 = __builtin_amdgcn_readlane(end, s); }     // (scalar)
-        for (; s < a.splits; ) {                            // 64 entries lie in one or two segments as a rule
-          if (g >= s0 && g < s1) w[u] = list[s * a.cap_split + g - s0];
-          if (s1 >= g0 + 64) break;
-          s0 = s1; ++s; s1 = __builtin_amdgcn_readlane(end, s);
-        }
-      }
-  } else {
-    n = a.cnt[i];
-    over = n > a.cap;
-#pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-      const int c = tid + u * NTHR;
-      if (u * NTHR < n && c < min(n, a.cap)) w[u] = list[c];
-    }
+  for (int u = 0; u < EPT; ++u) {
+    const int c = tid + u * NTHR;
+    if (u * NTHR < n && c < min(n, a.cap)) w[u] = list[c];
   }
   double* eid = reinterpret_cast<double*>(smem);
   for (int d = tid; d < a.PD; d += NTHR) eid[d] = (double)a.Ep[(int64_t)i * a.PD + d];
@@ -1704,7 +1755,7 @@ __global__ __launch_bounds__(kDirectThreads) void knn_direct_kernel(KnnArgs a, R
 
 struct KnnLayout {
   size_t o_ep, o_ef, o_es, o_ew, o_ews, o_norms, o_l1, o_hash, o_seen, o_twin, o_part, o_plan, o_reach, o_cnt, o_redo, o_cand, total;
-  int32_t PD, KS, Vp, cap, ib, vb, stride, ns, m, take_all, most, splits, cap_split, seen_shift;
+  int32_t PD, KS, Vp, cap, ib, vb, stride, ns, m, take_all, most, splits, seen_shift;
 };
 
 int log2_up(int x) { int l = 0; while ((1 << l) < x) ++l; return l; }
@@ -1733,15 +1784,8 @@ KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   L.cap = L.take_all ? L.Vp : (int32_t)std::min<size_t>(L.Vp, lpp_align_up((size_t)(expect + 5.0 * dev) + 64 + V / 256, 64));
   L.most = L.m + (int)std::max(0.0, (L.cap - expect) / (2.0 * L.stride));
   // long rows: blocks of 128 queries by `splits` shares of the code tiles, two blocks per compute unit
-  const int ntiles = (V + 15) / 16, groups = L.Vp / 128;
-  L.splits = L.KS ? std::max(1, std::min({2 * kUnits / groups, ntiles, kMaxSplits})) : 1;
-  L.cap_split = L.cap;
-  if (L.splits > 1) {
-    const int tiles = (ntiles + L.splits - 1) / L.splits;
-    const double share = (expect + 5.0 * dev) / L.splits + 16;
-    L.cap_split = L.take_all ? 16 * tiles : std::min(16 * tiles, (int)lpp_align_up((size_t)(share + 6.0 * sqrt(share)), 16));
-  }
-  const size_t entries = (size_t)std::max(L.cap, L.splits * L.cap_split);
+  const int groups = L.Vp / 128;
+  L.splits = L.KS ? std::max(1, std::min({2 * kUnits / groups, 8 * (groups / 2 + 1), kMaxSplits})) : 1;
   size_t o = 0;
   auto take = [&](size_t bytes) { const size_t at = o; o += lpp_align_up(bytes, 256); return at; };
   L.o_ep = take((size_t)V * L.PD * sizeof(float));
@@ -1759,9 +1803,9 @@ KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   L.o_part = take((size_t)kStatBlocks * sizeof(float4));
   L.o_plan = take((size_t)L.Vp * sizeof(RowPlan));
   L.o_reach = take(L.KS ? (size_t)L.Vp * sizeof(float) : 0);
-  L.o_cnt = take((size_t)V * L.splits * sizeof(int32_t));
+  L.o_cnt = take((size_t)V * sizeof(int32_t));
   L.o_redo = take((size_t)(V + 1) * sizeof(int32_t));
-  L.o_cand = take((size_t)V * entries * sizeof(uint32_t));
+  L.o_cand = take((size_t)V * L.cap * sizeof(uint32_t));
   L.total = o;
   return L;
 }
@@ -1864,7 +1908,7 @@ extern "C" int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, in
   unsigned char* w = reinterpret_cast<unsigned char*>(ws);
   KnnArgs a;
   a.E = E; a.V = V; a.D = D; a.k = k; a.PD = L.PD; a.Vp = L.Vp; a.cap = L.cap; a.ib = L.ib; a.vmask_bits = L.vb;
-  a.stride = L.stride; a.ns = L.ns; a.m = L.m; a.take_all = L.take_all; a.most = L.most; a.splits = L.splits; a.cap_split = L.cap_split;
+  a.stride = L.stride; a.ns = L.ns; a.m = L.m; a.take_all = L.take_all; a.most = L.most; a.splits = L.splits;
   a.Ep = reinterpret_cast<float*>(w + L.o_ep);
   a.Ef = reinterpret_cast<i32x4*>(w + L.o_ef);
   a.Es = reinterpret_cast<i32x4*>(w + L.o_es);

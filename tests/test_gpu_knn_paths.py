@@ -92,6 +92,20 @@ def test_knn_does_not_depend_on_what_the_workspace_held(V, D, k):
         assert np.array_equal(neigh.cpu().numpy()[rows], want[rows]), hex(fill)
 
 
+@pytest.mark.parametrize("order", ["random", "walk"])
+@pytest.mark.parametrize("V,D,k", [(120, 20, 9), (128, 64, 128), (129, 65, 40), (256, 33, 20), (257, 130, 257), (384, 17, 15), (500, 256, 60),
+                                   (640, 129, 33), (641, 64, 12), (1279, 40, 100), (2047, 24, 31)])
+def test_knn_long_rows_each_pair_of_groups_once(V, D, k, order):
+    # one group of 128 codes, two that lie opposite, odd and even numbers of them, a last one of a single code, of all
+    # but one; neighbours anywhere, or beside each other, so that all of a list comes from one side of the row
+    g = np.random.default_rng(V)
+    E = _unit(g, V, D)
+    if order == "walk":
+        E = np.cumsum(0.3 * E + 0.05, axis=0)
+        E = (E / np.linalg.norm(E, axis=1, keepdims=True)).astype(np.float32)
+    _check(E, k)
+
+
 def _least_ms(E, k):
     """Least time of one build, device time, of a few."""
     V, D = E.shape
