@@ -150,11 +150,13 @@ __device__ __forceinline__ Stats reduce_stats(const KnnArgs& a, int lane) {
     v[0] = fmaxf(v[0], x.x); v[1] = fmaxf(v[1], x.y); v[2] = fmaxf(v[2], x.z); v[3] = fmaxf(v[3], x.w);
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = fmaxf(v[q], __shfl_xor(v[q], o));
-#pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v[q])));
+  for (int q = 0; q < 4; ++q) {                             // (none is below zero)
+#define LPP_MAX(ctrl, rows) v[q] = fmaxf(v[q], __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[q]), ctrl, rows, 0xf, false)))
+    LPP_MAX(0x111, 0xf); LPP_MAX(0x112, 0xf); LPP_MAX(0x114, 0xf); LPP_MAX(0x118, 0xf);     // row_shr:1, 2, 4, 8
+    LPP_MAX(0x142, 0xa); LPP_MAX(0x143, 0xc);               // row_bcast:15, 31
+#undef LPP_MAX
+    v[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[q]), 63));
+  }
   return Stats{v[0], v[1], v[2], v[3]};
 }
 
@@ -347,9 +349,11 @@ __global__ __launch_bounds__(256) void knn_limb_kernel(KnnArgs a) {
 template <int N>
 struct HalfOperand {
   f16x8 x[N];
-  __device__ __forceinline__ void load_code(const i32x4* row, int g4) {
-    x[0] = __builtin_bit_cast(f16x8, row[N == 1 ? (g4 == 1 ? 1 : 0) : g4]);
-    if (N == 2) x[N - 1] = __builtin_bit_cast(f16x8, row[g4 & 1]);
+  // (tile: the same for the wave; its 16 codes are there, whatever those past the end hold)
+  __device__ __forceinline__ void load_code(const i32x4* tile, int l16, int g4) {
+    const uint32_t row = (uint32_t)(l16 * 2 * N);
+    x[0] = __builtin_bit_cast(f16x8, tile[row + (N == 1 ? (g4 == 1 ? 1 : 0) : g4)]);
+    if (N == 2) x[N - 1] = __builtin_bit_cast(f16x8, tile[row + (g4 & 1)]);
   }
   __device__ __forceinline__ void load_query(const i32x4* row, int g4) {
     const i32x4 zero = {0, 0, 0, 0};
@@ -396,27 +400,33 @@ struct CollectQuery {
   }
 };
 
-// Histogram of 16 rows' similarities with the sample, the threshold bin of each row, and its plan.
+// Histogram of 16 NQ rows' similarities with the sample, the threshold bin of each row, and its plan.
 // N: pieces of 8 dimensions (short rows, FIXED = false) or steps of 64 limbs (FIXED).  The
-// histogram is laid out bin by bin with the 16 rows side by side, so the 64 lanes of an LDS add,
+// histogram is laid out bin by bin with 16 rows side by side, so the 64 lanes of an LDS add,
 // four per row, meet in at most a few banks: [bins][16] counts, 64 KB, two
 // blocks per compute unit.  (With rows of bins one after the other the adds collide at random and a
-// wave-wide add takes about 29 cycles.)
-template <bool FIXED, int N>
-__global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a) {
+// wave-wide add takes about 29 cycles.)  NQ = 2: 32 rows, a word counts for row l16 in its lower half and for row 16 + l16 in its upper
+// one (a sample has fewer than 2 kSampleCodes codes).  What that halves: the sample's codes out of L2, which bound the
+// kernel for long rows (8192 x 256: 28.5 -> 21.5 us, 7.5 of it not the sweep), and the turns of blocks at everything that is not
+// the sweep (16384 x 8: 26 -> 21 us; 12.5 of 28 were not).
+template <bool FIXED, int N, int NQ>
+__global__ __launch_bounds__(kSampleThreads, FIXED && NQ == 2 && N >= 3 ? 4 : 8) void knn_sample_kernel(KnnArgs a) {
   extern __shared__ __align__(16) uint32_t s_hist[];      // [kSampleBins][16]
   constexpr int SEG = kSampleThreads / 16, SW = kSampleBins / SEG;   // segments of the bins, bins of each
-  __shared__ int s_seg[kSampleThreads / 64][16];           // counts of a wave's segments, per row
-  __shared__ int s_top[16], s_upper[16], s_bin[16], s_fine[16], s_crowded[17];   // [16]: any row
+  constexpr int R = 16 * NQ;                               // rows of the block
+  __shared__ uint32_t s_seg[kSampleThreads / 64][16];      // counts of a wave's segments, per row
+  __shared__ int s_top[R], s_upper[R], s_bin[R], s_fine[R], s_crowded[R + 1];   // [R]: any row
   constexpr int W = kSampleThreads / 64;
+  static_assert(2 * kSampleCodes <= 65536, "two counts in a word");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l16 = lane & 15;
-  const int row0 = blockIdx.x * 16, row = row0 + l16, rowc = min(row, a.V - 1);
-  // (for the look at the row's copies below, by waves 1 .. 8: asked for now)
-  const int own = min(max(row0 + 2 * (wave - 1) + (lane >> 5), 0), a.V - 1);
+  const int row0 = blockIdx.x * R;
+  // (for the look at the rows' copies below, two to a wave: asked for now; 16 rows: by waves 1 .. 8)
+  const int own = min(max(row0 + 2 * (NQ == 2 ? wave : wave - 1) + (lane >> 5), 0), a.V - 1);
   const uint32_t own_hash = FIXED ? a.hash[own] : 0u;
   const Stats st = reduce_stats(a, lane);
   const int seen1 = FIXED ? a.seen[seen_slot(a, own_hash)] : 0, seen2 = FIXED ? a.seen[other_slot(a, own_hash)] : 0;
+  // lane: row l16 of each 16 for the sweep, row `lane` for the plan
+  const int row = row0 + (lane & (R - 1)), rowc = min(row, a.V - 1);
   const float norm = a.norms[rowc], l1 = a.l1[rowc];
   const float top = norm * st.norm * 1.0001f;              // |similarity| stays below
   const bool wide = !FIXED && st.mabs * kHalfScale >= 65504.0f;
@@ -428,30 +438,40 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   const bool finite = top > 1e-30f && top < INFINITY && (FIXED || st.mabs * hscale < 65504.0f);
 
   if (!a.take_all) {
-    if (tid < 17) { s_top[tid & 15] = 0; s_bin[tid & 15] = 0; s_crowded[tid] = 0; }
+    if (tid < R) { s_top[tid] = 0; s_bin[tid] = 0; }
+    if (tid <= R) s_crowded[tid] = 0;
     const int ntiles = (a.ns + 15) / 16;
-    float per_bin = finite ? (kSampleBins / 2) * to_sim / top : 0.f, middle = kSampleBins / 2;
-    auto add = [&](float v, int l16) {
-      const uint32_t bin = min((uint32_t)__builtin_fmaf(v, per_bin, middle), kSampleBins - 1u);   // (negative, NaN: 0)
-      atomicAdd(&s_hist[bin * 16 + l16], 1u);
-    };
+    float per_bin[NQ], middle[NQ];
+    bool fin[NQ];
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      const float mine = finite ? (kSampleBins / 2) * to_sim / top : 0.f;
+      per_bin[n] = NQ == 1 ? mine : __shfl(mine, (lane & 15) + 16 * n);
+      middle[n] = kSampleBins / 2;
+      fin[n] = per_bin[n] != 0.f;
+    }
     // (codes past the sample's end are not counted, nor is the row itself: where it is in the sample its own similarity,
     // often far above the others, would stretch the list's values over a range that holds nobody: 8192 x 256, k = 1000,
     // half the rows: buckets of 15 entries instead of 3)
-    const int own_tile = row0 / a.stride >> 4;             // (16 rows from a multiple of 16 on: one tile of the sample)
-    auto count = [&](float x0, float x1, float x2, float x3, int t, int l16, int g4) {
+    auto count = [&](float x0, float x1, float x2, float x3, int t, int n, int l16, int g4) {
       const float x[4] = {x0, x1, x2, x3};
+      const uint32_t one = n ? 65536u : 1u;
+      auto add = [&](float v) {
+        const uint32_t bin = min((uint32_t)__builtin_fmaf(v, per_bin[n], middle[n]), kSampleBins - 1u);   // (negative, NaN: 0)
+        atomicAdd(&s_hist[bin * 16 + l16], one);
+      };
+      const int own_tile = (row0 + 16 * n) / a.stride >> 4;   // (16 rows from a multiple of 16 on: one tile of the sample)
       if ((t + 1) * 16 <= a.ns && !(FIXED && t == own_tile)) {   // uniform
 #pragma unroll
-        for (int r = 0; r < 4; ++r) add(x[r], l16);
+        for (int r = 0; r < 4; ++r) add(x[r]);
       } else {
-        const int own = FIXED ? sample_slot(a, row0 + l16) : -1;
+        const int own = FIXED ? sample_slot(a, row0 + 16 * n + l16) : -1;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (t * 16 + 4 * g4 + r < a.ns && t * 16 + 4 * g4 + r != own) add(x[r], l16);
+          if (t * 16 + 4 * g4 + r < a.ns && t * 16 + 4 * g4 + r != own) add(x[r]);
       }
     };
-    constexpr int U = FIXED && N >= 3 ? 1 : (FIXED && N == 2 ? 2 : 4);
+    constexpr int U = FIXED && N >= 3 ? NQ : (N == 2 && (FIXED || NQ == 2) ? 2 : 4);
     auto sweep = [&](int tid) {
       const int l16 = tid & 15, g4 = (tid >> 4) & 3;
       auto clear = [&]() {
@@ -460,9 +480,11 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
       };
       if constexpr (FIXED) {
         clear();
-        i32x4 q[N];
+        i32x4 q[NQ][N];
 #pragma unroll
-        for (int ks = 0; ks < N; ++ks) q[ks] = a.Ef[((int64_t)(blockIdx.x * N + ks) * 3) * 64 + (g4 * 16 + l16)];
+        for (int n = 0; n < NQ; ++n)
+#pragma unroll
+          for (int ks = 0; ks < N; ++ks) q[n][ks] = a.Ef[((int64_t)((blockIdx.x * NQ + n) * N + ks) * 3) * 64 + (g4 * 16 + l16)];
         for (int t0 = wave; t0 < ntiles; t0 += W * U) {
           i32x4 f[U][N];
 #pragma unroll
@@ -471,60 +493,86 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
             for (int ks = 0; ks < N; ++ks) f[u][ks] = a.Es[(min(t0 + W * u, ntiles - 1) * N + ks) * 64 + (g4 * 16 + l16)];
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            i32x4 acc = {0, 0, 0, 0};
+            i32x4 acc[NQ];
 #pragma unroll
-            for (int ks = 0; ks < N; ++ks) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[u][ks], q[ks], acc, 0, 0, 0);
-            if (t0 + W * u < ntiles) count((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3], t0 + W * u, l16, g4);
+            for (int n = 0; n < NQ; ++n) acc[n] = i32x4{0, 0, 0, 0};
+#pragma unroll
+            for (int ks = 0; ks < N; ++ks)
+#pragma unroll
+              for (int n = 0; n < NQ; ++n) acc[n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[u][ks], q[n][ks], acc[n], 0, 0, 0);
+            if (t0 + W * u < ntiles)
+#pragma unroll
+              for (int n = 0; n < NQ; ++n)
+                count((float)acc[n][0], (float)acc[n][1], (float)acc[n][2], (float)acc[n][3], t0 + W * u, n, l16, g4);
           }
         }
       } else {
         const i32x4* const sampled = wide ? a.Ews : a.Es;
-        HalfOperand<N> q, f[U];
+        HalfOperand<N> q[NQ], f[U];
         auto load = [&](int t0) {
 #pragma unroll
-          for (int u = 0; u < U; ++u) f[u].load_code(sampled + (int64_t)min((t0 + W * u) * 16 + l16, a.ns - 1) * 2 * N, g4);
+          for (int u = 0; u < U; ++u) f[u].load_code(sampled + (int64_t)min(t0 + W * u, ntiles - 1) * (32 * N), l16, g4);
         };
-        q.load_query((wide ? a.Ew : a.Ef) + (int64_t)min(row0 + l16, a.V - 1) * 2 * N, g4);
+#pragma unroll
+        for (int n = 0; n < NQ; ++n)
+          q[n].load_query((wide ? a.Ew : a.Ef) + (int64_t)min(row0 + 16 * n + l16, a.V - 1) * 2 * N, g4);
         clear();
         for (int t0 = wave; t0 < ntiles; t0 += W * U) {
           load(t0);
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            const f32x4 acc = f[u].times(q, f32x4{0.f, 0.f, 0.f, 0.f});
-            if (t0 + W * u < ntiles) count(acc[0], acc[1], acc[2], acc[3], t0 + W * u, l16, g4);
+            f32x4 acc[NQ];
+#pragma unroll
+            for (int n = 0; n < NQ; ++n) acc[n] = f[u].times(q[n], f32x4{0.f, 0.f, 0.f, 0.f});
+            if (t0 + W * u < ntiles)
+#pragma unroll
+              for (int n = 0; n < NQ; ++n) count(acc[n][0], acc[n][1], acc[n][2], acc[n][3], t0 + W * u, n, l16, g4);
           }
         }
       }
     };
     // thread (row, segment of bins): its count, then the segment the target-th largest lies in.  A wave
-    // holds four segments of every row: sums over the waves go through LDS, inside a wave over lanes.
+    // holds four segments of every row: sums over the waves go through LDS, inside a wave over lanes.  (Two rows' counts in
+    // a word are added as they are.)
     auto search = [&](int target, int* s_found, bool first, int tid) {
       const int hr = tid & 15, seg = tid >> 4, g4 = seg & 3;
-      int local = 0, high = -1;
+      auto part = [](uint32_t x, int n) { return (int)(NQ == 1 ? x : (n ? x >> 16 : x & 0xFFFFu)); };
+      uint32_t local = 0;
+      int high[NQ];
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) high[n] = -1;
 #pragma unroll
       for (int i = 0; i < SW; ++i) {
         const uint32_t c = s_hist[(seg * SW + i) * 16 + hr];
-        local += (int)c;
-        if (c) high = SW * seg + i;
+        local += c;
+#pragma unroll
+        for (int n = 0; n < NQ; ++n)
+          if (part(c, n)) high[n] = SW * seg + i;
       }
-      int above = 0;                                       // counts of the segments above mine
+      uint32_t above = 0;                                  // counts of the segments above mine
       {
-        const int x1 = __shfl_down(local, 16), x2 = __shfl_down(local, 32), x3 = __shfl_down(local, 48);
+        const uint32_t x1 = __shfl_down(local, 16), x2 = __shfl_down(local, 32), x3 = __shfl_down(local, 48);
         above = (g4 < 3 ? x1 : 0) + (g4 < 2 ? x2 : 0) + (g4 < 1 ? x3 : 0);
         if (g4 == 0) s_seg[wave][hr] = above + local;
       }
-      if (first && high >= 0) atomicMax(&s_top[hr], high);
+#pragma unroll
+      for (int n = 0; n < NQ; ++n)
+        if (first && high[n] >= 0) atomicMax(&s_top[hr + 16 * n], high[n]);
       __syncthreads();
       for (int w = wave + 1; w < W; ++w) above += s_seg[w][hr];
-      if (above < target && target <= above + local) {
-        int i = SW - 1;
-        for (;; --i) {
-          above += (int)s_hist[(seg * SW + i) * 16 + hr];
-          if (i == 0 || above >= target) break;
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        int over = part(above, n);
+        if (over < target && target <= over + part(local, n)) {
+          int i = SW - 1;
+          for (;; --i) {
+            over += part(s_hist[(seg * SW + i) * 16 + hr], n);
+            if (i == 0 || over >= target) break;
+          }
+          s_found[hr + 16 * n] = SW * seg + i;
+          // (bin 0 holds what lies below the range as well: no use looking closer)
+          if (!FIXED && first && fin[n] && over > a.most && SW * seg + i > 0) s_crowded[hr + 16 * n] = s_crowded[R] = 1;
         }
-        s_found[hr] = SW * seg + i;
-        // (bin 0 holds what lies below the range as well: no use looking closer)
-        if (!FIXED && first && finite && above > a.most && s_found[hr] > 0) s_crowded[hr] = s_crowded[16] = 1;
       }
       __syncthreads();
     };
@@ -536,11 +584,14 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
     // values then end where its upper eighth begins, what lies above is ordered by keys (only of the rows that asked).  16384 x 8, k = 16, 100,
     // 1000, one code of length 300: 7.0, 7.1, 6.2 ms on the exact path -> 0.13, 0.16, 0.62; 16384 x 2: k = 16 3.2 ->
     // 0.16 ms.  (Long rows: their upper limbs would not tell the parts apart.)
-    if (!FIXED && __builtin_amdgcn_readfirstlane(s_crowded[16])) {
+    if (!FIXED && __builtin_amdgcn_readfirstlane(s_crowded[R])) {
       const int t = formed_anew(tid);                      // (nothing of it is kept in registers before)
       search(max(a.m / 8, 1), s_upper, false, t);
-      per_bin *= kSampleBins;
-      middle = (float)(kSampleBins / 2 - s_bin[t & 15]) * kSampleBins;
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        per_bin[n] *= kSampleBins;
+        middle[n] = (float)(kSampleBins / 2 - s_bin[(t & 15) + 16 * n]) * kSampleBins;
+      }
       sweep(t);
       __syncthreads();
       search(a.m, s_fine, false, t);
@@ -548,8 +599,8 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
   }
   // A code that is the same as this one, the same for all of them, or the code itself.  (seen holds what was written to
   // the place last, and rubbish where nothing was: what counts is that the numbers are the same.)
-  // A row to 32 lanes; wave 0 has the plans to make.  (To four lanes: 14.0 us, not 11.1, 1024 x 256, each code four times.)
-  if (FIXED && wave >= 1 && wave <= 8) {
+  // A row to 32 lanes; of 16 rows none to wave 0, which has the plans to make.  (To four lanes: 14.0 us, not 11.1, 1024 x 256, each code four times.)
+  if (FIXED && (NQ == 2 || (wave >= 1 && wave <= 8))) {
     const int d = 4 * (lane & 31);
     auto holds = [&](int r) { return r >= 0 && r < a.V && a.hash[min(max(r, 0), a.V - 1)] == own_hash; };
     const bool first = holds(seen1), second = holds(seen2);
@@ -567,7 +618,7 @@ __global__ __launch_bounds__(kSampleThreads, 8) void knn_sample_kernel(KnnArgs a
     const bool all_same = (uint32_t)(__ballot(same) >> (lane & 32)) == 0xFFFFFFFFu;
     if (d == 0) a.twin[own] = all_same ? r : own;           // (rows past the end: the last one's again)
   }
-  if (tid >= 16) return;
+  if (tid >= R) return;
 
   // ---- the row's plan (lane = row)
   RowPlan p;
@@ -1791,9 +1842,9 @@ KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
   L.o_ep = take((size_t)V * L.PD * sizeof(float));
   const int n8 = D > 8 ? 2 : 1;
   L.o_ef = take(L.KS ? (size_t)(L.Vp / 16) * L.KS * 3 * 64 * 16 : (size_t)L.Vp * 2 * n8 * 16);
-  L.o_es = take(L.KS ? (size_t)((L.ns + 15) / 16) * L.KS * 64 * 16 : (size_t)L.ns * 2 * n8 * 16);
+  L.o_es = take(L.KS ? (size_t)((L.ns + 15) / 16) * L.KS * 64 * 16 : lpp_align_up((size_t)L.ns, 16) * 2 * n8 * 16);
   L.o_ew = take(L.KS ? 0 : (size_t)L.Vp * 2 * n8 * 16);
-  L.o_ews = take(L.KS ? 0 : (size_t)L.ns * 2 * n8 * 16);
+  L.o_ews = take(L.KS ? 0 : lpp_align_up((size_t)L.ns, 16) * 2 * n8 * 16);
   L.o_norms = take((size_t)V * sizeof(float));
   L.o_l1 = take((size_t)V * sizeof(float));
   L.o_hash = take(L.KS ? (size_t)V * sizeof(uint32_t) : 0);
@@ -1813,16 +1864,27 @@ KnnLayout knn_layout(int32_t V, int32_t D, int32_t k) {
 // LDS of one row's ranking
 size_t rank_lds(int P, int NB, int PD) { return (size_t)PD * 8 + (size_t)NB * 4 + (size_t)P * 8 + (size_t)P * 2; }
 
-template <bool FIXED, int N>
-int32_t launch_sample(const KnnArgs& a, hipStream_t s) {
+template <bool FIXED, int N, int NQ>
+int32_t launch_sample_as(const KnnArgs& a, hipStream_t s) {
   const size_t lds = (size_t)kSampleBins * 16 * sizeof(uint32_t);
-  auto kern = knn_sample_kernel<FIXED, N>;
+  auto kern = knn_sample_kernel<FIXED, N, NQ>;
   static LppLdsLimit limit;
   const int32_t st = lpp_ensure_lds(reinterpret_cast<const void*>(kern), limit, lds);
   if (st != LPP_OK) return st;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(a.Vp / 16)), dim3(kSampleThreads), lds, s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(a.Vp / (16 * NQ))), dim3(kSampleThreads), lds, s, a);
   LPP_HIP_TRY(hipGetLastError());
   return LPP_OK;
+}
+// 32 rows a block where blocks of 16 would come in more turns than one; both sides, the build: 16384 x 16, k = 1000 247.5 us
+// (16 rows) and 232.0 (32), 12000 x 13, k = 300 136.9 and 129.3, but 8192 x 8, k = 16 46.7 and 48.0, 4096 x 8, k = 100 29.9
+// and 34.3.  Rows of more than 64 floats already where some compute unit gets a second block (two of 16 rows are there at once,
+// but each reads all of the sample): 6001 x 129, k = 300 109.2 and 103.9, 8192 x 256, k = 1000 196.3 and 188.9; up to 64
+// floats it gives nothing: 8192 x 64, k = 100 81.5 and 82.7, 12000 x 64 151.9 and 153.2, 16384 x 64, k = 1000 329.9 and 328.6.
+template <bool FIXED, int N>
+int32_t launch_sample(const KnnArgs& a, hipStream_t s) {
+  if constexpr (!FIXED || N > 1)
+    if (a.Vp > (FIXED ? 16 : 32) * kUnits) return launch_sample_as<FIXED, N, 2>(a, s);
+  return launch_sample_as<FIXED, N, 1>(a, s);
 }
 
 template <int N>

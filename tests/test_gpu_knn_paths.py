@@ -92,6 +92,17 @@ def test_knn_does_not_depend_on_what_the_workspace_held(V, D, k):
         assert np.array_equal(neigh.cpu().numpy()[rows], want[rows]), hex(fill)
 
 
+@pytest.mark.parametrize("V,D,k", [(4096, 65, 20), (4097, 65, 20), (4225, 129, 300), (6001, 250, 60), (8191, 100, 700), (8192, 8, 60),
+                                   (8193, 16, 100), (8321, 7, 900), (16383, 3, 50), (16400, 13, 16)])
+def test_knn_sample_blocks_of_16_and_32_rows(V, D, k):
+    # either side of the sizes at which a block takes 32 rows; strides of one, two and four, a tile of the sample that is not full
+    g = np.random.default_rng(V + D)
+    E = _unit(g, V, D)
+    E[V - 3] *= 40.0 if D <= 16 else 1.0                     # (short rows: the threshold's bin looked at twice)
+    rows = np.concatenate([[0, 15, 16, 31, 32, V - 33, V - 17, V - 16, V - 3, V - 2, V - 1], g.choice(V, size=120)])
+    _check(E, k, np.unique(rows))
+
+
 @pytest.mark.parametrize("order", ["random", "walk"])
 @pytest.mark.parametrize("V,D,k", [(120, 20, 9), (128, 64, 128), (129, 65, 40), (256, 33, 20), (257, 130, 257), (384, 17, 15), (500, 256, 60),
                                    (640, 129, 33), (641, 64, 12), (1279, 40, 100), (2047, 24, 31)])
