@@ -103,6 +103,21 @@ def test_knn_sample_blocks_of_16_and_32_rows(V, D, k):
     _check(E, k, np.unique(rows))
 
 
+@pytest.mark.parametrize("V,D,k", [(1000, 8, 40), (1100, 8, 40), (1100, 64, 60), (1100, 256, 30)])
+def test_knn_codebook_that_starts_off_16_bytes(V, D, k):
+    # the same numbers 4 and 16 bytes into a buffer: read through a padded copy, and as they are
+    E = _unit(np.random.default_rng(V + D), V, D)
+    want = build_neighbours(E, k)
+    for off in (1, 4):
+        flat = torch.full((V * D + 4,), float("nan"), device=DEV)
+        e = flat[off:off + V * D].view(V, D)
+        e.copy_(dev(E))
+        neigh = torch.empty((V, k), dtype=torch.int32, device=DEV)
+        ws = torch.empty(lpp.lpp_build_neighbours_workspace(V, D, k), dtype=torch.uint8, device=DEV)
+        lpp.lpp_build_neighbours(e, k, neigh, ws)
+        assert np.array_equal(neigh.cpu().numpy(), want), off
+
+
 @pytest.mark.parametrize("order", ["random", "walk"])
 @pytest.mark.parametrize("V,D,k", [(120, 20, 9), (128, 64, 128), (129, 65, 40), (256, 33, 20), (257, 130, 257), (384, 17, 15), (500, 256, 60),
                                    (640, 129, 33), (641, 64, 12), (1279, 40, 100), (2047, 24, 31)])
