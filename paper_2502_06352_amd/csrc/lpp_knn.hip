@@ -2042,8 +2042,11 @@ extern "C" int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, in
     }
     if (st != LPP_OK) return st;
   }
-  // a list of up to eight words per thread: one wave for short lists (a block of four would mostly wait for
-  // its barriers), four for the usual ones
+  // a list of up to eight words per thread, which is as few waves as hold it: one, two, four or sixteen.  What a thread does
+  // beside its words, and the barriers, cost more than fewer rows at once: lists of 513 to 1024 by two waves instead of four,
+  // 16384 x 8, k = 200 133.4 -> 120.7 us, 4096 x 64, k = 500 63.3 -> 58.8, 8192 x 256, k = 300 150.3 -> 146.3,
+  // 16384 x 64, k = 400 268.8 -> 253.8; up to 2048 by eight instead of four 186 -> 211 (16384 x 8, k = 1000), by two
+  // with sixteen words each 186 -> 216.
   const bool staged = D > kShortRow;
   // Rows that fall through (heavy ties, infinities, norms far apart) in a launch of their own, which costs 2 us
   // whether there are any or not: where one such row would cost many times that in a ranking block (codebooks of 2^20
@@ -2059,6 +2062,7 @@ extern "C" int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, in
     return later ? launch_rank<NTHR, false, true>(a, sh, s) : launch_rank<NTHR, false, false>(a, sh, s);
   };
   if (L.cap <= 512) return rank(std::integral_constant<int, 64>(), 8);
+  if (L.cap <= 1024) return rank(std::integral_constant<int, 128>(), 9);
   if (L.cap <= 2048) return rank(std::integral_constant<int, 256>(), 10);
   if (L.cap > 8192) return LPP_EUNSUPPORTED;
   return rank(std::integral_constant<int, 1024>(), 12);

@@ -118,6 +118,16 @@ def test_knn_codebook_that_starts_off_16_bytes(V, D, k):
         assert np.array_equal(neigh.cpu().numpy(), want), off
 
 
+@pytest.mark.parametrize("V,D,k", [(16384, 8, 120), (16384, 8, 150), (16384, 8, 480), (16384, 8, 560), (5000, 6, 300), (4096, 64, 300),
+                                   (4096, 64, 500), (8192, 256, 240), (3000, 16, 500), (1500, 40, 1500)])
+def test_knn_lists_by_one_two_and_four_waves(V, D, k):
+    # lists on either side of 512, 1024 and 2048 words, codes four times over among them
+    g = np.random.default_rng(V + k)
+    E = _unit(g, V, D)
+    E[V // 2:V // 2 + 600] = E[np.arange(600) // 4]
+    _check(E, k, np.unique(np.concatenate([[0, 1, V // 2, V // 2 + 1, V - 1], g.choice(V, size=100)])))
+
+
 @pytest.mark.parametrize("order", ["random", "walk"])
 @pytest.mark.parametrize("V,D,k", [(120, 20, 9), (128, 64, 128), (129, 65, 40), (256, 33, 20), (257, 130, 257), (384, 17, 15), (500, 256, 60),
                                    (640, 129, 33), (641, 64, 12), (1279, 40, 100), (2047, 24, 31)])
