@@ -7,7 +7,7 @@
 //   S^T[32 keys x rows] = K_group * Q^T       (MFMA 16x16x32 bf16, K straight from HBM
 //                                              into the A operand, Q held in registers)
 //   softmax down the key axis, which is mostly lane-local in this layout; the
-//   reference maximum of a row only moves when a score exceeds it by 2^8, so the
+//   reference maximum of a row only moves when a score exceeds it by 2^8 (few blocks: 2), so the
 //   accumulators are rarely rescaled
 //   O^T[Dh x rows]    += V_group^T * P^T       (V rows go to a wave-private LDS tile as
 //                                              they are and come back through the
@@ -31,9 +31,6 @@
 
 #include "lpp_internal.h"
 
-#ifndef LIVEMIN
-#define LIVEMIN 5
-#endif
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -43,9 +40,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kMasked = -1.0e30f;  // finite stand-in for -inf
-constexpr float kLazy = 8.0f;        // log2 of the largest probability weight before a rescale
+// log2 of the largest probability weight before a rescale.  The largest weight of a reference's group is one, which bf16 has exactly;
+// with fewer waves fewer weights are, and a lower limit makes up for it (16 heads, 61 rows, 200 keys: error against float64
+// 1.35e-3 with 8 waves, 1.48e-3 with 4, 1.27e-3 with 4 and the lower limit; 4 times the scores, 48 heads, 1024 keys 5.4e-4, 7.4e-4,
+// 3.7e-4): where a launch of few blocks has fewer waves than blocks of 8 would.
+// Long sweeps would pay for it (129 rows, 4096 keys, 384 heads 107 -> 121 us), two tiles a wave too (96 heads, 61 rows, 1024 keys
+// 9.6 -> 10.4), one tile 2 %.
+constexpr float kLazy = 8.0f, kLazyFew[2] = {1.0f, 4.0f};      // (one and two tiles a wave)
 
-// Several layers of one step go out in one launch: block index / blocks_per_layer picks the layer,
+// Several layers of one step go out in one launch: unit / units_per_layer picks the layer,
 // whose tensors are looked up in a table inside the kernel arguments (a wave-uniform index).
 constexpr int kLayersPerLaunch = 16;
 struct LayerPtrs {
@@ -55,8 +58,13 @@ struct LayerPtrs {
 
 struct AttnArgs {
   // (what every block needs to find its place lies together: one line of the scalar cache)
-  uint32_t whole;                    // units (layer, head, row range) that one block each takes (a multiple of 8); those behind them are split
-  uint32_t blocks_per_layer, rc_bpl; // units of a layer (a multiple of 8: every layer maps to the XCDs the same way)
+  uint32_t whole;                    // units (layer, head, row range) that one block each takes (a multiple of 8 where others are split); those behind them are split
+  uint32_t units_per_layer, rc_upl;  // units of a layer: first those of its key/value heads in eights, then those of the heads left
+  uint32_t eights;                   // ... units of the former
+  uint32_t left, rc_left;            // key/value heads left, 0 to 7
+  uint32_t spin;                     // ... none, the last eight padded: how far its heads move from layer to layer
+  uint32_t split_eights;             // blocks of the split units in eights, and the split units left
+  uint32_t split_left, rc_split_left;
   int32_t nsplit; uint32_t rc_nsplit;   // key ranges of a split unit
   int32_t msplits; uint32_t rc_msplits; // row ranges of a head.  rc_d: ceil(2^32 / d): n / d = mulhi(n, rc) while n d < 2^32
   int32_t gq; uint32_t rc_gq;        // query heads per key/value head (H = Hkv * gq)
@@ -66,11 +74,11 @@ struct AttnArgs {
   const int32_t* seq_len;
   const uint64_t* anc;
   float scale_log2;                  // scale * log2(e)
+  float lazy;                        // kLazy or one of kLazyFew
   uint32_t ws_o_bytes, ws_ml_bytes;  // sizes of the two, each below 2^31
   float* ws_o;                       // [split unit][nsplit][rows of a block][Dh]   unnormalised partial O
   float* ws_ml;                      // [split unit][nsplit][rows of a block][2]    (reference max in log2 units, sum)
   int32_t* counters;                 // [split unit] zero between calls
-  int32_t n_layers;
   LayerPtrs layer[kLayersPerLaunch];
 };
 
@@ -145,7 +153,7 @@ struct Stage {
 };
 
 // NT = row tiles (of 16 tree rows) per wave, RW = waves along the rows, KW = waves along the keys:
-// a block covers NT * RW * 16 tree rows; wave (kw, rw) takes key groups gbeg + kw, + KW, ... for
+// a block covers NT * RW * 16 tree rows; wave (kw, rw) takes key groups by turns for
 // rows [rw NT 16, (rw + 1) NT 16).  The RW waves that share a key group load it independently; the
 // second read is served by the compute unit's own cache.
 template <int DH, int NT, int RW, int KW>
@@ -173,29 +181,38 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   const int kw = wave % KW, rw = wave / KW;
 
   // block -> unit = (layer, batch*head, row range) and key range; all blocks of one key/value head (every row range
-  // and every query head that reads it) share an XCD and follow each other in launch order
+  // and every query head that reads it) share an XCD, as long as all XCDs have one, and follow each other in launch order
   // (Every argument is asked for at once, then the layer's pointers and the item's length, and no branch up to the first
   // loads: left to the compiler, the scalar loads wait for each other four times, a few tenths of a microsecond each.)
-  uint32_t whole = a.whole, bpl = a.blocks_per_layer, rc_bpl = a.rc_bpl, rc_nsplit = a.rc_nsplit, rc_msplits = a.rc_msplits;
-  uint32_t rc_gq = a.rc_gq, rc_H = a.rc_H;
+  uint32_t whole = a.whole, upl = a.units_per_layer, rc_upl = a.rc_upl, eights = a.eights, left = a.left, rc_left = a.rc_left, spin = a.spin;
+  uint32_t split_eights = a.split_eights, split_left = a.split_left, rc_split_left = a.rc_split_left;
+  uint32_t rc_nsplit = a.rc_nsplit, rc_msplits = a.rc_msplits, rc_gq = a.rc_gq, rc_H = a.rc_H;
   int ranges = a.nsplit, msplits = a.msplits, gq = a.gq, H = a.H, KVBH = a.KVBH, S = a.S, M = a.M;
-  asm("" : "+s"(whole), "+s"(bpl), "+s"(rc_bpl), "+s"(rc_nsplit), "+s"(rc_msplits), "+s"(rc_gq), "+s"(rc_H), "+s"(ranges), "+s"(msplits),
-           "+s"(gq), "+s"(H), "+s"(KVBH), "+s"(S), "+s"(M) : "s"(a.words), "s"(a.anc), "s"(a.seq_len), "s"(a.scale_log2));
-  const uint32_t behind = blockIdx.x - whole, bslot = behind >> 3;
-  const uint32_t bunit = div_rc(bslot, (uint32_t)ranges, rc_nsplit);              // among the split units of this XCD
+  asm("" : "+s"(whole), "+s"(upl), "+s"(rc_upl), "+s"(eights), "+s"(left), "+s"(rc_left), "+s"(split_eights), "+s"(split_left),
+           "+s"(rc_split_left), "+s"(spin));
+  asm("" : "+s"(rc_nsplit), "+s"(rc_msplits), "+s"(rc_gq), "+s"(rc_H), "+s"(ranges), "+s"(msplits),
+           "+s"(gq), "+s"(H), "+s"(KVBH), "+s"(S), "+s"(M) : "s"(a.words), "s"(a.anc), "s"(a.seq_len), "s"(a.scale_log2), "s"(a.lazy));
+  // (split units by eights, a unit's blocks 8 apart: on one XCD; what is left of them one key range after the other)
   const bool is_split = blockIdx.x >= whole;
-  const uint32_t unit = is_split ? whole + bunit * 8 + (behind & 7) : blockIdx.x;
-  const int split = is_split ? (int)(bslot - bunit * (uint32_t)ranges) : 0, nsplit = is_split ? ranges : 1;
-  const uint32_t lyr = div_rc(unit, bpl, rc_bpl);
-  const uint32_t bid = unit - lyr * bpl;
+  const uint32_t behind = blockIdx.x - whole, bslot = behind >> 3, bunit = div_rc(bslot, (uint32_t)ranges, rc_nsplit);
+  const uint32_t tail = behind - split_eights, tsplit = div_rc(tail, split_left, rc_split_left);
+  const bool in_tail = is_split && behind >= split_eights;
+  const uint32_t first_left = div_rc(split_eights, (uint32_t)ranges, rc_nsplit);
+  const uint32_t unit = !is_split ? blockIdx.x
+                                  : whole + (in_tail ? first_left + tail - tsplit * split_left : bunit * 8 + (behind & 7));
+  const int split = !is_split ? 0 : (int)(in_tail ? tsplit : bslot - bunit * (uint32_t)ranges), nsplit = is_split ? ranges : 1;
+  const uint32_t lyr = div_rc(unit, upl, rc_upl);
+  const uint32_t bid = unit - lyr * upl;
   const LayerPtrs& L = a.layer[lyr];
-  const uint32_t xcd = bid & 7, slot = bid >> 3;
+  // (the heads that are left, fewer than XCDs, take turns: a block of each, so that no XCD idles)
+  const bool of_left = bid >= eights;
+  const uint32_t rest = bid - eights, turn = div_rc(rest, left, rc_left);
+  const uint32_t slot = of_left ? turn : bid >> 3;
   const uint32_t hq = div_rc(slot, (uint32_t)msplits, rc_msplits);
   const int ms = (int)(slot - hq * (uint32_t)msplits);
-  const uint32_t kvq = div_rc(hq, (uint32_t)gq, rc_gq), qg = hq - kvq * (uint32_t)gq;
-  // (no early exit for the padding blocks of the last XCD round: they redo the last head's work and write nothing)
-  const bool live = (int)(kvq * 8 + xcd) < KVBH;
-  const int kvbh = min((int)(kvq * 8 + xcd), KVBH - 1);     // batch * Hkv + key/value head
+  const uint32_t kvq = of_left ? 0u : div_rc(hq, (uint32_t)gq, rc_gq), qg = hq - kvq * (uint32_t)gq;
+  const int kvbh = (int)(of_left ? (uint32_t)KVBH - left + rest - turn * left : kvq * 8 + ((bid - lyr * spin) & 7));    // batch * Hkv + key/value head
+  if (kvbh >= KVBH) return;                                 // (padding)
   const int bh = kvbh * gq + (int)qg;                       // batch * H + query head
   const int b = (int)div_rc((uint32_t)bh, (uint32_t)H, rc_H);
   const int m0 = ms * ROWS + rw * WROWS;       // first row of this wave
@@ -203,8 +220,6 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   asm("" : "+s"(len) : "s"(L.q), "s"(L.kc), "s"(L.vc), "s"(L.kt), "s"(L.vt));
   const int seq = a.seq_len ? min(max(len, 0), S) : S;
   const int GC = (seq + 31) >> 5, GT = (M + 31) >> 5, G = GC + GT;
-  const int gbeg = (int)div_rc((uint32_t)(split * G), (uint32_t)nsplit, is_split ? rc_nsplit : 0u);
-  const int gend = (int)div_rc((uint32_t)((split + 1) * G), (uint32_t)nsplit, is_split ? rc_nsplit : 0u);
   const uint16_t* kc = reinterpret_cast<const uint16_t*>(L.kc) + (int64_t)kvbh * S * DH;
   const uint16_t* vc = reinterpret_cast<const uint16_t*>(L.vc) + (int64_t)kvbh * S * DH;
   const uint16_t* kt = reinterpret_cast<const uint16_t*>(L.kt) + (int64_t)kvbh * M * DH;
@@ -215,6 +230,9 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   // Key groups [0, GF) lie wholly inside the cache: no mask, no bounds.  The others (the ragged
   // end of the cache and the tree keys) go through the general path after them.
   const int GF = seq >> 5;
+  // The groups are dealt in turn to all waves of all blocks of the unit, whichever key range their block is: which wave gets
+  // what depends on the number of the waves alone.
+  const int waves = nsplit * KW, wave_no = kw * nsplit + split;             // (the blocks even: theirs differ by a wave's turn)
   // (in bytes, 32 bits: offsets to a wave-uniform pointer)
   const uint32_t koff = (uint32_t)(l16 * DH + g4 * 8) * 2;                  // my K chunk inside a group
   const uint32_t voff = (uint32_t)lane * 16;                                // my V chunks: + p * 64 chunks
@@ -344,7 +362,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
           v = fmaxf(v, sc);
         }
       mxl[nt] = v > 0.5f * kMasked ? v * a.scale_log2 : kMasked;   // (scale > 0: the maximum commutes with it)
-      need = need || (mxl[nt] > m_ref[nt] + kLazy);
+      need = need || (mxl[nt] > m_ref[nt] + a.lazy);
     }
     if (__ballot(need)) {   // some row's reference moves: rare after a wave's first group
 #pragma unroll
@@ -352,7 +370,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
         float v = mxl[nt];
         v = fmaxf(v, __shfl_xor(v, 16));
         v = fmaxf(v, __shfl_xor(v, 32));
-        const bool up = v > m_ref[nt] + kLazy;                 // decided per row: no row depends on another's scores
+        const bool up = v > m_ref[nt] + a.lazy;                // decided per row: no row depends on another's scores
         const float nm = up ? v : m_ref[nt];
         const float alpha = __builtin_amdgcn_exp2f(m_ref[nt] - nm);
         m_ref[nt] = nm;
@@ -408,46 +426,46 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   // been consumed.  The wave's first general group is fetched before them and worked on while
   // the ring's first loads are in flight.
   auto run = [&](auto live) {
-    const int h1 = min(gend, GF);                     // full groups: [gbeg, h1)
-    const int c0 = max(gbeg, GF);                     // general groups: [c0, gend)
     const uint64_t novis[NT] = {};
     Stage<DH> cst;
     uint64_t vis[NT];
-    int gx = c0 + kw;                                 // next general group of this wave
+    // next general group of this wave: [GF, G)  (the first waves': dealt on from the full ones, to waves with fewer of those, launches
+    // of few blocks take 0.5 to 0.7 us of 7 more)
+    int gx = GF + wave_no;
     if (GF >= 1) {
       constexpr int D = 2;   // (deeper rings were no faster on long caches and slower on short ones: the
                              //  eight waves of a block already have sixteen groups in flight)
       Stage<DH> st[D];
-      const bool pre = gx < gend;
+      const bool pre = gx < G;
       if (pre) { visibility(vis, gx); load_any(cst, gx); }
       // Ring loads are issued unconditionally (a group index past the end is clamped: a re-read
       // that is never used), so that the number of loads in flight is the same on every path and
       // each wait lets the younger loads stay in flight.
-      int g = gbeg + kw;
-      const int hl = max(h1 - 1, 0);
+      int g = wave_no;                            // full groups: [0, GF)
+      const int hl = GF - 1;
 #pragma unroll
       for (int d = 0; d < D; ++d)
-        if (!kLean || d < D - 1) load_full(st[d], min(g + d * KW, hl));
-      if (pre) { compute_group(cst, gx, vis, kAny, live); gx += KW; }   // while the ring's loads are in flight
-      if (kLean) load_full(st[D - 1], min(g + (D - 1) * KW, hl));
+        if (!kLean || d < D - 1) load_full(st[d], min(g + d * waves, hl));
+      if (pre) { compute_group(cst, gx, vis, kAny, live); gx += waves; }   // while the ring's loads are in flight
+      if (kLean) load_full(st[D - 1], min(g + (D - 1) * waves, hl));
       // whole rounds of the ring, as long as at least the round's first refill is a group of this
       // wave (a round that would refill nothing is left to the tail below: a wave with D groups or
       // fewer would else spend half of the compute unit's load issue on re-reads nobody uses)
-      while (g + D * KW < h1) {
+      while (g + D * waves < GF) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
           compute_group(st[d], g, novis, kFull, live);
-          load_full(st[d], min(g + D * KW, hl));
-          g += KW;
+          load_full(st[d], min(g + D * waves, hl));
+          g += waves;
         }
       }
 #pragma unroll
       for (int d = 0; d < D; ++d) {               // what is left: up to D groups, already loaded
-        if (g < h1) compute_group(st[d], g, novis, kFull, live);
-        g += KW;
+        if (g < GF) compute_group(st[d], g, novis, kFull, live);
+        g += waves;
       }
     }
-    for (; gx < gend; gx += KW) {                 // further general groups: rare, not pipelined
+    for (; gx < G; gx += waves) {                 // further general groups: rare, not pipelined
       visibility(vis, gx);
       load_any(cst, gx);
       compute_group(cst, gx, vis, kAny, live);
@@ -516,14 +534,14 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   // ---- write: final rows if this block saw every key, else an unnormalised partial
   constexpr int C4 = DH / 4;
   const int mb = ms * ROWS;                                     // first row of the block
-  // the unit's number among the split ones (all of them: without the padding of the last XCD round)
-  const uint32_t part = whole ? unit - whole : (lyr * (uint32_t)(KVBH * gq) + (uint32_t)bh) * (uint32_t)msplits + (uint32_t)ms;
+  // the unit's number among the split ones
+  const uint32_t part = unit - whole;
   const int64_t part0 = (int64_t)part * nsplit * ROWS;          // first row of its partials
   const __amdgpu_buffer_rsrc_t dev_o = device_buffer(a.ws_o, a.ws_o_bytes), dev_ml = device_buffer(a.ws_ml, a.ws_ml_bytes);
   for (int idx = threadIdx.x; idx < ROWS * C4; idx += W * 64) {
     const int r = idx / C4, c4 = idx % C4;
     const int m = mb + r;
-    if (m >= M || !live) continue;
+    if (m >= M) continue;
     float4 v = *reinterpret_cast<const float4*>(&s_o[r * OPITCH + c4 * 4]);
 #pragma unroll
     for (int w = 1; w < MS; ++w) {
@@ -541,7 +559,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
       if (c4 == 0) store_dev(dev_ml, (uint32_t)(prow * 8), make_float2(bm, bl));
     }
   }
-  if (nsplit == 1 || !live) return;
+  if (nsplit == 1) return;
 
   // ---- the block of this (head, row range) that finishes last adds the splits up, in split order
   // Every wave first waits until its own stores of the partial have completed (a device-scope
@@ -1018,6 +1036,7 @@ size_t f32_workspace(const lpp_tree* tree, int B, int H, int Dh, int layers, int
 struct AttnPlan {
   int nt, kw, msplits, nsplit, mtiles, groups;
   int asked;                        // key ranges that a workspace must have room for (with less than nsplit, fewer are made)
+  float lazy;                       // kLazy or kLazyFew
   size_t lds;
 };
 
@@ -1028,6 +1047,7 @@ struct AttnPlan {
 // the launch (all its layers) would leave compute units idle.
 AttnPlan plan_attention(const lpp_tree* tree, int B, int H, int S, int Dh, int layers) {
   AttnPlan p;
+  p.lazy = kLazy;
   p.mtiles = (tree->M + 15) / 16;
   const int G = (S + 31) / 32 + (tree->M + 31) / 32;
   const int64_t n_cu = tree->n_cu, heads = (int64_t)B * H * std::max(1, std::min(layers, kLayersPerLaunch));
@@ -1060,6 +1080,28 @@ AttnPlan plan_attention(const lpp_tree* tree, int B, int H, int S, int Dh, int l
     p.msplits = 1;
     whole_heads = true;
   }
+  // Launches of few blocks, which latency bounds (first bytes, in-block merge, merge of key ranges): a block costs what its waves
+  // have to merge, 4 to 16 KB of sums each, and what it reads.  One tile a wave, then two, while the blocks are no more than
+  // the compute units and each takes in no more than 330 KB (660 KB) of keys and values; blocks of 4 waves unless that means
+  // more than so many key ranges, or any where 8 waves need none, or where 8 waves make as many and that is two, or leaves a
+  // wave of 4 more than six groups.  Over 504 shapes (one layer, 8 to 128 heads, 9 to 100 rows, 64 to 4000 keys) launches take
+  // 1.011 times the best of all such choices, with the rules above and below alone 1.21: 16 heads of 64, 100 rows, 200 keys 11.6 -> 6.6 us, 27 rows, 1000 keys 7.5 -> 6.3; 32 heads of 128, 61 rows, 64 keys 10.3 -> 6.2, 1000
+  // keys 14.4 -> 11.6; 6 % slower at worst (48 heads of 64, 9 rows, 2000 keys 8.7 -> 9.3).
+  const int weight = Dh / 64;                     // a group of 32 keys and values: 8 KB each
+  bool few = false;
+  for (int nt = 1; nt <= std::min(2, p.mtiles) && !few; ++nt) {
+    const int64_t units = heads * ((p.mtiles + nt - 1) / nt);
+    if (units > n_cu || units * G * weight > 40 * nt * n_cu) continue;
+    const int64_t ns4 = std::max<int64_t>(1, std::min<int64_t>(n_cu / units, G / 8));
+    const int64_t ns8 = std::max<int64_t>(1, std::min<int64_t>(n_cu / units, G / 16));
+    p.nt = nt;
+    p.msplits = (p.mtiles + nt - 1) / nt;
+    p.kw = ns4 > (Dh == 64 ? 10 : 4) || (ns4 > 1 && ns8 == 1 && G * weight <= 48) ||
+                   (ns4 > 1 && ns4 == ns8 && (ns4 == 2 || G > 24 * ns4)) ? 8 : 4;
+    p.lazy = p.kw == 4 && ns4 < 2 * ns8 && G <= 40 * ns4 ? kLazyFew[nt - 1] : kLazy;      // (fewer waves than blocks of 8 would have)
+    few = true;
+    whole_heads = false;
+  }
   const int64_t blocks_bh = heads * p.msplits;
   // Blocks of 8 waves only where they are so few that every second compute unit would idle.  Blocks of 4 waves
   // share a compute unit and cover each other's fixed latencies (first bytes, in-block merge, write-out) and stalls, which
@@ -1067,13 +1109,13 @@ AttnPlan plan_attention(const lpp_tree* tree, int B, int H, int S, int Dh, int l
   // rows); 32 heads of 128 x 3 items x 12 layers, 100 keys: 44 -> 22.5 (20 rows); 24 heads x 8 items, 160 keys: 19.5 ->
   // 13.2 (116 rows).  Four tiles a wave on long caches: a block a compute unit, while that is enough for all (24
   // heads x 2 items x 2 layers, 2700 keys, 116 rows: 21.8 us, 22.8 with blocks of 4 waves).
-  p.kw = blocks_bh * 2 > n_cu && !(p.nt == 4 && blocks_bh <= n_cu && G >= 60) ? 4 : 8;
+  if (!few) p.kw = blocks_bh * 2 > n_cu && !(p.nt == 4 && blocks_bh <= n_cu && G >= 60) ? 4 : 8;
   int ns = (int)std::min<int64_t>(tree->n_cu / blocks_bh, 1 << 20);   // key splits only while a compute unit would idle
   const int max_ns = G / (2 * p.kw);              // at least two key groups per wave
   if (ns > max_ns) ns = max_ns;
   if (ns < 1) ns = 1;
   p.nsplit = ns;
-  p.asked = whole_heads ? 1 : ns;
+  p.asked = whole_heads || few ? 1 : ns;
   p.groups = G;
   const int rows = p.nt * 16;
   const size_t vt = (size_t)p.kw * 2 * 32 * (Dh * 2 + 32);
@@ -1084,13 +1126,12 @@ AttnPlan plan_attention(const lpp_tree* tree, int B, int H, int S, int Dh, int l
 }
 
 template <int DH, int NT, int RW, int KW>
-int32_t launch_bf16(const AttnArgs& a, const AttnPlan& p, hipStream_t s) {
+int32_t launch_bf16(const AttnArgs& a, const AttnPlan& p, int64_t blocks, hipStream_t s) {
   static LppLdsLimit limit;
   auto kern = tree_attn_bf16_kernel<DH, NT, RW, KW>;
   const int32_t st = lpp_ensure_lds(reinterpret_cast<const void*>(kern), limit, p.lds, 48 * 1024);
   if (st != LPP_OK) return st;
-  const uint32_t units = a.blocks_per_layer * (uint32_t)a.n_layers;
-  hipLaunchKernelGGL(kern, dim3(a.whole + (units - a.whole) * (uint32_t)a.nsplit), dim3(RW * KW * 64), p.lds, s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(RW * KW * 64), p.lds, s, a);
   LPP_HIP_TRY(hipGetLastError());
   return LPP_OK;
 }
@@ -1200,27 +1241,39 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
       const lpp_attention_layer& y = layers[l0 + std::min(l, nl - 1)];
       a.layer[l] = LayerPtrs{y.q, y.k_cache, y.v_cache, y.k_tree, y.v_tree, y.out};
     }
-    a.n_layers = nl;
     a.seq_len = seq_len; a.anc = tree->d_anc;
     a.H = H; a.S = S; a.M = tree->M; a.words = tree->words;
     a.KVBH = B * Hkv; a.gq = H / Hkv; a.out_bf16 = out_dtype == LPP_BF16;
     a.msplits = p.msplits;
     a.scale_log2 = scale * 1.44269504088896340736f;
-    const int64_t bpl = 8 * (((int64_t)B * Hkv + 7) / 8) * (H / Hkv) * p.msplits;
-    AttnSplit sp = split_units(tree, p, bpl * nl);
+    a.lazy = p.lazy;
+    // Key/value heads beyond a multiple of 8: in one layer, in few whose heads make no eight and where the keys are split, their blocks take turns on the XCDs
+    // (1 head of 4 in 4 items, 67 rows, 1313 keys 16.4 -> 8.2 us).  In more layers a head keeps to an XCD, whose L2 then has
+    // its keys for all blocks that read them, and the next layer's heads to the XCDs behind (5 heads for 20, 16 layers, 1286
+    // keys 34 us, in turns 38).
+    const int64_t per_head = (int64_t)(H / Hkv) * p.msplits;
+    const bool turns = nl * (a.KVBH & 7) < 8 || nl == 1 || p.nsplit > 1;        // (padding has no place among the partials)
+    const int64_t upl = (turns ? (int64_t)B * Hkv : ((int64_t)B * Hkv + 7) / 8 * 8) * per_head;
+    AttnSplit sp = split_units(tree, p, upl * nl);
     size_t o_bytes = 0, ml_bytes = 0;
     auto partials = [&]() {
-      const int64_t units = sp.whole ? bpl * nl - sp.whole : (int64_t)nl * B * H * p.msplits;
-      const size_t bytes = partial_bytes(split_rows(p, units, sp.ns), Dh, &o_bytes);
+      const size_t bytes = partial_bytes(split_rows(p, upl * nl - sp.whole, sp.ns), Dh, &o_bytes);
       ml_bytes = bytes - o_bytes;
       return bytes;
     };
-    while (partials() > ws_bytes) sp = sp.ns > 2 ? AttnSplit{sp.whole, sp.ns - 1} : AttnSplit{bpl * nl, 1};
-    if (sp.whole + (bpl * nl - sp.whole) * sp.ns >= (1ll << 31)) return LPP_EUNSUPPORTED;
+    while (partials() > ws_bytes) sp = sp.ns > 2 ? AttnSplit{sp.whole, sp.ns - 1} : AttnSplit{upl * nl, 1};
+    const int64_t parts = upl * nl - sp.whole, blocks = sp.whole + parts * sp.ns;
+    if (blocks >= (1ll << 31)) return LPP_EUNSUPPORTED;
     a.whole = (uint32_t)sp.whole; a.nsplit = sp.ns;
     a.rc_msplits = reciprocal((uint32_t)p.msplits); a.rc_H = reciprocal((uint32_t)H); a.rc_nsplit = reciprocal((uint32_t)sp.ns);
     a.rc_gq = reciprocal((uint32_t)(H / Hkv));
-    a.blocks_per_layer = (uint32_t)bpl; a.rc_bpl = reciprocal((uint32_t)bpl);
+    a.units_per_layer = nl == 1 ? 0xFFFFFFFFu : (uint32_t)upl;                  // (one layer: 0, however many units)
+    a.rc_upl = reciprocal(a.units_per_layer);
+    a.left = turns ? (uint32_t)(a.KVBH & 7) : 0u; a.rc_left = reciprocal(a.left);
+    a.eights = (uint32_t)(upl - a.left * per_head);
+    a.spin = turns ? 0u : (uint32_t)(a.KVBH & 7);
+    a.split_eights = (uint32_t)((parts & ~7ll) * sp.ns);
+    a.split_left = (uint32_t)(parts & 7); a.rc_split_left = reciprocal(a.split_left);
     a.counters = tree->d_counters + LPP_COUNTER_SLOTS;
     a.ws_o_bytes = (uint32_t)o_bytes; a.ws_ml_bytes = (uint32_t)ml_bytes;
     a.ws_o = reinterpret_cast<float*>(ws);
@@ -1228,14 +1281,14 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
 
     int32_t st = LPP_EUNSUPPORTED;
     if (Dh == 64) {
-      if (p.nt == 1) st = p.kw == 4 ? launch_bf16<64, 1, 1, 4>(a, p, s) : launch_bf16<64, 1, 1, 8>(a, p, s);
-      else if (p.nt == 2) st = p.kw == 4 ? launch_bf16<64, 2, 1, 4>(a, p, s) : launch_bf16<64, 2, 1, 8>(a, p, s);
-      else if (p.nt == 3) st = p.kw == 4 ? launch_bf16<64, 3, 1, 4>(a, p, s) : launch_bf16<64, 3, 1, 8>(a, p, s);
-      else if (p.nt == 4) st = p.kw == 4 ? launch_bf16<64, 4, 1, 4>(a, p, s) : launch_bf16<64, 4, 1, 8>(a, p, s);
-      else st = p.kw == 4 ? launch_bf16<64, 5, 1, 4>(a, p, s) : launch_bf16<64, 5, 1, 8>(a, p, s);
+      if (p.nt == 1) st = p.kw == 4 ? launch_bf16<64, 1, 1, 4>(a, p, blocks, s) : launch_bf16<64, 1, 1, 8>(a, p, blocks, s);
+      else if (p.nt == 2) st = p.kw == 4 ? launch_bf16<64, 2, 1, 4>(a, p, blocks, s) : launch_bf16<64, 2, 1, 8>(a, p, blocks, s);
+      else if (p.nt == 3) st = p.kw == 4 ? launch_bf16<64, 3, 1, 4>(a, p, blocks, s) : launch_bf16<64, 3, 1, 8>(a, p, blocks, s);
+      else if (p.nt == 4) st = p.kw == 4 ? launch_bf16<64, 4, 1, 4>(a, p, blocks, s) : launch_bf16<64, 4, 1, 8>(a, p, blocks, s);
+      else st = p.kw == 4 ? launch_bf16<64, 5, 1, 4>(a, p, blocks, s) : launch_bf16<64, 5, 1, 8>(a, p, blocks, s);
     } else {
-      if (p.nt == 1) st = p.kw == 4 ? launch_bf16<128, 1, 1, 4>(a, p, s) : launch_bf16<128, 1, 1, 8>(a, p, s);
-      else if (p.nt == 2) st = p.kw == 4 ? launch_bf16<128, 2, 1, 4>(a, p, s) : launch_bf16<128, 2, 1, 8>(a, p, s);
+      if (p.nt == 1) st = p.kw == 4 ? launch_bf16<128, 1, 1, 4>(a, p, blocks, s) : launch_bf16<128, 1, 1, 8>(a, p, blocks, s);
+      else if (p.nt == 2) st = p.kw == 4 ? launch_bf16<128, 2, 1, 4>(a, p, blocks, s) : launch_bf16<128, 2, 1, 8>(a, p, blocks, s);
     }
     if (st != LPP_OK) return st;
   }

@@ -214,3 +214,27 @@ def test_bf16_makes_fewer_parts_for_a_smaller_workspace(N, S, B, H):
     want = tree_attention(att["q"][-1:, -1:], att["kc"][-1:, -1:], att["vc"][-1:, -1:], att["kt"][-1:, -1:], att["vt"][-1:, -1:], parent)
     assert max(attention_error(o[-1:, -1:], want) for o in outs) <= TOL["bf16"]
     assert max(attention_error(o, outs[-1]) for o in outs) <= 2 * TOL["bf16"]
+
+
+@pytest.mark.parametrize("Dh", [64, 128])
+@pytest.mark.parametrize("B,H,Hkv,N,S,L", [
+    (1, 1, 1, 8, 4000, 1), (1, 2, 1, 15, 64, 1), (1, 3, 3, 16, 700, 2), (1, 4, 1, 99, 130, 1), (1, 5, 5, 20, 1500, 1), (1, 6, 2, 31, 33, 3),
+    (1, 7, 7, 60, 900, 1), (1, 9, 9, 26, 1024, 1), (3, 4, 2, 45, 500, 1), (1, 12, 6, 100, 300, 2), (2, 20, 20, 9, 800, 1), (5, 8, 4, 61, 0, 1),
+    (3, 16, 16, 43, 1200, 1), (1, 33, 11, 17, 31, 1)])
+def test_launches_of_few_blocks(Dh, B, H, Hkv, N, S, L):
+    # 1 to 96 heads: key/value heads that are no multiple of 8, alone and behind eights of them, one and two tiles a wave, blocks
+    # of 4 and 8 waves, up to 15 key ranges and none, ragged lengths with items that leave waves and whole ranges empty
+    cfg = CONFIGS[2].scaled(N=N, S=S, H=H, B=B, Dh=Dh, branching=(8, 4, 2, 2, 1, 1, 1, 1))
+    parent = static_tree(cfg.branching, cfg.N)
+    tree = lpp.Tree(parent)
+    atts = [_layer_inputs(cfg, Hkv, l) for l in range(L)]
+    for seq in (None, [S - b * S // B if b else S // 3 for b in range(B)]):
+        got = _run_layers(tree, atts, cfg, Hkv, seq_len=seq)
+        again = _run_layers(tree, atts, cfg, Hkv, seq_len=seq)
+        for l in range(L):
+            assert np.array_equal(got[l], again[l])
+            for b in range(B):
+                n = S if seq is None else seq[b]
+                want = tree_attention(atts[l]["q"][b:b + 1], atts[l]["kc"][b:b + 1, :, :n], atts[l]["vc"][b:b + 1, :, :n],
+                                      atts[l]["kt"][b:b + 1], atts[l]["vt"][b:b + 1], parent)
+                assert attention_error(got[l][b:b + 1], want) <= TOL["bf16"]
