@@ -280,6 +280,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
       qb[nt][ks] = __builtin_bit_cast(bf16x8, ld16(reinterpret_cast<const char*>(qh) + ((uint32_t)m * (DH * 2) + g4 * 16) + ks * 64));
   }
 
+  const float lazy = NT <= 2 ? a.lazy : kLazy;
   f32x4 oacc[DT][NT], lacc[NT];
   float m_ref[NT];
 #pragma unroll
@@ -362,7 +363,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
           v = fmaxf(v, sc);
         }
       mxl[nt] = v > 0.5f * kMasked ? v * a.scale_log2 : kMasked;   // (scale > 0: the maximum commutes with it)
-      need = need || (mxl[nt] > m_ref[nt] + a.lazy);
+      need = need || (mxl[nt] > m_ref[nt] + lazy);
     }
     if (__ballot(need)) {   // some row's reference moves: rare after a wave's first group
 #pragma unroll
@@ -370,7 +371,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
         float v = mxl[nt];
         v = fmaxf(v, __shfl_xor(v, 16));
         v = fmaxf(v, __shfl_xor(v, 32));
-        const bool up = v > m_ref[nt] + a.lazy;                // decided per row: no row depends on another's scores
+        const bool up = v > m_ref[nt] + lazy;                // decided per row: no row depends on another's scores
         const float nm = up ? v : m_ref[nt];
         const float alpha = __builtin_amdgcn_exp2f(m_ref[nt] - nm);
         m_ref[nt] = nm;
