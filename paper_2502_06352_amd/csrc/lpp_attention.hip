@@ -46,7 +46,7 @@ constexpr float kMasked = -1.0e30f;  // finite stand-in for -inf
 // 3.7e-4): where a launch of few blocks has fewer waves than blocks of 8 would.
 // Long sweeps would pay for it (129 rows, 4096 keys, 384 heads 107 -> 121 us), two tiles a wave too (96 heads, 61 rows, 1024 keys
 // 9.6 -> 10.4), one tile 2 %.
-constexpr float kLazy = 8.0f, kLazyFew[2] = {1.0f, 4.0f};      // (one and two tiles a wave)
+constexpr float kLazy = 8.0f, kLazyFew[2] = {1.0f, 4.0f};      // (one tile a wave or few groups; two tiles)
 
 // Several layers of one step go out in one launch: unit / units_per_layer picks the layer,
 // whose tensors are looked up in a table inside the kernel arguments (a wave-uniform index).
@@ -1099,7 +1099,7 @@ AttnPlan plan_attention(const lpp_tree* tree, int B, int H, int S, int Dh, int l
     p.msplits = (p.mtiles + nt - 1) / nt;
     p.kw = ns4 > (Dh == 64 ? 10 : 4) || (ns4 > 1 && ns8 == 1 && G * weight <= 48) ||
                    (ns4 > 1 && ns4 == ns8 && (ns4 == 2 || G > 24 * ns4)) ? 8 : 4;
-    p.lazy = p.kw == 4 && ns4 < 2 * ns8 && G <= 40 * ns4 ? kLazyFew[nt - 1] : kLazy;      // (fewer waves than blocks of 8 would have)
+    p.lazy = p.kw == 4 && ns4 < 2 * ns8 && G <= 40 * ns4 ? kLazyFew[nt > 1 && ns4 == 1] : kLazy;      // (fewer waves than blocks of 8 would have)
     few = true;
     whole_heads = false;
   }
