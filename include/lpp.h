@@ -133,7 +133,9 @@ int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, int32_t k,
  *   out       [device] float32 [B, H, M, Dh]
  * Softmax and accumulation are float32; bf16 inputs are multiplied on the matrix
  * cores.  LPP_F32: the keys are cut into as many ranges as idle compute units and ws_bytes allow (the query's
- * size allows all), so the last bits of the result depend on ws_bytes.  Errors: LPP_EINVAL (null, B/H/S/Dh < 1 -- S = 0 is allowed), LPP_EUNSUPPORTED
+ * size allows all), so the last bits of the result depend on ws_bytes.  LPP_BF16: how the keys fall to waves, and so where
+ * a row's weights are rounded to bf16, depends on the sizes alone; with less than the query's size (down to half
+ * of it, about; LPP_ENOWORKSPACE below) the float32 sums over waves may be added in another order.  Errors: LPP_EINVAL (null, B/H/S/Dh < 1 -- S = 0 is allowed), LPP_EUNSUPPORTED
  * (Dh not 64 or 128, dtype unknown, LPP_F32 with S + M > 36864), LPP_ENOWORKSPACE, LPP_EHIP.
  */
 size_t  lpp_tree_attention_workspace(const lpp_tree* tree, int32_t B, int32_t H,

@@ -7,7 +7,7 @@
 //   S^T[32 keys x rows] = K_group * Q^T       (MFMA 16x16x32 bf16, K straight from HBM
 //                                              into the A operand, Q held in registers)
 //   softmax down the key axis, which is mostly lane-local in this layout; the
-//   reference maximum of a row only moves when a score exceeds it by 2^8 (few blocks: 2), so the
+//   reference maximum of a row only moves when a score exceeds it by 2^8, so the
 //   accumulators are rarely rescaled
 //   O^T[Dh x rows]    += V_group^T * P^T       (V rows go to a wave-private LDS tile as
 //                                              they are and come back through the
@@ -40,13 +40,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kMasked = -1.0e30f;  // finite stand-in for -inf
-// log2 of the largest probability weight before a rescale.  The largest weight of a reference's group is one, which bf16 has exactly;
-// with fewer waves fewer weights are, and a lower limit makes up for it (16 heads, 61 rows, 200 keys: error against float64
-// 1.35e-3 with 8 waves, 1.48e-3 with 4, 1.27e-3 with 4 and the lower limit; 4 times the scores, 48 heads, 1024 keys 5.4e-4, 7.4e-4,
-// 3.7e-4): where a launch of few blocks has fewer waves than blocks of 8 would.
-// Long sweeps would pay for it (129 rows, 4096 keys, 384 heads 107 -> 121 us), two tiles a wave too (96 heads, 61 rows, 1024 keys
-// 9.6 -> 10.4), one tile 2 %.
-constexpr float kLazy = 8.0f, kLazyFew[2] = {1.0f, 4.0f};      // (one tile a wave or few groups; two tiles)
+// log2 of the largest probability weight before a rescale.  (Lower, long sweeps take longer: at 2^1, 129 rows, 4096 keys, 384 heads
+// 107 -> 121 us.)
+constexpr float kLazy = 8.0f;
 
 // Several layers of one step go out in one launch: unit / units_per_layer picks the layer,
 // whose tensors are looked up in a table inside the kernel arguments (a wave-uniform index).
@@ -58,14 +54,15 @@ struct LayerPtrs {
 
 struct AttnArgs {
   // (what every block needs to find its place lies together: one line of the scalar cache)
-  uint32_t whole;                    // units (layer, head, row range) that one block each takes (a multiple of 8 where others are split); those behind them are split
   uint32_t units_per_layer, rc_upl;  // units of a layer: first those of its key/value heads in eights, then those of the heads left
   uint32_t eights;                   // ... units of the former
   uint32_t left, rc_left;            // key/value heads left, 0 to 7
   uint32_t spin;                     // ... none, the last eight padded: how far its heads move from layer to layer
-  uint32_t split_eights;             // blocks of the split units in eights, and the split units left
-  uint32_t split_left, rc_split_left;
-  int32_t nsplit; uint32_t rc_nsplit;   // key ranges of a split unit
+  uint32_t whole_eights;             // the launch's units (layer, head, row range) in eights, and those left
+  uint32_t units_left, rc_units_left;
+  int32_t nsplit; uint32_t rc_nsplit;   // blocks of a unit: `share` for each of its key ranges
+  int32_t ranges; uint32_t rc_ranges;
+  int32_t share_bits;                // log2(share)
   int32_t msplits; uint32_t rc_msplits; // row ranges of a head.  rc_d: ceil(2^32 / d): n / d = mulhi(n, rc) while n d < 2^32
   int32_t gq; uint32_t rc_gq;        // query heads per key/value head (H = Hkv * gq)
   int32_t H; uint32_t rc_H;
@@ -74,11 +71,11 @@ struct AttnArgs {
   const int32_t* seq_len;
   const uint64_t* anc;
   float scale_log2;                  // scale * log2(e)
-  float lazy;                        // kLazy or one of kLazyFew
   uint32_t ws_o_bytes, ws_ml_bytes;  // sizes of the two, each below 2^31
-  float* ws_o;                       // [split unit][nsplit][rows of a block][Dh]   unnormalised partial O
-  float* ws_ml;                      // [split unit][nsplit][rows of a block][2]    (reference max in log2 units, sum)
-  int32_t* counters;                 // [split unit] zero between calls
+  int32_t rows_pad;                  // ceil(M / 16) * 16
+  float* ws_o;                       // [layer][BH][nsplit][rows_pad][Dh]   unnormalised partial O
+  float* ws_ml;                      // [layer][BH][nsplit][rows_pad][2]    (reference max in log2 units, sum)
+  int32_t* counters;                 // [unit] zero between calls
   LayerPtrs layer[kLayersPerLaunch];
 };
 
@@ -153,7 +150,7 @@ struct Stage {
 };
 
 // NT = row tiles (of 16 tree rows) per wave, RW = waves along the rows, KW = waves along the keys:
-// a block covers NT * RW * 16 tree rows; wave (kw, rw) takes key groups by turns for
+// a block covers NT * RW * 16 tree rows; of the KW * share waves of a key range wave w takes its groups gbeg + w, + KW * share, ... for
 // rows [rw NT 16, (rw + 1) NT 16).  The RW waves that share a key group load it independently; the
 // second read is served by the compute unit's own cache.
 template <int DH, int NT, int RW, int KW>
@@ -184,23 +181,20 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   // and every query head that reads it) share an XCD, as long as all XCDs have one, and follow each other in launch order
   // (Every argument is asked for at once, then the layer's pointers and the item's length, and no branch up to the first
   // loads: left to the compiler, the scalar loads wait for each other four times, a few tenths of a microsecond each.)
-  uint32_t whole = a.whole, upl = a.units_per_layer, rc_upl = a.rc_upl, eights = a.eights, left = a.left, rc_left = a.rc_left, spin = a.spin;
-  uint32_t split_eights = a.split_eights, split_left = a.split_left, rc_split_left = a.rc_split_left;
-  uint32_t rc_nsplit = a.rc_nsplit, rc_msplits = a.rc_msplits, rc_gq = a.rc_gq, rc_H = a.rc_H;
-  int ranges = a.nsplit, msplits = a.msplits, gq = a.gq, H = a.H, KVBH = a.KVBH, S = a.S, M = a.M;
-  asm("" : "+s"(whole), "+s"(upl), "+s"(rc_upl), "+s"(eights), "+s"(left), "+s"(rc_left), "+s"(split_eights), "+s"(split_left),
-           "+s"(rc_split_left), "+s"(spin));
-  asm("" : "+s"(rc_nsplit), "+s"(rc_msplits), "+s"(rc_gq), "+s"(rc_H), "+s"(ranges), "+s"(msplits),
-           "+s"(gq), "+s"(H), "+s"(KVBH), "+s"(S), "+s"(M) : "s"(a.words), "s"(a.anc), "s"(a.seq_len), "s"(a.scale_log2), "s"(a.lazy));
-  // (split units by eights, a unit's blocks 8 apart: on one XCD; what is left of them one key range after the other)
-  const bool is_split = blockIdx.x >= whole;
-  const uint32_t behind = blockIdx.x - whole, bslot = behind >> 3, bunit = div_rc(bslot, (uint32_t)ranges, rc_nsplit);
-  const uint32_t tail = behind - split_eights, tsplit = div_rc(tail, split_left, rc_split_left);
-  const bool in_tail = is_split && behind >= split_eights;
-  const uint32_t first_left = div_rc(split_eights, (uint32_t)ranges, rc_nsplit);
-  const uint32_t unit = !is_split ? blockIdx.x
-                                  : whole + (in_tail ? first_left + tail - tsplit * split_left : bunit * 8 + (behind & 7));
-  const int split = !is_split ? 0 : (int)(in_tail ? tsplit : bslot - bunit * (uint32_t)ranges), nsplit = is_split ? ranges : 1;
+  uint32_t upl = a.units_per_layer, rc_upl = a.rc_upl, eights = a.eights, left = a.left, rc_left = a.rc_left, spin = a.spin;
+  uint32_t whole_eights = a.whole_eights, units_left = a.units_left, rc_units_left = a.rc_units_left;
+  uint32_t rc_nsplit = a.rc_nsplit, rc_ranges = a.rc_ranges, rc_msplits = a.rc_msplits, rc_gq = a.rc_gq, rc_H = a.rc_H;
+  int nsplit = a.nsplit, ranges = a.ranges, share_bits = a.share_bits, msplits = a.msplits, gq = a.gq, H = a.H, KVBH = a.KVBH, S = a.S, M = a.M;
+  asm("" : "+s"(upl), "+s"(rc_upl), "+s"(eights), "+s"(left), "+s"(rc_left), "+s"(whole_eights), "+s"(units_left),
+           "+s"(rc_units_left), "+s"(spin), "+s"(ranges), "+s"(rc_ranges), "+s"(share_bits));
+  asm("" : "+s"(rc_nsplit), "+s"(rc_msplits), "+s"(rc_gq), "+s"(rc_H), "+s"(nsplit), "+s"(msplits),
+           "+s"(gq), "+s"(H), "+s"(KVBH), "+s"(S), "+s"(M) : "s"(a.words), "s"(a.anc), "s"(a.seq_len), "s"(a.scale_log2));
+  // (units by eights, a unit's blocks 8 apart: on one XCD; what is left of them one key range after the other)
+  const uint32_t octet = blockIdx.x >> 3, oct_unit = div_rc(octet, (uint32_t)nsplit, rc_nsplit);
+  const uint32_t tail = blockIdx.x - whole_eights * (uint32_t)nsplit, tsplit = div_rc(tail, units_left, rc_units_left);
+  const bool in_tail = blockIdx.x >= whole_eights * (uint32_t)nsplit;
+  const uint32_t unit = in_tail ? whole_eights + tail - tsplit * units_left : oct_unit * 8 + (blockIdx.x & 7);
+  const int split = (int)(in_tail ? tsplit : octet - oct_unit * (uint32_t)nsplit);
   const uint32_t lyr = div_rc(unit, upl, rc_upl);
   const uint32_t bid = unit - lyr * upl;
   const LayerPtrs& L = a.layer[lyr];
@@ -220,6 +214,9 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   asm("" : "+s"(len) : "s"(L.q), "s"(L.kc), "s"(L.vc), "s"(L.kt), "s"(L.vt));
   const int seq = a.seq_len ? min(max(len, 0), S) : S;
   const int GC = (seq + 31) >> 5, GT = (M + 31) >> 5, G = GC + GT;
+  const int range = split >> share_bits, waves = KW << share_bits, wave_no = (split - (range << share_bits)) * KW + kw;
+  const int gbeg = (int)div_rc((uint32_t)(range * G), (uint32_t)ranges, rc_ranges);
+  const int gend = (int)div_rc((uint32_t)((range + 1) * G), (uint32_t)ranges, rc_ranges);
   const uint16_t* kc = reinterpret_cast<const uint16_t*>(L.kc) + (int64_t)kvbh * S * DH;
   const uint16_t* vc = reinterpret_cast<const uint16_t*>(L.vc) + (int64_t)kvbh * S * DH;
   const uint16_t* kt = reinterpret_cast<const uint16_t*>(L.kt) + (int64_t)kvbh * M * DH;
@@ -230,9 +227,6 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   // Key groups [0, GF) lie wholly inside the cache: no mask, no bounds.  The others (the ragged
   // end of the cache and the tree keys) go through the general path after them.
   const int GF = seq >> 5;
-  // The groups are dealt in turn to all waves of all blocks of the unit, whichever key range their block is: which wave gets
-  // what depends on the number of the waves alone.
-  const int waves = nsplit * KW, wave_no = kw * nsplit + split;             // (the blocks even: theirs differ by a wave's turn)
   // (in bytes, 32 bits: offsets to a wave-uniform pointer)
   const uint32_t koff = (uint32_t)(l16 * DH + g4 * 8) * 2;                  // my K chunk inside a group
   const uint32_t voff = (uint32_t)lane * 16;                                // my V chunks: + p * 64 chunks
@@ -280,7 +274,6 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
       qb[nt][ks] = __builtin_bit_cast(bf16x8, ld16(reinterpret_cast<const char*>(qh) + ((uint32_t)m * (DH * 2) + g4 * 16) + ks * 64));
   }
 
-  const float lazy = NT <= 2 ? a.lazy : kLazy;
   f32x4 oacc[DT][NT], lacc[NT];
   float m_ref[NT];
 #pragma unroll
@@ -363,7 +356,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
           v = fmaxf(v, sc);
         }
       mxl[nt] = v > 0.5f * kMasked ? v * a.scale_log2 : kMasked;   // (scale > 0: the maximum commutes with it)
-      need = need || (mxl[nt] > m_ref[nt] + lazy);
+      need = need || (mxl[nt] > m_ref[nt] + kLazy);
     }
     if (__ballot(need)) {   // some row's reference moves: rare after a wave's first group
 #pragma unroll
@@ -371,7 +364,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
         float v = mxl[nt];
         v = fmaxf(v, __shfl_xor(v, 16));
         v = fmaxf(v, __shfl_xor(v, 32));
-        const bool up = v > m_ref[nt] + lazy;                // decided per row: no row depends on another's scores
+        const bool up = v > m_ref[nt] + kLazy;               // decided per row: no row depends on another's scores
         const float nm = up ? v : m_ref[nt];
         const float alpha = __builtin_amdgcn_exp2f(m_ref[nt] - nm);
         m_ref[nt] = nm;
@@ -427,23 +420,23 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   // been consumed.  The wave's first general group is fetched before them and worked on while
   // the ring's first loads are in flight.
   auto run = [&](auto live) {
+    const int h1 = min(gend, GF);                     // full groups: [gbeg, h1)
+    const int c0 = max(gbeg, GF);                     // general groups: [c0, gend)
     const uint64_t novis[NT] = {};
     Stage<DH> cst;
     uint64_t vis[NT];
-    // next general group of this wave: [GF, G)  (the first waves': dealt on from the full ones, to waves with fewer of those, launches
-    // of few blocks take 0.5 to 0.7 us of 7 more)
-    int gx = GF + wave_no;
+    int gx = c0 + wave_no;                               // next general group of this wave
     if (GF >= 1) {
       constexpr int D = 2;   // (deeper rings were no faster on long caches and slower on short ones: the
                              //  eight waves of a block already have sixteen groups in flight)
       Stage<DH> st[D];
-      const bool pre = gx < G;
+      const bool pre = gx < gend;
       if (pre) { visibility(vis, gx); load_any(cst, gx); }
       // Ring loads are issued unconditionally (a group index past the end is clamped: a re-read
       // that is never used), so that the number of loads in flight is the same on every path and
       // each wait lets the younger loads stay in flight.
-      int g = wave_no;                            // full groups: [0, GF)
-      const int hl = GF - 1;
+      int g = gbeg + wave_no;
+      const int hl = max(h1 - 1, 0);
 #pragma unroll
       for (int d = 0; d < D; ++d)
         if (!kLean || d < D - 1) load_full(st[d], min(g + d * waves, hl));
@@ -452,7 +445,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
       // whole rounds of the ring, as long as at least the round's first refill is a group of this
       // wave (a round that would refill nothing is left to the tail below: a wave with D groups or
       // fewer would else spend half of the compute unit's load issue on re-reads nobody uses)
-      while (g + D * waves < GF) {
+      while (g + D * waves < h1) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
           compute_group(st[d], g, novis, kFull, live);
@@ -462,11 +455,11 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
       }
 #pragma unroll
       for (int d = 0; d < D; ++d) {               // what is left: up to D groups, already loaded
-        if (g < GF) compute_group(st[d], g, novis, kFull, live);
+        if (g < h1) compute_group(st[d], g, novis, kFull, live);
         g += waves;
       }
     }
-    for (; gx < G; gx += waves) {                 // further general groups: rare, not pipelined
+    for (; gx < gend; gx += waves) {                 // further general groups: rare, not pipelined
       visibility(vis, gx);
       load_any(cst, gx);
       compute_group(cst, gx, vis, kAny, live);
@@ -535,9 +528,8 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   // ---- write: final rows if this block saw every key, else an unnormalised partial
   constexpr int C4 = DH / 4;
   const int mb = ms * ROWS;                                     // first row of the block
-  // the unit's number among the split ones
-  const uint32_t part = unit - whole;
-  const int64_t part0 = (int64_t)part * nsplit * ROWS;          // first row of its partials
+  // first row of the unit's partials (the launch has a few hundred of them where there are any)
+  const int part0 = ((int)lyr * KVBH * gq + bh) * nsplit * a.rows_pad + mb;
   const __amdgpu_buffer_rsrc_t dev_o = device_buffer(a.ws_o, a.ws_o_bytes), dev_ml = device_buffer(a.ws_ml, a.ws_ml_bytes);
   for (int idx = threadIdx.x; idx < ROWS * C4; idx += W * 64) {
     const int r = idx / C4, c4 = idx % C4;
@@ -555,7 +547,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
       v.x *= inv; v.y *= inv; v.z *= inv; v.w *= inv;
       store_out4(out, a.out_bf16 != 0, ((int64_t)bh * M + m) * DH + c4 * 4, v);
     } else {   // read by another block of this launch: stores that are visible device-wide when they complete
-      const int64_t prow = part0 + split * ROWS + r;
+      const int prow = part0 + split * a.rows_pad + r;
       store_dev(dev_o, (uint32_t)((prow * DH + c4 * 4) * 4), v);
       if (c4 == 0) store_dev(dev_ml, (uint32_t)(prow * 8), make_float2(bm, bl));
     }
@@ -573,7 +565,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __syncthreads();
   if (threadIdx.x == 0)
-    s_ticket = __hip_atomic_fetch_add(&a.counters[part], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_ticket = __hip_atomic_fetch_add(&a.counters[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   if (s_ticket != nsplit - 1) return;
   for (int idx = threadIdx.x; idx < ROWS * C4; idx += W * 64) {
@@ -588,7 +580,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
       float4 o[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int64_t prow = part0 + min(s0 + u, nsplit - 1) * ROWS + r;      // (a split past the end: read again, weight 0)
+        const int prow = part0 + min(s0 + u, nsplit - 1) * a.rows_pad + r;    // (a split past the end: read again, weight 0)
         ml[u] = load_dev2(dev_ml, (uint32_t)(prow * 8));
         o[u] = load_dev4(dev_o, (uint32_t)((prow * DH + c4 * 4) * 4));
       }
@@ -611,7 +603,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
                make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv));
   }
   if (threadIdx.x == 0)   // ready for the next call
-    __hip_atomic_store(&a.counters[part], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&a.counters[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---------------------------------------------------------------- fp32 path
@@ -1035,9 +1027,8 @@ size_t f32_workspace(const lpp_tree* tree, int B, int H, int Dh, int layers, int
 }
 
 struct AttnPlan {
-  int nt, kw, msplits, nsplit, mtiles, groups;
-  int asked;                        // key ranges that a workspace must have room for (with less than nsplit, fewer are made)
-  float lazy;                       // kLazy or kLazyFew
+  int mtiles, nt, msplits;          // row tiles of 16, those of a wave, row ranges of a (batch, head)
+  int ranges, share, kw;            // key ranges of a (batch, head), the blocks that share one, the waves of a block
   size_t lds;
 };
 
@@ -1046,12 +1037,17 @@ struct AttnPlan {
 // read the same keys at about the same time and sit on the same XCD, so that the second read is
 // served by its L2.  Key splits (which cost a pass through the workspace) are only added while
 // the launch (all its layers) would leave compute units idle.
-AttnPlan plan_attention(const lpp_tree* tree, int B, int H, int S, int Dh, int layers) {
+// How the keys fall to waves says where a row's weights, of which the largest of each wave's reference is exact, are rounded to
+// bf16, and so how large the error is: 4 waves instead of 8, or instead of 24 in three ranges, make it 5 to 15 % larger against
+// float64 (scores of unit spread), 25 to 60 % with four times the scores.  Hence two parts: the waves and ranges of a
+// (batch, head), by the blocks that two or more tiles a wave would make; then which of these waves, and which rows, share a block.  That
+// only changes time (and the order of the float32 sums over waves).
+AttnPlan plan_attention(const lpp_tree* tree, int B, int H, int S, int Dh, int layers, bool may_share = true) {
   AttnPlan p;
-  p.lazy = kLazy;
   p.mtiles = (tree->M + 15) / 16;
-  const int G = (S + 31) / 32 + (tree->M + 31) / 32;
+  const int GT = (tree->M + 31) / 32, G = (S + 31) / 32 + GT;
   const int64_t n_cu = tree->n_cu, heads = (int64_t)B * H * std::max(1, std::min(layers, kLayersPerLaunch));
+  // ---- how the keys fall to waves: `ranges` of them, of 4 or 8 waves each
   // Up to 64 rows: two tiles per wave and one or two blocks per head (enough blocks to fill the
   // chip at small batch).  More rows: up to five tiles per wave, so that as few blocks as possible
   // stream the same K/V out of L2.
@@ -1069,55 +1065,50 @@ AttnPlan plan_attention(const lpp_tree* tree, int B, int H, int S, int Dh, int l
     p.msplits = (p.mtiles + 4) / 5;
     p.nt = (p.mtiles + p.msplits - 1) / p.msplits;
   }
-  // 33 to 64 rows: all of them in one block where the heads alone are enough blocks, so that K/V leave L2 once: 16 layers of
-  // 4 items x 24 heads, 61 rows, 1024 keys 86.8 -> 75.5 us, 8 layers 52.5 -> 46.5; 2 layers of 4096 keys 55.4 -> 40.9.  Not where
-  // four tiles a wave end in a second round that is short (61 rows, 1024 keys, 288 heads 19.9 -> 22.1 us, 384 heads
-  // 20.3 -> 23.1; 480 heads 29.7 -> 25.7); with fewer heads only on long caches, where the key splits fill the chip better
-  // (46 rows, 4000 keys, 72 heads 22.1 -> 15.2 us; 1300 keys, 96 heads 10.0 -> 10.7).
-  bool whole_heads = false;
-  if (Dh == 64 && (p.mtiles == 3 || p.mtiles == 4) && p.nt == 2 &&
-      (heads * 2 > n_cu ? p.mtiles == 3 || G >= 48 || heads <= n_cu || heads * 4 >= n_cu * 7 : heads * 4 > n_cu && G >= 90)) {
-    p.nt = p.mtiles;
-    p.msplits = 1;
-    whole_heads = true;
-  }
+  const int64_t blocks_bh = heads * p.msplits;
+  // Ranges of 8 waves, a block on a compute unit -- unless the launch has more blocks than compute units
+  // and a wave of a 4-wave block still has two groups or more: then two or three such blocks share
+  // a compute unit and cover each other's fixed latencies (first bytes, in-block merge, write-out)
+  // and stalls, which the waves of one block, in step with each other, cannot.  With three tiles or
+  // more per wave (two waves per SIMD either way) that pays from two rounds of blocks on.
+  const int waves = G >= 8 && ((p.nt == 2 && blocks_bh > n_cu) || (p.nt >= 3 && Dh == 64 && blocks_bh >= 2 * n_cu)) ? 4 : 8;
+  // key splits only while a compute unit would idle, at least two key groups per wave
+  p.ranges = (int)std::max<int64_t>(1, std::min<int64_t>(n_cu / blocks_bh, G / (2 * waves)));
+
+  // ---- the blocks
+  p.kw = waves;
+  p.share = 1;
   // Launches of few blocks, which latency bounds (first bytes, in-block merge, merge of key ranges): a block costs what its waves
-  // have to merge, 4 to 16 KB of sums each, and what it reads.  One tile a wave, then two, while the blocks are no more than
-  // the compute units and each takes in no more than 330 KB (660 KB) of keys and values; blocks of 4 waves unless that means
-  // more than so many key ranges, or any where 8 waves need none, or where 8 waves make as many and that is two, or leaves a
-  // wave of 4 more than six groups.  Over 504 shapes (one layer, 8 to 128 heads, 9 to 100 rows, 64 to 4000 keys) launches take
-  // 1.011 times the best of all such choices, with the rules above and below alone 1.21: 16 heads of 64, 100 rows, 200 keys 11.6 -> 6.6 us, 27 rows, 1000 keys 7.5 -> 6.3; 32 heads of 128, 61 rows, 64 keys 10.3 -> 6.2, 1000
-  // keys 14.4 -> 11.6; 6 % slower at worst (48 heads of 64, 9 rows, 2000 keys 8.7 -> 9.3).
+  // have to merge, 4 to 16 KB of sums each, and what it reads.  One tile a wave, then two, while the blocks are no more than the
+  // compute units and these take in no more than 330 KB (660 KB) of keys and values on average.  Over 220 shapes (up to 256 heads,
+  // 9 to 129 rows, 64 to 4096 keys), with the rule for shared ranges, launches take 1.01 times the best of all such choices and 0.92 of
+  // what they take without the two, none of them more: 4 heads of 64, 100 rows, 1313 keys 15.3 -> 7.6 us; 40 heads, 121 rows, 1914 keys
+  // 26.1 -> 16.4; 4 heads of 128, 27 rows, 1621 keys 13.8 -> 10.1.
   const int weight = Dh / 64;                     // a group of 32 keys and values: 8 KB each
-  bool few = false;
-  for (int nt = 1; nt <= std::min(2, p.mtiles) && !few; ++nt) {
+  for (int nt = 1; nt <= 2 && nt < p.nt; ++nt) {
     const int64_t units = heads * ((p.mtiles + nt - 1) / nt);
-    if (units > n_cu || units * G * weight > 40 * nt * n_cu) continue;
-    const int64_t ns4 = std::max<int64_t>(1, std::min<int64_t>(n_cu / units, G / 8));
-    const int64_t ns8 = std::max<int64_t>(1, std::min<int64_t>(n_cu / units, G / 16));
+    if (units * p.ranges > n_cu || units * G * weight > 40 * nt * n_cu) continue;
     p.nt = nt;
     p.msplits = (p.mtiles + nt - 1) / nt;
-    p.kw = ns4 > (Dh == 64 ? 10 : 4) || (ns4 > 1 && ns8 == 1 && G * weight <= 48) ||
-                   (ns4 > 1 && ns4 == ns8 && (ns4 == 2 || G > 24 * ns4)) ? 8 : 4;
-    p.lazy = p.kw == 4 && ns4 < 2 * ns8 && G <= 40 * ns4 ? kLazyFew[nt > 1 && ns4 == 1] : kLazy;      // (fewer waves than blocks of 8 would have)
-    few = true;
-    whole_heads = false;
   }
-  const int64_t blocks_bh = heads * p.msplits;
-  // Blocks of 8 waves only where they are so few that every second compute unit would idle.  Blocks of 4 waves
-  // share a compute unit and cover each other's fixed latencies (first bytes, in-block merge, write-out) and stalls, which
-  // the waves of one block, in step with each other, cannot: 12 heads x 12 items x 5 layers, 160 keys: 18.7 -> 9.6 us (14
-  // rows); 32 heads of 128 x 3 items x 12 layers, 100 keys: 44 -> 22.5 (20 rows); 24 heads x 8 items, 160 keys: 19.5 ->
-  // 13.2 (116 rows).  Four tiles a wave on long caches: a block a compute unit, while that is enough for all (24
-  // heads x 2 items x 2 layers, 2700 keys, 116 rows: 21.8 us, 22.8 with blocks of 4 waves).
-  if (!few) p.kw = blocks_bh * 2 > n_cu && !(p.nt == 4 && blocks_bh <= n_cu && G >= 60) ? 4 : 8;
-  int ns = (int)std::min<int64_t>(tree->n_cu / blocks_bh, 1 << 20);   // key splits only while a compute unit would idle
-  const int max_ns = G / (2 * p.kw);              // at least two key groups per wave
-  if (ns > max_ns) ns = max_ns;
-  if (ns < 1) ns = 1;
-  p.nsplit = ns;
-  p.asked = whole_heads || few ? 1 : ns;
-  p.groups = G;
+  // Ranges of 8 waves in two blocks of 4, which merge less each, while every compute unit has one at most: 16 heads, 27 rows, 1024 keys
+  // 8.6 -> 7.3 us.  (From five ranges on the merge of twice as many costs more: 20 heads, 11 rows, 4075 keys 9.7 -> 10.5 us.)
+  if (waves == 8 && may_share && p.ranges >= 2 && p.ranges <= 4 && heads * p.msplits * p.ranges * 2 <= n_cu) {
+    p.kw = 4;
+    p.share = 2;
+  }
+  // Full groups and the others are each dealt from the first wave on: with four of each at most, waves 5 to 8 have none.
+  // Without them a compute unit holds more than one block: 512 heads, 24 rows, 77 keys, 4 layers 44.1 -> 22.6 us; 60 heads, 31 rows, 100 keys 6.1 -> 5.1.
+  if (S / 32 <= 4 && GT <= 3) p.kw = 4;
+  // 33 to 64 rows in blocks of 4 waves: all of them in one block, so that K/V leave L2 once: 16 layers of 4 items x 24 heads, 61 rows,
+  // 1024 keys 86.8 -> 75.5 us, 8 layers 52.5 -> 46.5.  Four tiles a wave only from 24 groups on (160 heads, 52 rows, 246 keys 9.1 -> 10.0
+  // us; 576 heads, 19 groups 8 % more, 1024 heads, 31 groups 13 % less), and not where
+  // they end in a second round that is short (61 rows, 1024 keys, 288 heads 19.9 -> 22.1 us, 384 heads 20.3 -> 23.1; 480 heads 29.7 -> 25.7).
+  if (Dh == 64 && p.mtiles >= 3 && p.nt == 2 && waves == 4 &&
+      (p.mtiles == 3 || G >= 48 || (G >= 24 && (heads <= n_cu || heads * 4 >= n_cu * 7)))) {
+    p.nt = p.mtiles;
+    p.msplits = 1;
+  }
   const int rows = p.nt * 16;
   const size_t vt = (size_t)p.kw * 2 * 32 * (Dh * 2 + 32);
   const int ms = (size_t)p.kw * rows * (Dh + 4) * 4 <= std::max<size_t>(vt, (size_t)p.kw * 12 * 1024) ? p.kw : p.kw / 2;
@@ -1137,29 +1128,17 @@ int32_t launch_bf16(const AttnArgs& a, const AttnPlan& p, int64_t blocks, hipStr
   return LPP_OK;
 }
 
-// Which of a launch's units (layer, head, row range; a block each) are split over several blocks by keys.  A launch
-// of fewer units than compute units: all of them, p.nsplit times.  Otherwise those behind the last full round of
-// compute units, so many times that they fill one more, where that saves more than the merge of the parts costs
-// (about 3 us): 31 rows, 3000 keys, 288 heads 54.0 -> 43.8 us, 384 heads 60.4 -> 56.5; 1024 keys, 288 heads 18.0 -> 16.7, but
-// 384 heads, in two parts, 18.4 -> 21.0.
-struct AttnSplit { int64_t whole; int ns; };
-AttnSplit split_units(const lpp_tree* tree, const AttnPlan& p, int64_t units) {
-  if (p.nsplit > 1) return {0, p.nsplit};
-  const int64_t round = std::max(8, tree->n_cu & ~7), rest = units % round;
-  if (rest == units || rest == 0) return {units, 1};
-  const int ns = (int)std::min<int64_t>(round / rest, p.groups / (2 * p.kw));
-  return p.groups < 32 || ns < (p.groups < 80 ? 4 : 2) ? AttnSplit{units, 1} : AttnSplit{units - rest, ns};
-}
-size_t split_rows(const AttnPlan& p, int64_t split, int ns) { return ns < 2 ? 0 : (size_t)split * ns * p.nt * 16; }
-
 // Bytes of so many partial rows: [O | max, sum].
 size_t partial_bytes(size_t rows, int Dh, size_t* o_bytes) {
   if (o_bytes) *o_bytes = lpp_align_up(rows * Dh * sizeof(float), 256);
   return lpp_align_up(rows * Dh * sizeof(float), 256) + lpp_align_up(rows * 2 * sizeof(float), 256);
 }
-// What a call asks for per layer, at least (with less than it could use, a launch has fewer split units).
-size_t layer_workspace(const AttnPlan& p, int B, int H, int Dh) {
-  return partial_bytes((size_t)B * H * p.asked * p.mtiles * 16, Dh, nullptr);
+// What a call asks for, at least (with less than p.share times as many rows no range is shared).
+size_t least_workspace(const AttnPlan& p, int B, int H, int Dh, int L) {
+  return std::min(L, kLayersPerLaunch) * partial_bytes((size_t)B * H * p.ranges * p.mtiles * 16, Dh, nullptr);
+}
+size_t partials_of(const AttnPlan& p, int B, int H, int Dh, int L, size_t* o_bytes) {
+  return p.ranges < 2 ? 0 : partial_bytes((size_t)std::min(L, kLayersPerLaunch) * B * H * p.ranges * p.share * p.mtiles * 16, Dh, o_bytes);
 }
 
 }  // namespace
@@ -1173,11 +1152,7 @@ extern "C" size_t lpp_tree_attention_layers_workspace(const lpp_tree* tree, int3
                                                       int32_t S, int32_t Dh) {
   if (!tree || L < 1 || B < 1 || H < 1 || S < 0 || (Dh != 64 && Dh != 128)) return 0;
   const AttnPlan p = plan_attention(tree, B, H, S, Dh, L);
-  const int nl = std::min(L, kLayersPerLaunch);
-  // (the split units behind the last full round, whatever the number of key/value heads: their blocks are a round at most)
-  const size_t rows = std::max(split_rows(p, (int64_t)nl * B * H * p.msplits, p.nsplit),
-                               p.nsplit > 1 || (int64_t)nl * B * H * p.msplits * 8 < tree->n_cu ? 0 : (size_t)tree->n_cu * p.nt * 16);
-  return std::max({(size_t)nl * layer_workspace(p, B, H, Dh), partial_bytes(rows, Dh, nullptr),
+  return std::max({least_workspace(p, B, H, Dh, L), partials_of(p, B, H, Dh, L, nullptr),
                    f32_workspace(tree, B, H, Dh, L, f32_splits(tree, B, H, S, L), nullptr)});
 }
 
@@ -1199,10 +1174,11 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
   if (out_dtype != LPP_F32 && out_dtype != LPP_BF16) return LPP_EUNSUPPORTED;
   if ((int64_t)B * H > (1 << 24) || (int64_t)B * H * H >= (1ll << 32)) return LPP_EUNSUPPORTED;
   if ((int64_t)S * Dh >= (1ll << 31) || (int64_t)tree->M * Dh >= (1ll << 31)) return LPP_EUNSUPPORTED;   // 32-bit offsets inside one head
-  const AttnPlan p = plan_attention(tree, B, H, S, Dh, L);
+  AttnPlan p = plan_attention(tree, B, H, S, Dh, L);
   // (what bf16 needs; the float32 kernel takes as many key ranges as the workspace has room for)
-  const size_t need = (size_t)std::min(L, kLayersPerLaunch) * layer_workspace(p, B, H, Dh);
+  const size_t need = least_workspace(p, B, H, Dh, L);
   if (!ws || ws_bytes < need) return LPP_ENOWORKSPACE;
+  if (ws_bytes < partials_of(p, B, H, Dh, L, nullptr)) p = plan_attention(tree, B, H, S, Dh, L, false);
   if (!tree->d_anc) return LPP_EHIP;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if (scale == 0.f) scale = 1.0f / sqrtf((float)Dh);
@@ -1245,38 +1221,32 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
     a.seq_len = seq_len; a.anc = tree->d_anc;
     a.H = H; a.S = S; a.M = tree->M; a.words = tree->words;
     a.KVBH = B * Hkv; a.gq = H / Hkv; a.out_bf16 = out_dtype == LPP_BF16;
-    a.msplits = p.msplits;
+    a.msplits = p.msplits; a.nsplit = p.ranges * p.share; a.ranges = p.ranges; a.share_bits = p.share == 2; a.rows_pad = p.mtiles * 16;
     a.scale_log2 = scale * 1.44269504088896340736f;
-    a.lazy = p.lazy;
     // Key/value heads beyond a multiple of 8: in one layer, in few whose heads make no eight and where the keys are split, their blocks take turns on the XCDs
     // (1 head of 4 in 4 items, 67 rows, 1313 keys 16.4 -> 8.2 us).  In more layers a head keeps to an XCD, whose L2 then has
     // its keys for all blocks that read them, and the next layer's heads to the XCDs behind (5 heads for 20, 16 layers, 1286
     // keys 34 us, in turns 38).
     const int64_t per_head = (int64_t)(H / Hkv) * p.msplits;
-    const bool turns = nl * (a.KVBH & 7) < 8 || nl == 1 || p.nsplit > 1;        // (padding has no place among the partials)
+    const bool turns = nl * (a.KVBH & 7) < 8 || nl == 1 || p.ranges > 1;        // (padding has no place among the partials)
     const int64_t upl = (turns ? (int64_t)B * Hkv : ((int64_t)B * Hkv + 7) / 8 * 8) * per_head;
-    AttnSplit sp = split_units(tree, p, upl * nl);
-    size_t o_bytes = 0, ml_bytes = 0;
-    auto partials = [&]() {
-      const size_t bytes = partial_bytes(split_rows(p, upl * nl - sp.whole, sp.ns), Dh, &o_bytes);
-      ml_bytes = bytes - o_bytes;
-      return bytes;
-    };
-    while (partials() > ws_bytes) sp = sp.ns > 2 ? AttnSplit{sp.whole, sp.ns - 1} : AttnSplit{upl * nl, 1};
-    const int64_t parts = upl * nl - sp.whole, blocks = sp.whole + parts * sp.ns;
+    const int64_t units = upl * nl, blocks = units * a.nsplit;
     if (blocks >= (1ll << 31)) return LPP_EUNSUPPORTED;
-    a.whole = (uint32_t)sp.whole; a.nsplit = sp.ns;
-    a.rc_msplits = reciprocal((uint32_t)p.msplits); a.rc_H = reciprocal((uint32_t)H); a.rc_nsplit = reciprocal((uint32_t)sp.ns);
+    a.rc_msplits = reciprocal((uint32_t)p.msplits); a.rc_H = reciprocal((uint32_t)H); a.rc_nsplit = reciprocal((uint32_t)a.nsplit);
+    a.rc_ranges = reciprocal((uint32_t)p.ranges);
     a.rc_gq = reciprocal((uint32_t)(H / Hkv));
     a.units_per_layer = nl == 1 ? 0xFFFFFFFFu : (uint32_t)upl;                  // (one layer: 0, however many units)
     a.rc_upl = reciprocal(a.units_per_layer);
     a.left = turns ? (uint32_t)(a.KVBH & 7) : 0u; a.rc_left = reciprocal(a.left);
     a.eights = (uint32_t)(upl - a.left * per_head);
     a.spin = turns ? 0u : (uint32_t)(a.KVBH & 7);
-    a.split_eights = (uint32_t)((parts & ~7ll) * sp.ns);
-    a.split_left = (uint32_t)(parts & 7); a.rc_split_left = reciprocal(a.split_left);
+    a.whole_eights = (uint32_t)(units & ~7ll);
+    a.units_left = (uint32_t)(units & 7); a.rc_units_left = reciprocal(a.units_left);
+    // (partials only where the launch has no more blocks than compute units: they and the units are few)
+    size_t o_bytes = 0;
+    const size_t bytes = partials_of(p, B, H, Dh, nl, &o_bytes);
     a.counters = tree->d_counters + LPP_COUNTER_SLOTS;
-    a.ws_o_bytes = (uint32_t)o_bytes; a.ws_ml_bytes = (uint32_t)ml_bytes;
+    a.ws_o_bytes = (uint32_t)o_bytes; a.ws_ml_bytes = (uint32_t)(bytes - o_bytes);
     a.ws_o = reinterpret_cast<float*>(ws);
     a.ws_ml = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(ws) + o_bytes);
 
