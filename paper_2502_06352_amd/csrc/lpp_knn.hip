@@ -270,8 +270,8 @@ __global__ __launch_bounds__(kStatThreads) void knn_stats_kernel(KnnArgs a) {
           }
           if (j >= 0) put_halves(wide ? a.Ews : a.Es, j, n8, d, h, l);
 #pragma unroll
-          for (int e = 0; e < 4; ++e)                         // (see CollectQuery; the code is left out when it is ranked)
-            if (v[e] != v[e]) { h[e] = (_Float16)0.f; l[e] = (_Float16)0.f; }
+          for (int e = 0; e < 4; ++e)                         // (see CollectQuery: NaN, and what the scale takes beyond the halves' range)
+            if (!(fabsf((float)h[e]) < INFINITY)) { h[e] = (_Float16)0.f; l[e] = (_Float16)0.f; }
           put_halves(wide ? a.Ew : a.Ef, row, n8, d, h, l);
         }
       }
@@ -395,8 +395,10 @@ struct HalfOperand {
 // The same for the collecting sweep, whose loads bring 64 bytes a cycle and compute unit whatever is in them: every piece of a
 // code is loaded once, and a second MFMA takes the products with the query's lower parts.  N = 1: an operand holds the
 // pieces of two tiles, h l of the one and h l of the other, against h h 0 0 and l 0 0 0 or 0 0 h h and 0 0 l 0; N = 2:
-// h0 h1 l0 l1 against h0 h1 h0 h1 and l0 l1 0 0.  (A code's numbers meet zeros of another's lane: no NaN is in there, nor in the
-// rows from V on, and where one is infinite all rows take the exact path.)
+// h0 h1 l0 l1 against h0 h1 h0 h1 and l0 l1 0 0.  A code's numbers meet zeros in place of another's, and zero times infinity is
+// NaN: every half has to be finite, also in the rows from V on and in a code that holds a NaN, whose other numbers may be as large as
+// they like (it takes no part in the codebook's largest magnitude).  knn_stats puts zeros where one is not.  That changes nobody's
+// similarity: a code that holds a NaN is left out when it is ranked, and of other codes such a number takes all rows to the exact path.
 template <int N>
 struct CollectQuery {
   f16x8 h[3 - N], l[3 - N];
@@ -758,7 +760,7 @@ __global__ __launch_bounds__(kCollectMaxWaves * 64) void knn_collect_f16_kernel(
   const int l16 = lane & 15, g4 = lane >> 4;
   const int row = blockIdx.x * 16 + l16, rowc = min(row, a.V - 1);
   const RowPlan p = a.plan[row];
-  const int windows = a.Vp / kWindowCodes;                 // (rows V .. Vp - 1 are there, whatever they hold)
+  const int windows = a.Vp / kWindowCodes;                 // (rows V .. Vp - 1 are there and hold zeros, see CollectQuery)
   const float c0 = -p.thr;
   const i32x4* const Ef = __builtin_amdgcn_readfirstlane(p.flags) & kWide ? a.Ew : a.Ef;
   CollectQuery<N> q;

@@ -76,6 +76,19 @@ def test_knn_codes_that_hold_a_nan_come_last(V, D, k):
     _check(E, k, np.unique(np.concatenate([[3, 7, 11, V // 2, V - 2], g.choice(V, size=100)])))
 
 
+@pytest.mark.parametrize("other", [20.0, 20000.0, 3e38, np.inf, -np.inf])
+@pytest.mark.parametrize("V,D,k", [(1030, 8, 40), (1500, 5, 1500), (2500, 2, 300), (1100, 13, 60), (1100, 40, 60)])
+def test_knn_large_numbers_beside_a_nan_spoil_no_other_code(V, D, k, other):
+    # beyond the halves' range at either scale: the codes that share an operand with such a one (four places before it or
+    # behind) are neighbours as ever
+    g = np.random.default_rng(V + D)
+    E = _unit(g, V, D)
+    bad = np.array([3, 9, 127, 128, 500, 503, V - 6, V - 1])
+    E[bad] = other
+    E[bad, np.arange(len(bad)) % D] = np.nan
+    _check(E, k)
+
+
 @pytest.mark.parametrize("V,D,k", [(1030, 8, 40), (2500, 6, 300), (2047, 13, 64), (1100, 16, 1100), (700, 40, 30)])
 def test_knn_does_not_depend_on_what_the_workspace_held(V, D, k):
     # NaN and infinities in every piece of it, and codes that hold a NaN beside others
