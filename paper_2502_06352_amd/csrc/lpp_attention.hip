@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "lpp_internal.h"
+#include "lpp_reciprocal.h"
 
 namespace {
 
@@ -63,7 +64,8 @@ struct AttnArgs {
   int32_t nsplit; uint32_t rc_nsplit;   // blocks of a unit: `share` for each of its key ranges
   int32_t ranges; uint32_t rc_ranges;
   int32_t share_bits;                // log2(share)
-  int32_t msplits; uint32_t rc_msplits; // row ranges of a head.  rc_d: ceil(2^32 / d): n / d = mulhi(n, rc) while n d < 2^32
+  int32_t msplits; uint32_t rc_msplits; // row ranges of a head.  rc_d: for div_rc; n d < 2^32 as blocks < 2^31, B H^2 < 2^32, msplits <= 8
+                                     // (16 where the blocks are few), the layers as layers_per_launch has them
   int32_t gq; uint32_t rc_gq;        // query heads per key/value head (H = Hkv * gq)
   int32_t H; uint32_t rc_H;
   int32_t KVBH, S, M, words;         // KVBH: batch * key/value heads
@@ -86,19 +88,6 @@ __device__ __forceinline__ int formed_anew(int x) {
   return x;
 }
 
-// n / d for wave-uniform operands through the host's reciprocal (0: d = 1): scalar multiplies, no division
-__device__ __forceinline__ uint32_t div_rc(uint32_t n, uint32_t d, uint32_t rc) {
-  const uint32_t q = (uint32_t)(((uint64_t)n * rc) >> 32);   // (rc = 0 for d = 1)
-  return rc == 0 ? n : q;
-}
-// The same, rc = 1 where n d can reach 2^32: divided.
-__device__ __forceinline__ uint32_t div_or_rc(uint32_t n, uint32_t d, uint32_t rc) {
-  return rc == 1 ? n / d : div_rc(n, d, rc);
-}
-// ceil(2^32 / d) as the two take it; n_max: the largest n (div_rc: kept below 2^32 / d by its callers)
-uint32_t reciprocal(uint32_t d, uint64_t n_max = 0) {
-  return d <= 1 ? 0u : (n_max * d >= 0x100000000ull ? 1u : (uint32_t)((0x100000000ull + d - 1) / d));
-}
 __device__ __forceinline__ uint4 ld16(const char* p) { return *reinterpret_cast<const uint4*>(p); }
 __device__ __forceinline__ uint4 ld16(const uint16_t* p) {
   return *reinterpret_cast<const uint4*>(p);
@@ -215,6 +204,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   const int seq = a.seq_len ? min(max(len, 0), S) : S;
   const int GC = (seq + 31) >> 5, GT = (M + 31) >> 5, G = GC + GT;
   const int range = split >> share_bits, waves = KW << share_bits, wave_no = (split - (range << share_bits)) * KW + kw;
+  // (beyond 2^32 / ranges, a few million keys, a bound may come out one group up, for both ranges that it parts; the last one, G, not)
   const int gbeg = (int)div_rc((uint32_t)(range * G), (uint32_t)ranges, rc_ranges);
   const int gend = (int)div_rc((uint32_t)((range + 1) * G), (uint32_t)ranges, rc_ranges);
   const uint16_t* kc = reinterpret_cast<const uint16_t*>(L.kc) + (int64_t)kvbh * S * DH;
@@ -1183,10 +1173,12 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if (scale == 0.f) scale = 1.0f / sqrtf((float)Dh);
 
-  // up to kLayersPerLaunch layers per launch; the launches of one call follow each other on the
-  // stream and share the workspace
-  for (int32_t l0 = 0; l0 < L; l0 += kLayersPerLaunch) {
-    const int32_t nl = std::min(L - l0, kLayersPerLaunch);
+  // up to kLayersPerLaunch layers per launch (bf16: fewer of more than 16384 units each); the launches of one call follow
+  // each other on the stream and share the workspace
+  const int64_t per_head = (int64_t)(H / Hkv) * p.msplits, padded = ((int64_t)B * Hkv + 7) / 8 * 8 * per_head;
+  const int32_t most = dtype == LPP_F32 ? kLayersPerLaunch : layers_per_launch(padded, kLayersPerLaunch);
+  for (int32_t l0 = 0; l0 < L; l0 += most) {
+    const int32_t nl = std::min(L - l0, most);
     if (dtype == LPP_F32) {
       AttnArgsF32 a;
       for (int32_t l = 0; l < kLayersPerLaunch; ++l) {
@@ -1227,9 +1219,8 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
     // (1 head of 4 in 4 items, 67 rows, 1313 keys 16.4 -> 8.2 us).  In more layers a head keeps to an XCD, whose L2 then has
     // its keys for all blocks that read them, and the next layer's heads to the XCDs behind (5 heads for 20, 16 layers, 1286
     // keys 34 us, in turns 38).
-    const int64_t per_head = (int64_t)(H / Hkv) * p.msplits;
     const bool turns = nl * (a.KVBH & 7) < 8 || nl == 1 || p.ranges > 1;        // (padding has no place among the partials)
-    const int64_t upl = (turns ? (int64_t)B * Hkv : ((int64_t)B * Hkv + 7) / 8 * 8) * per_head;
+    const int64_t upl = turns ? (int64_t)B * Hkv * per_head : padded;
     const int64_t units = upl * nl, blocks = units * a.nsplit;
     if (blocks >= (1ll << 31)) return LPP_EUNSUPPORTED;
     a.rc_msplits = reciprocal((uint32_t)p.msplits); a.rc_H = reciprocal((uint32_t)H); a.rc_nsplit = reciprocal((uint32_t)a.nsplit);

@@ -239,3 +239,24 @@ def test_launches_of_few_blocks(Dh, B, H, Hkv, N, S, L):
                 want = tree_attention(atts[l]["q"][b:b + 1], atts[l]["kc"][b:b + 1, :, :n], atts[l]["vc"][b:b + 1, :, :n],
                                       atts[l]["kt"][b:b + 1], atts[l]["vt"][b:b + 1], parent)
                 assert attention_error(got[l][b:b + 1], want) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("B,H,Hkv", [(65, 256, 256), (1041, 20, 4)])
+def test_layers_of_many_units_are_those_of_single_calls(B, H, Hkv):
+    # 16640 and 20820 heads a layer: more than a launch of 16 layers can tell apart by reciprocals
+    tree = lpp.Tree(np.asarray([-1, 0, 0, 1], dtype=np.int32))
+    M, S, Dh, L = 4, 16, 64, 17
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B)
+
+    def normal(heads, rows):
+        return torch.randn(B, heads, rows, Dh, generator=gen, device=DEV).to(torch.bfloat16)
+
+    layers = [dict(q=normal(H, M), k_cache=normal(Hkv, S), v_cache=normal(Hkv, S), k_tree=normal(Hkv, M), v_tree=normal(Hkv, M),
+                   out=torch.full((B, H, M, Dh), float("nan"), device=DEV)) for _ in range(L)]
+    ws = torch.empty(lpp.lpp_tree_attention_layers_workspace(tree, L, B, H, S, Dh), dtype=torch.uint8, device=DEV)
+    lpp.lpp_tree_attention_layers(tree, lpp.LPP_BF16, lpp.LPP_F32, layers, None, B, H, Hkv, S, Dh, 0.0, ws)
+    one = torch.empty(B, H, M, Dh, device=DEV)
+    for y in layers:
+        lpp.lpp_tree_attention_layers(tree, lpp.LPP_BF16, lpp.LPP_F32, [dict(y, out=one)], None, B, H, Hkv, S, Dh, 0.0, ws)
+        assert torch.equal(y["out"], one)
