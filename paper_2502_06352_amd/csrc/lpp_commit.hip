@@ -39,7 +39,7 @@ __global__ __launch_bounds__(64) void commit_kv_kernel(CommitArgs a) {
   if (slot > n) return;
   const int pos = base + slot;
   if (pos >= a.S) return;                                  // past the capacity: dropped
-  const int row = slot > 0 ? min(max(node, 0), a.M - 1) : 0;
+  const int row = slot > 0 ? min(max(node, 0), a.M - 1) : 0;     // (M = 1: the root, whatever was read)
   const int64_t src = ((int64_t)bh * a.M + row) * a.row_bytes, dst = ((int64_t)bh * a.S + pos) * a.row_bytes;
   for (int o = threadIdx.x * 16; o < a.row_bytes; o += 64 * 16) {
     const uint4 k = *reinterpret_cast<const uint4*>(a.kt + src + o), v = *reinterpret_cast<const uint4*>(a.vt + src + o);
@@ -65,7 +65,8 @@ extern "C" int32_t lpp_commit_kv(const lpp_tree* tree, int32_t dtype, const void
   CommitArgs a;
   a.kt = (const unsigned char*)k_tree; a.vt = (const unsigned char*)v_tree;
   a.kc = (unsigned char*)k_cache; a.vc = (unsigned char*)v_cache;
-  a.path = path; a.accept_len = accept_len; a.seq_len = seq_len; a.new_len = new_len;
+  // (a tree of the root alone has no path entries, [B, 0]: what the kernel reads ahead is then something else of B words)
+  a.path = tree->depth > 0 ? path : seq_len; a.accept_len = accept_len; a.seq_len = seq_len; a.new_len = new_len;
   a.rc_H = H == 1 ? 0u : ((int64_t)B * H * H < (1ll << 32) ? (uint32_t)(((1ll << 32) + H - 1) / H) : 1u);
   a.H = H; a.S = S; a.M = tree->M; a.depth = tree->depth > 0 ? tree->depth : 1;
   a.row_bytes = Dh * esz;

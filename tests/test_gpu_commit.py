@@ -48,6 +48,23 @@ def test_commit_after_verify_matches_oracle(idx, kv):
     assert np.array_equal(_host(t["vc"], cfg), vc)
 
 
+@pytest.mark.parametrize("B,H", [(1, 1), (3, 4)])
+def test_commit_of_the_root_alone(B, H):
+    # a tree without drafted nodes: path is [B, 0], of which nothing may be read (here: what lies at its address is no row)
+    cfg = CONFIGS[1].scaled(B=B, H=H, N=4, S=40)
+    att = make_attention_inputs(cfg)
+    tree = lpp.Tree(np.asarray([-1], dtype=np.int32))
+    root = {n: (v[:, :, :1] if n in ("kt", "vt") else v) for n, v in att.items() if n in ("kc", "vc", "kt", "vt")}
+    seq_len, accepted = np.array([0, 17, 39][:B], dtype=np.int32), np.zeros(B, dtype=np.int32)
+    t = {n: dev(v) for n, v in root.items()}
+    junk = torch.full((B,), 1 << 30, dtype=torch.int32, device=DEV)
+    new_len = torch.full((B,), -7, dtype=torch.int32, device=DEV)
+    lpp.lpp_commit_kv(tree, lpp.LPP_F32, t["kt"], t["vt"], junk, dev(accepted), dev(seq_len), B, H, cfg.S, cfg.Dh, t["kc"], t["vc"], new_len)
+    kc, vc, nl = commit_kv(root["kc"], root["vc"], root["kt"], root["vt"], np.zeros((B, 0), dtype=np.int32), accepted, seq_len)
+    assert np.array_equal(new_len.cpu().numpy(), nl)
+    assert np.array_equal(t["kc"].cpu().numpy(), kc) and np.array_equal(t["vc"].cpu().numpy(), vc)
+
+
 def test_commit_after_a_walk_that_gave_up_commits_the_root_only():
     # accept_len = -1 and path = -1 are what lpp_relaxed_verify writes for an item whose walk gave
     # up: the commit must treat it as "nothing accepted" (root only), like the oracle on a length of 0.
