@@ -19,6 +19,11 @@
  *   - `ws` is caller-provided device scratch of at least the size returned by the
  *     matching *_workspace query (256-byte aligned).  Its contents are undefined
  *     between calls; two calls that share one workspace must be ordered on a stream.
+ *   - A tree handle holds a few words that kernels of lpp_relaxed_verify and of
+ *     lpp_tree_attention, in all their forms, leave for each other: calls of these two that
+ *     share a handle must be ordered on a stream, whatever their workspaces.  Work that
+ *     may overlap takes a handle of its own.  (bf16 attention uses them where a launch of less than half as many
+ *     blocks as compute units cuts the keys in ranges; a caller does better not to count on that.)
  *   - Rows: a tree has M = N+1 rows; row 0 is the root (the last committed token),
  *     rows 1..N are the drafted nodes.
  */

@@ -217,6 +217,21 @@ def test_bf16_shares_no_range_for_a_smaller_workspace(N, S, B, H, sizes):
     assert max(attention_error(o, outs[-1]) for o in outs) <= 2e-6
 
 
+@pytest.mark.parametrize("N,S,B,H,Dh", [(30, 3000, 12, 24, 64), (45, 1100, 12, 24, 64), (128, 1100, 11, 12, 64), (20, 2600, 11, 30, 128), (60, 3000, 5, 20, 64)])
+def test_launches_of_many_blocks_leave_workspace_and_handle_alone(N, S, B, H, Dh):
+    # no partial results, and so no tickets in the tree handle: such a call has nothing that another on the same handle could take
+    cfg = CONFIGS[2].scaled(N=N, branching=(8, 4, 2, 2, 1, 1, 1, 1), S=S, H=H, B=B, Dh=Dh)
+    tree = lpp.Tree(static_tree(cfg.branching, cfg.N))
+
+    def zeros(rows):
+        return torch.zeros(B, H, rows, Dh, dtype=torch.bfloat16, device=DEV)
+
+    ws = torch.full((lpp.lpp_tree_attention_workspace(tree, B, H, S, Dh),), 0x5A, dtype=torch.uint8, device=DEV)
+    out = torch.empty(B, H, cfg.M, Dh, device=DEV)
+    lpp.lpp_tree_attention(tree, lpp.LPP_BF16, zeros(cfg.M), zeros(S), zeros(S), zeros(cfg.M), zeros(cfg.M), None, B, H, S, Dh, 0.0, out, ws)
+    assert bool((ws == 0x5A).all()) and bool((out == 0).all())
+
+
 @pytest.mark.parametrize("Dh", [64, 128])
 @pytest.mark.parametrize("B,H,Hkv,N,S,L", [
     (1, 1, 1, 8, 4000, 1), (1, 2, 1, 15, 64, 1), (1, 3, 3, 16, 700, 2), (1, 4, 1, 99, 130, 1), (1, 5, 5, 20, 1500, 1), (1, 6, 2, 31, 33, 3),
