@@ -117,7 +117,7 @@ int32_t lpp_tree_set_walk_patience(lpp_tree* tree, int32_t rounds);
  * or where |e| times the largest |e| is below 1e-30; of long rows, those whose entries are below about 1/100 of
  * the codebook's largest (8192 x 256, a third of the rows scaled by 0.02: 1.3 to 2 ms instead of 0.2 to 0.3).
  * Workspace: the lists (a 32-bit word for every code above a row's threshold, with room to spare) are most
- * of it: 119 MB at 16384 x 8, k = 1000; 35 MB at k = 100; 1.9 GB at 65536 codes, k = 4096.
+ * of it: 120 MB at 16384 x 8, k = 1000; 36 MB at k = 100; 1.9 GB at 65536 codes, k = 4096.
  */
 size_t  lpp_build_neighbours_workspace(int32_t V, int32_t D, int32_t k);
 int32_t lpp_build_neighbours(const float* E, int32_t V, int32_t D, int32_t k,

@@ -5,7 +5,7 @@
 // order) with ties to the lower index, so it does not depend on how the matrix
 // cores round.  The V x V similarities are never written out and the float64 keys
 // are only formed where they decide something:
-//   stats    padded float32 copy of the codebook (and halves of short rows), norms, 1-norms, largest magnitude
+//   stats    norms, 1-norms, largest magnitude, halves of short rows, a padded copy where rows do not start on 16 bytes
 //   limbs    (rows of more than 16 floats) fixed-point image of the codebook as three
 //            8-bit limbs, in matrix-core fragment order
 //   sample   per row: histogram of its similarities with a hashed, stratified sample of
@@ -31,8 +31,9 @@
 // The approximate similarities and their bound e:
 //   rows of up to 16 floats: x = h + l in halves of 11 bits, h h' + l h' + h l' on the f16 matrix
 //   cores; what is left out is below 3 2^-22 |e_i| |e_j|.  The products are exact in float32; that each of
-//   the 32 N additions is off by at most 2^-23 of |e_i| |e_j| is how the matrix cores are taken to add, not
-//   something their documents promise.  The halves are of 4096 x, or of 4 x in codebooks with entries from 16 on;
+//   the additions, 32 N at most, is off by at most 2^-23 of |e_i| |e_j| is how the matrix cores are taken to add, not
+//   something their documents promise.  (24 N products are not zero by construction.  The collecting sweep adds up 64 for either N, the
+//   sample 32 N; the others are exact zeros, which round nothing.)  The halves are of 4096 x, or of 4 x in codebooks with entries from 16 on;
 //   from 16376 on every row takes the exact path.
 //   longer rows: x = q D + d with a 24-bit integer q = 2^16 a + 2^8 b + c (a, b, c signed 8-bit
 //   limbs), |d| <= D / 2, D = largest magnitude / (127 2^16).  All limb products but c c are summed
@@ -668,7 +669,7 @@ __global__ __launch_bounds__(kSampleThreads, FIXED && NQ == 2 && N >= 3 ? 4 : 8)
     const double trunc = 3.0 * 16777216.0 * u * u;         // cut low parts: below three units of the value kept
     e = (float)(0.5005 * u * ((double)l1 + (double)st.l1) * 1.001 + a.D * u * u + trunc);
   } else {
-    // 32 N products on top of the threshold, each sum rounded by 2^-23; l l' and what the halves leave of
+    // up to 32 N products that are not zero on top of the threshold, each sum rounded by 2^-23; l l' and what the halves leave of
     // each number: 3 2^-22, or 2^-25 of the scaled number
     e = (float)(32 * N + 6) * 1.1920929e-07f * (norm * st.norm + fabsf(thr)) * 1.001f + 7.2e-07f * norm * st.norm +
         2.9802322e-08f / hscale * (l1 + st.l1) * 1.001f + 1e-30f;
