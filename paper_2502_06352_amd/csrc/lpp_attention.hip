@@ -1215,10 +1215,10 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
     a.KVBH = B * Hkv; a.gq = H / Hkv; a.out_bf16 = out_dtype == LPP_BF16;
     a.msplits = p.msplits; a.nsplit = p.ranges * p.share; a.ranges = p.ranges; a.share_bits = p.share == 2; a.rows_pad = p.mtiles * 16;
     a.scale_log2 = scale * 1.44269504088896340736f;
-    // Key/value heads beyond a multiple of 8: in one layer, in few whose heads make no eight and where the keys are split, their blocks take turns on the XCDs
-    // (1 head of 4 in 4 items, 67 rows, 1313 keys 16.4 -> 8.2 us).  In more layers a head keeps to an XCD, whose L2 then has
-    // its keys for all blocks that read them, and the next layer's heads to the XCDs behind (5 heads for 20, 16 layers, 1286
-    // keys 34 us, in turns 38).
+    // Key/value heads beyond a multiple of 8: in one layer, in few whose heads make no eight and where the keys are cut in ranges,
+    // their blocks take turns on the XCDs (1 head of 4 in 4 items, 67 rows, 1313 keys 16.2 -> 9.6 us).  In more layers a head keeps to
+    // an XCD, whose L2 then has its keys for all blocks that read them, and the next layer's heads to the XCDs behind (5 heads for 20,
+    // 61 rows, 16 layers, 1286 keys 25 us, in turns 35).
     const bool turns = nl * (a.KVBH & 7) < 8 || nl == 1 || p.ranges > 1;        // (padding has no place among the partials)
     const int64_t upl = turns ? (int64_t)B * Hkv * per_head : padded;
     const int64_t units = upl * nl, blocks = units * a.nsplit;
