@@ -1123,9 +1123,10 @@ size_t partial_bytes(size_t rows, int Dh, size_t* o_bytes) {
   if (o_bytes) *o_bytes = lpp_align_up(rows * Dh * sizeof(float), 256);
   return lpp_align_up(rows * Dh * sizeof(float), 256) + lpp_align_up(rows * 2 * sizeof(float), 256);
 }
-// What a call asks for, at least (with less than p.share times as many rows no range is shared).
-size_t least_workspace(const AttnPlan& p, int B, int H, int Dh, int L) {
-  return std::min(L, kLayersPerLaunch) * partial_bytes((size_t)B * H * p.ranges * p.mtiles * 16, Dh, nullptr);
+// What a call asks for, at least: room for so many ranges (bf16: all, but with less than p.share times as much none is shared; float32, which
+// makes as many as there is room for: one).
+size_t least_workspace(const AttnPlan& p, int ranges, int B, int H, int Dh, int L) {
+  return std::min(L, kLayersPerLaunch) * partial_bytes((size_t)B * H * ranges * p.mtiles * 16, Dh, nullptr);
 }
 size_t partials_of(const AttnPlan& p, int B, int H, int Dh, int L, size_t* o_bytes) {
   return p.ranges < 2 ? 0 : partial_bytes((size_t)std::min(L, kLayersPerLaunch) * B * H * p.ranges * p.share * p.mtiles * 16, Dh, o_bytes);
@@ -1142,7 +1143,7 @@ extern "C" size_t lpp_tree_attention_layers_workspace(const lpp_tree* tree, int3
                                                       int32_t S, int32_t Dh) {
   if (!tree || L < 1 || B < 1 || H < 1 || S < 0 || (Dh != 64 && Dh != 128)) return 0;
   const AttnPlan p = plan_attention(tree, B, H, S, Dh, L);
-  return std::max({least_workspace(p, B, H, Dh, L), partials_of(p, B, H, Dh, L, nullptr),
+  return std::max({least_workspace(p, p.ranges, B, H, Dh, L), partials_of(p, B, H, Dh, L, nullptr),
                    f32_workspace(tree, B, H, Dh, L, f32_splits(tree, B, H, S, L), nullptr)});
 }
 
@@ -1165,8 +1166,7 @@ int32_t tree_attention_impl(const lpp_tree* tree, int32_t dtype, int32_t out_dty
   if ((int64_t)B * H > (1 << 24) || (int64_t)B * H * H >= (1ll << 32)) return LPP_EUNSUPPORTED;
   if ((int64_t)S * Dh >= (1ll << 31) || (int64_t)tree->M * Dh >= (1ll << 31)) return LPP_EUNSUPPORTED;   // 32-bit offsets inside one head
   AttnPlan p = plan_attention(tree, B, H, S, Dh, L);
-  // (what bf16 needs; the float32 kernel takes as many key ranges as the workspace has room for)
-  const size_t need = least_workspace(p, B, H, Dh, L);
+  const size_t need = least_workspace(p, dtype == LPP_F32 ? 1 : p.ranges, B, H, Dh, L);
   if (!ws || ws_bytes < need) return LPP_ENOWORKSPACE;
   if (ws_bytes < partials_of(p, B, H, Dh, L, nullptr)) p = plan_attention(tree, B, H, S, Dh, L, false);
   if (!tree->d_anc) return LPP_EHIP;

@@ -155,6 +155,20 @@ def test_float32_takes_fewer_ranges_for_a_smaller_workspace(Dh):
     assert 1 <= least < 32
 
 
+def test_float32_needs_room_for_one_range_only():
+    # of 16 that the query's size has room for, whatever bf16 would ask for at these sizes (8)
+    cfg = CONFIGS[2].scaled(N=20, S=4000, H=4, B=1, kv_dtype="f32")
+    parent = static_tree(cfg.branching, cfg.N)
+    att = _layer_inputs(cfg, cfg.H, 0)
+    t = {n: dev(att[n]) for n in ("q", "kc", "vc", "kt", "vt")}
+    ws = torch.empty(cfg.H * 32 * (cfg.Dh + 2) * 4 + 256, dtype=torch.uint8, device=DEV)
+    out = torch.full((1, cfg.H, cfg.M, cfg.Dh), float("nan"), device=DEV)
+    tree = lpp.Tree(parent)
+    lpp.lpp_tree_attention(tree, lpp.LPP_F32, t["q"], t["kc"], t["vc"], t["kt"], t["vt"], None, 1, cfg.H, cfg.S, cfg.Dh, 0.0, out, ws)
+    want = tree_attention(att["q"], att["kc"], att["vc"], att["kt"], att["vt"], parent)
+    assert attention_error(out.cpu().numpy(), want) <= 1e-4
+
+
 @pytest.mark.parametrize("N,S,B,H,Hkv,Dh,L,ragged", [
     (45, 100, 12, 24, 24, 64, 1, False),     # 288 heads, seven key groups
     (60, 70, 8, 30, 10, 64, 1, True),        # four
