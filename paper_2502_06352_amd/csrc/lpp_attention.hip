@@ -518,8 +518,8 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
   // ---- write: final rows if this block saw every key, else an unnormalised partial
   constexpr int C4 = DH / 4;
   const int mb = ms * ROWS;                                     // first row of the block
-  // first row of the unit's partials (the launch has a few hundred of them where there are any)
-  const int part0 = ((int)lyr * KVBH * gq + bh) * nsplit * a.rows_pad + mb;
+  // first row of the unit's partials, where there are any (the launch then has a few hundred blocks)
+  const uint32_t part0 = (lyr * (uint32_t)(KVBH * gq) + (uint32_t)bh) * (uint32_t)(nsplit * a.rows_pad) + (uint32_t)mb;
   const __amdgpu_buffer_rsrc_t dev_o = device_buffer(a.ws_o, a.ws_o_bytes), dev_ml = device_buffer(a.ws_ml, a.ws_ml_bytes);
   for (int idx = threadIdx.x; idx < ROWS * C4; idx += W * 64) {
     const int r = idx / C4, c4 = idx % C4;
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
       v.x *= inv; v.y *= inv; v.z *= inv; v.w *= inv;
       store_out4(out, a.out_bf16 != 0, ((int64_t)bh * M + m) * DH + c4 * 4, v);
     } else {   // read by another block of this launch: stores that are visible device-wide when they complete
-      const int prow = part0 + split * a.rows_pad + r;
+      const uint32_t prow = part0 + (uint32_t)(split * a.rows_pad + r);
       store_dev(dev_o, (uint32_t)((prow * DH + c4 * 4) * 4), v);
       if (c4 == 0) store_dev(dev_ml, (uint32_t)(prow * 8), make_float2(bm, bl));
     }
@@ -570,7 +570,7 @@ __global__ __launch_bounds__(RW * KW * 64, (RW * KW == 4 ? (NT <= 2 && DH == 64 
       float4 o[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int prow = part0 + min(s0 + u, nsplit - 1) * a.rows_pad + r;    // (a split past the end: read again, weight 0)
+        const uint32_t prow = part0 + (uint32_t)(min(s0 + u, nsplit - 1) * a.rows_pad + r);    // (a split past the end: read again, weight 0)
         ml[u] = load_dev2(dev_ml, (uint32_t)(prow * 8));
         o[u] = load_dev4(dev_o, (uint32_t)((prow * DH + c4 * 4) * 4));
       }
